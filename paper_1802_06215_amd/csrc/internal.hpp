@@ -16,6 +16,7 @@ constexpr int kHorizon = HDX_MAX_HORIZON;
 constexpr int kSenseEntries = 2 * (kMaxGrid - 1) * (kMaxGrid - 1) + 1;  // squared distances
 constexpr int kMaxLeaf = HDX_MAX_LEAF_SCENARIOS;
 constexpr int kMaxNavLeaf = HDX_MAX_NAV_LEAF_SCENARIOS;
+constexpr int kNavActions = 9;
 
 enum : uint32_t { kTagStep = 0, kTagInit = 1, kTagPolicy = 2 };
 constexpr uint64_t kEmptyKey = ~0ull;
@@ -39,16 +40,18 @@ struct ModelHdr {
     float path_len, dt, step_len, half_sigma, coll_r2, reach, ih_scale;
     float r_collision, r_step, r_goal, pad2;
     uint64_t fail_thr;  // action fails iff word < fail_thr (driving, navigation)
-    // navigation: goal column (on the bottom row), wall row, gate columns,
-    // per cell -1 known free / -2 known wall / unknown cell index, and the
-    // reading error (a neighbour's bit flips iff word < err_thr)
+    // navigation: goal column (on the bottom row), wall row, gate columns and
+    // the reading error (a neighbour's bit flips iff word < err_thr)
     int32_t nav_goal_x, nav_wall, nav_gate_x[2];
-    int16_t nav_cell[HDX_MAX_NAV_GRID * HDX_MAX_NAV_GRID];
     uint64_t err_thr;
-    // navigation rollouts: the known walls as bits 16 y + x (four words) and
-    // each unknown cell's bit position 16 y + x
-    uint64_t nav_wall_bits[4];
-    uint8_t nav_unknown_pos[HDX_MAX_NAV_UNKNOWN];
+    // navigation map as rows of 16 cells, two per word: the known walls and
+    // the cells off the map, and the unknown cells in runs of consecutive
+    // indices on consecutive cells -- run i of word h, h's runs being
+    // [nav_run_begin[h], nav_run_begin[h + 1]): first bit in its source word
+    // (bits 0-4), length (5-9), first bit in word h (10-14), source word (15-16)
+    uint32_t nav_wall_rows[8];
+    int32_t nav_run_begin[9];
+    uint32_t nav_runs[HDX_MAX_NAV_UNKNOWN];
 };
 
 constexpr int kGpowLds = 256;
@@ -57,6 +60,7 @@ struct DevModel {
     ModelHdr h;
     uint32_t sense_thr_m1[kSenseEntries];  // floor(acc(d) 2^32) - 1, by squared distance
     float gpow[kHorizon];                  // discount powers gamma^j rounded to FP32
+    double gsum[kHorizon + 1];             // 1 + gamma + ... + gamma^(j-1)
 };
 
 struct StatesPtr {
@@ -71,7 +75,8 @@ struct StatesPtr {
 // One leaf as the expansion kernel sees it (built on the host from hdx_leaf).
 struct LeafTask {
     const DevModel *model;
-    int32_t kind, n_actions;
+    int16_t kind, tile_actions;  // actions per tile
+    int32_t n_actions;
     uint32_t k0, k1;
     int32_t policy, const_action, max_steps, max_depth;
     StatesPtr parent;
@@ -94,6 +99,8 @@ struct LeafTask {
     int32_t *child_of;
 };
 
+// A tile: actions [action, action + tile_actions) of a leaf (fewer at the
+// end of the leaf's actions).
 struct Tile {
     int32_t leaf, action;
 };
@@ -179,64 +186,54 @@ __host__ __device__ inline LdsLayout make_layout(int32_t np, bool small = false)
     L.child = take(4u * np);
     L.perm = take(4u * L.p2);
     L.misc = take(64 + 4u * 64);
-    // discount powers, goal points, the navigation cell table (int16) and
-    // the unknown cells' grid bits
-    L.gpow = take(4u * (kGpowLds + 2 * kMaxGoals) + 2u * HDX_MAX_NAV_GRID * HDX_MAX_NAV_GRID + HDX_MAX_NAV_UNKNOWN);
+    L.gpow = take(4u * (kGpowLds + 2 * kMaxGoals));  // discount powers, goal points
     L.total = o;
     return L;
 }
 
-// Medium observation alphabet (navigation: every key below kMedKeys).
-// Regions, each in use for the whole tile:
-//   gpow        discount powers, goal points and the navigation cell table
-//   key, rank   per scenario: observation key (16 bits) and its rank among
-//               the scenarios of that key in its wavefront's chunks
-//   ub, lb      per scenario: U and L
-//   perm        grouped order (leaf positions)
-//   su, sl      segmented sums over 64-aligned chunks of the grouped order
-//   wcnt        per run of chunks (one wavefront each) and key: scenario
-//               count, then the key's count in earlier runs
-//   kcnt, koff, kci  per key: count, child offset, child index
-//   cof, cnc    per child: offset, count
-//   chunk_r     per 64-scenario chunk: step reward sum
-// A leaf of up to kMaxMedLeaf scenarios fits one tile.
-constexpr int kMedKeys = 264;  // 257 navigation observations, rounded up
-constexpr int kMedWaves = 16;  // wavefronts of the widest workgroup
-constexpr int kMaxMedLeaf = kMaxNavLeaf;
-struct MedLayout {
-    uint32_t gpow, key, rank, ub, lb, perm, su, sl, wcnt, kcnt, koff, kci, cof, cnc, chunk_r, misc, total;
-    int32_t np;
+// Navigation tile: na actions of a leaf of n scenarios, run by `waves`
+// wavefronts.  Regions:
+//   gsum, ub    discount sums and the bound by distance
+//   code        per (action, scenario): NavCode
+//   val         per (action, scenario): rollout value, for the policies that
+//               run step by step (the default policy's follows from the code)
+//   rows, perm  while scenarios are stepped, each wavefront's map rows;
+//               afterwards the grouped order of each action
+//   cnt, meta   per action and observation: scenario count, then the next
+//               place in the grouped order; child index << 16 | count
+//   chunk_r     per action and 64-scenario chunk: step reward sum
+constexpr int kNavKeys = 257;  // 256 readings and the terminal one
+constexpr int kNavSums = 128;  // discount sums staged in LDS
+constexpr int kNavRowBytes = 64 * 8 * 4;  // one wavefront's map rows
+struct NavLayout {
+    uint32_t gsum, ub, code, val, rows, perm, cnt, meta, chunk_r, misc, total;
 };
-__host__ __device__ inline MedLayout make_med_layout(int32_t np) {
-    MedLayout L;
-    if (np < 1) np = 1;
-    L.np = np;
-    const uint32_t n = (uint32_t)np, chunks = (n + 63u) / 64u;
+// pairs = na * n; stepped: the rollouts run step by step
+__host__ __device__ inline NavLayout make_nav_layout(uint32_t pairs, uint32_t na, uint32_t chunks, uint32_t waves,
+                                                     bool stepped) {
+    NavLayout L;
     uint32_t o = 0;
     auto take = [&](uint32_t bytes) {
         uint32_t at = o;
         o += (bytes + 15u) & ~15u;
         return at;
     };
-    L.gpow = take(4u * (kGpowLds + 2 * kMaxGoals) + 2u * HDX_MAX_NAV_GRID * HDX_MAX_NAV_GRID + HDX_MAX_NAV_UNKNOWN);
-    L.key = take(2u * n);
-    L.rank = take(2u * n);
-    L.ub = take(4u * n);
-    L.lb = take(4u * n);
-    L.perm = take(2u * n);
-    L.su = take(4u * n);
-    L.sl = take(4u * n);
-    L.wcnt = take(4u * (chunks < (uint32_t)kMedWaves ? chunks : (uint32_t)kMedWaves) * kMedKeys);
-    L.kcnt = take(4u * kMedKeys);
-    L.koff = take(4u * kMedKeys);
-    L.kci = take(4u * kMedKeys);
-    L.cof = take(4u * kMedKeys);
-    L.cnc = take(4u * kMedKeys);
-    L.chunk_r = take(4u * chunks);
-    L.misc = take(64 + 4u * 64);
+    L.gsum = take(8u * (kNavSums + 1));
+    L.ub = take(4u * 32);
+    L.misc = take(16);
+    L.chunk_r = take(4u * na * chunks);
+    L.cnt = take(4u * na * kNavKeys);
+    L.meta = take(4u * na * kNavKeys);
+    L.code = take(4u * pairs);
+    L.val = stepped ? take(4u * pairs) : L.code;
+    L.rows = take(kNavRowBytes * waves > 2u * pairs ? kNavRowBytes * waves : 2u * pairs);
+    L.perm = L.rows;
     L.total = o;
     return L;
 }
+// Actions per navigation tile of a leaf of n scenarios, at most `most`: as
+// many as its LDS holds beside 16 wavefronts.
+int32_t nav_tile_actions(int32_t n, int32_t policy, int32_t most);
 
 // Kernel variant a set of leaves needs: mode 0 RockSample only, 1 driving
 // only, 2 both; pm = pedestrian capacity of the register state; n_max sizes
@@ -246,6 +243,9 @@ struct Variant {
     // driving only: the kernel instance whose tiles expand a leaf one lane
     // per pedestrian when n times the group width fits a wavefront
     int32_t group = 0;
+    // navigation: the largest (action, scenario) pairs of a tile, counted
+    // twice where the rollouts run step by step
+    int32_t pairs = 1;
 };
 Variant pick_variant(int32_t has_rs, int32_t has_ped, int32_t ped_max, int32_t n_max, int32_t has_mars,
                      int32_t has_nav);
@@ -291,18 +291,18 @@ inline Variant group_variant(int g) {
 }
 struct ClassPlan {
     int64_t begin[kGroups], count[kGroups];
-    int32_t n_max[kGroups];
+    int32_t n_max[kGroups], pairs[kGroups];
 };
 // Reorder tiles[0, n_tiles) by group, largest leaf first inside a group
 // (variant[leaf] is the leaf's model variant); fills plan.
 void plan_classes(const LeafTask *tasks, const int8_t *variant, Tile *tiles, int64_t n_tiles, ClassPlan *plan,
                   bool split);
 // One launch per non-empty group in mask (bit g = group g); lds_n[g] sizes
-// group g's LDS (>= its n_max); sch[g] is its schedule (its width capped at
+// group g's LDS (>= its n_max), for navigation with lds_pairs[g]; sch[g] is its schedule (its width capped at
 // what the group's leaves and model need).
 hipError_t launch_classes(const LeafTask *d_tasks, const Tile *d_tiles, TileQueue *d_queues, const ClassPlan &plan,
-                          const int32_t *lds_n, const Schedule *sch, int32_t n_cu, hipStream_t stream,
-                          uint64_t mask = ~0ull);
+                          const int32_t *lds_n, const int32_t *lds_pairs, const Schedule *sch, int32_t n_cu,
+                          hipStream_t stream, uint64_t mask = ~0ull);
 // Default schedule of a group whose largest leaf has n_max scenarios.
 // Latency form (a few leaves, split groups): two scenarios per lane up to
 // 256 lanes (navigation: 1024), one workgroup per tile, XCD-contiguous.
@@ -319,7 +319,7 @@ constexpr int kArgLeaves = 11;
 struct ArgPack {
     LeafTask t[kArgLeaves];
     int32_t tile_begin[kArgLeaves + 1];
-    int32_t n_leaves, n_max, xcd_remap;
+    int32_t n_leaves, n_max, pairs, xcd_remap;
 };
 hipError_t launch_expand_args(const ArgPack &pack, const Variant &v, const Schedule &sch, hipStream_t stream);
 

@@ -7,7 +7,9 @@
 // k = tid, tid + T, ...: it gathers the parent state (struct-of-arrays,
 // coalesced along k), applies the last action, steps the tile's action,
 // evaluates the upper-bound heuristic and runs the default-policy rollout in
-// registers.  Then the scenarios are grouped by observation, two ways:
+// registers.  Then the scenarios are grouped by observation, three ways:
+//  - navigation (257 observations): one wavefront per action over a table of
+//    the keys, see run_tile_nav (a tile there is several actions of a leaf);
 //  - observation alphabets below 32 keys (RockSample): in registers, per
 //    64-scenario chunk one ballot per key present gives counts and ranks
 //    and DPP row reductions the key's U and L sums; one wavefront turns the
@@ -22,6 +24,7 @@
 //    chunk partials added in order.
 // Either way the floating-point order depends only on the data, never on
 // the workgroup size or the schedule.
+#include <algorithm>
 #include <type_traits>
 
 #include "models.hpp"
@@ -232,7 +235,6 @@ __device__ void run_tile(const HDX_CONST LeafTask *T, const int a, unsigned char
         stepc[1] = 0;
     }
     if constexpr (Ops::kLdsModel) stage_gpow(T->model, gpow_lds);
-    if constexpr (std::is_same<Ops, NavOps>::value) stage_cells(T->model, gpow_lds);
     __syncthreads();
 
     RolloutParams RP;
@@ -674,58 +676,83 @@ __device__ void run_tile(const HDX_CONST LeafTask *T, const int a, unsigned char
     __syncthreads();  // LDS is reused by the next tile
 }
 
-// One (leaf, action) tile of a model whose observation keys are all below
-// kMedKeys (navigation: 8 reading bits, or the terminal key 256), for
-// leaves of up to kMaxMedLeaf scenarios.  No hash table and no sort: every
-// key is its own table index.
-//  - ranks: the 64-scenario chunks are split into contiguous runs, one per
-//    wavefront; a wavefront walks its run in order and keeps a running count
-//    per key, so a scenario's rank is the count of its key in earlier chunks
-//    of the run plus the lanes below it in its chunk with the same key;
-//  - a key's count in earlier runs, its child offset (ascending key) and its
-//    child index come from prefix sums over the runs and over the keys;
-//  - the per-child U and L sums are the same segmented scans over 64-aligned
-//    chunks of the grouped order as in the hashed path, chunk partials added
-//    in chunk order, so both paths give identical results for a leaf either
-//    can expand.
-// kGroup: the kernel-argument launches (a search's small leaves) roll out
-// with the map held as bits in registers (NavOps::rollout_grid).
-template <class Ops, bool kGroup>
-__device__ void run_tile_med(const HDX_CONST LeafTask *T, const int a, unsigned char *lds, const MedLayout &Ly) {
-    static_assert(Ops::kTerminalObs < (uint64_t)kMedKeys, "observation keys exceed the medium alphabet");
-    float *gpow_lds = (float *)(lds + Ly.gpow);
-    const MView M = make_view(T->model, gpow_lds);
-    const int n = T->n;
-    const int cap = T->cap;
-    const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id(), wid = tid >> 6, nw = nt >> 6;
-    uint16_t *keyb = (uint16_t *)(lds + Ly.key);
-    uint16_t *rnk = (uint16_t *)(lds + Ly.rank);
-    float *ub = (float *)(lds + Ly.ub);
-    float *lb = (float *)(lds + Ly.lb);
-    int16_t *permb = (int16_t *)(lds + Ly.perm);
-    float *su = (float *)(lds + Ly.su);
-    float *sl = (float *)(lds + Ly.sl);
-    int32_t *wcnt = (int32_t *)(lds + Ly.wcnt);
-    int32_t *kcnt = (int32_t *)(lds + Ly.kcnt);
-    int32_t *koff = (int32_t *)(lds + Ly.koff);
-    int32_t *kci = (int32_t *)(lds + Ly.kci);
-    int32_t *cof = (int32_t *)(lds + Ly.cof);
-    int32_t *cnc = (int32_t *)(lds + Ly.cnc);
-    float *chunk_r = (float *)(lds + Ly.chunk_r);
-    int32_t *misc = (int32_t *)(lds + Ly.misc);
-    unsigned long long *stepc = (unsigned long long *)(misc + 4);  // expansion, rollout steps
-    int32_t *scan_scratch = misc + 16;
-    const int nch = (n + 63) >> 6;
-    const int run_len = nch > 0 ? (nch + nw - 1) / nw : 1;  // chunks per wavefront run
-    const int runs = (nch + run_len - 1) / run_len;        // <= min(nw, nch)
-
-    for (int i = tid; i < runs * kMedKeys; i += nt) wcnt[i] = 0;
-    if (tid == 0) {
-        stepc[0] = 0;
-        stepc[1] = 0;
+// Navigation: na actions [a0, a0 + na) of one leaf.
+//
+// What bounds it: instruction issue (the walks and the random blocks); the
+// map, the update step, the random numbers of the step and the failure words
+// of the rollouts are the same for all nine actions of a scenario, so a tile
+// takes as many actions as its LDS holds (nav_tile_actions) and a lane does a
+// scenario's actions one after another.  What an action yields is a word
+// (NavCode) in LDS; rollouts of the default policy are settled from the walk
+// and the failure words (NavOps::walk).  Measured on 1024 leaves of 125..2000
+// scenarios: 0.37 ms (1.1e8 VALU instructions of a wavefront, 0.48 of the
+// issue slots) against 3.26 ms with one action per tile and every rollout
+// step taken; eleven leaves of one to five scenarios 16 against 67 us.
+//
+// Grouping, one wavefront per action, so no barrier is needed between its
+// passes: a count per observation (each key is its own table index), one
+// scan over the keys for child offsets and indices, the grouped order -- a
+// scenario's rank among the 64 of its chunk from one ballot per key bit --
+// and segmented DPP scans over 64-aligned chunks of the grouped order, a
+// child's chunk partials added in chunk order.  The floating-point order
+// depends on the data alone, never on the width or the actions per tile.
+struct NavCode {
+    // bits 0-8 observation, 9-13 distance, 14-15 how the walk ends,
+    // 16 settled, 17-29 moves of the walk; once settled, depths to its end
+    // (stepped policies: steps of the rollout)
+    static constexpr uint32_t kSettled = 1u << 16, kMax = 0x1fffu;
+    __device__ static uint32_t make(uint32_t z, int d, int kind, bool settled, int m) {
+        return z | ((uint32_t)d << 9) | ((uint32_t)kind << 14) | (settled ? kSettled : 0u) | ((uint32_t)m << 17);
     }
-    stage_gpow(T->model, gpow_lds);
-    stage_cells(T->model, gpow_lds);
+    __device__ static uint32_t obs(uint32_t c) { return c & 511u; }
+    __device__ static int dist(uint32_t c) { return (int)((c >> 9) & 31u); }
+    __device__ static int kind(uint32_t c) { return (int)((c >> 14) & 3u); }
+    __device__ static int count(uint32_t c) { return (int)((c >> 17) & kMax); }
+};
+
+// A value from the lane CTRL names (0 where there is none).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_srci(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, true);
+}
+// One step of a segmented inclusive scan of two sums: f set where the
+// segment's first lane has been reached.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void seg_step(float &u, float &l, int &f) {
+    const float ou = dpp_src<CTRL, ROWS>(u), ol = dpp_src<CTRL, ROWS>(l);
+    const int of = dpp_srci<CTRL, ROWS>(f);
+    u = f ? u : ou + u;
+    l = f ? l : ol + l;
+    f |= of;
+}
+
+// LDS traffic of one wavefront stays in order; this keeps the compiler from
+// moving it.
+__device__ __forceinline__ void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+__device__ __forceinline__ void run_tile_nav(const HDX_CONST LeafTask *T, const int a0, const int na, unsigned char *lds) {
+    using Ops = NavOps;
+    const int n = T->n, cap = T->cap, nch = (n + 63) >> 6;
+    const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id(), wid = tid >> 6, nw = nt >> 6;
+    const bool stepped = T->policy != HDX_POLICY_DEFAULT;
+    const NavLayout Ly = make_nav_layout((uint32_t)(na * n), (uint32_t)na, (uint32_t)nch, (uint32_t)nw, stepped);
+    double *gsum = (double *)(lds + Ly.gsum);
+    float *ub = (float *)(lds + Ly.ub);
+    uint32_t *code = (uint32_t *)(lds + Ly.code);
+    float *val = (float *)(lds + Ly.val);
+    uint32_t *rows = (uint32_t *)(lds + Ly.rows) + wid * (kNavRowBytes / 4) + lane;
+    uint16_t *perm = (uint16_t *)(lds + Ly.perm);
+    int32_t *cnt = (int32_t *)(lds + Ly.cnt);
+    uint32_t *meta = (uint32_t *)(lds + Ly.meta);
+    float *chunk_r = (float *)(lds + Ly.chunk_r);
+    int32_t *expanded = (int32_t *)(lds + Ly.misc);
+    const MView M = make_view(T->model, nullptr);
+
+    for (int j = tid; j <= kNavSums; j += nt) gsum[j] = M.gpow_sum(j);
+    for (int d = tid; d <= Ops::kNoDistance; d += nt)
+        ub[d] = d == Ops::kNoDistance ? 0.0f : 20.0f * M.gpow_uniform(d > 0 ? d - 1 : 1);
+    for (int i = tid; i < na * kNavKeys; i += nt) cnt[i] = 0;
+    if (tid == 0) *expanded = 0;
     __syncthreads();
 
     RolloutParams RP;
@@ -737,186 +764,237 @@ __device__ void run_tile_med(const HDX_CONST LeafTask *T, const int a, unsigned 
     RP.max_depth = T->max_depth;
     RP.n_actions = T->n_actions;
     const int depth = T->depth, last_action = T->last_action;
+    const int R = rollout_length(RP, depth + 1);
     const StatesPtr parent = load_states(&T->parent);
     const StatesPtr leaf_out = load_states(&T->out);
     const StatesPtr sprime = load_states(&T->sprime);
-    const bool write_leaf = (a == 0);
     const bool pair_out = has_states(sprime);
-    // the optional per-pair outputs, tested once per tile rather than per round
-    const bool pair_vals = T->r != nullptr || T->z != nullptr || T->U != nullptr || T->L != nullptr;
 
     // -- gather + update + expand + bounds + rollouts (Eq. 10, 12, 13) ------
-    int my_exp = 0, my_roll = 0;
-    for (int base = 0; base < n; base += nt) {
-        const int k = base + tid;
+    int my_exp = 0;
+    for (int base = wid * 64; base < n; base += nt) {
+        const int k = base + lane;
         const bool valid = k < n;
-        float r = 0.0f;
+        Ops::State st;
+        Ops::make_terminal(st);
+        uint32_t id = 0;
         if (valid) {
-            const int p = T->idx[k];
-            const uint32_t id = T->parent_ids[p];
-            typename Ops::State st;
+            const uint32_t p = (uint16_t)T->idx[(uint32_t)k];
+            id = T->parent_ids[p];
             Ops::load(M, parent, p, st);
-            if (last_action >= 0) {
-                float r0;
-                uint64_t z0;
-                Ops::template step<false>(M, st, last_action, id, (uint32_t)(depth - 1), RP.k0, RP.k1, r0, z0);
+        }
+        Ops::make_rows(M, st, rows);
+        if (last_action >= 0 && !Ops::terminal(st)) {
+            float r0;
+            Ops::move(M, rows, st, last_action,
+                      last_action == 0 ? 0u : philox(id, (uint32_t)(depth - 1), 0, kTagStep, RP.k0, RP.k1).x, r0);
+        }
+        if (a0 == 0 && valid) {
+            Ops::store(M, leaf_out, k, st);
+            T->ids_out[k] = id;
+        }
+        const bool live = valid && !Ops::terminal(st);
+        my_exp += live ? 1 : 0;
+        uint32_t u_fail = 0, err = 0, around = 0;
+        if (live) {
+            u_fail = philox(id, (uint32_t)depth, 0, kTagStep, RP.k0, RP.k1).x;
+            err = Ops::reading_errors(M, id, (uint32_t)depth, RP.k0, RP.k1);
+            around = Ops::neighbours(M, rows, st.p & 15, (st.p >> 4) & 15);
+        }
+        const Ops::Target target = Ops::target_of(M, st);
+        int need = 0;  // moves of the longest walk to settle
+        for (int i = 0; i < na; ++i) {
+            const int a = a0 + i;
+            float r = 0.0f;
+            uint32_t z = Ops::kTerminalObs;
+            int d = Ops::kNoDistance, kind = Ops::kStuck, m = 0;
+            bool settled = true;
+            Ops::State s1 = st;
+            float L = 0.0f;
+            if (live) {
+                Ops::move(M, s1, a, u_fail, a == 0 ? 0 : (int)((around >> (a - 1)) & 1u), r);
+                if (!Ops::terminal(s1)) {
+                    const int x = s1.p & 15, y = (s1.p >> 4) & 15;
+                    z = Ops::neighbours(M, rows, x, y) ^ err;
+                    d = Ops::distance(M, s1);
+                    if (stepped) {
+                        if (R > 0) L = Ops::rollout_steps(M, RP, rows, s1, id, depth + 1, R, m);
+                    } else if (R > 0) {
+                        kind = Ops::walk(M, rows, target, x, y, R, m);
+                        settled = kind == Ops::kOver || m == 0;
+                        need = settled || need > m ? need : m;
+                    } else {
+                        kind = Ops::kOver;
+                    }
+                }
             }
-            if (write_leaf) {
-                Ops::store(M, leaf_out, k, st);
-                T->ids_out[k] = id;
-            }
-            my_exp += Ops::terminal(st) ? 0 : 1;
-            uint64_t z;
-            Ops::template step<true>(M, st, a, id, (uint32_t)depth, RP.k0, RP.k1, r, z);
-            const float U = Ops::upper(M, st);
-            const int64_t pk = (int64_t)a * n + k;
-            if (pair_out) Ops::store(M, sprime, pk, st);
-            int ns = 0;
-            float L;
-            if constexpr (kGroup)
-                L = Ops::rollout_grid(M, RP, st, id, depth + 1, ns);
-            else
-                L = rollout<Ops>(M, RP, st, id, depth + 1, ns);
-            my_roll += ns;
-            keyb[k] = (uint16_t)z;
-            ub[k] = U;
-            lb[k] = L;
-            if (pair_vals) {
+            if (valid) {
+                code[i * n + k] = NavCode::make(z, d, kind, settled, m);
+                if (stepped) val[i * n + k] = L;
+                const int64_t pk = (int64_t)a * n + k;
+                if (pair_out) Ops::store(M, sprime, pk, s1);
                 if (T->r) T->r[pk] = r;
                 if (T->z) T->z[pk] = z;
-                if (T->U) T->U[pk] = U;
-                if (T->L) T->L[pk] = L;
+                if (T->U) T->U[pk] = ub[d];
             }
+            // mean step reward: sum of this 64-scenario chunk (lanes past n add 0)
+            const float r_chunk = __ballot(r != 0.0f) ? wave_total(r) : 0.0f;
+            if (lane == 0) chunk_r[i * nch + (base >> 6)] = r_chunk;
         }
-        // mean step reward: sum of this 64-scenario chunk (lanes past n add 0;
-        // a chunk without a reward sums to +0 without the reduction)
-        const float r_chunk = __ballot(r != 0.0f) ? wave_total(r) : 0.0f;
-        if (lane == 0 && base + wid * 64 < n) chunk_r[(base >> 6) + wid] = r_chunk;
+        // the depth at which each walk's moves have all succeeded
+        for (int from = 0; from < R && __ballot(need > 0);) {
+            uint64_t F;
+            const int j = Ops::failures(M, id, depth + 1, from, R, need, RP.k0, RP.k1, F);
+            const int got = j - __popcll(F);
+            if (need > 0) {
+                for (int i = 0; i < na; ++i) {
+                    const uint32_t c = code[i * n + k];
+                    if (c & NavCode::kSettled) continue;
+                    const int m = NavCode::count(c);
+                    const bool done = m <= got;
+                    const int v = done ? from + Ops::depths_until(F, m) : m - got;
+                    code[i * n + k] =
+                        (c & ~(NavCode::kMax << 17)) | ((uint32_t)v << 17) | (done ? NavCode::kSettled : 0u);
+                }
+            }
+            need -= got;
+            from += j;
+        }
     }
     my_exp = wave_total_i(my_exp);
-    my_roll = wave_total_i(my_roll);
-    if (lane == 0) {
-        atomicAdd(&stepc[0], (unsigned long long)my_exp);
-        atomicAdd(&stepc[1], (unsigned long long)my_roll);
-    }
+    if (lane == 0 && my_exp) atomicAdd(expanded, my_exp);
     __syncthreads();
 
-    // -- ranks inside each wavefront's run of chunks ----------------------------
-    if (wid < runs) {
-        int32_t *cw = wcnt + wid * kMedKeys;
-        const int t_end = min(nch, (wid + 1) * run_len);
-        for (int t = wid * run_len; t < t_end; ++t) {
+    // -- grouping and per-child sums, one wavefront per action -----------------
+    for (int i = wid; i < na; i += nw) {
+        const int a = a0 + i;
+        const uint32_t *codes = code + i * n;
+        int32_t *next = cnt + i * kNavKeys;
+        uint32_t *info = meta + i * kNavKeys;
+        uint16_t *order = perm + i * n;
+        for (int k = lane; k < n; k += 64) atomicAdd(&next[NavCode::obs(codes[k])], 1);
+        wave_fence();
+        // lane l owns keys 5 l .. 5 l + 4: packed scenario count and presence
+        constexpr int kPer = (kNavKeys + 63) / 64;
+        int c[kPer], sum = 0;
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) {
+            const int v = lane * kPer + e;
+            c[e] = v < kNavKeys ? next[v] : 0;
+            sum += c[e] + (c[e] > 0 ? 1 << 16 : 0);
+        }
+        int incl = sum;
+        incl += dpp_srci<0x111, 0xf>(incl);
+        incl += dpp_srci<0x112, 0xf>(incl);
+        incl += dpp_srci<0x114, 0xf>(incl);
+        incl += dpp_srci<0x118, 0xf>(incl);
+        incl += dpp_srci<0x142, 0xa>(incl);
+        incl += dpp_srci<0x143, 0xc>(incl);
+        int run = incl - sum;
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) {
+            const int v = lane * kPer + e;
+            if (c[e] > 0) {
+                const int o = run & 0xFFFF, ci = run >> 16;
+                next[v] = o;
+                info[v] = ((uint32_t)ci << 16) | (uint32_t)c[e];
+                if (ci < cap) {
+                    const int64_t q = (int64_t)a * cap + ci;
+                    T->child_z[q] = (uint64_t)v;
+                    T->child_n[q] = c[e];
+                    T->child_off[q] = o;
+                }
+                run += c[e] + (1 << 16);
+            }
+        }
+        if (lane == 63) T->n_children[a] = incl >> 16;
+        wave_fence();
+        int32_t *const child_of = T->child_of;
+        for (int t = 0; t < nch; ++t) {
             const int k = t * 64 + lane;
             const bool valid = k < n;
-            const uint32_t key = valid ? keyb[k] : 0xFFFFFFFFu;
-            uint64_t rem = __ballot(valid);
-            int rank = 0;
-            while (rem) {
-                const int leader = __ffsll((unsigned long long)rem) - 1;
-                const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)key, leader);
-                const bool mine = key == v;
-                const uint64_t bv = __ballot(mine);
-                const int before = cw[v];  // one address: a broadcast read
-                if (mine) rank = before + __popcll(bv & __lanemask_lt());
-                if (lane == leader) cw[v] = before + __popcll(bv);
-                rem &= ~bv;
-            }
-            if (valid) rnk[k] = (uint16_t)rank;
-        }
-    }
-    __syncthreads();
-
-    // -- per key: count in earlier runs, total, child offset and index ----------
-    // koff packs the count (low 16 bits, at most kMaxMedLeaf) and presence
-    // (high bits) so one exclusive scan gives both the offset and the index.
-    for (int v = tid; v < kMedKeys; v += nt) {
-        int run = 0;
-        for (int w = 0; w < runs; ++w) {
-            const int c = wcnt[w * kMedKeys + v];
-            wcnt[w * kMedKeys + v] = run;
-            run += c;
-        }
-        kcnt[v] = run;
-        koff[v] = run + (run > 0 ? (1 << 16) : 0);
-    }
-    __syncthreads();
-    block_exclusive_scan(koff, kMedKeys, scan_scratch);
-    const int last = kMedKeys - 1;
-    const int D = (koff[last] >> 16) + (kcnt[last] > 0 ? 1 : 0);
-    for (int v = tid; v < kMedKeys; v += nt) {
-        const int packed = koff[v];
-        const int c = kcnt[v];
-        const int o = packed & 0xFFFF, ci = packed >> 16;
-        koff[v] = o;
-        kci[v] = ci;
-        if (c > 0) {
-            cof[ci] = o;
-            cnc[ci] = c;
-            if (ci < cap) {
-                const int64_t q = (int64_t)a * cap + ci;
-                T->child_z[q] = (uint64_t)v;
-                T->child_n[q] = c;
-                T->child_off[q] = o;
-            }
-        }
-    }
-    if (tid == 0) T->n_children[a] = D;
-    __syncthreads();
-
-    // -- grouped order: child offset + count in earlier runs + rank -------------
-    for (int k = tid; k < n; k += nt) {
-        const int v = keyb[k];
-        const int w = (k >> 6) / run_len;
-        permb[koff[v] + wcnt[w * kMedKeys + v] + rnk[k]] = (int16_t)k;
-        if (T->child_of) T->child_of[(int64_t)a * n + k] = kci[v];
-    }
-    __syncthreads();
-    for (int i = tid; i < n; i += nt) T->perm[(int64_t)a * n + i] = permb[i];
-
-    // -- per-child sums: segmented wavefront scans over the grouped order ------
-    for (int t = wid; t < nch; t += nw) {
-        const int i = t * 64 + lane;
-        const bool valid = i < n;
-        const int k = valid ? permb[i] : 0;
-        float vu = valid ? ub[k] : 0.0f;
-        float vl = valid ? lb[k] : 0.0f;
-        const int c = valid ? (int)keyb[k] : -1;
-        const int c_prev = __shfl_up(c, 1, 64);
-        bool head = (lane == 0) || (c_prev != c);
+            const uint32_t key = valid ? NavCode::obs(codes[k]) : 511u;
+            // the lanes of this chunk with the same key
+            uint64_t same = ~0ull;
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const float ou = __shfl_up(vu, d, 64);
-            const float ol = __shfl_up(vl, d, 64);
-            const int oh = __shfl_up((int)head, d, 64);
-            if (lane >= d && !head) {
-                vu = ou + vu;
-                vl = ol + vl;
-                head = oh != 0;
+            for (int b = 0; b < 9; ++b) {
+                const bool on = (key >> b) & 1u;
+                const uint64_t bal = __ballot(on);
+                same &= on ? bal : ~bal;
             }
+            const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+            if (valid) {
+                const int at = next[key] + rank;
+                order[at] = (uint16_t)k;
+                if (child_of) child_of[(int64_t)a * n + k] = (int32_t)(info[key] >> 16);
+                wave_fence();
+                if (rank == 0) next[key] = at + __popcll(same);
+            }
+            wave_fence();
         }
-        if (valid) {
-            su[i] = vu;
-            sl[i] = vl;
+        int steps = 0;
+        float carry_u = 0.0f, carry_l = 0.0f;  // sums so far of a child that the last chunk did not end
+        for (int t = 0; t < nch; ++t) {
+            const int q = t * 64 + lane;
+            const bool valid = q < n;
+            const int k = valid ? order[q] : 0;
+            const uint32_t cd = codes[k];
+            const uint32_t key = NavCode::obs(cd);
+            float u = 0.0f, l = 0.0f;
+            int end = 0;
+            uint32_t inf = 0;
+            if (valid) {
+                end = next[key];
+                inf = info[key];
+                u = ub[NavCode::dist(cd)];
+                int s = 0;
+                if (NavCode::dist(cd) != Ops::kNoDistance) {
+                    if (stepped) {
+                        l = val[i * n + k];
+                        s = NavCode::count(cd);
+                    } else {
+                        const int kind = (cd & NavCode::kSettled) ? NavCode::kind(cd) : (int)Ops::kOver;
+                        l = Ops::walk_value(kind, NavCode::count(cd), R,
+                                            [&](int j) { return j <= kNavSums ? gsum[j] : M.gpow_sum(j); }, s);
+                    }
+                }
+                steps += s;
+                T->perm[(int64_t)a * n + q] = (int16_t)k;
+                if (T->L) T->L[(int64_t)a * n + k] = l;
+            }
+            const int count = (int)(inf & 0xFFFFu);
+            const int start = end - count;  // the child's first place
+            int f = (!valid || q == start || lane == 0) ? 1 : 0;
+            const bool carried = start < t * 64;  // the child began in an earlier chunk
+            seg_step<0x111, 0xf>(u, l, f);
+            seg_step<0x112, 0xf>(u, l, f);
+            seg_step<0x114, 0xf>(u, l, f);
+            seg_step<0x118, 0xf>(u, l, f);
+            seg_step<0x142, 0xa>(u, l, f);
+            seg_step<0x143, 0xc>(u, l, f);
+            if (valid && carried) {
+                u = carry_u + u;
+                l = carry_l + l;
+            }
+            if (valid && q + 1 == end) {
+                const int ci = (int)(inf >> 16);
+                if (ci < cap) {
+                    T->child_u0[(int64_t)a * cap + ci] = u / (float)count;
+                    T->child_l0[(int64_t)a * cap + ci] = l / (float)count;
+                }
+            }
+            carry_u = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(u), 63));
+            carry_l = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l), 63));
         }
-    }
-    __syncthreads();
-    for (int c = tid; c < D && c < cap; c += nt) {
-        const int start = cof[c], end = start + cnc[c];
-        float tu = 0.0f, tl = 0.0f;
-        for (int t = start >> 6; t <= (end - 1) >> 6; ++t) {
-            const int e = min(end, (t + 1) * 64) - 1;
-            tu = tu + su[e];
-            tl = tl + sl[e];
+        steps = wave_total_i(steps);
+        if (lane == 0) {
+            float tr = 0.0f;
+            for (int t = 0; t < nch; ++t) tr = tr + chunk_r[i * nch + t];
+            T->r_mean[a] = n > 0 ? tr / (float)n : 0.0f;
+            T->steps[2 * a + 0] = (int64_t)*expanded;
+            T->steps[2 * a + 1] = (int64_t)steps;
         }
-        T->child_u0[(int64_t)a * cap + c] = tu / (float)cnc[c];
-        T->child_l0[(int64_t)a * cap + c] = tl / (float)cnc[c];
-    }
-    if (tid == 0) {
-        float tr = 0.0f;
-        for (int t = 0; t < nch; ++t) tr = tr + chunk_r[t];
-        T->r_mean[a] = n > 0 ? tr / (float)n : 0.0f;
-        T->steps[2 * a + 0] = (int64_t)stepc[0];
-        T->steps[2 * a + 1] = (int64_t)stepc[1];
     }
     __syncthreads();  // LDS is reused by the next tile
 }
@@ -936,7 +1014,7 @@ __device__ __forceinline__ int remap_xcd(int b, int grid) {
 // MODE 0: RockSample only; 1: crowd driving only; 2: both; 3: multi-agent
 // RockSample only; 4: navigation only.  Workgroups of the driving model are
 // capped at 256 lanes so its per-lane state can stay in registers;
-// navigation (83 registers) takes up to 1024, because one large leaf's LDS
+// navigation (94 registers) takes up to 1024, because one large leaf's LDS
 // carve-up leaves room for one workgroup per CU.
 template <int MODE>
 constexpr bool small_obs_mode() { return MODE == 0 || MODE == 3; }
@@ -949,10 +1027,10 @@ constexpr int min_waves() { return small_obs_mode<MODE>() ? 7 : 1; }
 
 template <int MODE, int PM, bool kGroup = false>
 __device__ __forceinline__ void run_mode(const HDX_CONST LeafTask *T, int a, unsigned char *lds, const LdsLayout &Ly) {
-    if (MODE == 3) {
+    if constexpr (MODE == 3) {
         run_tile<MarsOps>(T, a, lds, Ly);
-    } else if (MODE == 4) {
-        run_tile_med<NavOps, kGroup>(T, a, lds, make_med_layout(Ly.np));
+    } else if constexpr (MODE == 4) {
+        run_tile_nav(T, a, min((int)T->tile_actions, T->n_actions - a), lds);
     } else if (MODE == 0 || (MODE == 2 && T->kind == HDX_ROCKSAMPLE)) {
         run_tile<RsOps>(T, a, lds, Ly);
     } else {
@@ -1018,13 +1096,17 @@ __global__ __launch_bounds__(max_threads<MODE>()) void expand_args(const ArgPack
     int i = 0;
     while (i + 1 < n_leaves && t >= P->tile_begin[i + 1]) ++i;
     const HDX_CONST LeafTask *T = &P->t[i];
-    run_mode<MODE, PM, true>(T, t - P->tile_begin[i], lds, Ly);
+    run_mode<MODE, PM, true>(T, (t - P->tile_begin[i]) * T->tile_actions, lds, Ly);
 }
 
-// Dynamic LDS of one workgroup for leaves of up to n_max scenarios.
+// Dynamic LDS of one workgroup for leaves of up to n_max scenarios (and, for
+// navigation, tiles of up to `pairs` pairs).
 template <int MODE>
-uint32_t lds_bytes(int32_t n_max) {
-    return MODE == 4 ? make_med_layout(n_max).total : make_layout(n_max, small_obs_mode<MODE>()).total;
+uint32_t lds_bytes(int32_t n_max, int32_t pairs, int32_t threads) {
+    if (MODE != 4) return make_layout(n_max, small_obs_mode<MODE>()).total;
+    const uint32_t b = make_nav_layout((uint32_t)pairs, kNavActions, (uint32_t)(n_max + 63) / 64, (uint32_t)threads / 64,
+                                       false).total;
+    return std::min(b, (uint32_t)max_dynamic_lds());
 }
 
 template <int MODE, int PM>
@@ -1032,7 +1114,7 @@ hipError_t configure_t() {
     hipError_t e = hipFuncSetAttribute((const void *)expand_tiles<MODE, PM>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, max_dynamic_lds());
     if (e != hipSuccess) return e;
-    if (MODE == 1) {
+    if constexpr (MODE == 1) {
         e = hipFuncSetAttribute((const void *)expand_tiles<MODE, PM, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 max_dynamic_lds());
         if (e != hipSuccess) return e;
@@ -1046,21 +1128,22 @@ hipError_t launch_args_t(const ArgPack &pack, const Schedule &sch, hipStream_t s
     const int grid = pack.tile_begin[pack.n_leaves];
     if (grid < 1) return hipSuccess;
     const int threads = sch.threads > max_threads<MODE>() ? max_threads<MODE>() : sch.threads;
-    hipLaunchKernelGGL((expand_args<MODE, PM>), dim3(grid), dim3(threads), lds_bytes<MODE>(pack.n_max), stream,
+    hipLaunchKernelGGL((expand_args<MODE, PM>), dim3(grid), dim3(threads),
+                       lds_bytes<MODE>(pack.n_max, pack.pairs, threads), stream,
                        pack);
     return hipGetLastError();
 }
 
 template <int MODE, int PM, bool kGroup = false>
 hipError_t launch_expand_t(const LeafTask *d_tasks, const Tile *d_tiles, TileQueue *d_queue, int32_t n_tiles,
-                           int32_t n_max, const Schedule &sch, int32_t n_cu, hipStream_t stream) {
+                           int32_t n_max, int32_t pairs, const Schedule &sch, int32_t n_cu, hipStream_t stream) {
     // persistent: a fixed grid that drains the tile queue, so a captured
     // graph stays valid for any tile count
     const int grid = sch.persistent > 0 ? n_cu * sch.persistent : n_tiles;
     if (grid < 1) return hipSuccess;
     const int threads = sch.threads > max_threads<MODE>() ? max_threads<MODE>() : sch.threads;
-    hipLaunchKernelGGL((expand_tiles<MODE, PM, kGroup>), dim3(grid), dim3(threads), lds_bytes<MODE>(n_max), stream, d_tasks,
-                       d_tiles, d_queue, n_max, sch.persistent > 0 ? 1 : 0, sch.xcd_remap);
+    hipLaunchKernelGGL((expand_tiles<MODE, PM, kGroup>), dim3(grid), dim3(threads),
+                       lds_bytes<MODE>(n_max, pairs, threads), stream, d_tasks, d_tiles, d_queue, n_max, sch.persistent > 0 ? 1 : 0, sch.xcd_remap);
     return hipGetLastError();
 }
 
@@ -1140,17 +1223,7 @@ __global__ void sample_kernel(const SampleArgs *args) {
 // ---------------------------------------------------------------------------
 // rollout_bounds: one lane per state
 // ---------------------------------------------------------------------------
-template <class Ops>
-__global__ __launch_bounds__(256) void bounds_kernel(const BoundsArgs A) {
-    __shared__ float gpow_lds[kModelLdsFloats];
-    stage_gpow(A.model, gpow_lds);
-    if constexpr (std::is_same<Ops, NavOps>::value) stage_cells(A.model, gpow_lds);
-    __syncthreads();
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= A.n) return;
-    const MView M = make_view(A.model, gpow_lds);
-    typename Ops::State st;
-    Ops::load(M, A.states, k, st);
+__device__ __forceinline__ RolloutParams bounds_params(const BoundsArgs &A, const MView &M) {
     RolloutParams RP;
     RP.k0 = A.k0;
     RP.k1 = A.k1;
@@ -1159,9 +1232,47 @@ __global__ __launch_bounds__(256) void bounds_kernel(const BoundsArgs A) {
     RP.max_steps = A.max_steps;
     RP.max_depth = A.max_depth;
     RP.n_actions = M.h->n_actions;
+    return RP;
+}
+
+template <class Ops>
+__global__ __launch_bounds__(256) void bounds_kernel(const BoundsArgs A) {
+    __shared__ float gpow_lds[kModelLdsFloats];
+    stage_gpow(A.model, gpow_lds);
+    __syncthreads();
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= A.n) return;
+    const MView M = make_view(A.model, gpow_lds);
+    typename Ops::State st;
+    Ops::load(M, A.states, k, st);
+    const RolloutParams RP = bounds_params(A, M);
     int ns = 0;
     A.U[k] = Ops::upper(M, st);
     A.L[k] = rollout<Ops>(M, RP, st, A.ids[k], A.depths[k], ns);
+    if (A.steps) A.steps[k] = ns;
+}
+
+// Navigation: the map's rows in LDS, the wavefront's lanes together.
+__global__ __launch_bounds__(256) void bounds_nav(const BoundsArgs A) {
+    __shared__ float gpow_lds[kModelLdsFloats];
+    __shared__ uint32_t rows_lds[4 * kNavRowBytes / 4];
+    stage_gpow(A.model, gpow_lds);
+    __syncthreads();
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const bool valid = k < A.n;
+    const MView M = make_view(A.model, gpow_lds);
+    NavOps::State st;
+    NavOps::make_terminal(st);
+    if (valid) NavOps::load(M, A.states, k, st);
+    uint32_t *rows = rows_lds + (threadIdx.x >> 6) * (kNavRowBytes / 4) + lane_id();
+    NavOps::make_rows(M, st, rows);
+    const RolloutParams RP = bounds_params(A, M);
+    const int d0 = valid ? A.depths[k] : 0;
+    int ns = 0;
+    const float L = NavOps::rollout(M, RP, rows, st, valid ? A.ids[k] : 0u, d0, rollout_length(RP, d0), valid, ns);
+    if (!valid) return;
+    A.U[k] = NavOps::upper(M, st);
+    A.L[k] = L;
     if (A.steps) A.steps[k] = ns;
 }
 
@@ -1196,6 +1307,18 @@ hipError_t launch_fp32_selftest(const float *a, const float *b, const float *c, 
 
 int32_t max_dynamic_lds() { return 160 * 1024 - 256; }
 
+int32_t nav_tile_actions(int32_t n, int32_t policy, int32_t most) {
+    const bool stepped = policy != HDX_POLICY_DEFAULT;
+    const uint32_t chunks = (uint32_t)(n + 63) / 64;
+    for (int32_t w = most; w > 1; --w) {
+        // the launch reserves counters for all nine actions
+        const uint32_t pairs = (uint32_t)(w * n) * (stepped ? 2u : 1u);
+        if (kNavActions % w == 0 && make_nav_layout(pairs, kNavActions, chunks, 16, false).total <= (uint32_t)max_dynamic_lds())
+            return w;
+    }
+    return 1;
+}
+
 Variant pick_variant(int32_t has_rs, int32_t has_ped, int32_t ped_max, int32_t n_max, int32_t has_mars,
                      int32_t has_nav) {
     Variant v;
@@ -1225,8 +1348,8 @@ hipError_t configure_expand_kernels() {
 
 hipError_t launch_expand(const LeafTask *d_tasks, const Tile *d_tiles, TileQueue *d_queue, int32_t n_tiles,
                          const Variant &v, const Schedule &sch, int32_t n_cu, hipStream_t stream) {
-#define HDX_LAUNCH(M, P) launch_expand_t<M, P>(d_tasks, d_tiles, d_queue, n_tiles, v.n_max, sch, n_cu, stream)
-#define HDX_LAUNCH_G(P) launch_expand_t<1, P, true>(d_tasks, d_tiles, d_queue, n_tiles, v.n_max, sch, n_cu, stream)
+#define HDX_LAUNCH(M, P) launch_expand_t<M, P>(d_tasks, d_tiles, d_queue, n_tiles, v.n_max, v.pairs, sch, n_cu, stream)
+#define HDX_LAUNCH_G(P) launch_expand_t<1, P, true>(d_tasks, d_tiles, d_queue, n_tiles, v.n_max, v.pairs, sch, n_cu, stream)
     if (v.mode == 0) return HDX_LAUNCH(0, 1);
     if (v.mode == 3) return HDX_LAUNCH(3, 1);
     if (v.mode == 4) return HDX_LAUNCH(4, 1);
@@ -1265,7 +1388,7 @@ hipError_t launch_bounds(const BoundsArgs &args, int32_t kind, int32_t n_peds, h
     } else if (kind == HDX_MARS) {
         hipLaunchKernelGGL(bounds_kernel<MarsOps>, dim3((unsigned)blocks), dim3(threads), 0, stream, args);
     } else if (kind == HDX_NAV) {
-        hipLaunchKernelGGL(bounds_kernel<NavOps>, dim3((unsigned)blocks), dim3(threads), 0, stream, args);
+        hipLaunchKernelGGL(bounds_nav, dim3((unsigned)blocks), dim3(threads), 0, stream, args);
     } else if (n_peds <= 8) {
         hipLaunchKernelGGL(bounds_kernel<PedOps<8>>, dim3((unsigned)blocks), dim3(threads), 0, stream, args);
     } else if (n_peds <= 16) {

@@ -34,11 +34,12 @@ struct MView {
     const HDX_CONST ModelHdr *h;
     const HDX_CONST uint32_t *thr;
     const HDX_CONST float *gg;
+    const HDX_CONST double *gs;
     const float *gl;
-    const int16_t *cl;  // navigation cell table, staged in LDS after the goal points
-    const uint8_t *up;  // navigation: grid bit of each unknown cell, staged after the cell table
     __device__ float gpow_uniform(int j) const { return gg[j]; }
     __device__ float gpow_lane(int j) const { return j < kGpowLds ? gl[j] : gg[j]; }
+    // 1 + gamma + ... + gamma^(j-1), j = 0..kHorizon
+    __device__ double gpow_sum(int j) const { return gs[j]; }
     // goal point coordinates, staged in LDS after the discount powers
     __device__ float goal_x(int g) const { return gl[kGpowLds + g]; }
     __device__ float goal_y(int g) const { return gl[kGpowLds + kMaxGoals + g]; }
@@ -49,9 +50,8 @@ __device__ __forceinline__ MView make_view(const DevModel *gm, const float *gpow
     v.h = (const HDX_CONST ModelHdr *)&gm->h;
     v.thr = (const HDX_CONST uint32_t *)gm->sense_thr_m1;
     v.gg = (const HDX_CONST float *)gm->gpow;
+    v.gs = (const HDX_CONST double *)gm->gsum;
     v.gl = gpow_lds;
-    v.cl = (const int16_t *)(gpow_lds + kGpowLds + 2 * kMaxGoals);
-    v.up = (const uint8_t *)(v.cl + HDX_MAX_NAV_GRID * HDX_MAX_NAV_GRID);
     return v;
 }
 
@@ -68,11 +68,9 @@ __device__ __forceinline__ StatesPtr load_states(const HDX_CONST StatesPtr *s) {
 }
 
 // Stage the first kGpowLds discount powers and the goal points of a model
-// into LDS, and for navigation its cell table and the unknown cells' grid
-// bits after them (kModelLdsFloats floats in all; the caller synchronises
+// into LDS (kModelLdsFloats floats in all; the caller synchronises
 // afterwards).
-constexpr int kNavCells = HDX_MAX_NAV_GRID * HDX_MAX_NAV_GRID;
-constexpr int kModelLdsFloats = kGpowLds + 2 * kMaxGoals + kNavCells / 2 + HDX_MAX_NAV_UNKNOWN / 4;
+constexpr int kModelLdsFloats = kGpowLds + 2 * kMaxGoals;
 __device__ __forceinline__ void stage_gpow(const DevModel *gm, float *gpow_lds) {
     const HDX_CONST float *g = (const HDX_CONST float *)gm->gpow;
     const HDX_CONST ModelHdr *h = (const HDX_CONST ModelHdr *)&gm->h;
@@ -83,14 +81,6 @@ __device__ __forceinline__ void stage_gpow(const DevModel *gm, float *gpow_lds) 
         else v = h->goal_y[j - kGpowLds - kMaxGoals];
         gpow_lds[j] = v;
     }
-}
-// The navigation cell table, after the goal points (navigation kernels only).
-__device__ __forceinline__ void stage_cells(const DevModel *gm, float *gpow_lds) {
-    const HDX_CONST ModelHdr *h = (const HDX_CONST ModelHdr *)&gm->h;
-    int16_t *cells = (int16_t *)(gpow_lds + kGpowLds + 2 * kMaxGoals);
-    for (int c = threadIdx.x; c < kNavCells; c += blockDim.x) cells[c] = h->nav_cell[c];
-    uint8_t *pos = (uint8_t *)(cells + kNavCells);
-    for (int c = threadIdx.x; c < HDX_MAX_NAV_UNKNOWN; c += blockDim.x) pos[c] = h->nav_unknown_pos[c];
 }
 
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds of two
@@ -491,220 +481,260 @@ struct NavOps {
         int32_t p;
         uint32_t m0, m1, m2, m3;
     };
-    static constexpr bool kHashObs = true;
-    static constexpr bool kSplitRollout = true;
-    static constexpr bool kSmallObs = false;  // 8 reading bits: 256 observations
-    static constexpr bool kLdsModel = true;   // discount powers staged in LDS
-    static constexpr bool kWaveUpper = false;
-    static constexpr bool kGroupRollout = false;
-    struct WaveUpper {};
     static constexpr uint32_t kDx = nav_pack_dir(false), kDy = nav_pack_dir(true);
     static constexpr uint64_t kAction = nav_action_table();
-    static constexpr uint64_t kTerminalObs = 256;
+    static constexpr uint32_t kTerminalObs = 256;
 
-    __device__ static int dx(int a) { return (int)((kDx >> (2 * a)) & 3u) - 1; }
-    __device__ static int dy(int a) { return (int)((kDy >> (2 * a)) & 3u) - 1; }
+    __device__ __forceinline__ static int dx(int a) { return (int)((kDx >> (2 * a)) & 3u) - 1; }
+    __device__ __forceinline__ static int dy(int a) { return (int)((kDy >> (2 * a)) & 3u) - 1; }
 
-    __device__ static void load(const MView &, const StatesPtr &S, int64_t p, State &st) {
+    __device__ __forceinline__ static void load(const MView &, const StatesPtr &S, int64_t p, State &st) {
         st.p = S.w[p];
         st.m0 = (uint32_t)S.w[S.stride + p];
         st.m1 = (uint32_t)S.w[2 * S.stride + p];
         st.m2 = (uint32_t)S.w[3 * S.stride + p];
         st.m3 = (uint32_t)S.w[4 * S.stride + p];
     }
-    __device__ static void make_terminal(State &st) {
+    __device__ __forceinline__ static void make_terminal(State &st) {
         st.p = 1 << 30;
         st.m0 = st.m1 = st.m2 = st.m3 = 0;
     }
-    __device__ static void store(const MView &, const StatesPtr &S, int64_t p, const State &st) {
+    __device__ __forceinline__ static void store(const MView &, const StatesPtr &S, int64_t p, const State &st) {
         S.w[p] = st.p;
         S.w[S.stride + p] = (int32_t)st.m0;
         S.w[2 * S.stride + p] = (int32_t)st.m1;
         S.w[3 * S.stride + p] = (int32_t)st.m2;
         S.w[4 * S.stride + p] = (int32_t)st.m3;
     }
-    __device__ static bool terminal(const State &st) { return (st.p >> 30) & 1; }
+    __device__ __forceinline__ static bool terminal(const State &st) { return (st.p >> 30) & 1; }
 
-    // The scenario's map as bits 16 y + x (a wall or an occupied unknown
-    // cell), built once for a rollout: the walls from the model, then the
-    // grid bit of each occupied unknown cell.
-    struct Grid {
-        uint64_t w0, w1, w2, w3;
-    };
-    __device__ static Grid grid_of(const MView &M, const State &st) {
-        Grid g{M.h->nav_wall_bits[0], M.h->nav_wall_bits[1], M.h->nav_wall_bits[2], M.h->nav_wall_bits[3]};
-        const uint32_t words[4] = {st.m0, st.m1, st.m2, st.m3};
+    // The scenario's map as rows of 16 cells (a set bit: a wall, an occupied
+    // unknown cell, or a cell off the map), two rows per word, held in LDS:
+    // word h of this lane at rows[64 h], so 64 lanes read 64 banks whatever
+    // rows they look at.  A test of a cell is then one LDS read and a shift,
+    // with no table of cells; the unknown cells are moved to their grid
+    // places by runs of consecutive cells (a field extract and a shift each).
+    __device__ __forceinline__ static void make_rows(const MView &M, const State &st, uint32_t *rows) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            uint32_t w = words[q];
-            while (w) {
-                const int c = 32 * q + __builtin_ctz(w);
-                w &= w - 1u;
-                const int bit = M.up[c];
-                const uint64_t b = 1ull << (bit & 63);
-                const int h = bit >> 6;
-                g.w0 |= h == 0 ? b : 0ull;
-                g.w1 |= h == 1 ? b : 0ull;
-                g.w2 |= h == 2 ? b : 0ull;
-                g.w3 |= h == 3 ? b : 0ull;
+        for (int h = 0; h < 8; ++h) {
+            uint32_t g = M.h->nav_wall_rows[h];
+            const int end = M.h->nav_run_begin[h + 1];
+            for (int i = M.h->nav_run_begin[h]; i < end; ++i) {
+                const uint32_t d = M.h->nav_runs[i];
+                const uint32_t q = (d >> 15) & 3u;
+                const uint32_t src = q < 2 ? (q == 0 ? st.m0 : st.m1) : (q == 2 ? st.m2 : st.m3);
+                g |= __builtin_amdgcn_ubfe(src, d & 31u, (d >> 5) & 31u) << ((d >> 10) & 31u);
             }
+            rows[64 * h] = g;
         }
-        return g;
     }
-    __device__ static int occupied_grid(const MView &M, const Grid &g, int x, int y) {
+    __device__ __forceinline__ static uint32_t row(const uint32_t *rows, int y) {
+        return (rows[64 * (y >> 1)] >> (16 * (y & 1))) & 0xffffu;
+    }
+    __device__ __forceinline__ static int occupied(const MView &M, const uint32_t *rows, int x, int y) {
         const int n = M.h->grid;
         if (x < 0 || y < 0 || x >= n || y >= n) return 1;
-        const int bit = 16 * y + x;
-        const uint64_t lo = bit < 64 ? g.w0 : g.w1, hi = bit < 192 ? g.w2 : g.w3;
-        return (int)(((bit < 128 ? lo : hi) >> (bit & 63)) & 1u);
+        return (int)((row(rows, y) >> x) & 1u);
     }
-
-    // Occupied in this scenario; off the map counts as occupied.
-    __device__ static int occupied(const MView &M, const State &st, int x, int y) {
-        const int n = M.h->grid;
-        if (x < 0 || y < 0 || x >= n || y >= n) return 1;
-        const int c = M.cl[y * n + x];
-        if (c < 0) return c == -2 ? 1 : 0;
-        // two 64-bit halves and a select: a four-way select chain becomes a
-        // private array indexed by c / 32 (scratch memory)
-        const uint64_t lo = (uint64_t)st.m0 | ((uint64_t)st.m1 << 32);
-        const uint64_t hi = (uint64_t)st.m2 | ((uint64_t)st.m3 << 32);
-        const uint64_t half = c < 64 ? lo : hi;
-        return (int)((half >> (c & 63)) & 1u);
+    // The eight neighbours of (x, y), bit j that of action j + 1 (1 =
+    // occupied; off the map reads occupied).
+    __device__ __forceinline__ static uint32_t neighbours(const MView &M, const uint32_t *rows, int x, int y) {
+        const uint32_t up = y > 0 ? row(rows, y - 1) : 0xffffu;
+        const uint32_t dn = y + 1 < M.h->grid ? row(rows, y + 1) : 0xffffu;
+        const uint32_t edge = 0x20001u;  // the columns left of 0 and right of 15
+        const uint32_t u = ((up << 1) | edge) >> x, m = ((row(rows, y) << 1) | edge) >> x, d = ((dn << 1) | edge) >> x;
+        return ((u >> 1) & 3u) | (m & 4u) | ((d & 4u) << 1) | ((d & 2u) << 3) | ((d & 1u) << 5) | ((m & 1u) << 6) |
+               ((u & 1u) << 7);
     }
 
     // The motion of a step from a live state, with the failure word (word 0
-    // of the step block) already drawn (a stay draws none) and the cells'
-    // occupancy given by occ(x, y).
-    template <class Occ>
-    __device__ static void move(const MView &M, State &st, int a, uint32_t u_fail, float &r, const Occ &occ) {
+    // of the step block) already drawn (a stay draws none) and the occupancy
+    // of the cell the action heads for.
+    __device__ __forceinline__ static void move(const MView &M, State &st, int a, uint32_t u_fail, int blocked, float &r) {
         int x = st.p & 15, y = (st.p >> 4) & 15;
         int term = 0;
         if (a == 0) {
             r = -0.2f;
         } else if ((uint64_t)u_fail < M.h->fail_thr) {
             r = -0.1f;  // the move fails: the robot stays
+        } else if (blocked) {
+            r = -1.0f;  // crash: the robot stays
         } else {
-            const int tx = x + dx(a), ty = y + dy(a);
-            if (occ(tx, ty)) {
-                r = -1.0f;  // crash: the robot stays
+            x += dx(a);
+            y += dy(a);
+            if (x == M.h->nav_goal_x && y == M.h->grid - 1) {
+                r = 20.0f;
+                term = 1;
             } else {
-                x = tx;
-                y = ty;
-                if (x == M.h->nav_goal_x && y == M.h->grid - 1) {
-                    r = 20.0f;
-                    term = 1;
-                } else {
-                    r = -0.1f;
-                }
+                r = -0.1f;
             }
         }
         st.p = x | (y << 4) | (term << 30);
     }
+    __device__ __forceinline__ static void move(const MView &M, const uint32_t *rows, State &st, int a, uint32_t u_fail, float &r) {
+        move(M, st, a, u_fail, a == 0 ? 0 : occupied(M, rows, (st.p & 15) + dx(a), ((st.p >> 4) & 15) + dy(a)), r);
+    }
 
-    template <bool kObs>
-    __device__ static void step(const MView &M, State &st, int a, uint32_t id, uint32_t depth, uint32_t k0,
-                                uint32_t k1, float &r, uint64_t &z) {
-        r = 0.0f;
-        z = kTerminalObs;
-        if ((st.p >> 30) & 1) return;  // absorbing
-        const State s0 = st;
-        move(M, st, a, a == 0 ? 0u : philox(id, depth, 0, kTagStep, k0, k1).x, r,
-             [&](int cx, int cy) { return occupied(M, s0, cx, cy); });
-        if (!kObs || ((st.p >> 30) & 1)) return;
-        const int x = st.p & 15, y = (st.p >> 4) & 15;
+    // The bits of a reading that are flipped (blocks 1 and 2 of the step).
+    __device__ __forceinline__ static uint32_t reading_errors(const MView &M, uint32_t id, uint32_t depth, uint32_t k0, uint32_t k1) {
         const uint4 b1 = philox(id, depth, 1, kTagStep, k0, k1);
         const uint4 b2 = philox(id, depth, 2, kTagStep, k0, k1);
         const uint32_t words[8] = {b1.x, b1.y, b1.z, b1.w, b2.x, b2.y, b2.z, b2.w};
-        uint64_t obs = 0;
+        uint32_t e = 0;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            int bit = occupied(M, st, x + dx(j + 1), y + dy(j + 1));
-            if ((uint64_t)words[j] < M.h->err_thr) bit ^= 1;
-            obs |= (uint64_t)bit << j;
-        }
-        z = obs;
+        for (int j = 0; j < 8; ++j) e |= ((uint64_t)words[j] < M.h->err_thr ? 1u : 0u) << j;
+        return e;
     }
 
     // The goal reward on the shortest 8-connected path, no costs; it is paid
     // on entering the goal, so a robot standing on it must leave and re-enter
-    // (two moves).
-    __device__ static float upper(const MView &M, const State &st) {
-        if ((st.p >> 30) & 1) return 0.0f;
+    // (two moves).  Distances are 0..15; kNoDistance marks a terminal state.
+    static constexpr int kNoDistance = 16;
+    __device__ __forceinline__ static int distance(const MView &M, const State &st) {
+        if ((st.p >> 30) & 1) return kNoDistance;
         const int ax = abs((st.p & 15) - M.h->nav_goal_x), ay = abs(((st.p >> 4) & 15) - (M.h->grid - 1));
-        const int d = ax > ay ? ax : ay;
-        return 20.0f * M.gpow_lane(d > 0 ? d - 1 : 1);
+        return ax > ay ? ax : ay;
     }
-    __device__ static float upper_wave(const MView &M, const State &st, WaveUpper &) { return upper(M, st); }
+    __device__ __forceinline__ static float bound_at(const MView &M, int d) {
+        return d == kNoDistance ? 0.0f : 20.0f * M.gpow_lane(d > 0 ? d - 1 : 1);
+    }
+    __device__ __forceinline__ static float upper(const MView &M, const State &st) { return bound_at(M, distance(M, st)); }
 
-    // Head for the open gate while above the wall, then for the goal: the
-    // diagonal step towards the target, else its vertical part, else its
-    // horizontal part, the first that lands on a free cell; else stay.
-    template <class Occ>
-    __device__ static int default_action_occ(const MView &M, const State &st, const Occ &occ) {
-        const int x = st.p & 15, y = (st.p >> 4) & 15;
-        int tx = M.h->nav_goal_x, ty = M.h->grid - 1;
-        if (y < M.h->nav_wall) {
-            const int g = !(st.m0 & 1u) ? 0 : (!(st.m0 & 2u) ? 1 : -1);
-            if (g >= 0) {
-                tx = M.h->nav_gate_x[g];
-                ty = M.h->nav_wall;
+    // The default policy heads for the open gate while above the wall, then
+    // for the goal: the diagonal step towards the target, else its vertical
+    // part, else its horizontal part, the first that lands on a free cell;
+    // else the robot stays, and as nothing changes by staying, it stays until
+    // the horizon.  It never heads for an occupied cell, so a move that fails
+    // only delays the walk, at the cost of a move.  The rollout is then
+    // settled by the walk itself -- how many moves it takes, and whether it
+    // ends at the goal or stuck; no random numbers -- and by the depth at
+    // which that many moves have succeeded, from the failure words.
+    enum { kStuck = 0, kGoal = 1, kOver = 2 };
+    struct Target {
+        bool gate;  // a gate is open: the target above the wall
+        int gx;
+    };
+    __device__ __forceinline__ static Target target_of(const MView &M, const State &st) {
+        Target t;
+        t.gate = (st.m0 & 3u) != 3u;
+        t.gx = !(st.m0 & 1u) ? M.h->nav_gate_x[0] : M.h->nav_gate_x[1];
+        return t;
+    }
+    // Moves of the walk from (x, y) until the goal, a dead end, or `limit`
+    // moves (kOver); m receives their number.  Every move goes down, or along
+    // a row towards its target.
+    __device__ __forceinline__ static int walk(const MView &M, const uint32_t *rows, const Target &t, int x, int y, int limit, int &m) {
+        const int goal = M.h->nav_goal_x, last = M.h->grid - 1, wall = M.h->nav_wall;
+        m = 0;
+        uint32_t here = row(rows, y), below = row(rows, y < 15 ? y + 1 : 15);
+        for (;;) {
+            const int tx = t.gate && y < wall ? t.gx : goal;
+            const int xs = x + (tx > x ? 1 : 0) - (tx < x ? 1 : 0);
+            const uint32_t diag = (below >> xs) & 1u, vert = (below >> x) & 1u, side = (here >> xs) & 1u;
+            const bool dn = y < last;
+            const bool down = dn && !(diag & vert);
+            const int nx = dn && !diag ? xs : down ? x : side ? x : xs;
+            if (!down && nx == x) return kStuck;
+            ++m;
+            x = nx;
+            if (down) {
+                ++y;
+                here = below;
+                below = row(rows, y < 15 ? y + 1 : 15);
             }
+            if (x == goal && y == last) return kGoal;
+            if (m >= limit) return kOver;
         }
-        const int sx = tx > x ? 1 : (tx < x ? -1 : 0), sy = ty > y ? 1 : (ty < y ? -1 : 0);
-        const int cx[3] = {sx, 0, sx}, cy[3] = {sy, sy, 0};
+    }
+
+    // Failures of the moves at depths d0 + base, ... (at most 64), as bits,
+    // until `need` moves have succeeded on every lane or n_roll depths are
+    // drawn; returns the depths drawn (the same for the wavefront).
+    __device__ __forceinline__ static int failures(const MView &M, uint32_t id, int d0, int base, int n_roll, int need, uint32_t k0,
+                                   uint32_t k1, uint64_t &F) {
+        F = 0;
+        int j = 0;
+        while (j < 64 && base + j < n_roll && __ballot(j - __popcll(F) < need)) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            if (cx[c] == 0 && cy[c] == 0) continue;
-            if (occ(x + cx[c], y + cy[c])) continue;
-            return (int)((kAction >> (4 * ((cy[c] + 1) * 3 + cx[c] + 1))) & 15u);
+            for (int e = 0; e < 4; ++e) {  // independent blocks in flight
+                const uint32_t u = philox(id, (uint32_t)(d0 + base + j + e), 0, kTagStep, k0, k1).x;
+                F |= ((uint64_t)u < M.h->fail_thr ? 1ull : 0ull) << (j + e);
+            }
+            j += 4;
         }
-        return 0;
+        return j;
     }
-    __device__ static int default_action(const MView &M, const State &st) {
-        return default_action_occ(M, st, [&](int cx, int cy) { return occupied(M, st, cx, cy); });
+    // Depths until the m-th success (m of them at least among the bits of F).
+    __device__ __forceinline__ static int depths_until(uint64_t F, int m) {
+        int T = m;
+        for (;;) {
+            const int t = m + __popcll(F & (T >= 64 ? ~0ull : ((1ull << T) - 1ull)));
+            if (t == T) return T;
+            T = t;
+        }
     }
 
-    // A rollout (rollout_loop's operations and order) with the map held as
-    // bits in registers for its whole length: the occupancy tests of the
-    // policy and of the moves read no table.  Shorter for the lone
-    // wavefronts of small leaves; a batch of full tiles keeps the table
-    // lookups, which need fewer registers.
-    template <int POL>
-    __device__ static float rollout_grid_p(const MView &M, const RolloutParams &P, State st, uint32_t id, int d0,
-                                           int n_roll, int &nsteps) {
-        float value = 0.0f;
-        if (n_roll <= 0 || terminal(st)) return value;
-        const Grid g = grid_of(M, st);
-        const auto occ = [&](int cx, int cy) { return occupied_grid(M, g, cx, cy); };
-        for (int j = 0; j < n_roll; ++j) {
-            if (terminal(st)) break;
-            const uint32_t depth = (uint32_t)(d0 + j);
-            int a;
-            if (POL == HDX_POLICY_CONST) {
-                a = P.const_action;
-            } else if (POL == HDX_POLICY_RANDOM) {
-                a = (int)(philox(id, depth, 0, kTagPolicy, P.k0, P.k1).x % (uint32_t)P.n_actions);
-            } else {
-                a = default_action_occ(M, st, occ);
+    // Value and steps of a rollout of at most R steps whose walk ends as
+    // `kind` after T depths (T > R: not within the rollout), from the sums
+    // S(j) = 1 + gamma + ... + gamma^(j-1).
+    template <class Sum>
+    __device__ __forceinline__ static float walk_value(int kind, int T, int R, const Sum &S, int &steps) {
+        steps = R > 0 ? R : 0;
+        if (R <= 0) return 0.0f;
+        const double move_cost = (double)-0.1f, stay_cost = (double)-0.2f;
+        const double all = S(R);
+        if (kind == kOver || T > R) return (float)(move_cost * all);
+        const double sT = S(T);
+        if (kind == kStuck) return (float)(move_cost * sT + stay_cost * (all - sT));
+        const double sE = S(T - 1);
+        steps = T;
+        return (float)(move_cost * sE + 20.0 * (sT - sE));
+    }
+
+    // A whole rollout of one state (the stand-alone bounds call; all lanes of
+    // a wavefront together, `live` those with a rollout to run).
+    __device__ __forceinline__ static float rollout(const MView &M, const RolloutParams &P, const uint32_t *rows, State st, uint32_t id,
+                                    int d0, int R, bool live, int &nsteps) {
+        nsteps = 0;
+        live = live && R > 0 && !terminal(st);
+        if (P.policy != HDX_POLICY_DEFAULT) return live ? rollout_steps(M, P, rows, st, id, d0, R, nsteps) : 0.0f;
+        int m = 0, kind = kOver;
+        if (live) kind = walk(M, rows, target_of(M, st), st.p & 15, (st.p >> 4) & 15, R, m);
+        int need = live && kind != kOver ? m : 0, T = 0, base = 0;
+        bool open = need > 0;
+        while (__ballot(open && base < R)) {
+            uint64_t F;
+            // lanes differ in d0 and R; a lane past its own R only pads
+            const int j = failures(M, id, d0, base, kHorizon, open ? need : 0, P.k0, P.k1, F);
+            const int got = j - __popcll(F);
+            if (open && need <= got) {
+                T = base + depths_until(F, need);
+                open = false;
             }
+            need -= got;
+            base += j;
+        }
+        if (open) kind = kOver;
+        if (!live) return 0.0f;
+        return walk_value(kind, T, R, [&](int j) { return M.gpow_sum(j); }, nsteps);
+    }
+
+    // Step by step, for the constant and the random policy.
+    __device__ __forceinline__ static float rollout_steps(const MView &M, const RolloutParams &P, const uint32_t *rows, State st,
+                                          uint32_t id, int d0, int n_roll, int &nsteps) {
+        float value = 0.0f;
+        for (int j = 0; j < n_roll && !terminal(st); ++j) {
+            const uint32_t depth = (uint32_t)(d0 + j);
+            const int a = P.policy == HDX_POLICY_CONST
+                              ? P.const_action
+                              : (int)(philox(id, depth, 0, kTagPolicy, P.k0, P.k1).x % (uint32_t)P.n_actions);
             float r;
-            move(M, st, a, a == 0 ? 0u : philox(id, depth, 0, kTagStep, P.k0, P.k1).x, r, occ);
+            move(M, rows, st, a, a == 0 ? 0u : philox(id, depth, 0, kTagStep, P.k0, P.k1).x, r);
             value += M.gpow_uniform(j) * r;
             ++nsteps;
         }
         return value;
     }
-    __device__ static float rollout_grid(const MView &M, const RolloutParams &P, const State &st, uint32_t id,
-                                         int d0, int &nsteps) {
-        int n_roll = P.max_steps;
-        if (P.max_depth >= 0 && P.max_depth - d0 < n_roll) n_roll = P.max_depth - d0;
-        if (n_roll > kHorizon) n_roll = kHorizon;
-        if (P.policy == HDX_POLICY_CONST) return rollout_grid_p<HDX_POLICY_CONST>(M, P, st, id, d0, n_roll, nsteps);
-        if (P.policy == HDX_POLICY_RANDOM) return rollout_grid_p<HDX_POLICY_RANDOM>(M, P, st, id, d0, n_roll, nsteps);
-        return rollout_grid_p<HDX_POLICY_DEFAULT>(M, P, st, id, d0, n_roll, nsteps);
-    }
-
 };
 
 // ---------------------------------------------------------------------------
@@ -1104,6 +1134,13 @@ struct PedOps {
     }
 };
 
+// Steps a rollout from depth d0 may take.
+__device__ __forceinline__ int rollout_length(const RolloutParams &P, int d0) {
+    int n = P.max_steps;
+    if (P.max_depth >= 0 && P.max_depth - d0 < n) n = P.max_depth - d0;
+    return n > kHorizon ? kHorizon : n;  // the discount table's length
+}
+
 // Default-policy rollout from depth d0 (Eq. 13): discounted from d0, stops
 // at a terminal state or after min(max_steps, max_depth - d0) steps; the
 // tail value past the horizon is 0.  Accumulates in FP32 in step order.
@@ -1137,9 +1174,7 @@ __device__ __forceinline__ float rollout_loop(const MView &M, const RolloutParam
 template <class Ops>
 __device__ __forceinline__ float rollout(const MView &M, const RolloutParams &P, typename Ops::State st,
                                          uint32_t id, int d0, int &nsteps) {
-    int n_roll = P.max_steps;
-    if (P.max_depth >= 0 && P.max_depth - d0 < n_roll) n_roll = P.max_depth - d0;
-    if (n_roll > kHorizon) n_roll = kHorizon;  // the discount table's length
+    const int n_roll = rollout_length(P, d0);
     if (!Ops::kSplitRollout) {
         float value = 0.0f;
         for (int j = 0; j < n_roll; ++j) {

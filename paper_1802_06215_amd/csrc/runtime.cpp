@@ -307,13 +307,30 @@ hdx_status hdx_upload_model(hdx_ctx *ctx, const hdx_model_desc *d, hdx_model **o
         h->nav_wall = d->nav_wall;
         h->nav_gate_x[0] = d->nav_gate_x[0];
         h->nav_gate_x[1] = d->nav_gate_x[1];
-        for (int c = 0; c < HDX_MAX_NAV_GRID * HDX_MAX_NAV_GRID; ++c) h->nav_cell[c] = c < n * n ? d->nav_cell[c] : -2;
-        for (int y = 0; y < n; ++y)
-            for (int x = 0; x < n; ++x) {
-                const int v = d->nav_cell[y * n + x], bit = 16 * y + x;
-                if (v == -2) h->nav_wall_bits[bit >> 6] |= 1ull << (bit & 63);
-                if (v >= 0) h->nav_unknown_pos[v] = (uint8_t)bit;
+        // the map as rows of 16 cells: walls and cells off the map, then the
+        // unknown cells in runs of consecutive indices along a row (cut where
+        // the index crosses a state word)
+        int n_runs = 0;
+        for (int w = 0; w < 8; ++w) {
+            h->nav_run_begin[w] = n_runs;
+            int prev = -2;  // the last cell's unknown index
+            for (int b = 0; b < 32; ++b) {
+                const int x = b & 15, y = 2 * w + (b >> 4);
+                const int v = x < n && y < n ? d->nav_cell[y * n + x] : -2;
+                if (v == -2) h->nav_wall_rows[w] |= 1u << b;
+                if (v < 0) {
+                    prev = -2;
+                    continue;
+                }
+                if (x > 0 && v == prev + 1 && (v & 31) != 0) {
+                    h->nav_runs[n_runs - 1] += 1u << 5;  // one cell longer
+                } else {
+                    h->nav_runs[n_runs++] = (uint32_t)(v & 31) | (1u << 5) | ((uint32_t)b << 10) | ((uint32_t)(v >> 5) << 15);
+                }
+                prev = v;
             }
+        }
+        h->nav_run_begin[8] = n_runs;
         h->fail_thr = prob_threshold(d->p_fail);
         h->err_thr = prob_threshold(d->p_err);
     } else if (d->kind == HDX_PEDNAV) {
@@ -357,7 +374,11 @@ hdx_status hdx_upload_model(hdx_ctx *ctx, const hdx_model_desc *d, hdx_model **o
         delete dm;
         return fail(ctx, HDX_E_INVALID, "n_actions does not match the model");
     }
-    for (int j = 0; j < kHorizon; ++j) dm->gpow[j] = (float)pow(d->gamma, j);
+    for (int j = 0; j < kHorizon; ++j) {
+        const double g = pow(d->gamma, j);
+        dm->gpow[j] = (float)g;
+        dm->gsum[j + 1] = dm->gsum[j] + g;
+    }
     hipSetDevice(ctx->device);
     hdx_model *m = new hdx_model();
     m->desc = *d;
@@ -590,14 +611,37 @@ hdx_status validate_leaves(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t n_leave
     return HDX_OK;
 }
 
-void pack_leaves(const hdx_leaf *leaves, int32_t n_leaves, LeafTask *tasks, Tile *tiles) {
+// Actions per tile of a leaf.  Navigation: a tile's actions share the map,
+// the random numbers and the failure words of each scenario, so it takes all
+// nine (or as many as LDS holds) once the leaves alone fill the GPU; fewer
+// leaves are spread over more tiles, shortening the longest one.
+int32_t tile_actions(const hdx_leaf &L, int64_t call_tiles, int32_t n_cu) {
+    if (L.model->desc.kind != HDX_NAV) return 1;
+    const int32_t most = call_tiles >= kNavActions * (int64_t)n_cu ? kNavActions
+                         : call_tiles >= 3 * (int64_t)n_cu         ? 3
+                                                                   : 1;
+    return nav_tile_actions(L.n, L.rollout.policy, most);
+}
+
+int32_t tiles_of(const LeafTask &T) { return (T.n_actions + T.tile_actions - 1) / T.tile_actions; }
+
+// Pairs of a tile as the navigation layout counts them.
+int32_t tile_pairs(const LeafTask &T) {
+    return T.n * T.tile_actions * (T.policy != HDX_POLICY_DEFAULT ? 2 : 1);
+}
+
+// Descriptors (and tiles) of a call of call_tiles (leaf, action) pairs;
+// returns the number of tiles.
+int64_t pack_leaves(const hdx_leaf *leaves, int32_t n_leaves, LeafTask *tasks, Tile *tiles, int64_t call_tiles,
+                    int32_t n_cu) {
     int64_t t = 0;
     for (int32_t i = 0; i < n_leaves; ++i) {
         const hdx_leaf &L = leaves[i];
         LeafTask &T = tasks[i];
         memset(&T, 0, sizeof(T));
         T.model = L.model->d_model;
-        T.kind = L.model->desc.kind;
+        T.kind = (int16_t)L.model->desc.kind;
+        T.tile_actions = (int16_t)tile_actions(L, call_tiles, n_cu);
         T.n_actions = L.model->desc.n_actions;
         T.k0 = L.seed;
         T.k1 = L.step;
@@ -630,8 +674,9 @@ void pack_leaves(const hdx_leaf *leaves, int32_t n_leaves, LeafTask *tasks, Tile
         T.L = L.L;
         T.child_of = L.child_of;
         if (tiles)
-            for (int a = 0; a < T.n_actions; ++a) tiles[t++] = Tile{i, a};
+            for (int a = 0; a < T.n_actions; a += T.tile_actions) tiles[t++] = Tile{i, a};
     }
+    return t;
 }
 
 }  // namespace
@@ -647,11 +692,12 @@ void hdx::plan_classes(const LeafTask *tasks, const int8_t *variant, Tile *tiles
         return v * kSizeClasses + size_class(split ? tasks[t.leaf].n : vmax[v]);
     };
     int64_t cnt[kGroups] = {0};
-    for (int g = 0; g < kGroups; ++g) plan->n_max[g] = 0;
+    for (int g = 0; g < kGroups; ++g) plan->n_max[g] = plan->pairs[g] = 0;
     for (int64_t t = 0; t < n_tiles; ++t) {
         const int g = group(tiles[t]);
         cnt[g]++;
         plan->n_max[g] = std::max(plan->n_max[g], tasks[tiles[t].leaf].n);
+        plan->pairs[g] = std::max(plan->pairs[g], tile_pairs(tasks[tiles[t].leaf]));
     }
     int64_t at = 0;
     for (int g = 0; g < kGroups; ++g) {
@@ -704,12 +750,13 @@ Schedule hdx::class_default_schedule(int32_t n_max, int32_t max_threads, int32_t
 }
 
 hipError_t hdx::launch_classes(const LeafTask *d_tasks, const Tile *d_tiles, TileQueue *d_queues,
-                               const ClassPlan &plan, const int32_t *lds_n, const Schedule *sch, int32_t n_cu,
+                               const ClassPlan &plan, const int32_t *lds_n, const int32_t *lds_pairs, const Schedule *sch, int32_t n_cu,
                                hipStream_t stream, uint64_t mask) {
     for (int g = 0; g < kGroups; ++g) {
         if (plan.count[g] == 0 || !(mask & (1ull << g))) continue;
         Variant vg = group_variant(g);
         vg.n_max = std::max(lds_n[g], plan.n_max[g]);
+        vg.pairs = std::max(lds_pairs[g], plan.pairs[g]);
         // driving leaves small enough for every scenario's pedestrians to
         // get lanes of their own (n times the pedestrian bound fits a
         // wavefront): the element-level instance
@@ -732,13 +779,13 @@ namespace {
 // graph branches), so one group's slow tail overlaps the others; a single
 // group launches on `st` directly.
 hipError_t launch_classes_forked(const LeafTask *d_tasks, const Tile *d_tiles, TileQueue *d_queues,
-                                 const ClassPlan &plan, const int32_t *lds_n, const Schedule *sch, int32_t n_cu,
+                                 const ClassPlan &plan, const int32_t *lds_n, const int32_t *lds_pairs, const Schedule *sch, int32_t n_cu,
                                  hipStream_t st, const hipStream_t *cls, hipEvent_t fork, const hipEvent_t *join,
                                  uint64_t mask = ~0ull) {
     int active = 0;
     for (int g = 0; g < kGroups; ++g)
         if (plan.count[g] > 0 && (mask & (1ull << g))) ++active;
-    if (active <= 1) return launch_classes(d_tasks, d_tiles, d_queues, plan, lds_n, sch, n_cu, st, mask);
+    if (active <= 1) return launch_classes(d_tasks, d_tiles, d_queues, plan, lds_n, lds_pairs, sch, n_cu, st, mask);
     hipError_t e = hipEventRecord(fork, st);
     // largest leaves first: their tails are the longest
     for (int c = kSizeClasses - 1; c >= 0 && e == hipSuccess; --c)
@@ -746,7 +793,7 @@ hipError_t launch_classes_forked(const LeafTask *d_tasks, const Tile *d_tiles, T
             const int g = v * kSizeClasses + c;
             if (plan.count[g] == 0 || !(mask & (1ull << g))) continue;
             e = hipStreamWaitEvent(cls[g], fork, 0);
-            if (e == hipSuccess) e = launch_classes(d_tasks, d_tiles, d_queues, plan, lds_n, sch, n_cu, cls[g], 1ull << g);
+            if (e == hipSuccess) e = launch_classes(d_tasks, d_tiles, d_queues, plan, lds_n, lds_pairs, sch, n_cu, cls[g], 1ull << g);
             if (e == hipSuccess) e = hipEventRecord(join[g], cls[g]);
             if (e == hipSuccess) e = hipStreamWaitEvent(st, join[g], 0);
         }
@@ -800,9 +847,13 @@ bool launch_in_args(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t n_leaves, cons
     static_assert(sizeof(ArgPack) <= 4096, "kernel argument pack too large");
     ArgPack pack;
     memset(&pack, 0, sizeof(pack));
-    pack_leaves(leaves, n_leaves, pack.t, nullptr);
+    pack_leaves(leaves, n_leaves, pack.t, nullptr, sh.n_tiles, ctx->n_cu);
     pack.tile_begin[0] = 0;
-    for (int32_t i = 0; i < n_leaves; ++i) pack.tile_begin[i + 1] = pack.tile_begin[i] + pack.t[i].n_actions;
+    pack.pairs = 1;
+    for (int32_t i = 0; i < n_leaves; ++i) {
+        pack.tile_begin[i + 1] = pack.tile_begin[i] + tiles_of(pack.t[i]);
+        pack.pairs = std::max(pack.pairs, tile_pairs(pack.t[i]));
+    }
     pack.n_leaves = n_leaves;
     pack.n_max = v0.n_max;
     const Schedule sch =
@@ -836,7 +887,7 @@ hdx_status launch_staged(hdx_ctx *ctx, const LeafTask *h_tasks, const Tile *h_ti
                                                            few ? -2 : group_variant(g).mode);
         if (few) sch[g].xcd_remap = 0;
     }
-    e = launch_classes_forked(d_tasks, d_tiles, d_queue, plan, no_lds, sch, ctx->n_cu, hs, ctx->cls_stream, fork,
+    e = launch_classes_forked(d_tasks, d_tiles, d_queue, plan, no_lds, no_lds, sch, ctx->n_cu, hs, ctx->cls_stream, fork,
                               join);
     if (e != hipSuccess) return hip_fail(ctx, e, "expand launch");
     e = hipEventRecord(done, hs);
@@ -855,11 +906,12 @@ void plan_fixed(const LeafTask *tasks, const int8_t *variant, int32_t n_leaves, 
     auto group = [&](int32_t i) { return variant[i] * kSizeClasses + size_class(vmax[variant[i]]); };
     for (int g = 0; g < kGroups; ++g) {
         plan->count[g] = 0;
-        plan->n_max[g] = 0;
+        plan->n_max[g] = plan->pairs[g] = 0;
     }
     for (int32_t i = 0; i < n_leaves; ++i) {
-        plan->count[group(i)] += tasks[i].n_actions;
+        plan->count[group(i)] += tiles_of(tasks[i]);
         plan->n_max[group(i)] = std::max(plan->n_max[group(i)], tasks[i].n);
+        plan->pairs[group(i)] = std::max(plan->pairs[group(i)], tile_pairs(tasks[i]));
     }
     int64_t at = 0;
     for (int g = 0; g < kGroups; ++g) {
@@ -890,7 +942,7 @@ void plan_fixed(const LeafTask *tasks, const int8_t *variant, int32_t n_leaves, 
         int64_t o = 0;
         if (count < 2 * kXcds) {
             for (int32_t r = lo; r < hi; ++r)
-                for (int a = 0; a < tasks[order[r]].n_actions; ++a) t[o++] = Tile{order[r], a};
+                for (int a = 0; a < tasks[order[r]].n_actions; a += tasks[order[r]].tile_actions) t[o++] = Tile{order[r], a};
         } else {
             // XCD x takes the leaves of rank x, x + 8, ...; one tile from
             // each XCD's list in turn
@@ -905,7 +957,8 @@ void plan_fixed(const LeafTask *tasks, const int8_t *variant, int32_t n_leaves, 
                     if (rank[x] >= nl) continue;
                     const int32_t leaf = order[lo + rank[x]];
                     t[o++] = Tile{leaf, act[x]};
-                    if (++act[x] == tasks[leaf].n_actions) {
+                    act[x] += tasks[leaf].tile_actions;
+                    if (act[x] >= tasks[leaf].n_actions) {
                         act[x] = 0;
                         rank[x] += kXcds;
                     }
@@ -936,12 +989,12 @@ hdx_status hdx_expand_leaf(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t n_leave
     st = grow_pinned(ctx, &s.h_tasks, &s.d_tasks, &s.cap_tasks, &s.h_tiles, &s.d_tiles, &s.cap_tiles, n_leaves,
                      sh.n_tiles);
     if (st != HDX_OK) return st;
-    pack_leaves(leaves, n_leaves, s.h_tasks, s.h_tiles);
+    const int64_t n_tiles = pack_leaves(leaves, n_leaves, s.h_tasks, s.h_tiles, sh.n_tiles, ctx->n_cu);
     std::vector<int8_t> var(n_leaves);
     leaf_variants(leaves, n_leaves, var.data());
     ClassPlan plan;
-    plan_classes(s.h_tasks, var.data(), s.h_tiles, sh.n_tiles, &plan, false);
-    st = launch_staged(ctx, s.h_tasks, s.h_tiles, s.h_queue, s.d_tasks, s.d_tiles, s.d_queue, n_leaves, sh.n_tiles,
+    plan_classes(s.h_tasks, var.data(), s.h_tiles, n_tiles, &plan, false);
+    st = launch_staged(ctx, s.h_tasks, s.h_tiles, s.h_queue, s.d_tasks, s.d_tiles, s.d_queue, n_leaves, n_tiles,
                        plan, (hipStream_t)stream, s.fork, s.join, s.done);
     if (st == HDX_OK) s.used = true;
     return st;
@@ -964,7 +1017,9 @@ hdx_status hdx_expand_leaf_noalloc(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t
         const hipError_t e = hipEventSynchronize(ctx->na_done);
         if (e != hipSuccess) return hip_fail(ctx, e, "staging wait");
     }
-    pack_leaves(leaves, n_leaves, ctx->na_h_tasks, nullptr);
+    pack_leaves(leaves, n_leaves, ctx->na_h_tasks, nullptr, sh.n_tiles, ctx->n_cu);
+    int64_t n_tiles = 0;
+    for (int32_t i = 0; i < n_leaves; ++i) n_tiles += tiles_of(ctx->na_h_tasks[i]);
     leaf_variants(leaves, n_leaves, ctx->na_var);
     ClassPlan plan;
     plan_fixed(ctx->na_h_tasks, ctx->na_var, n_leaves, ctx->na_h_tiles, ctx->na_order, &plan);
@@ -972,7 +1027,7 @@ hdx_status hdx_expand_leaf_noalloc(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t
     Tile *d_tiles = (Tile *)(ctx->na_scratch + kNaTilesOff);
     TileQueue *d_queue = (TileQueue *)(ctx->na_scratch + kNaQueueOff);
     st = launch_staged(ctx, ctx->na_h_tasks, ctx->na_h_tiles, ctx->na_h_queue, d_tasks, d_tiles, d_queue, n_leaves,
-                       sh.n_tiles, plan, (hipStream_t)stream, ctx->na_fork, ctx->na_join, ctx->na_done);
+                       n_tiles, plan, (hipStream_t)stream, ctx->na_fork, ctx->na_join, ctx->na_done);
     if (st == HDX_OK) ctx->na_used = true;
     return st;
 }
@@ -988,9 +1043,10 @@ struct hdx_batch {
     int32_t n_leaves = 0;
     int64_t n_tiles = 0;
     ClassPlan plan{};
-    int32_t lds_c[kGroups] = {};  // per launch group: largest leaf seen
+    // per launch group: largest leaf seen, most pairs of a tile seen
+    int32_t lds_c[kGroups] = {}, lds_p[kGroups] = {};
     ClassPlan g_plan{};
-    int32_t g_lds[kGroups] = {};
+    int32_t g_lds[kGroups] = {}, g_ldp[kGroups] = {};
     Schedule sched[kGroups];  // per launch group
     bool sched_set[kGroups] = {};
     hipStream_t work = nullptr;      // capture and tuning stream
@@ -1011,7 +1067,7 @@ namespace {
 
 hipError_t batch_direct_launch(hdx_ctx *ctx, hdx_batch *b, const Schedule *s, hipStream_t st,
                                uint64_t mask = ~0ull) {
-    return launch_classes_forked(b->d_tasks, b->d_tiles, b->d_queue, b->plan, b->lds_c, s, ctx->n_cu, st, b->cls,
+    return launch_classes_forked(b->d_tasks, b->d_tiles, b->d_queue, b->plan, b->lds_c, b->lds_p, s, ctx->n_cu, st, b->cls,
                                  b->fork, b->join, mask);
 }
 
@@ -1040,6 +1096,7 @@ hipError_t replan(hdx_batch *b, hipStream_t st) {
     for (int g = 0; g < kGroups; ++g) {
         b->h_queue[g] = TileQueue{0, 0, (int32_t)b->plan.count[g], 0};
         b->lds_c[g] = std::max(b->lds_c[g], b->plan.n_max[g]);
+        b->lds_p[g] = std::max(b->lds_p[g], b->plan.pairs[g]);
     }
     hipError_t e = hipSuccess;
     if (b->n_tiles > 0) e = hipMemcpyAsync(b->d_tiles, b->h_tiles, b->n_tiles * sizeof(Tile), hipMemcpyHostToDevice, st);
@@ -1121,11 +1178,10 @@ hdx_status hdx_batch_set_leaves(hdx_ctx *ctx, hdx_batch *b, const hdx_leaf *leav
         hipError_t e = hipEventSynchronize(b->staged);
         if (e != hipSuccess) return hip_fail(ctx, e, "staging wait");
     }
-    pack_leaves(leaves, n_leaves, b->h_tasks, b->h_tiles);
+    b->n_tiles = pack_leaves(leaves, n_leaves, b->h_tasks, b->h_tiles, sh.n_tiles, ctx->n_cu);
     b->var.assign(std::max(n_leaves, 1), 0);
     leaf_variants(leaves, n_leaves, b->var.data());
     b->n_leaves = n_leaves;
-    b->n_tiles = sh.n_tiles;
     // LDS sized for the largest leaf a group has seen, so graphs survive smaller batches
     hipStream_t hs = (hipStream_t)stream;
     hipError_t e = hipSuccess;
@@ -1243,6 +1299,7 @@ hdx_status hdx_batch_launch(hdx_ctx *ctx, hdx_batch *b, hdx_stream stream) {
     bool groups_same = true;
     for (int g = 0; g < kGroups; ++g)
         groups_same = groups_same && b->plan.begin[g] == b->g_plan.begin[g] && b->lds_c[g] == b->g_lds[g] &&
+                      b->lds_p[g] == b->g_ldp[g] &&
                       same_schedule(b->sched[g], b->g_sched[g]) &&
                       (b->sched[g].persistent > 0 ? (b->plan.count[g] > 0) == (b->g_plan.count[g] > 0)
                                                   : b->plan.count[g] == b->g_plan.count[g]);
@@ -1265,6 +1322,7 @@ hdx_status hdx_batch_launch(hdx_ctx *ctx, hdx_batch *b, hdx_stream stream) {
         b->g_plan = b->plan;
         for (int g = 0; g < kGroups; ++g) {
             b->g_lds[g] = b->lds_c[g];
+            b->g_ldp[g] = b->lds_p[g];
             b->g_sched[g] = b->sched[g];
         }
     }
