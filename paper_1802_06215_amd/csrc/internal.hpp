@@ -17,6 +17,7 @@ constexpr int kSenseEntries = 2 * (kMaxGrid - 1) * (kMaxGrid - 1) + 1;  // squar
 constexpr int kMaxLeaf = HDX_MAX_LEAF_SCENARIOS;
 constexpr int kMaxNavLeaf = HDX_MAX_NAV_LEAF_SCENARIOS;
 constexpr int kNavActions = 9;
+constexpr int kPedActions = 3;
 
 enum : uint32_t { kTagStep = 0, kTagInit = 1, kTagPolicy = 2 };
 constexpr uint64_t kEmptyKey = ~0ull;
@@ -38,7 +39,8 @@ struct ModelHdr {
     int32_t joint_inv;
     float goal_x[kMaxGoals], goal_y[kMaxGoals];
     float path_len, dt, step_len, half_sigma, coll_r2, reach, ih_scale;
-    float r_collision, r_step, r_goal, pad2;
+    float r_collision, r_step, r_goal;
+    float near_d2;  // sqrt(d2) <= step_len iff d2 <= near_d2
     uint64_t fail_thr;  // action fails iff word < fail_thr (driving, navigation)
     // navigation: goal column (on the bottom row), wall row, gate columns and
     // the reading error (a neighbour's bit flips iff word < err_thr)
@@ -118,75 +120,68 @@ struct Schedule {
     int32_t xcd_remap;   // keep consecutive tiles (one leaf) on one XCD
 };
 
-// LDS carve-up of one tile, the same on host (for the launch size) and
-// device.  General carve-up (any model); regions live in phases and are
-// reused:
-//   zkey | tab    observations, then the open-addressing hash; after the
-//                 children are ranked the pair holds the chunk count table
-//                 (cnt), and later the grouped per-scenario sums (su, sl)
-//   dslot         slot of each distinct observation, then child sizes (nc)
-//   off           child offsets in the grouped order
-//   ubuf, lbuf    per-scenario U and L
-//   child         child index of each scenario (bits 0-15) and its rank
-//                 inside its 64-scenario chunk (bits 16-23)
-//   perm          grouped order (or the bitonic keys of the fallback path)
-// Small carve-up (RockSample-only launches: every observation key is below
-// 32, no model table staged):
-//   zkey          per 64-scenario chunk and key: count, U sum, L sum
-//   dslot         per chunk: mask of the keys present
-//   off           per key: child offset and child index
-//   child         key of each scenario (bits 0-15) and its rank inside its
-//                 chunk among the scenarios of that key (bits 16-23)
-struct LdsLayout {
-    uint32_t zkey, tab, dslot, off, ubuf, lbuf, child, perm, misc, gpow, total;
-    int32_t np, p2, h, table_cap;
-    int32_t small;
-};
-
 __host__ __device__ inline int32_t pow2_at_least(int32_t v) {
     int32_t p = 1;
     while (p < v) p <<= 1;
     return p;
 }
 
-__host__ __device__ inline LdsLayout make_layout(int32_t np, bool small = false) {
+// LDS carve-up of one RockSample tile (either model: every observation key
+// is below 32), the same on host (for the launch size) and device.
+//   zkey          per 64-scenario chunk and key: count, U sum, L sum
+//   dslot         per chunk: mask of the keys present
+//   off           per key: child offset and child index
+//   child         key of each scenario (bits 0-4) and its rank inside its
+//                 chunk among the scenarios of that key (bits 5-10)
+struct LdsLayout {
+    uint32_t zkey, dslot, off, child, misc, total;
+    int32_t np;
+};
+__host__ __device__ inline LdsLayout make_layout(int32_t np) {
     LdsLayout L;
     if (np < 1) np = 1;
     L.np = np;
-    L.small = small ? 1 : 0;
-    L.p2 = pow2_at_least(np) < 64 ? 64 : pow2_at_least(np);
-    L.h = pow2_at_least(2 * np) < 64 ? 64 : pow2_at_least(2 * np);
     uint32_t o = 0;
     auto take = [&](uint32_t bytes) {
         uint32_t at = o;
         o += (bytes + 15u) & ~15u;
         return at;
     };
-    if (small) {
-        const uint32_t chunks = (uint32_t)((np + 63) / 64);
-        L.zkey = take(3u * 4u * 32u * chunks);
-        L.tab = L.zkey;
-        L.table_cap = 0;
-        L.dslot = take(4u * chunks);
-        L.off = take(4u * 64u);
-        L.ubuf = L.lbuf = L.perm = L.off;  // not used by the small path
-        L.child = take(2u * np);  // per scenario: key | rank << 5 (int16)
-        L.misc = take(64 + 4u * 64);
-        L.gpow = L.misc;
-        L.total = o;
-        return L;
-    }
-    L.zkey = take(8u * L.p2);
-    L.tab = take(8u * L.h + 16u);
-    L.table_cap = (int32_t)((8u * L.p2 + 8u * L.h + 16u) / 4u);
-    L.dslot = take(4u * L.p2);
-    L.off = take(4u * L.p2);
-    L.ubuf = take(4u * np);
-    L.lbuf = take(4u * np);
-    L.child = take(4u * np);
-    L.perm = take(4u * L.p2);
+    const uint32_t chunks = (uint32_t)((np + 63) / 64);
+    L.zkey = take(3u * 4u * 32u * chunks);
+    L.dslot = take(4u * chunks);
+    L.off = take(4u * 64u);
+    L.child = take(2u * np);
     L.misc = take(64 + 4u * 64);
-    L.gpow = take(4u * (kGpowLds + 2 * kMaxGoals));  // discount powers, goal points
+    L.total = o;
+    return L;
+}
+
+// Driving tile: the three actions of a leaf of n scenarios.
+//   zkey, pos   per action: (observation, position) pairs, sorted in place,
+//               p2 of them (a power of two)
+//   ub, lb      per action and scenario: U and L
+//   rcode       per action and scenario: which step reward
+//   misc        live scenarios, rollout steps per action
+struct PedLayout {
+    uint32_t zkey, pos, ub, lb, rcode, misc, total;
+    int32_t p2;
+};
+__host__ __device__ inline PedLayout make_ped_layout(int32_t n) {
+    PedLayout L;
+    L.p2 = pow2_at_least(n < 64 ? 64 : n);
+    uint32_t o = 0;
+    auto take = [&](uint32_t bytes) {
+        uint32_t at = o;
+        o += (bytes + 15u) & ~15u;
+        return at;
+    };
+    L.zkey = take(8u * kPedActions * L.p2);
+    L.pos = take(2u * kPedActions * L.p2);
+    L.ub = take(4u * kPedActions * n);
+    L.lb = take(4u * kPedActions * n);
+    L.rcode = take(1u * kPedActions * n);
+    L.misc = take(4u * (1 + kPedActions));
     L.total = o;
     return L;
 }
@@ -240,8 +235,7 @@ int32_t nav_tile_actions(int32_t n, int32_t policy, int32_t most);
 // the LDS carve-up.
 struct Variant {
     int32_t mode, pm, n_max;
-    // driving only: the kernel instance whose tiles expand a leaf one lane
-    // per pedestrian when n times the group width fits a wavefront
+    // driving only: the kernel instance with 8 or 16 lanes per scenario
     int32_t group = 0;
     // navigation: the largest (action, scenario) pairs of a tile, counted
     // twice where the rollouts run step by step
@@ -250,6 +244,8 @@ struct Variant {
 Variant pick_variant(int32_t has_rs, int32_t has_ped, int32_t ped_max, int32_t n_max, int32_t has_mars,
                      int32_t has_nav);
 int32_t variant_max_threads(const Variant &v);
+// Lanes a leaf of n scenarios can use.
+int32_t variant_lanes(const Variant &v, int32_t n);
 
 // Kernel launchers (kernels.hip).  The expansion kernel reads the tile
 // count from d_queue->n_tiles; n_tiles here only sizes a non-persistent grid.
@@ -303,14 +299,15 @@ void plan_classes(const LeafTask *tasks, const int8_t *variant, Tile *tiles, int
 hipError_t launch_classes(const LeafTask *d_tasks, const Tile *d_tiles, TileQueue *d_queues, const ClassPlan &plan,
                           const int32_t *lds_n, const int32_t *lds_pairs, const Schedule *sch, int32_t n_cu,
                           hipStream_t stream, uint64_t mask = ~0ull);
-// Default schedule of a group whose largest leaf has n_max scenarios.
-// Latency form (a few leaves, split groups): two scenarios per lane up to
-// 256 lanes (navigation: 1024), one workgroup per tile, XCD-contiguous.
-// Throughput form (one group per model): both RockSample models one
+// Default schedule of a group whose largest leaf has v.n_max scenarios.  Few
+// tiles (a call far smaller than the GPU): a lane for every scenario (driving:
+// its lanes), so each tile ends sooner.  Otherwise both RockSample models one
 // wavefront per tile (the most tiles in flight, barriers of a single
-// wavefront), driving and navigation as the latency form; workgroups in
-// tile order (largest first spreads over the XCDs).
-Schedule class_default_schedule(int32_t n_max, int32_t max_threads, int32_t mode = -1);
+// wavefront), navigation half a lane per scenario; driving a quarter of its
+// lanes with more than one tile per CU (512 leaves of 125..500 scenarios: 500
+// us at 512 lanes, 526 at 1024), else half (256 leaves among others: 930 and
+// 769 us).  Workgroups in tile order, one per tile.
+Schedule class_default_schedule(const Variant &v, int64_t tiles, int32_t n_cu, bool few);
 hipError_t configure_expand_kernels();
 
 // Up to kArgLeaves leaves passed by value in the kernel arguments (the

@@ -15,13 +15,9 @@
 //    and DPP row reductions the key's U and L sums; one wavefront turns the
 //    per-chunk tables into children (ascending key), offsets and means,
 //    chunk partials added in chunk order;
-//  - hashed observations (driving): an open-addressing LDS hash collects
-//    the distinct observations, which are sorted (one wavefront bitonic
-//    network, or an LDS bitonic network past 64 keys); scenario positions
-//    inside each child come from wavefront ballots per 64-scenario chunk
-//    and a prefix over chunks, and the per-child sums of U and L from
-//    segmented wavefront scans over 64-aligned chunks of the grouped order,
-//    chunk partials added in order.
+//  - hashed observations (driving): sorted in LDS with their positions, then
+//    walked in order by one wavefront per action (run_tile_ped; a tile there
+//    is a whole leaf).
 // Either way the floating-point order depends only on the data, never on
 // the workgroup size or the schedule.
 #include <algorithm>
@@ -63,158 +59,20 @@ __device__ __forceinline__ int wave_total_i(int v) {
     return __builtin_amdgcn_readlane(v, 63);
 }
 
-__device__ __forceinline__ uint64_t mix_key(uint64_t z) {
-    return (z * 0x9E3779B97F4A7C15ull) >> 32;
-}
-
-// Lexicographic (key, val) compare-exchange used by both sorting networks.
-__device__ __forceinline__ bool pair_less(uint64_t ka, uint32_t va, uint64_t kb, uint32_t vb) {
-    return ka < kb || (ka == kb && va < vb);
-}
-
-// Bitonic sort of up to 64 (key, val) pairs held one per lane of a wavefront.
-__device__ void wave_sort_pairs(uint64_t *keys, uint32_t *vals, int count) {
-    const int lane = lane_id();
-    uint64_t k = lane < count ? keys[lane] : kEmptyKey;
-    uint32_t v = lane < count ? vals[lane] : 0xFFFFFFFFu;
-#pragma unroll
-    for (int size = 2; size <= 64; size <<= 1) {
-#pragma unroll
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            const uint32_t klo = __shfl_xor((uint32_t)k, stride, 64);
-            const uint32_t khi = __shfl_xor((uint32_t)(k >> 32), stride, 64);
-            const uint32_t ov = __shfl_xor(v, stride, 64);
-            const uint64_t ok = ((uint64_t)khi << 32) | klo;
-            const bool ascending = (lane & size) == 0;
-            const bool lower = (lane & stride) == 0;
-            const bool other_smaller = pair_less(ok, ov, k, v);
-            // the lower lane of an ascending pair keeps the smaller element
-            const bool take = (lower == ascending) ? other_smaller : !other_smaller;
-            if (take) {
-                k = ok;
-                v = ov;
-            }
-        }
-    }
-    if (lane < count) {
-        keys[lane] = k;
-        vals[lane] = v;
-    }
-}
-
-// Bitonic sort in LDS of p (a power of two) (key, val) pairs.
-__device__ void block_sort_pairs(uint64_t *keys, uint32_t *vals, int p) {
-    const int tid = threadIdx.x, nt = blockDim.x;
-    for (int size = 2; size <= p; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int i = tid; i < p; i += nt) {
-                const int j = i ^ stride;
-                if (j > i) {
-                    const bool ascending = (i & size) == 0;
-                    const bool swap = ascending ? pair_less(keys[j], vals[j], keys[i], vals[i])
-                                                : pair_less(keys[i], vals[i], keys[j], vals[j]);
-                    if (swap) {
-                        const uint64_t tk = keys[i];
-                        keys[i] = keys[j];
-                        keys[j] = tk;
-                        const uint32_t tv = vals[i];
-                        vals[i] = vals[j];
-                        vals[j] = tv;
-                    }
-                }
-            }
-            __syncthreads();
-        }
-    }
-}
-
-// Bitonic sort in LDS of p (a power of two) uint32 keys.
-__device__ void block_sort_u32(uint32_t *keys, int p) {
-    const int tid = threadIdx.x, nt = blockDim.x;
-    for (int size = 2; size <= p; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int i = tid; i < p; i += nt) {
-                const int j = i ^ stride;
-                if (j > i) {
-                    const bool ascending = (i & size) == 0;
-                    const uint32_t a = keys[i], b = keys[j];
-                    if (ascending ? (b < a) : (a < b)) {
-                        keys[i] = b;
-                        keys[j] = a;
-                    }
-                }
-            }
-            __syncthreads();
-        }
-    }
-}
-
-// Exclusive prefix sum of len ints, in place, by the whole workgroup.
-// scratch holds one int per wavefront plus one.
-__device__ void block_exclusive_scan(int32_t *a, int len, int32_t *scratch) {
-    const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id(), wid = tid >> 6, nw = nt >> 6;
-    const int per = (len + nt - 1) / nt;
-    const int lo = tid * per, hi = min(lo + per, len);
-    int32_t local = 0;
-    for (int i = lo; i < hi; ++i) local += a[i];
-    int32_t incl = local;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int32_t o = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += o;
-    }
-    if (lane == 63) scratch[wid] = incl;
-    __syncthreads();
-    if (tid == 0) {
-        int32_t run = 0;
-        for (int w = 0; w < nw; ++w) {
-            const int32_t t = scratch[w];
-            scratch[w] = run;
-            run += t;
-        }
-    }
-    __syncthreads();
-    int32_t run = scratch[wid] + incl - local;
-    for (int i = lo; i < hi; ++i) {
-        const int32_t t = a[i];
-        a[i] = run;
-        run += t;
-    }
-    __syncthreads();
-}
-
 __device__ __forceinline__ bool has_states(const StatesPtr &S) { return S.w != nullptr || S.s != nullptr; }
 
-// One (leaf, action) tile.
-// kGroup: compile the element-level expansion of small leaves in (the
-// kernel-argument launches of the search threads and batchers; the staged
-// batched launch leaves it out, since its registers would cost the driving
-// model a wavefront per SIMD).
-template <class Ops, bool kGroup = false>
+// One (leaf, action) tile of a RockSample model.
+template <class Ops>
 __device__ void run_tile(const HDX_CONST LeafTask *T, const int a, unsigned char *lds, const LdsLayout &Ly) {
-    float *gpow_lds = (float *)(lds + Ly.gpow);
-    const MView M = make_view(T->model, gpow_lds);
+    const MView M = make_view(T->model, nullptr);
     const int n = T->n;
     const int cap = T->cap;
-    const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id(), wid = tid >> 6, nw = nt >> 6;
-    uint64_t *zk = (uint64_t *)(lds + Ly.zkey);
-    uint64_t *tab = (uint64_t *)(lds + Ly.tab);
-    uint32_t *dslot = (uint32_t *)(lds + Ly.dslot);
-    int32_t *nc = (int32_t *)(lds + Ly.dslot);  // after ranking
-    int32_t *off = (int32_t *)(lds + Ly.off);
-    float *ub = (float *)(lds + Ly.ubuf);
-    float *lb = (float *)(lds + Ly.lbuf);
-    int32_t *child = (int32_t *)(lds + Ly.child);
-    int16_t *kchild = (int16_t *)(lds + Ly.child);  // small alphabets: key | rank << 5
-    int32_t *permb = (int32_t *)(lds + Ly.perm);
-    // per-chunk child counts: over zkey and tab (contiguous)
-    int32_t *cnt = (int32_t *)(lds + Ly.zkey);
-    int32_t *misc = (int32_t *)(lds + Ly.misc);                   // [0] distinct count, [1] sentinel seen
+    const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id(), wid = tid >> 6;
+    int16_t *kchild = (int16_t *)(lds + Ly.child);  // key | rank << 5
+    int32_t *misc = (int32_t *)(lds + Ly.misc);
     unsigned long long *stepc = (unsigned long long *)(misc + 4);  // expansion, rollout steps
     float *chunk_r = (float *)(misc + 8);                          // per-chunk reward sums (<= 32)
-    int32_t *scan_scratch = misc + 48;
-    const int H = Ly.h;
-    // small observation alphabet (keys below 32): per 64-scenario chunk t and
+    // per 64-scenario chunk t and
     // key v, the scenario count and the U and L sums (entry t * 32 + v, over
     // zkey), the chunk's key mask (over dslot), and per key the child offset
     // and child index (over off)
@@ -226,15 +84,10 @@ __device__ void run_tile(const HDX_CONST LeafTask *T, const int a, unsigned char
     int32_t *koff = (int32_t *)(lds + Ly.off);
     int32_t *kci = koff + 32;
 
-    if constexpr (!Ops::kSmallObs)
-        for (int h = tid; h < H; h += nt) tab[h] = kEmptyKey;
     if (tid == 0) {
-        misc[0] = 0;
-        misc[1] = 0;
         stepc[0] = 0;
         stepc[1] = 0;
     }
-    if constexpr (Ops::kLdsModel) stage_gpow(T->model, gpow_lds);
     __syncthreads();
 
     RolloutParams RP;
@@ -253,18 +106,10 @@ __device__ void run_tile(const HDX_CONST LeafTask *T, const int a, unsigned char
     const bool pair_out = has_states(sprime);
     // the optional per-pair outputs, tested once per tile rather than per round
     const bool pair_vals = T->r != nullptr || T->z != nullptr || T->U != nullptr || T->L != nullptr;
-    // element-level expansion when the leaf is small enough for every
-    // scenario to get a group of lanes of wavefront 0 (tile-uniform)
-    int group_lanes = 0;
-    if constexpr (Ops::kGroupRollout && kGroup) {
-        const int G = pow2_at_least(M.h->n_peds > 0 ? M.h->n_peds : 1);
-        if (n * G <= 64) group_lanes = G;
-    }
-
     // -- gather + update + expand + bounds + rollouts (Eq. 10, 12, 13) ------
     // Every lane of a wavefront runs the same number of rounds, so a
-    // 64-scenario chunk's reward (and, for small alphabets, its per-key
-    // tables) are reduced by the whole wavefront right here.
+    // 64-scenario chunk's reward and its per-key tables
+    // are reduced by the whole wavefront right here.
     int my_exp = 0, my_roll = 0;
     typename Ops::WaveUpper wave_upper;
     for (int base = 0; base < n; base += nt) {
@@ -295,55 +140,17 @@ __device__ void run_tile(const HDX_CONST LeafTask *T, const int a, unsigned char
         };
         float U = 0.0f;
         float L = 0.0f;
-        bool grouped = false;
-        if constexpr (Ops::kGroupRollout && kGroup) {
-            if (group_lanes > 0) {
-                // n * G <= 64: one round; wavefront 0 expands the leaf with
-                // one pedestrian per lane (leaf and stepped states stored
-                // inside) and lane k receives scenario k's results
-                grouped = true;
-                if (wid == 0) {
-                    const typename Ops::GroupOut o =
-                        Ops::group_expand(M, RP, T->idx, T->parent_ids, parent, leaf_out, T->ids_out, sprime,
-                                          write_leaf, pair_out, a, depth, last_action, n, group_lanes);
-                    if (valid) {
-                        r = o.r;
-                        z = o.z;
-                        U = o.U;
-                        L = o.L;
-                        id = o.id;
-                        my_exp += o.expanded;
-                        my_roll += o.steps;
-                    }
-                }
-            }
-        }
-        if (!grouped) {
-            if constexpr (Ops::kWaveUpper) {
-                // every lane of the wavefront takes part in the bound (it
-                // shares per-rock terms across lanes); lanes past n stay
-                // terminal
-                Ops::make_terminal(st);
-                if (valid) expand_one();
-                U = Ops::upper_wave(M, st, wave_upper);
-            } else if (valid) {
-                expand_one();
-                U = Ops::upper(M, st);
-            }
-        }
+        // every lane of the wavefront takes part in the bound (it shares
+        // per-rock terms across lanes); lanes past n stay terminal
+        Ops::make_terminal(st);
+        if (valid) expand_one();
+        U = Ops::upper_wave(M, st, wave_upper);
         if (valid) {
             const int64_t pk = (int64_t)a * n + k;
-            if (!grouped) {
-                if (pair_out) Ops::store(M, sprime, pk, st);
-                int ns = 0;
-                L = rollout<Ops>(M, RP, st, id, depth + 1, ns);
-                my_roll += ns;
-            }
-            if constexpr (!Ops::kSmallObs) {
-                zk[k] = z;
-                ub[k] = U;
-                lb[k] = L;
-            }
+            if (pair_out) Ops::store(M, sprime, pk, st);
+            int ns = 0;
+            L = rollout<Ops>(M, RP, st, id, depth + 1, ns);
+            my_roll += ns;
             if (pair_vals) {
                 if (T->r) T->r[pk] = r;
                 if (T->z) T->z[pk] = z;
@@ -352,7 +159,7 @@ __device__ void run_tile(const HDX_CONST LeafTask *T, const int a, unsigned char
             }
         }
         const bool chunk_live = base + wid * 64 < n;  // wavefront-uniform
-        if constexpr (Ops::kSmallObs) {
+        {
             // this chunk's scenarios by key: counts, ranks, and the U and L
             // sums of each key present (keys in order of first appearance)
             if (chunk_live) {
@@ -396,9 +203,8 @@ __device__ void run_tile(const HDX_CONST LeafTask *T, const int a, unsigned char
         atomicAdd(&stepc[1], (unsigned long long)my_roll);
     }
 
-    int D;
-    if constexpr (Ops::kSmallObs) {
-        // -- small observation alphabet: children from the per-chunk key tables --
+    {
+        // -- children from the per-chunk key tables --
         // Lane v of wavefront 0 owns key v: its scenario count (turning the
         // per-chunk counts into prefixes over chunks) and its U and L sums,
         // chunk partials added in chunk order.  A present key's child index
@@ -428,7 +234,7 @@ __device__ void run_tile(const HDX_CONST LeafTask *T, const int a, unsigned char
             }
             const bool present = run > 0;
             const uint32_t mask = (uint32_t)__ballot(present);
-            D = __popc(mask);
+            const int D = __popc(mask);
             const int ci = lane < 32 ? __popc(mask & ((1u << v) - 1u)) : 0;
             // inclusive prefix over lanes 0-31: shifts inside rows of 16
             // lanes, then row 0's total broadcast into row 1 (lanes past 31
@@ -472,209 +278,28 @@ __device__ void run_tile(const HDX_CONST LeafTask *T, const int a, unsigned char
             if (child_of) child_of[(uint32_t)(a * n + k)] = kci[v];
         }
         __syncthreads();  // LDS is reused by the next tile
-        return;
-    } else {
-        // -- LDS hash of the observations ----------------------------------------
-        for (int k = tid; k < n; k += nt) {
-            const uint64_t z = zk[k];
-            int slot;
-            if (z == kEmptyKey) {
-                slot = H;
-                misc[1] = 1;
-            } else {
-                int h = (int)(mix_key(z) & (uint64_t)(H - 1));
-                for (;;) {
-                    const unsigned long long old = atomicCAS((unsigned long long *)&tab[h], kEmptyKey, z);
-                    if (old == kEmptyKey || old == z) break;
-                    h = (h + 1) & (H - 1);
-                }
-                slot = h;
-            }
-            child[k] = slot;
-        }
-        __syncthreads();
-
-        // -- distinct observations, sorted ascending -----------------------------
-        uint64_t *dkey = zk;
-        for (int h = tid; h <= H; h += nt) {
-            const bool occupied = (h < H) ? (tab[h] != kEmptyKey) : (misc[1] != 0);
-            if (occupied) {
-                const int i = atomicAdd(&misc[0], 1);
-                dkey[i] = (h < H) ? tab[h] : kEmptyKey;
-                dslot[i] = (uint32_t)h;
-            }
-        }
-        __syncthreads();
-        D = misc[0];
-        if (D <= 64) {
-            if (wid == 0) wave_sort_pairs(dkey, dslot, D);
-            __syncthreads();
-        } else {
-            const int p = pow2_at_least(D);
-            for (int i = D + tid; i < p; i += nt) {
-                dkey[i] = kEmptyKey;
-                dslot[i] = 0xFFFFFFFFu;
-            }
-            __syncthreads();
-            block_sort_pairs(dkey, dslot, p);
-        }
-
-        // -- child index of each scenario -----------------------------------------
-        // rank_of_slot overlays the hash table; the distinct keys stay in zkey
-        int32_t *rank_of_slot = (int32_t *)tab;
-        for (int i = tid; i < D; i += nt) {
-            rank_of_slot[dslot[i]] = i;
-            if (i < cap) T->child_z[(int64_t)a * cap + i] = dkey[i];
-        }
-        if (tid == 0) T->n_children[a] = D;
-        __syncthreads();
-        for (int k = tid; k < n; k += nt) {
-            const int c = rank_of_slot[child[k]];
-            child[k] = c;
-            if (T->child_of) T->child_of[(int64_t)a * n + k] = c;
-        }
-        __syncthreads();
-
     }
-
-    // -- stable grouping: position of each scenario in perm --------------------
-    const int nchunks = (n + 63) >> 6;
-    if ((int64_t)nchunks * D <= Ly.table_cap) {
-        for (int i = tid; i < nchunks * D; i += nt) cnt[i] = 0;
-        __syncthreads();
-        for (int t = wid; t < nchunks; t += nw) {
-            const int k = t * 64 + lane;
-            const bool valid = k < n;
-            const int c = valid ? child[k] : -1;
-            uint64_t rem = __ballot(valid);
-            int myrank = 0;
-            while (rem) {
-                const int leader = __ffsll((unsigned long long)rem) - 1;
-                const int cl = __shfl(c, leader, 64);
-                const uint64_t m = __ballot(valid && c == cl);
-                if (valid && c == cl) myrank = __popcll(m & __lanemask_lt());
-                if (lane == leader) cnt[t * D + cl] = __popcll(m);
-                rem &= ~m;
-            }
-            if (valid) child[k] = c | (myrank << 16);
-        }
-        __syncthreads();
-        if (D <= 64) {
-            // one wavefront: lane c turns child c's chunk counts into an
-            // exclusive prefix, then the child offsets are a lane scan
-            if (wid == 0) {
-                int run = 0;
-                if (lane < D)
-                    for (int t = 0; t < nchunks; ++t) {
-                        const int v = cnt[t * D + lane];
-                        cnt[t * D + lane] = run;
-                        run += v;
-                    }
-                int incl = run;
-#pragma unroll
-                for (int d = 1; d < 64; d <<= 1) {
-                    const int o = __shfl_up(incl, d, 64);
-                    if (lane >= d) incl += o;
-                }
-                if (lane < D) {
-                    nc[lane] = run;
-                    off[lane] = incl - run;
-                }
-            }
-            __syncthreads();
-        } else {
-            for (int c = tid; c < D; c += nt) {
-                int run = 0;
-                for (int t = 0; t < nchunks; ++t) {
-                    const int v = cnt[t * D + c];
-                    cnt[t * D + c] = run;
-                    run += v;
-                }
-                nc[c] = run;
-                off[c] = run;
-            }
-            __syncthreads();
-            block_exclusive_scan(off, D, scan_scratch);
-        }
-        for (int k = tid; k < n; k += nt) {
-            const int cw = child[k];
-            const int c = cw & 0xFFFF;
-            permb[off[c] + cnt[(k >> 6) * D + c] + (cw >> 16)] = k;
-            child[k] = c;
-        }
-        __syncthreads();
-    } else {
-        uint32_t *comp = (uint32_t *)permb;
-        const int p = pow2_at_least(n);
-        for (int i = tid; i < p; i += nt) comp[i] = (i < n) ? (((uint32_t)child[i] << 16) | (uint32_t)i) : 0xFFFFFFFFu;
-        __syncthreads();
-        block_sort_u32(comp, p);
-        for (int i = tid; i < n; i += nt) {
-            const uint32_t v = comp[i];
-            const int c = (int)(v >> 16);
-            if (i == 0 || (comp[i - 1] >> 16) != (uint32_t)c) off[c] = i;
-        }
-        __syncthreads();
-        for (int c = tid; c < D; c += nt) nc[c] = ((c + 1 < D) ? off[c + 1] : n) - off[c];
-        __syncthreads();
-        for (int i = tid; i < n; i += nt) permb[i] = (int32_t)(comp[i] & 0xFFFFu);
-        __syncthreads();
-    }
-    for (int i = tid; i < n; i += nt) T->perm[(int64_t)a * n + i] = (int16_t)permb[i];
-    for (int c = tid; c < D && c < cap; c += nt) {
-        T->child_n[(int64_t)a * cap + c] = nc[c];
-        T->child_off[(int64_t)a * cap + c] = off[c];
-    }
-
-    // -- per-child sums: segmented wavefront scans over the grouped order ------
-    float *su = (float *)(lds + Ly.zkey);  // keys, table and counts are done
-    float *sl = su + Ly.p2;
-    for (int t = wid; t < nchunks; t += nw) {
-        const int i = t * 64 + lane;
-        const bool valid = i < n;
-        const int k = valid ? permb[i] : 0;
-        float vu = valid ? ub[k] : 0.0f;
-        float vl = valid ? lb[k] : 0.0f;
-        const int c = valid ? child[k] : -1;
-        const int c_prev = __shfl_up(c, 1, 64);
-        bool head = (lane == 0) || (c_prev != c);
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const float ou = __shfl_up(vu, d, 64);
-            const float ol = __shfl_up(vl, d, 64);
-            const int oh = __shfl_up((int)head, d, 64);
-            if (lane >= d && !head) {
-                vu = ou + vu;
-                vl = ol + vl;
-                head = oh != 0;
-            }
-        }
-        if (valid) {
-            su[i] = vu;
-            sl[i] = vl;
-        }
-    }
-    __syncthreads();
-    for (int c = tid; c < D && c < cap; c += nt) {
-        const int start = off[c], end = start + nc[c];
-        float tu = 0.0f, tl = 0.0f;
-        for (int t = start >> 6; t <= (end - 1) >> 6; ++t) {
-            const int e = min(end, (t + 1) * 64) - 1;
-            tu = tu + su[e];
-            tl = tl + sl[e];
-        }
-        T->child_u0[(int64_t)a * cap + c] = tu / (float)nc[c];
-        T->child_l0[(int64_t)a * cap + c] = tl / (float)nc[c];
-    }
-    if (tid == 0) {
-        float tr = 0.0f;
-        for (int t = 0; t < nchunks; ++t) tr = tr + chunk_r[t];
-        T->r_mean[a] = n > 0 ? tr / (float)n : 0.0f;
-        T->steps[2 * a + 0] = (int64_t)stepc[0];
-        T->steps[2 * a + 1] = (int64_t)stepc[1];
-    }
-    __syncthreads();  // LDS is reused by the next tile
 }
+
+// A value from the lane CTRL names (0 where there is none).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_srci(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, true);
+}
+// One step of a segmented inclusive scan of two sums: f set where the
+// segment's first lane has been reached.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void seg_step(float &u, float &l, int &f) {
+    const float ou = dpp_src<CTRL, ROWS>(u), ol = dpp_src<CTRL, ROWS>(l);
+    const int of = dpp_srci<CTRL, ROWS>(f);
+    u = f ? u : ou + u;
+    l = f ? l : ol + l;
+    f |= of;
+}
+
+// LDS traffic of one wavefront stays in order; this keeps the compiler from
+// moving it.
+__device__ __forceinline__ void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // Navigation: na actions [a0, a0 + na) of one leaf.
 //
@@ -709,26 +334,6 @@ struct NavCode {
     __device__ static int kind(uint32_t c) { return (int)((c >> 14) & 3u); }
     __device__ static int count(uint32_t c) { return (int)((c >> 17) & kMax); }
 };
-
-// A value from the lane CTRL names (0 where there is none).
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int dpp_srci(int v) {
-    return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, true);
-}
-// One step of a segmented inclusive scan of two sums: f set where the
-// segment's first lane has been reached.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ void seg_step(float &u, float &l, int &f) {
-    const float ou = dpp_src<CTRL, ROWS>(u), ol = dpp_src<CTRL, ROWS>(l);
-    const int of = dpp_srci<CTRL, ROWS>(f);
-    u = f ? u : ou + u;
-    l = f ? l : ol + l;
-    f |= of;
-}
-
-// LDS traffic of one wavefront stays in order; this keeps the compiler from
-// moving it.
-__device__ __forceinline__ void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 __device__ __forceinline__ void run_tile_nav(const HDX_CONST LeafTask *T, const int a0, const int na, unsigned char *lds) {
     using Ops = NavOps;
@@ -999,9 +604,329 @@ __device__ __forceinline__ void run_tile_nav(const HDX_CONST LeafTask *T, const 
     __syncthreads();  // LDS is reused by the next tile
 }
 
-template <int PM, bool kGroup>
-__device__ __forceinline__ void run_ped(const HDX_CONST LeafTask *T, int a, unsigned char *lds, const LdsLayout &Ly) {
-    run_tile<PedOps<PM>, kGroup>(T, a, lds, Ly);
+// One compare-exchange of a bitonic network over (key, position) pairs in
+// LDS: elements i and i + stride of a run sorted in blocks of `size`.
+__device__ __forceinline__ void exchange(uint64_t *keys, uint16_t *vals, int i, int stride, int size) {
+    const uint64_t ka = keys[i], kb = keys[i + stride];
+    const uint32_t va = vals[i], vb = vals[i + stride];
+    const bool less = kb < ka || (kb == ka && vb < va);
+    if (less == ((i & size) == 0)) {
+        keys[i] = kb;
+        keys[i + stride] = ka;
+        vals[i] = (uint16_t)vb;
+        vals[i + stride] = (uint16_t)va;
+    }
+}
+
+// Sort the (key, position) pairs of the three actions, p2 (a power of two of
+// at least 64) each, ascending.  Strides below 64 stay inside the 128
+// elements (64 of a run of 64) that one wavefront handles, so only longer
+// ones need a barrier.
+__device__ __forceinline__ void sort_actions(uint64_t *zk, uint16_t *pos, int p2) {
+    const int lane = lane_id(), wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const int block = p2 < 128 ? p2 : 128, blocks = kPedActions * p2 / block, half = p2 >> 1;
+    const int log_half = 31 - __clz(half);
+    for (int size = 2; size <= p2; size <<= 1) {
+        int stride = size >> 1;
+        for (; stride >= block; stride >>= 1) {
+            for (int e = threadIdx.x; e < kPedActions * half; e += blockDim.x) {
+                const int a = e >> log_half, q = e & (half - 1);
+                const int i = ((q & ~(stride - 1)) << 1) | (q & (stride - 1));
+                exchange(zk + a * p2, pos + a * p2, i, stride, size);
+            }
+            __syncthreads();
+        }
+        // the strides inside a block; every size up to a block at once
+        const int top = size < block ? block : size;
+        for (int b = wid; b < blocks; b += nw) {
+            const int at = b * block, a = at / p2, o = at - a * p2;
+            for (int sz = size < block ? 2 : size; sz <= top; sz <<= 1)
+                for (int st = sz >> 1 < block ? sz >> 1 : block >> 1; st > 0; st >>= 1) {
+                    if (lane < block >> 1)
+                        exchange(zk + a * p2, pos + a * p2, o + (((lane & ~(st - 1)) << 1) | (lane & (st - 1))), st, sz);
+                    wave_fence();
+                }
+        }
+        __syncthreads();
+        if (size < block) size = block;
+    }
+}
+
+// Driving: the three actions of one leaf, a scenario on G lanes (PedLanes).
+//
+// What bounds it: instruction issue, two thirds of it the random blocks and
+// the walks of the pedestrians.  These are the same for the three actions, so
+// a tile is a whole leaf and takes each pedestrian's step once (one action
+// per tile took it three times).  Four lanes per scenario with up to PM / 4
+// pedestrians each leave the work of a scenario within a few percent of one
+// lane's (the cars are repeated on four lanes, their failure words drawn one
+// depth per lane) and give four times the wavefronts at a third of the
+// registers; 8 or 16 lanes (one or two pedestrians each) cost a quarter more
+// work and are for leaves too few or too small to fill the GPU otherwise.
+// Measured with 16 pedestrians and rollouts of 50 steps: 512 leaves of
+// 125..500 scenarios 0.50 ms (2.4e8 VALU instructions of a wavefront, 0.77 of
+// the issue slots) against 1.35-1.48 ms, one leaf of 500 scenarios 0.40
+// against 0.61 ms.
+//
+// Grouping: (observation, position) pairs of the three actions sorted in LDS
+// (the observations are hashes, most of them distinct), then one wavefront
+// per action walks the grouped order with segmented DPP scans over 64-aligned
+// chunks, a child's chunk partials added in chunk order.
+template <int G, int PP>
+__device__ __forceinline__ void run_tile_ped(const HDX_CONST LeafTask *T, unsigned char *lds) {
+    constexpr int A = kPedActions;
+    const int n = T->n, cap = T->cap;
+    const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id(), wid = tid >> 6, nw = nt >> 6;
+    const PedLayout Ly = make_ped_layout(n);
+    uint64_t *zk = (uint64_t *)(lds + Ly.zkey);
+    uint16_t *pos = (uint16_t *)(lds + Ly.pos);
+    float *ub = (float *)(lds + Ly.ub), *lb = (float *)(lds + Ly.lb);
+    uint8_t *rc = (uint8_t *)(lds + Ly.rcode);
+    int32_t *count = (int32_t *)(lds + Ly.misc);  // live scenarios, then rollout steps per action
+    const int p2 = Ly.p2;
+    const MView M = make_view(T->model, nullptr);
+    if (tid < 1 + A) count[tid] = 0;
+    for (int i = tid; i < A * p2; i += nt)
+        if ((i & (p2 - 1)) >= n) {
+            zk[i] = kEmptyKey;
+            pos[i] = 0xFFFFu;
+        }
+    __syncthreads();
+
+    RolloutParams RP;
+    RP.k0 = T->k0;
+    RP.k1 = T->k1;
+    RP.policy = T->policy;
+    RP.const_action = T->const_action;
+    RP.max_steps = T->max_steps;
+    RP.max_depth = T->max_depth;
+    RP.n_actions = T->n_actions;
+    const PedConst C = ped_const(M);
+    const int depth = T->depth, last_action = T->last_action, P = C.n_peds;
+    const int d0 = depth + 1, R = rollout_length(RP, d0);
+    const StatesPtr parent = load_states(&T->parent);
+    const StatesPtr leaf_out = load_states(&T->out);
+    const StatesPtr sprime = load_states(&T->sprime);
+    const bool pair_out = has_states(sprime);
+    const int j = lane & (G - 1), first = lane & ~(G - 1);  // lane of the group, its first lane
+    const int car = min(lane & 3, A - 1);                   // the action whose car this lane owns
+
+    // -- gather + update + expand + bounds + rollouts (Eq. 10, 12, 13) ------
+    int my_exp = 0, my_steps = 0;
+    for (int base = wid * (64 / G); base < n; base += nt / G) {
+        const int k = base + lane / G;
+        const bool valid = k < n;
+        PedLanes<G, PP> E;
+        E.clear();
+        uint32_t id = 0, goals = 0;  // four bits per slot
+        float s = 0.0f, lv = 0.0f;
+        bool live = false;
+        int car_in = 0;
+        if (valid) {
+            const uint32_t p = (uint16_t)T->idx[(uint32_t)k];
+            id = T->parent_ids[p];
+            s = parent.s[p];
+            car_in = parent.car[p];
+            lv = (float)(car_in & 0xff);
+            live = !((car_in >> 8) & 1);
+#pragma unroll
+            for (int q = 0; q < PP; ++q) {
+                const int ped = q * G + j;
+                if (ped < P) {
+                    const int g = parent.goal[ped * parent.stride + p];
+                    E.px[q] = parent.px[ped * parent.stride + p];
+                    E.py[q] = parent.py[ped * parent.stride + p];
+                    E.gx[q] = M.h->goal_x[g];
+                    E.gy[q] = M.h->goal_y[g];
+                    goals |= (uint32_t)g << (4 * q);
+                }
+            }
+        }
+        if (last_action >= 0) {
+            if (live) {
+                const bool failed = philox(id, (uint32_t)(depth - 1), 0, kTagStep, RP.k0, RP.k1).x < C.fail_thr;
+                lv = ped_level(C, lv, (float)(1 - last_action), failed);
+                s = ped_advance(C, s, lv);
+                E.walk(C, j, id, (uint32_t)(depth - 1), RP.k0, RP.k1);
+            }
+            const uint32_t see = E.look(C, s, car);
+            live &= !((lv > 0.0f) & ((see & 1u) != 0)) & !(s >= C.path_len);
+        }
+        if (valid) {
+            if (j == 0) {
+                leaf_out.s[k] = s;
+                leaf_out.car[k] = (int)lv | (live ? 0 : 0x100);
+                T->ids_out[k] = id;
+            }
+#pragma unroll
+            for (int q = 0; q < PP; ++q) {
+                const int ped = q * G + j;
+                if (ped < P) {
+                    leaf_out.px[ped * leaf_out.stride + k] = E.px[q];
+                    leaf_out.py[ped * leaf_out.stride + k] = E.py[q];
+                    leaf_out.goal[ped * leaf_out.stride + k] = (uint8_t)((goals >> (4 * q)) & 15u);
+                }
+            }
+        }
+        // the step of this lane's action
+        if (live) {
+            const bool failed = philox(id, (uint32_t)depth, 0, kTagStep, RP.k0, RP.k1).x < C.fail_thr;
+            lv = ped_level(C, lv, (float)(1 - car), failed);
+            s = ped_advance(C, s, lv);
+            E.walk(C, j, id, (uint32_t)depth, RP.k0, RP.k1);
+        }
+        uint32_t see = E.look(C, s, car);
+        const bool hit0 = (lv > 0.0f) & ((see & 1u) != 0), there0 = s >= C.path_len;
+        const int code = !live ? 0 : hit0 ? 2 : there0 ? 3 : 1;
+        bool alive = live & !hit0 & !there0;
+        const bool term = !alive;
+        // the observation: a hash chained over the level and the floored positions, in pedestrian order
+        uint64_t z = kPedTerminalObs;
+        {
+            uint64_t h = hash_field(0x243F6A8885A308D3ull, (int32_t)lv);
+#pragma unroll
+            for (int q = 0; q < PP; ++q) {
+                if (q * G < P) {
+                    const int fx = (int32_t)floorf(E.px[q]), fy = (int32_t)floorf(E.py[q]);
+                    for (int i = 0; i < G && q * G + i < P; ++i) {
+                        h = hash_field(h, __shfl(fx, first + i, 64));
+                        h = hash_field(h, __shfl(fy, first + i, 64));
+                    }
+                }
+            }
+            if (alive) z = h == kPedTerminalObs ? kPedTerminalObs - 1 : h;
+        }
+        const float U = ped_upper(M, s, term ? 1 : 0);
+        if (pair_out && valid) {
+            if (j < A) {
+                const int64_t at = (int64_t)j * n + k;
+                sprime.s[at] = s;
+                sprime.car[at] = (int)lv | (term ? 0x100 : 0);
+            }
+#pragma unroll
+            for (int q = 0; q < PP; ++q) {
+                const int ped = q * G + j;
+                if (ped < P)
+                    for (int a = 0; a < A; ++a) {
+                        const int64_t at = ped * sprime.stride + (int64_t)a * n + k;
+                        sprime.px[at] = E.px[q];
+                        sprime.py[at] = E.py[q];
+                        sprime.goal[at] = (uint8_t)((goals >> (4 * q)) & 15u);
+                    }
+            }
+        }
+        // the rollouts of the three actions together
+        float value = 0.0f;
+        int steps = 0;
+        uint32_t fails = 0, pol = 0;
+        for (int t = 0; t < R && __ballot(alive); ++t) {
+            const int tg = t & (G - 1);
+            if (tg == 0) {
+                // the next G depths' failure words, one depth per lane
+                const uint32_t d = (uint32_t)(d0 + t + j);
+                fails = (uint32_t)(__ballot(philox(id, d, 0, kTagStep, RP.k0, RP.k1).x < C.fail_thr) >> first);
+                if (RP.policy == HDX_POLICY_RANDOM) {
+                    const uint32_t w = philox(id, d, 0, kTagPolicy, RP.k0, RP.k1).x % (uint32_t)A;
+                    const uint64_t b0 = __ballot(w & 1u), b1 = __ballot(w & 2u);
+                    pol = ((uint32_t)(b0 >> first) & 0xffffu) | ((uint32_t)(b1 >> first) << 16);
+                }
+            }
+            float change = (see & 256u) ? -1.0f : 1.0f;  // brake, or accelerate
+            if (RP.policy == HDX_POLICY_CONST) change = (float)(1 - RP.const_action);
+            if (RP.policy == HDX_POLICY_RANDOM)
+                change = (float)(1 - ((int)((pol >> tg) & 1u) | ((int)((pol >> (16 + tg)) & 1u) << 1)));
+            lv = ped_level(C, lv, change, ((fails >> tg) & 1u) != 0);
+            s = ped_advance(C, s, lv);
+            E.walk(C, j, id, (uint32_t)(d0 + t), RP.k0, RP.k1);
+            see = E.look(C, s, car);
+            const bool hit = (lv > 0.0f) & ((see & 1u) != 0), there = s >= C.path_len;
+            const float v = value + M.gpow_uniform(t) * (hit ? C.r_hit : there ? C.r_goal : C.r_step);
+            value = alive ? v : value;
+            steps += alive ? 1 : 0;
+            alive &= !(hit | there);
+        }
+        if (valid && j < A) {
+            zk[j * p2 + k] = z;
+            pos[j * p2 + k] = (uint16_t)k;
+            ub[j * n + k] = U;
+            lb[j * n + k] = value;
+            rc[j * n + k] = (uint8_t)code;
+            my_exp += j == 0 && live ? 1 : 0;
+            my_steps += steps;
+            const int64_t at = (int64_t)j * n + k;
+            if (T->r) T->r[at] = code == 0 ? 0.0f : code == 1 ? C.r_step : code == 2 ? C.r_hit : C.r_goal;
+            if (T->z) T->z[at] = z;
+            if (T->U) T->U[at] = U;
+            if (T->L) T->L[at] = value;
+        }
+    }
+    if (j < A && my_exp) atomicAdd(&count[0], my_exp);
+    if (j < A && my_steps) atomicAdd(&count[1 + j], my_steps);
+    __syncthreads();
+
+    // -- observations ascending, positions ascending within one ----------------
+    sort_actions(zk, pos, p2);
+
+    // -- children and their sums, one wavefront per action -----------------------
+    for (int a = wid; a < A; a += nw) {
+        const uint64_t *z = zk + a * p2;
+        const uint16_t *order = pos + a * p2;
+        float carry_u = 0.0f, carry_l = 0.0f, tr = 0.0f;  // a child's sums so far; the rewards'
+        int children = 0, open = 0;                       // children so far; the open child's first place
+        int32_t *const child_of = T->child_of;
+        for (int t = 0; t * 64 < n; ++t) {
+            const int i = t * 64 + lane;
+            const bool valid = i < n;
+            const int k = valid ? order[i] : 0;
+            const uint64_t key = valid ? z[i] : 0;
+            const bool head = valid && (i == 0 || z[i - 1] != key);
+            const bool last = valid && (i + 1 == n || z[i + 1] != key);
+            const uint64_t heads = __ballot(head);
+            const uint64_t mine = heads & (~0ull >> (63 - lane));  // heads at or below this lane
+            const int start = mine ? t * 64 + 63 - __clzll((long long)mine) : open;
+            const int ci = children + __popcll(mine) - 1;
+            float u = valid ? ub[a * n + k] : 0.0f, l = valid ? lb[a * n + k] : 0.0f;
+            int f = (head || !valid || lane == 0) ? 1 : 0;
+            seg_step<0x111, 0xf>(u, l, f);
+            seg_step<0x112, 0xf>(u, l, f);
+            seg_step<0x114, 0xf>(u, l, f);
+            seg_step<0x118, 0xf>(u, l, f);
+            seg_step<0x142, 0xa>(u, l, f);
+            seg_step<0x143, 0xc>(u, l, f);
+            if (mine == 0) {
+                u = carry_u + u;
+                l = carry_l + l;
+            }
+            if (valid) {
+                T->perm[(int64_t)a * n + i] = (int16_t)k;
+                if (child_of) child_of[(int64_t)a * n + k] = ci;
+            }
+            if (last && ci < cap) {
+                const int64_t at = (int64_t)a * cap + ci;
+                const int cn = i + 1 - start;
+                T->child_z[at] = key;
+                T->child_n[at] = cn;
+                T->child_off[at] = start;
+                T->child_u0[at] = u / (float)cn;
+                T->child_l0[at] = l / (float)cn;
+            }
+            carry_u = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(u), 63));
+            carry_l = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l), 63));
+            children += __popcll(heads);
+            open = __builtin_amdgcn_readlane(start, 63);
+            // mean step reward: this 64-scenario chunk in scenario order
+            const int c = valid ? rc[a * n + i] : 0;
+            const float r = c == 0 ? 0.0f : c == 1 ? C.r_step : c == 2 ? C.r_hit : C.r_goal;
+            tr = tr + (__ballot(r != 0.0f) ? wave_total(r) : 0.0f);
+        }
+        if (lane == 0) {
+            T->n_children[a] = children;
+            T->r_mean[a] = n > 0 ? tr / (float)n : 0.0f;
+            T->steps[2 * a + 0] = (int64_t)count[0];
+            T->steps[2 * a + 1] = (int64_t)count[1 + a];
+        }
+    }
+    __syncthreads();  // LDS is reused by the next tile
 }
 
 __device__ __forceinline__ int remap_xcd(int b, int grid) {
@@ -1012,20 +937,24 @@ __device__ __forceinline__ int remap_xcd(int b, int grid) {
 }
 
 // MODE 0: RockSample only; 1: crowd driving only; 2: both; 3: multi-agent
-// RockSample only; 4: navigation only.  Workgroups of the driving model are
-// capped at 256 lanes so its per-lane state can stay in registers;
-// navigation (94 registers) takes up to 1024, because one large leaf's LDS
-// carve-up leaves room for one workgroup per CU.
+// RockSample only; 4: navigation only.  Workgroups of RockSample and driving
+// are capped at 512 lanes; navigation (94 registers) takes up to 1024,
+// because one large leaf's LDS carve-up leaves room for one workgroup per CU.
 template <int MODE>
-constexpr bool small_obs_mode() { return MODE == 0 || MODE == 3; }
+constexpr bool rock_mode() { return MODE == 0 || MODE == 3; }
 template <int MODE>
-constexpr int max_threads() { return small_obs_mode<MODE>() ? 512 : MODE == 4 ? 1024 : 256; }
+constexpr int max_threads() { return rock_mode<MODE>() ? 512 : 1024; }
 // RockSample tiles: keep 7 wavefronts per SIMD resident (at most 72 VGPRs,
-// no spills); the driving model's register state decides its own.
+// no spills); the others' register state decides their own.
 template <int MODE>
-constexpr int min_waves() { return small_obs_mode<MODE>() ? 7 : 1; }
+constexpr int min_waves() { return rock_mode<MODE>() ? 7 : 1; }
 
-template <int MODE, int PM, bool kGroup = false>
+// Lanes per scenario of the driving tiles: at most four pedestrians per lane,
+// or (kSpread) one or two.
+template <int PM, bool kSpread>
+constexpr int ped_lanes() { return !kSpread ? (PM == 32 ? 8 : 4) : PM == 8 ? 8 : 16; }
+
+template <int MODE, int PM, bool kSpread>
 __device__ __forceinline__ void run_mode(const HDX_CONST LeafTask *T, int a, unsigned char *lds, const LdsLayout &Ly) {
     if constexpr (MODE == 3) {
         run_tile<MarsOps>(T, a, lds, Ly);
@@ -1033,12 +962,12 @@ __device__ __forceinline__ void run_mode(const HDX_CONST LeafTask *T, int a, uns
         run_tile_nav(T, a, min((int)T->tile_actions, T->n_actions - a), lds);
     } else if (MODE == 0 || (MODE == 2 && T->kind == HDX_ROCKSAMPLE)) {
         run_tile<RsOps>(T, a, lds, Ly);
-    } else {
-        run_ped<PM, kGroup>(T, a, lds, Ly);
+    } else if constexpr (MODE == 1 || MODE == 2) {
+        run_tile_ped<ped_lanes<PM, kSpread>(), PM / ped_lanes<PM, kSpread>()>(T, lds);
     }
 }
 
-template <int MODE, int PM, bool kGroup = false>
+template <int MODE, int PM, bool kSpread = false>
 __global__ __launch_bounds__(max_threads<MODE>(), min_waves<MODE>()) void expand_tiles(const LeafTask *tasks,
                                                                                        const Tile *tiles,
                                                                                        TileQueue *queue,
@@ -1047,7 +976,7 @@ __global__ __launch_bounds__(max_threads<MODE>(), min_waves<MODE>()) void expand
                                                                                        int32_t xcd_remap) {
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ int32_t s_tile;
-    const LdsLayout Ly = make_layout(n_max, small_obs_mode<MODE>());
+    const LdsLayout Ly = make_layout(n_max);
     const int32_t n_tiles = __builtin_amdgcn_readfirstlane(queue->n_tiles);
     int iter = 0;
     for (;;) {
@@ -1065,7 +994,7 @@ __global__ __launch_bounds__(max_threads<MODE>(), min_waves<MODE>()) void expand
         if (t >= n_tiles) break;
         const HDX_CONST Tile *tile = (const HDX_CONST Tile *)(tiles + t);
         const HDX_CONST LeafTask *T = (const HDX_CONST LeafTask *)(tasks + tile->leaf);
-        run_mode<MODE, PM, kGroup>(T, tile->action, lds, Ly);
+        run_mode<MODE, PM, kSpread>(T, tile->action, lds, Ly);
     }
     if (persistent && threadIdx.x == 0) {
         __threadfence();
@@ -1088,7 +1017,7 @@ __global__ __launch_bounds__(max_threads<MODE>()) void expand_args(const ArgPack
 #else
     const ArgPack *P = &pack;
 #endif
-    const LdsLayout Ly = make_layout(P->n_max, small_obs_mode<MODE>());
+    const LdsLayout Ly = make_layout(P->n_max);
     const int n_leaves = P->n_leaves;
     const int n_tiles = P->tile_begin[n_leaves];
     const int t = P->xcd_remap ? remap_xcd((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
@@ -1103,24 +1032,26 @@ __global__ __launch_bounds__(max_threads<MODE>()) void expand_args(const ArgPack
 // navigation, tiles of up to `pairs` pairs).
 template <int MODE>
 uint32_t lds_bytes(int32_t n_max, int32_t pairs, int32_t threads) {
-    if (MODE != 4) return make_layout(n_max, small_obs_mode<MODE>()).total;
+    if (rock_mode<MODE>()) return make_layout(n_max).total;
+    if (MODE == 1) return make_ped_layout(n_max).total;
+    if (MODE == 2) return std::max(make_layout(n_max).total, make_ped_layout(n_max).total);
     const uint32_t b = make_nav_layout((uint32_t)pairs, kNavActions, (uint32_t)(n_max + 63) / 64, (uint32_t)threads / 64,
                                        false).total;
     return std::min(b, (uint32_t)max_dynamic_lds());
 }
 
+template <class K>
+hipError_t allow_lds(K *kernel) {
+    return hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, max_dynamic_lds());
+}
 template <int MODE, int PM>
 hipError_t configure_t() {
-    hipError_t e = hipFuncSetAttribute((const void *)expand_tiles<MODE, PM>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, max_dynamic_lds());
-    if (e != hipSuccess) return e;
-    if constexpr (MODE == 1) {
-        e = hipFuncSetAttribute((const void *)expand_tiles<MODE, PM, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                max_dynamic_lds());
-        if (e != hipSuccess) return e;
-    }
-    return hipFuncSetAttribute((const void *)expand_args<MODE, PM>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               max_dynamic_lds());
+    hipError_t e = allow_lds(expand_args<MODE, PM>);
+    if constexpr (MODE != 2)  // calls that mix the two models launch one kernel per model
+        if (e == hipSuccess) e = allow_lds(expand_tiles<MODE, PM>);
+    if constexpr (MODE == 1)
+        if (e == hipSuccess) e = allow_lds(expand_tiles<MODE, PM, true>);
+    return e;
 }
 
 template <int MODE, int PM>
@@ -1134,7 +1065,7 @@ hipError_t launch_args_t(const ArgPack &pack, const Schedule &sch, hipStream_t s
     return hipGetLastError();
 }
 
-template <int MODE, int PM, bool kGroup = false>
+template <int MODE, int PM, bool kSpread = false>
 hipError_t launch_expand_t(const LeafTask *d_tasks, const Tile *d_tiles, TileQueue *d_queue, int32_t n_tiles,
                            int32_t n_max, int32_t pairs, const Schedule &sch, int32_t n_cu, hipStream_t stream) {
     // persistent: a fixed grid that drains the tile queue, so a captured
@@ -1142,7 +1073,7 @@ hipError_t launch_expand_t(const LeafTask *d_tasks, const Tile *d_tiles, TileQue
     const int grid = sch.persistent > 0 ? n_cu * sch.persistent : n_tiles;
     if (grid < 1) return hipSuccess;
     const int threads = sch.threads > max_threads<MODE>() ? max_threads<MODE>() : sch.threads;
-    hipLaunchKernelGGL((expand_tiles<MODE, PM, kGroup>), dim3(grid), dim3(threads),
+    hipLaunchKernelGGL((expand_tiles<MODE, PM, kSpread>), dim3(grid), dim3(threads),
                        lds_bytes<MODE>(n_max, pairs, threads), stream, d_tasks, d_tiles, d_queue, n_max, sch.persistent > 0 ? 1 : 0, sch.xcd_remap);
     return hipGetLastError();
 }
@@ -1328,9 +1259,11 @@ Variant pick_variant(int32_t has_rs, int32_t has_ped, int32_t ped_max, int32_t n
     return v;
 }
 
-int32_t variant_max_threads(const Variant &v) {
-    return v.mode == 0 ? max_threads<0>() : v.mode == 3 ? max_threads<3>() : v.mode == 4 ? max_threads<4>()
-                                                                            : max_threads<1>();
+int32_t variant_max_threads(const Variant &v) { return v.mode == 0 || v.mode == 3 ? max_threads<0>() : max_threads<1>(); }
+
+int32_t variant_lanes(const Variant &v, int32_t n) {
+    if (v.mode != 1 && v.mode != 2) return n;
+    return n * (!v.group ? (v.pm == 32 ? 8 : 4) : v.pm <= 8 ? 8 : 16);
 }
 
 hipError_t configure_expand_kernels() {
@@ -1355,8 +1288,7 @@ hipError_t launch_expand(const LeafTask *d_tasks, const Tile *d_tiles, TileQueue
     if (v.mode == 4) return HDX_LAUNCH(4, 1);
     if (v.mode == 1 && v.group)
         return v.pm == 8 ? HDX_LAUNCH_G(8) : v.pm == 16 ? HDX_LAUNCH_G(16) : HDX_LAUNCH_G(32);
-    if (v.mode == 1) return v.pm == 8 ? HDX_LAUNCH(1, 8) : v.pm == 16 ? HDX_LAUNCH(1, 16) : HDX_LAUNCH(1, 32);
-    return v.pm == 8 ? HDX_LAUNCH(2, 8) : v.pm == 16 ? HDX_LAUNCH(2, 16) : HDX_LAUNCH(2, 32);
+    return v.pm == 8 ? HDX_LAUNCH(1, 8) : v.pm == 16 ? HDX_LAUNCH(1, 16) : HDX_LAUNCH(1, 32);
 #undef HDX_LAUNCH_G
 #undef HDX_LAUNCH
 }

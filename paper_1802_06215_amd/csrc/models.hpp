@@ -83,6 +83,15 @@ __device__ __forceinline__ void stage_gpow(const DevModel *gm, float *gpow_lds) 
     }
 }
 
+// a ^ b ^ c in one instruction.
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return (uint32_t)__builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+#else
+    return a ^ b ^ c;
+#endif
+}
+
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds of two
 // 32x32->64 multiplies, the key advanced by the Weyl increments in between.
 __device__ __forceinline__ uint4 philox(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
@@ -94,12 +103,12 @@ __device__ __forceinline__ uint4 philox(uint32_t c0, uint32_t c1, uint32_t c2, u
             k1 += 0xBB67AE85u;
         }
         // one 32x32->64 product each (a single v_mad_u64_u32 instead of
-        // separate high and low multiplies)
+        // separate high and low multiplies, at the rate of any other instruction)
         const uint64_t p0 = (uint64_t)0xD2511F53u * (uint64_t)c0;
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c2;
         const uint32_t hi0 = (uint32_t)(p0 >> 32), lo0 = (uint32_t)p0;
         const uint32_t hi1 = (uint32_t)(p1 >> 32), lo1 = (uint32_t)p1;
-        const uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
+        const uint32_t n0 = xor3(hi1, c1, k0), n2 = xor3(hi0, c3, k1);
         c0 = n0;
         c1 = lo1;
         c2 = n2;
@@ -137,12 +146,7 @@ struct RsOps {
     struct State {
         int32_t w;
     };
-    static constexpr bool kHashObs = false;
     static constexpr bool kSplitRollout = true;  // small step: one rollout loop per policy
-    static constexpr bool kSmallObs = true;       // observations 0 (none), 1, 2 (sensor readings)
-    static constexpr bool kLdsModel = false;      // expansion reads no per-lane table from LDS
-    static constexpr bool kWaveUpper = true;      // upper bound evaluated by whole wavefronts
-    static constexpr bool kGroupRollout = false;  // one lane per scenario in rollouts
 
     __device__ static void load(const MView &, const StatesPtr &S, int64_t p, State &st) { st.w = S.w[p]; }
     __device__ static void make_terminal(State &st) { st.w = 1 << 30; }
@@ -285,12 +289,7 @@ struct MarsOps {
     struct State {
         int32_t p, rk;
     };
-    static constexpr bool kHashObs = false;
     static constexpr bool kSplitRollout = true;
-    static constexpr bool kSmallObs = true;  // 9 joint observations
-    static constexpr bool kLdsModel = false;
-    static constexpr bool kWaveUpper = true;
-    static constexpr bool kGroupRollout = false;
     static constexpr int kGone0 = 20, kTerm = 30;
     static constexpr int kFar = 62;  // beyond any Manhattan distance on a 31 x 31 grid
 
@@ -750,6 +749,166 @@ __device__ __forceinline__ uint64_t hash_field(uint64_t h, int32_t f) {
     return mix64((h ^ (uint64_t)(uint32_t)f) + 0x9E3779B97F4A7C15ull);
 }
 
+// One pedestrian's walk towards its goal (gx, gy) with heading noise from the
+// four words of its block: px, py move by one step, or onto the goal when it
+// is within one.
+//
+// Each operation is rounded to nearest once, as an IEEE-754 evaluation of
+// the same formulas rounds it.  The root and the four quotients are the
+// larger part of a step, and the general sequences for them spend most of
+// their instructions on operands near the ends of the exponent range.  Here
+// the operands are checked to lie in a middle range (all but a vanishing
+// share of them, and a wavefront with one outside takes the general
+// operations), where the textbook sequences round correctly: the root by
+// Goldschmidt's iteration with a final residual, and quotients by a
+// correctly rounded reciprocal -- shared by the two quotients of one
+// denominator -- and a residual (Markstein 1990).  Root and reciprocal have
+// been compared with the general operations over every significand and the
+// exponents -62..62.
+__device__ __forceinline__ float recip_rn(float b) {  // 2^-62 <= b < 2^62
+    const float r = __builtin_amdgcn_rcpf(b);
+    return __builtin_fmaf(__builtin_fmaf(-b, r, 1.0f), r, r);
+}
+__device__ __forceinline__ float quot_rn(float a, float b, float rb) {  // rb = recip_rn(b)
+    const float q = a * rb;
+    return __builtin_fmaf(__builtin_fmaf(-b, q, a), rb, q);
+}
+__device__ __forceinline__ float sqrt_rn(float x) {  // 2^-62 <= x < 2^62
+    const float y = __builtin_amdgcn_rsqf(x);
+    const float s = x * y, h = 0.5f * y;
+    const float e = __builtin_fmaf(-h, s, 0.5f);
+    const float s1 = __builtin_fmaf(s, e, s), h1 = __builtin_fmaf(h, e, h);
+    return __builtin_fmaf(__builtin_fmaf(-s1, s1, x), h1, s1);
+}
+// The driving model's constants, read once and kept in scalar registers (left
+// to itself the compiler reads them again in every rollout step and waits).
+struct PedConst {
+    float near_d2, step_len, half_sigma, ih_scale, coll_r2, dt, path_len, top, r_step, r_hit, r_goal;
+    uint32_t fail_thr;  // p_fail < 1: 32 bits hold it
+    int n_peds;
+};
+__device__ __forceinline__ PedConst ped_const(const MView &M) {
+    auto pin = [](float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); };
+    PedConst C;
+    C.near_d2 = pin(M.h->near_d2);
+    C.step_len = pin(M.h->step_len);
+    C.half_sigma = pin(M.h->half_sigma);
+    C.ih_scale = pin(M.h->ih_scale);
+    C.coll_r2 = pin(M.h->coll_r2);
+    C.dt = pin(M.h->dt);
+    C.path_len = pin(M.h->path_len);
+    C.top = pin((float)(M.h->n_levels - 1));
+    C.r_step = pin(M.h->r_step);
+    C.r_hit = pin(M.h->r_step + M.h->r_collision);
+    C.r_goal = pin(M.h->r_step + M.h->r_goal);
+    C.fail_thr = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)M.h->fail_thr);
+    C.n_peds = __builtin_amdgcn_readfirstlane(M.h->n_peds);
+    return C;
+}
+
+__device__ __forceinline__ void move_ped(const PedConst &C, const uint4 &u, float gx, float gy, float &px, float &py) {
+    const int32_t sum = (int32_t)((u.x >> 8) + (u.y >> 8) + (u.z >> 8) + (u.w >> 8));
+    const float noise = (float)(sum - 33554430) * C.ih_scale;
+    const float dx = gx - px;
+    const float dy = gy - py;
+    const float d2 = dx * dx + dy * dy;
+    const bool near = d2 <= C.near_d2;  // sqrt(d2) <= step_len
+    const float t = C.half_sigma * noise;
+    const float t2 = t * t;
+    const float den = 1.0f + t2, num = 1.0f - t2, two_t = 2.0f * t;
+    const float least = fminf(fminf(fabsf(dx), fabsf(dy)), fminf(fabsf(num), fabsf(two_t)));
+    const bool middle = (least >= 0x1p-30f) & (d2 < 0x1p60f) & (den < 0x1p60f);
+    const float dist = sqrt_rn(d2), rd = recip_rn(dist), rn = recip_rn(den);
+    float ux = quot_rn(dx, dist, rd), uy = quot_rn(dy, dist, rd);
+    float c = quot_rn(num, den, rn), sn = quot_rn(two_t, den, rn);
+    if (__builtin_expect(!(near | middle), 0)) {
+        const float root = __builtin_sqrtf(d2);
+        ux = dx / root;
+        uy = dy / root;
+        c = num / den;
+        sn = two_t / den;
+    }
+    const float rx = ux * c - uy * sn;
+    const float ry = ux * sn + uy * c;
+    px = near ? gx : px + C.step_len * rx;
+    py = near ? gy : py + C.step_len * ry;
+}
+
+// The car: its speed level (a small whole number, held as a float) after an
+// action, its position a step later, and the bound of a state.  Action a
+// changes the level by 1 - a within 0..top.
+__device__ __forceinline__ float ped_level(const PedConst &C, float level, float change, bool failed) {
+    const float l = level + (failed ? 0.0f : change);
+    return ((l >= 0.0f) & (l <= C.top)) ? l : level;
+}
+__device__ __forceinline__ float ped_advance(const PedConst &C, float s, float level) {
+    const float v = 0.5f * level;
+    return s + v * C.dt;
+}
+__device__ __forceinline__ float ped_upper(const MView &M, float s, int term) {
+    if (term) return 0.0f;
+    const float T = ceilf((M.h->path_len - s) / M.h->reach);
+    int Ti = (int)T;
+    if (Ti < 1) Ti = 1;
+    if (Ti > kHorizon) Ti = kHorizon;
+    return M.h->r_goal * M.gg[Ti - 1];
+}
+
+// A scenario spread over G lanes (a power of two, 4 to 16), pedestrian q G + j
+// in slot q of lane j; lane j also owns the car of action j mod 4 (the fourth
+// lane of every four repeats the third action's).  The pedestrians' walk does
+// not depend on the car and the random numbers of a depth are the same for
+// all actions, so the three actions share every pedestrian's step.
+template <int G, int PP>
+struct PedLanes {
+    float px[PP], py[PP], gx[PP], gy[PP];
+
+    // A slot past the last pedestrian holds a point that never moves and is
+    // never near a car.
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int q = 0; q < PP; ++q) px[q] = py[q] = gx[q] = gy[q] = 3e38f;
+    }
+    __device__ __forceinline__ void walk(const PedConst &C, int j, uint32_t id, uint32_t depth, uint32_t k0,
+                                         uint32_t k1) {
+#pragma unroll
+        for (int q = 0; q < PP; ++q)
+            if (q == 0 || q * G < C.n_peds) {
+                const uint4 u = philox(id, depth, (uint32_t)(q * G + j + 1), kTagStep, k0, k1);
+                move_ped(C, u, gx[q], gy[q], px[q], py[q]);
+            }
+    }
+    // What the lane's car at s sees: bit 0 a pedestrian within the collision
+    // radius, bit 8 one to brake for.  car: j mod 4, at most 2.
+    __device__ __forceinline__ uint32_t look(const PedConst &C, float s, int car) const {
+        float at[kPedActions];
+        at[0] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x00, 0xf, 0xf, true));
+        at[1] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x55, 0xf, 0xf, true));
+        at[2] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0xAA, 0xf, 0xf, true));
+        bool hit[kPedActions] = {}, brake[kPedActions] = {};
+#pragma unroll
+        for (int q = 0; q < PP; ++q)
+            if (q == 0 || q * G < C.n_peds) {
+                const float py2 = py[q] * py[q];
+                const bool beside = fabsf(py[q]) < 1.5f;
+#pragma unroll
+                for (int c = 0; c < kPedActions; ++c) {
+                    const float dx = px[q] - at[c];
+                    hit[c] |= dx * dx + py2 < C.coll_r2;
+                    brake[c] |= beside & (dx >= 0.0f) & (dx <= 3.0f);
+                }
+            }
+        int b = 0;
+#pragma unroll
+        for (int c = 0; c < kPedActions; ++c) b |= (hit[c] ? 1 << c : 0) | (brake[c] ? 256 << c : 0);
+        b |= __builtin_amdgcn_update_dpp(0, b, 0xB1, 0xf, 0xf, true);  // quad_perm 1,0,3,2
+        b |= __builtin_amdgcn_update_dpp(0, b, 0x4E, 0xf, 0xf, true);  // quad_perm 2,3,0,1
+        if (G >= 8) b |= __builtin_amdgcn_update_dpp(0, b, 0x141, 0xf, 0xf, true);   // row_half_mirror
+        if (G >= 16) b |= __builtin_amdgcn_update_dpp(0, b, 0x140, 0xf, 0xf, true);  // row_mirror
+        return (uint32_t)b >> car;
+    }
+};
+
 template <int PM>
 struct PedOps {
     struct State {
@@ -758,41 +917,7 @@ struct PedOps {
         float px[PM], py[PM];
         int32_t goal[PM];
     };
-    static constexpr bool kHashObs = true;
     static constexpr bool kSplitRollout = false;  // large step: one loop keeps the code small
-    static constexpr bool kSmallObs = false;      // 64-bit hashed observations
-    static constexpr bool kLdsModel = true;       // discount powers and goal points staged in LDS
-    static constexpr bool kWaveUpper = false;     // per-lane upper bound
-    static constexpr bool kGroupRollout = true;   // small leaves: one lane per pedestrian (group_expand)
-    struct WaveUpper {};
-
-    // One pedestrian's walk towards its goal with heading noise from the
-    // four words of its block (shared by the one-lane step and the
-    // element-level rollout, so both take the same operations).
-    __device__ static void move_ped(const MView &M, const uint4 &u, int goal, float &px, float &py) {
-        const int32_t sum = (int32_t)((u.x >> 8) + (u.y >> 8) + (u.z >> 8) + (u.w >> 8));
-        const float noise = (float)(sum - 33554430) * M.h->ih_scale;
-        const float gx = M.goal_x(goal), gy = M.goal_y(goal);
-        const float dx = gx - px;
-        const float dy = gy - py;
-        const float dist = __builtin_sqrtf(dx * dx + dy * dy);
-        const float step_len = M.h->step_len;
-        if (dist <= step_len) {
-            px = gx;
-            py = gy;
-        } else {
-            const float ux = dx / dist, uy = dy / dist;
-            const float t = M.h->half_sigma * noise;
-            const float t2 = t * t;
-            const float den = 1.0f + t2;
-            const float c = (1.0f - t2) / den;
-            const float sn = (2.0f * t) / den;
-            const float rx = ux * c - uy * sn;
-            const float ry = ux * sn + uy * c;
-            px = px + step_len * rx;
-            py = py + step_len * ry;
-        }
-    }
 
     __device__ static void load(const MView &M, const StatesPtr &S, int64_t p, State &st) {
         st.s = S.s[p];
@@ -812,93 +937,51 @@ struct PedOps {
             }
         }
     }
-    __device__ static void store(const MView &M, const StatesPtr &S, int64_t p, const State &st) {
-        S.s[p] = st.s;
-        S.car[p] = (st.level & 0xff) | (st.term ? 0x100 : 0);
-#pragma unroll
-        for (int j = 0; j < PM; ++j) {
-            if (j < M.h->n_peds) {
-                S.px[j * S.stride + p] = st.px[j];
-                S.py[j * S.stride + p] = st.py[j];
-                S.goal[j * S.stride + p] = (uint8_t)st.goal[j];
-            }
-        }
-    }
     __device__ static bool terminal(const State &st) { return st.term != 0; }
 
+    // One step of one scenario on one lane (the stand-alone bounds call).
     template <bool kObs>
     __device__ static void step(const MView &M, State &st, int a, uint32_t id, uint32_t depth, uint32_t k0,
                                 uint32_t k1, float &r, uint64_t &z) {
-        if (st.term) {
-            r = 0.0f;
-            z = kPedTerminalObs;
-            return;
-        }
+        static_assert(!kObs, "observations come from the tiles");
+        z = 0;
+        r = 0.0f;
+        if (st.term) return;
+        const PedConst C = ped_const(M);
         const uint4 u0 = philox(id, depth, 0, kTagStep, k0, k1);
-        const bool failed = (uint64_t)u0.x < M.h->fail_thr;
-        int level = st.level;
-        if (a == 0 && !failed && level < M.h->n_levels - 1) level = level + 1;
-        if (a == 2 && !failed && level > 0) level = level - 1;
-        const float v = 0.5f * (float)level;
-        const float s_next = st.s + v * M.h->dt;
+        const float level = ped_level(C, (float)st.level, (float)(1 - a), u0.x < C.fail_thr);
+        const float s_next = ped_advance(C, st.s, level);
 #pragma unroll
         for (int j = 0; j < PM; ++j) {
             if (j < M.h->n_peds) {
                 const uint4 u = philox(id, depth, (uint32_t)(j + 1), kTagStep, k0, k1);
-                move_ped(M, u, st.goal[j], st.px[j], st.py[j]);
+                move_ped(C, u, M.goal_x(st.goal[j]), M.goal_y(st.goal[j]), st.px[j], st.py[j]);
             }
         }
         bool collided = false;
-        if (level > 0) {
-            const float r2 = M.h->coll_r2;
+        if (level > 0.0f) {
 #pragma unroll
             for (int j = 0; j < PM; ++j) {
                 if (j < M.h->n_peds) {
                     const float ddx = st.px[j] - s_next;
                     const float d2 = ddx * ddx + st.py[j] * st.py[j];
-                    collided = collided || (d2 < r2);
+                    collided = collided || (d2 < M.h->coll_r2);
                 }
             }
         }
-        float reward = M.h->r_step;
+        r = M.h->r_step;
         if (collided) {
-            reward = M.h->r_step + M.h->r_collision;
+            r = M.h->r_step + M.h->r_collision;
             st.term = 1;
         } else if (s_next >= M.h->path_len) {
-            reward = M.h->r_step + M.h->r_goal;
+            r = M.h->r_step + M.h->r_goal;
             st.term = 1;
         }
         st.s = s_next;
-        st.level = level;
-        r = reward;
-        if (kObs) {
-            if (st.term) {
-                z = kPedTerminalObs;
-            } else {
-                uint64_t h = 0x243F6A8885A308D3ull;
-                h = hash_field(h, level);
-#pragma unroll
-                for (int j = 0; j < PM; ++j) {
-                    if (j < M.h->n_peds) {
-                        h = hash_field(h, (int32_t)floorf(st.px[j]));
-                        h = hash_field(h, (int32_t)floorf(st.py[j]));
-                    }
-                }
-                z = (h == kPedTerminalObs) ? kPedTerminalObs - 1 : h;
-            }
-        } else {
-            z = 0;
-        }
+        st.level = (int32_t)level;
     }
 
-    __device__ static float upper(const MView &M, const State &st) {
-        if (st.term) return 0.0f;
-        const float T = ceilf((M.h->path_len - st.s) / M.h->reach);
-        int Ti = (int)T;
-        if (Ti < 1) Ti = 1;
-        if (Ti > kHorizon) Ti = kHorizon;
-        return M.h->r_goal * M.gpow_lane(Ti - 1);
-    }
+    __device__ static float upper(const MView &M, const State &st) { return ped_upper(M, st.s, st.term); }
 
     __device__ static int default_action(const MView &M, const State &st) {
         bool brake = false;
@@ -910,227 +993,6 @@ struct PedOps {
             }
         }
         return brake ? 2 : 0;
-    }
-
-    // Element-level work on a small leaf (Sec. III-D: the parallelism inside
-    // one step of a scenario).  Scenario g of the wavefront's first n
-    // scenarios runs on lanes [g*G, g*G + G), lane g*G + j holding
-    // pedestrian j (G a power of two >= the pedestrian count, n * G <= 64);
-    // every lane of a group carries the car, the reward and the value;
-    // collisions and the braking rule are ORs of the group's ballot bits, and
-    // the observation hash is chained over the group's lanes in pedestrian
-    // order by shuffles.  The operations and their order are those of the
-    // one-lane step and rollout, so the results are the same bits.
-    struct Lanes {
-        int g, j;        // scenario of the group, pedestrian of the lane
-        bool active;     // g < n
-        bool ped;        // active and j < n_peds
-        uint64_t gmask;  // the group's lanes
-    };
-    __device__ static Lanes lanes(const MView &M, int n, int G) {
-        Lanes L;
-        const int lane = (int)__lane_id();
-        L.g = lane / G;
-        L.j = lane - L.g * G;
-        L.active = L.g < n;
-        L.ped = L.active && L.j < M.h->n_peds;
-        L.gmask = (G >= 64 ? ~0ull : ((1ull << G) - 1ull)) << (L.g * G);
-        return L;
-    }
-
-    // One step of one scenario spread over its group (PedOps::step).
-    template <bool kObs>
-    __device__ static void group_step(const MView &M, const Lanes &E, int G, int a, uint32_t id, uint32_t depth,
-                                      uint32_t k0, uint32_t k1, float &s, int &level, int &term, float &px,
-                                      float &py, int goal, float &r, uint64_t &z) {
-        r = 0.0f;
-        z = kObs ? kPedTerminalObs : 0;
-        if (term) return;  // group-uniform
-        const uint4 u0 = philox(id, depth, 0, kTagStep, k0, k1);
-        const bool failed = (uint64_t)u0.x < M.h->fail_thr;
-        if (a == 0 && !failed && level < M.h->n_levels - 1) level = level + 1;
-        if (a == 2 && !failed && level > 0) level = level - 1;
-        const float v = 0.5f * (float)level;
-        const float s_next = s + v * M.h->dt;
-        if (E.ped) {
-            const uint4 u = philox(id, depth, (uint32_t)(E.j + 1), kTagStep, k0, k1);
-            move_ped(M, u, goal, px, py);
-        }
-        bool hit = false;
-        if (level > 0 && E.ped) {
-            const float ddx = px - s_next;
-            const float d2 = ddx * ddx + py * py;
-            hit = d2 < M.h->coll_r2;
-        }
-        const bool collided = (__ballot(hit) & E.gmask) != 0;
-        float reward = M.h->r_step;
-        if (collided) {
-            reward = M.h->r_step + M.h->r_collision;
-            term = 1;
-        } else if (s_next >= M.h->path_len) {
-            reward = M.h->r_step + M.h->r_goal;
-            term = 1;
-        }
-        s = s_next;
-        r = reward;
-        if (!kObs) return;
-        // the chained hash, in pedestrian order: every lane of the group
-        // walks the chain over its group's lanes
-        const int fx = (int32_t)floorf(px), fy = (int32_t)floorf(py);
-        uint64_t h = hash_field(0x243F6A8885A308D3ull, level);
-        const int base = E.g * G;
-        for (int q = 0; q < M.h->n_peds; ++q) {
-            const int qx = __shfl(fx, base + q, 64);
-            const int qy = __shfl(fy, base + q, 64);
-            h = hash_field(h, qx);
-            h = hash_field(h, qy);
-        }
-        if (!term) z = (h == kPedTerminalObs) ? kPedTerminalObs - 1 : h;
-    }
-
-    // The default-policy rollout of one scenario spread over its group,
-    // from the lanes' element state (rollout_loop's operations).
-    __device__ static float group_roll(const MView &M, const RolloutParams &P, const Lanes &E, float s, int level,
-                                       int term, uint32_t sid, float px, float py, int goal, int d0, int &steps) {
-        int n_roll = P.max_steps;
-        if (P.max_depth >= 0 && P.max_depth - d0 < n_roll) n_roll = P.max_depth - d0;
-        if (n_roll > kHorizon) n_roll = kHorizon;
-        float value = 0.0f;
-        steps = 0;
-        for (int t = 0; t < n_roll; ++t) {
-            if (term) break;
-            const uint32_t depth = (uint32_t)(d0 + t);
-            int a;
-            if (P.policy == HDX_POLICY_CONST) {
-                a = P.const_action;
-            } else if (P.policy == HDX_POLICY_RANDOM) {
-                a = (int)(philox(sid, depth, 0, kTagPolicy, P.k0, P.k1).x % (uint32_t)P.n_actions);
-            } else {
-                const float ahead = px - s;
-                const bool b = E.ped && ahead >= 0.0f && ahead <= 3.0f && fabsf(py) < 1.5f;
-                a = (__ballot(b) & E.gmask) ? 2 : 0;
-            }
-            const uint4 u0 = philox(sid, depth, 0, kTagStep, P.k0, P.k1);
-            const bool failed = (uint64_t)u0.x < M.h->fail_thr;
-            if (a == 0 && !failed && level < M.h->n_levels - 1) level = level + 1;
-            if (a == 2 && !failed && level > 0) level = level - 1;
-            const float v = 0.5f * (float)level;
-            const float s_next = s + v * M.h->dt;
-            if (E.ped) {
-                const uint4 u = philox(sid, depth, (uint32_t)(E.j + 1), kTagStep, P.k0, P.k1);
-                move_ped(M, u, goal, px, py);
-            }
-            bool hit = false;
-            if (level > 0 && E.ped) {
-                const float ddx = px - s_next;
-                const float d2 = ddx * ddx + py * py;
-                hit = d2 < M.h->coll_r2;
-            }
-            const bool collided = (__ballot(hit) & E.gmask) != 0;
-            float reward = M.h->r_step;
-            if (collided) {
-                reward = M.h->r_step + M.h->r_collision;
-                term = 1;
-            } else if (s_next >= M.h->path_len) {
-                reward = M.h->r_step + M.h->r_goal;
-                term = 1;
-            }
-            s = s_next;
-            value += M.gpow_uniform(t) * reward;
-            ++steps;
-        }
-        return value;
-    }
-
-    // What one scenario of a small leaf yields in the element-level
-    // expansion; lane k < n holds scenario k's.
-    struct GroupOut {
-        float r, U, L;
-        uint64_t z;
-        uint32_t id;
-        int expanded, steps;
-    };
-
-    // Element-level expansion of a small leaf's tile: gather and update (the
-    // parent's last action), the step of action a with its observation, the
-    // upper bound and the rollout, all with one pedestrian per lane.  Leaf
-    // states (write_leaf) and stepped states (sprime) are stored by the
-    // owning lanes.  All 64 lanes of a wavefront call this.
-    __device__ static GroupOut group_expand(const MView &M, const RolloutParams &P, const int16_t *idx,
-                                            const uint32_t *parent_ids, const StatesPtr &parent,
-                                            const StatesPtr &leaf_out, uint32_t *ids_out, const StatesPtr &sprime,
-                                            bool write_leaf, bool pair_out, int a, int depth, int last_action, int n,
-                                            int G) {
-        const Lanes E = lanes(M, n, G);
-        float s = 0.0f, px = 0.0f, py = 0.0f;
-        int level = 0, term = 1, goal = 0;
-        uint32_t id = 0;
-        int p = 0;
-        if (E.active) {
-            p = idx[E.g];
-            id = parent_ids[p];
-            s = parent.s[p];
-            const int32_t car = parent.car[p];
-            level = car & 0xff;
-            term = (car >> 8) & 1;
-            if (E.ped) {
-                px = parent.px[E.j * parent.stride + p];
-                py = parent.py[E.j * parent.stride + p];
-                goal = parent.goal[E.j * parent.stride + p];
-            }
-        }
-        float r0;
-        uint64_t z0;
-        if (last_action >= 0)
-            group_step<false>(M, E, G, last_action, id, (uint32_t)(depth - 1), P.k0, P.k1, s, level, term, px, py,
-                              goal, r0, z0);
-        const int k = E.g;
-        if (write_leaf && E.active) {
-            if (E.j == 0) {
-                leaf_out.s[k] = s;
-                leaf_out.car[k] = (level & 0xff) | (term ? 0x100 : 0);
-                ids_out[k] = id;
-            }
-            if (E.ped) {
-                leaf_out.px[E.j * leaf_out.stride + k] = px;
-                leaf_out.py[E.j * leaf_out.stride + k] = py;
-                leaf_out.goal[E.j * leaf_out.stride + k] = (uint8_t)goal;
-            }
-        }
-        const int expanded = term ? 0 : 1;
-        float r;
-        uint64_t z;
-        group_step<true>(M, E, G, a, id, (uint32_t)depth, P.k0, P.k1, s, level, term, px, py, goal, r, z);
-        if (pair_out && E.active) {
-            const int64_t q = (int64_t)a * n + k;
-            if (E.j == 0) {
-                sprime.s[q] = s;
-                sprime.car[q] = (level & 0xff) | (term ? 0x100 : 0);
-            }
-            if (E.ped) {
-                sprime.px[E.j * sprime.stride + q] = px;
-                sprime.py[E.j * sprime.stride + q] = py;
-                sprime.goal[E.j * sprime.stride + q] = (uint8_t)goal;
-            }
-        }
-        State up;
-        up.s = s;
-        up.term = term;
-        const float U = upper(M, up);
-        int steps = 0;
-        const float L = group_roll(M, P, E, s, level, term, id, px, py, goal, depth + 1, steps);
-        // scenario k's results from its group's first lane to lane k
-        const int from = ((int)__lane_id() < n ? (int)__lane_id() : 0) * G;
-        GroupOut o;
-        o.r = __shfl(r, from, 64);
-        o.U = __shfl(U, from, 64);
-        o.L = __shfl(L, from, 64);
-        o.z = ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(z >> 32), from, 64) << 32) |
-              (uint32_t)__shfl((int)(uint32_t)z, from, 64);
-        o.id = (uint32_t)__shfl((int)id, from, 64);
-        o.expanded = __shfl(expanded, from, 64);
-        o.steps = __shfl(steps, from, 64);
-        return o;
     }
 };
 

@@ -5,6 +5,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <limits>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -366,6 +367,16 @@ hdx_status hdx_upload_model(hdx_ctx *ctx, const hdx_model_desc *d, hdx_model **o
         h->r_step = d->r_step;
         h->r_goal = d->r_goal;
         h->fail_thr = prob_threshold(d->p_fail);
+        // the largest squared distance within one step
+        h->near_d2 = -1.0f;
+        if (h->step_len >= 0.0f) {
+            float q = std::min(h->step_len * h->step_len, std::numeric_limits<float>::max());
+            while (q > 0.0f && sqrtf(q) > h->step_len) q = nextafterf(q, -1.0f);
+            for (float up; q < std::numeric_limits<float>::infinity() &&
+                           sqrtf(up = nextafterf(q, std::numeric_limits<float>::infinity())) <= h->step_len;)
+                q = up;
+            h->near_d2 = q;
+        }
     } else {
         delete dm;
         return fail(ctx, HDX_E_UNSUPPORTED, "unknown model kind");
@@ -611,11 +622,13 @@ hdx_status validate_leaves(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t n_leave
     return HDX_OK;
 }
 
-// Actions per tile of a leaf.  Navigation: a tile's actions share the map,
+// Actions per tile of a leaf.  Driving: all three, which share every
+// pedestrian's step.  Navigation: a tile's actions share the map,
 // the random numbers and the failure words of each scenario, so it takes all
 // nine (or as many as LDS holds) once the leaves alone fill the GPU; fewer
 // leaves are spread over more tiles, shortening the longest one.
 int32_t tile_actions(const hdx_leaf &L, int64_t call_tiles, int32_t n_cu) {
+    if (L.model->desc.kind == HDX_PEDNAV) return kPedActions;
     if (L.model->desc.kind != HDX_NAV) return 1;
     const int32_t most = call_tiles >= kNavActions * (int64_t)n_cu ? kNavActions
                          : call_tiles >= 3 * (int64_t)n_cu         ? 3
@@ -738,15 +751,22 @@ void hdx::plan_classes(const LeafTask *tasks, const int8_t *variant, Tile *tiles
     }
 }
 
-Schedule hdx::class_default_schedule(int32_t n_max, int32_t max_threads, int32_t mode) {
+Schedule hdx::class_default_schedule(const Variant &v, int64_t tiles, int32_t n_cu, bool few) {
+    const int32_t lanes = pow2_at_least(std::max(variant_lanes(v, v.n_max), 1));
     Schedule s;
-    s.threads = std::min(std::max(64, pow2_at_least(std::max(n_max, 1)) / 2), std::min(mode == 4 ? 1024 : 256, max_threads));
-    s.persistent = 0;
-    s.xcd_remap = mode < 0 ? 1 : 0;
-    if (mode == 0 || mode == 3) s.threads = 64;
-    // latency form: one scenario per lane where the model's width allows
-    if (mode == -2) s.threads = std::min(std::max(64, pow2_at_least(std::max(n_max, 1))), max_threads);
+    s.persistent = s.xcd_remap = 0;
+    if (few) s.threads = lanes;
+    else s.threads = v.mode == 0 || v.mode == 3 ? 64 : v.mode == 1 && tiles > n_cu ? lanes / 4 : lanes / 2;
+    s.threads = std::min(std::max(s.threads, 64), variant_max_threads(v));
     return s;
+}
+
+// Driving: 8 or 16 lanes per scenario instead of 4 cost a quarter more work
+// per scenario and finish one sooner: for leaves of at most twelve scenarios
+// (a wavefront of four lanes each would mostly idle) and for launches of fewer
+// wavefronts than two per SIMD.
+static int32_t spread_lanes(const Variant &v, int64_t tiles, int32_t n_max, int32_t n_cu) {
+    return v.mode == 1 && (n_max <= 12 || tiles * ((n_max + 15) / 16) <= 8 * (int64_t)n_cu) ? 1 : 0;
 }
 
 hipError_t hdx::launch_classes(const LeafTask *d_tasks, const Tile *d_tiles, TileQueue *d_queues,
@@ -757,12 +777,9 @@ hipError_t hdx::launch_classes(const LeafTask *d_tasks, const Tile *d_tiles, Til
         Variant vg = group_variant(g);
         vg.n_max = std::max(lds_n[g], plan.n_max[g]);
         vg.pairs = std::max(lds_pairs[g], plan.pairs[g]);
-        // driving leaves small enough for every scenario's pedestrians to
-        // get lanes of their own (n times the pedestrian bound fits a
-        // wavefront): the element-level instance
-        vg.group = vg.mode == 1 && plan.n_max[g] * vg.pm <= 64 ? 1 : 0;
+        vg.group = spread_lanes(vg, plan.count[g], plan.n_max[g], n_cu);
         // a workgroup no wider than the group's leaves need
-        const int need = std::min(variant_max_threads(vg), std::max(64, pow2_at_least(std::max(vg.n_max, 1))));
+        const int need = std::min(variant_max_threads(vg), std::max(64, pow2_at_least(std::max(variant_lanes(vg, vg.n_max), 1))));
         Schedule sc = sch[g];
         if (sc.threads > need) sc.threads = need;
         const hipError_t e = launch_expand(d_tasks, d_tiles + plan.begin[g], d_queues + g, (int32_t)plan.count[g], vg,
@@ -843,7 +860,7 @@ bool launch_in_args(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t n_leaves, cons
                     hdx_status *st) {
     const int kernels = (sh.has_rs || sh.has_ped ? 1 : 0) + sh.has_mars + sh.has_nav;
     if (n_leaves > kArgLeaves || kernels > 1) return false;
-    const Variant v0 = pick_variant(sh.has_rs, sh.has_ped, sh.ped_max, sh.n_max, sh.has_mars, sh.has_nav);
+    Variant v0 = pick_variant(sh.has_rs, sh.has_ped, sh.ped_max, sh.n_max, sh.has_mars, sh.has_nav);
     static_assert(sizeof(ArgPack) <= 4096, "kernel argument pack too large");
     ArgPack pack;
     memset(&pack, 0, sizeof(pack));
@@ -856,8 +873,8 @@ bool launch_in_args(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t n_leaves, cons
     }
     pack.n_leaves = n_leaves;
     pack.n_max = v0.n_max;
-    const Schedule sch =
-        ctx->sched_fixed ? ctx->sched : class_default_schedule(v0.n_max, variant_max_threads(v0), -2);
+    v0.group = 1;  // the driving kernels of these calls spread a scenario over 8 or 16 lanes
+    const Schedule sch = ctx->sched_fixed ? ctx->sched : class_default_schedule(v0, sh.n_tiles, ctx->n_cu, true);
     pack.xcd_remap = sch.xcd_remap;
     const hipError_t e = launch_expand_args(pack, v0, sch, stream);
     *st = e == hipSuccess ? HDX_OK : hip_fail(ctx, e, "expand launch");
@@ -882,10 +899,10 @@ hdx_status launch_staged(hdx_ctx *ctx, const LeafTask *h_tasks, const Tile *h_ti
     // bound: wider workgroups finish each tile sooner
     const bool few = n_tiles < 8 * (int64_t)ctx->n_cu;
     for (int g = 0; g < kGroups; ++g) {
-        sch[g] = ctx->sched_fixed ? ctx->sched
-                                  : class_default_schedule(plan.n_max[g], variant_max_threads(group_variant(g)),
-                                                           few ? -2 : group_variant(g).mode);
-        if (few) sch[g].xcd_remap = 0;
+        Variant v = group_variant(g);
+        v.n_max = plan.n_max[g];
+        v.group = spread_lanes(v, plan.count[g], v.n_max, ctx->n_cu);
+        sch[g] = ctx->sched_fixed ? ctx->sched : class_default_schedule(v, plan.count[g], ctx->n_cu, few);
     }
     e = launch_classes_forked(d_tasks, d_tiles, d_queue, plan, no_lds, no_lds, sch, ctx->n_cu, hs, ctx->cls_stream, fork,
                               join);
@@ -1040,6 +1057,7 @@ struct hdx_batch {
     TileQueue *h_queue = nullptr, *d_queue = nullptr;
     int64_t cap_tasks = 0, cap_tiles = 0;
     int64_t max_leaves = 0, max_tiles = 0;  // capacity the caller asked for
+    int32_t n_cu = 256;
     int32_t n_leaves = 0;
     int64_t n_tiles = 0;
     ClassPlan plan{};
@@ -1071,10 +1089,17 @@ hipError_t batch_direct_launch(hdx_ctx *ctx, hdx_batch *b, const Schedule *s, hi
                                  b->fork, b->join, mask);
 }
 
+Variant batch_variant(const hdx_batch *b, int g) {
+    Variant v = group_variant(g);
+    v.n_max = std::max(b->lds_c[g], b->plan.n_max[g]);
+    v.group = spread_lanes(v, b->plan.count[g], b->plan.n_max[g], b->n_cu);
+    return v;
+}
+
 // Widest workgroup group g can use: its model's cap and its leaves' need.
 int32_t group_width_cap(const hdx_batch *b, int g) {
-    const int32_t n_max = std::max(b->lds_c[g], b->plan.n_max[g]);
-    return std::min(variant_max_threads(group_variant(g)), std::max(64, pow2_at_least(std::max(n_max, 1))));
+    const Variant v = batch_variant(b, g);
+    return std::min(variant_max_threads(v), std::max(64, pow2_at_least(std::max(variant_lanes(v, v.n_max), 1))));
 }
 
 bool same_schedule(const Schedule &a, const Schedule &b) {
@@ -1085,8 +1110,7 @@ bool same_schedule(const Schedule &a, const Schedule &b) {
 void default_schedules(hdx_batch *b) {
     for (int g = 0; g < kGroups; ++g)
         if (!b->sched_set[g])
-            b->sched[g] = class_default_schedule(std::max(b->lds_c[g], 1), variant_max_threads(group_variant(g)),
-                                                 group_variant(g).mode);
+            b->sched[g] = class_default_schedule(batch_variant(b, g), b->plan.count[g], b->n_cu, false);
 }
 
 // Plan the staged tiles (split or merged groups) and copy tiles and queues
@@ -1120,6 +1144,7 @@ hdx_status hdx_batch_create(hdx_ctx *ctx, int32_t max_leaves, int64_t max_tiles,
     if (!ctx || !out || max_leaves < 1 || max_tiles < 1) return fail(ctx, HDX_E_INVALID, "bad argument");
     hipSetDevice(ctx->device);
     hdx_batch *b = new hdx_batch();
+    b->n_cu = ctx->n_cu;
     b->max_leaves = max_leaves;
     b->max_tiles = max_tiles;
     hdx_status st = grow_pinned(ctx, &b->h_tasks, &b->d_tasks, &b->cap_tasks, &b->h_tiles, &b->d_tiles, &b->cap_tiles,

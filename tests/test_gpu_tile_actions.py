@@ -89,3 +89,55 @@ def test_navigation_tiles(ctx, case):
     grid, marks, p_fail, policy, steps, horizon, count = case
     desc = dict(W.nav_model(3, n=grid, n_landmarks=marks), p_fail=p_fail)
     check(ctx, desc, W.nav_leaf, count, cfg_pair(policy, steps, horizon, 4), 500)
+
+
+# (pedestrians, policy, max_steps, sigma_h, speed, leaves, sizes): every lane
+# split (4, 8 and 16 lanes per scenario; 3, 8, 9, 16, 17, 32 pedestrians),
+# sorts of one wavefront, one block and several, rollouts of 0, 1 and 17
+# steps, no heading noise and steps past every goal (the general operations)
+DRIVING = [
+    (3, 0, 17, 0.3, 1.2, 30, [1, 5, 16, 17, 64, 65, 130]),
+    (8, 0, 17, 0.3, 1.2, 30, [1, 5, 16, 17, 64, 65, 130]),
+    (9, 2, 17, 0.3, 1.2, 30, [1, 5, 16, 17, 64, 65, 130]),
+    (16, 0, 17, 0.3, 1.2, 30, [1, 5, 16, 17, 64, 65, 130]),
+    (16, 0, 17, 0.3, 1.2, 40, [1, 2, 3, 4, 11, 12, 13]),
+    (17, 1, 17, 0.3, 1.2, 30, [1, 5, 16, 17, 64, 65, 130]),
+    (32, 0, 17, 0.3, 1.2, 30, [1, 5, 16, 17, 64, 65, 130]),
+    (0, 0, 17, 0.3, 1.2, 30, [1, 5, 16, 17, 64, 65, 130]),
+    (16, 0, 0, 0.3, 1.2, 30, [1, 5, 16, 17, 64, 65, 130]),
+    (16, 0, 1, 0.0, 1.2, 30, [1, 5, 16, 17, 64, 65, 130]),
+    (16, 0, 17, 0.3, 90.0, 30, [1, 5, 16, 17, 64, 65, 130]),
+    (16, 0, 17, 5.0, 0.0, 30, [1, 5, 16, 17, 64, 65, 130]),
+    (16, 0, 5, 0.3, 1.2, 2, [257, 513, 1024, 2048]),
+    (16, 0, 5, 0.3, 1.2, 300, [1, 130, 257]),
+]
+
+
+@pytest.mark.parametrize("case", DRIVING)
+def test_driving_tiles(ctx, case):
+    peds, policy, steps, sigma, speed, count, sizes = case
+    desc = dict(W.pednav_model(peds, 5, 3), sigma_h=sigma, ped_speed=speed)
+    check(ctx, desc, W.pednav_leaf, count, cfg_pair(policy, steps, -1, 1), 900, sizes)
+
+
+def test_pedestrian_steps_at_the_ends_of_the_range(ctx):
+    """Pedestrians on their goal, a hair from it, straight above it, and far away: the middle range of the step's
+    root and quotients and the general operations beside it, bit for bit with the oracle."""
+    desc = W.pednav_model(16, 5, 3)
+    n = 64
+    lf = W.pednav_leaf(desc, n, n, 5, depth=3)
+    gx, gy = desc["goal_x"][lf["goal"]], desc["goal_y"][lf["goal"]]
+    off = np.array([0.0, 1e-9, 1e-4, 0.5999999, 0.6, 0.6000001, 1.0, 1e6, 1e12, 1e25, -1e-40, 3e-30, 2.0, 1e19, -7.0, 0.0],
+                   np.float32)[:, None]
+    lf["px"] = (gx - off).astype(np.float32)
+    lf["py"] = np.where(np.arange(n)[None, :] % 3 == 0, gy, np.where(np.arange(n)[None, :] % 3 == 1, gy - off, gy + 3)
+                        ).astype(np.float32)
+    m = ctx.upload_model(desc)
+    cfgs = cfg_pair(0, 10)
+    par = oracle.parent_states(desc, lf)
+    from gpu_util import run_gpu_leaf
+    for last in (-1, 0):
+        gpu = run_gpu_leaf(ctx, m, par, lf["ids"], lf["idx"], lf["depth"], last, 41, 3, cfgs[1])
+        ref = oracle.expand_leaf(desc, cfgs[0], par, lf["ids"].astype(np.uint32), lf["idx"], lf["depth"], last, 41, 3,
+                                 per_pair=True)
+        compare_leaf(desc, gpu, ref, n)
