@@ -77,8 +77,9 @@ struct StatesPtr {
 // One leaf as the expansion kernel sees it (built on the host from hdx_leaf).
 struct LeafTask {
     const DevModel *model;
-    int16_t kind, tile_actions;  // actions per tile
-    int32_t n_actions;
+    // actions per tile, and per row that no tile crosses (two robots: robot
+    // 2's actions under one of robot 1; otherwise all)
+    int16_t kind, tile_actions, n_actions, row_actions;
     uint32_t k0, k1;
     int32_t policy, const_action, max_steps, max_depth;
     StatesPtr parent;
@@ -126,33 +127,45 @@ __host__ __device__ inline int32_t pow2_at_least(int32_t v) {
     return p;
 }
 
-// LDS carve-up of one RockSample tile (either model: every observation key
-// is below 32), the same on host (for the launch size) and device.
-//   zkey          per 64-scenario chunk and key: count, U sum, L sum
-//   dslot         per chunk: mask of the keys present
-//   off           per key: child offset and child index
-//   child         key of each scenario (bits 0-4) and its rank inside its
-//                 chunk among the scenarios of that key (bits 5-10)
-struct LdsLayout {
-    uint32_t zkey, dslot, off, child, misc, total;
-    int32_t np;
+// RockSample tile (one robot, or two): up to kRockActions actions of a leaf
+// of n scenarios, the same on host (for the launch size) and device; the
+// regions are described in run_tile_rocks.
+constexpr int kRockActions = 5 + kMaxRocks;
+constexpr int kRockSuccs = 6;              // a robot's moves, its sample, and no change
+constexpr int kRockCols = kMaxRocks + 1;   // a column per rock, and one for all scenarios
+constexpr int kRockSets = kMaxRocks + 2;   // live, acting, and per rock those reading it good
+constexpr int kRockTerms = 2 * kMaxGrid + 2;  // distances on a grid are below
+struct RockSucc {
+    double value;            // rollout of a live scenario
+    int32_t reward, steps;   // the live scenarios' rewards / 10; steps of one's rollout
 };
-__host__ __device__ inline LdsLayout make_layout(int32_t np) {
-    LdsLayout L;
-    if (np < 1) np = 1;
-    L.np = np;
+struct RockLayout {
+    uint32_t zmask, cmask, term, coef, succ, cells, state, ub, lb, cnt, sums, place, size, pre, misc, total;
+};
+__host__ __device__ inline RockLayout make_rock_layout(int32_t n, bool two) {
+    RockLayout L;
     uint32_t o = 0;
     auto take = [&](uint32_t bytes) {
         uint32_t at = o;
         o += (bytes + 15u) & ~15u;
         return at;
     };
-    const uint32_t chunks = (uint32_t)((np + 63) / 64);
-    L.zkey = take(3u * 4u * 32u * chunks);
-    L.dslot = take(4u * chunks);
-    L.off = take(4u * 64u);
-    L.child = take(2u * np);
-    L.misc = take(64 + 4u * 64);
+    const uint32_t chunks = (uint32_t)((n + 63) / 64), splits = two ? 3 : 1, keys = two ? 9 : 3;
+    L.zmask = take(8u * kMaxRocks * chunks);
+    L.cmask = take(8u * (two ? 4 : 1) * chunks);
+    L.term = take(8u * kRockTerms);
+    L.coef = take(8u * kRockSuccs * kRockCols);
+    L.succ = take((uint32_t)sizeof(RockSucc) * kRockSuccs);
+    L.cells = take(4u * chunks);
+    L.state = take(4u * (two ? 2 : 1) * n);
+    L.ub = take(4u * n);
+    L.lb = take(4u * n);
+    L.cnt = take(4u * splits * (kRockSets + 1) * 32);
+    L.sums = take(4u * kRockActions * keys * 2);
+    L.place = take(4u * kRockActions * keys);
+    L.size = take(4u * kRockActions * keys);
+    L.pre = take(2u * splits * kRockSets * chunks);
+    L.misc = take(4u * (1 + 2 * kRockSuccs));
     L.total = o;
     return L;
 }
@@ -301,9 +314,9 @@ hipError_t launch_classes(const LeafTask *d_tasks, const Tile *d_tiles, TileQueu
                           hipStream_t stream, uint64_t mask = ~0ull);
 // Default schedule of a group whose largest leaf has v.n_max scenarios.  Few
 // tiles (a call far smaller than the GPU): a lane for every scenario (driving:
-// its lanes), so each tile ends sooner.  Otherwise both RockSample models one
-// wavefront per tile (the most tiles in flight, barriers of a single
-// wavefront), navigation half a lane per scenario; driving a quarter of its
+// its lanes), so each tile ends sooner.  Otherwise half a lane per scenario,
+// for RockSample four wavefronts at most (2048 leaves of 31..500 scenarios: 61,
+// 38, 31 and 39 us at 1, 2, 4 and 8); driving a quarter of its
 // lanes with more than one tile per CU (512 leaves of 125..500 scenarios: 500
 // us at 512 lanes, 526 at 1024), else half (256 leaves among others: 930 and
 // 769 us).  Workgroups in tile order, one per tile.
@@ -314,9 +327,9 @@ hipError_t configure_expand_kernels();
 // pack stays under the 4 KB kernel-argument limit).
 constexpr int kArgLeaves = 11;
 struct ArgPack {
-    LeafTask t[kArgLeaves];
+    int32_t n_leaves, n_max, pairs;
     int32_t tile_begin[kArgLeaves + 1];
-    int32_t n_leaves, n_max, pairs, xcd_remap;
+    LeafTask t[kArgLeaves];
 };
 hipError_t launch_expand_args(const ArgPack &pack, const Variant &v, const Schedule &sch, hipStream_t stream);
 

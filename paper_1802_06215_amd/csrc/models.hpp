@@ -40,6 +40,8 @@ struct MView {
     __device__ float gpow_lane(int j) const { return j < kGpowLds ? gl[j] : gg[j]; }
     // 1 + gamma + ... + gamma^(j-1), j = 0..kHorizon
     __device__ double gpow_sum(int j) const { return gs[j]; }
+    // gamma^j in FP64, j < kHorizon
+    __device__ double gpow_exact(int j) const { return gs[j + 1] - gs[j]; }
     // goal point coordinates, staged in LDS after the discount powers
     __device__ float goal_x(int g) const { return gl[kGpowLds + g]; }
     __device__ float goal_y(int g) const { return gl[kGpowLds + kMaxGoals + g]; }
@@ -274,6 +276,52 @@ struct RsOps {
     }
 
     __device__ static int default_action(const MView &, const State &) { return 2; }  // move east
+
+    // A state as the tiles hold it (run_tile_rocks): the robot's cell, its
+    // actions below 5, and what follows from a cell alone.
+    static constexpr bool kTwo = false;
+    __device__ static int cell(const State &st) { return st.w & 0x3ff; }
+    __device__ static int cell_x(int c) { return c & 31; }
+    __device__ static int cell_y(int c) { return (c >> 5) & 31; }
+    __device__ static uint32_t rocks(const State &st) { return ((uint32_t)st.w >> 10) & 0xFFFFFu; }
+    __device__ static void from_words(State &st, int32_t w, int32_t) { st.w = w; }
+    __device__ static void from_cell(State &st, int c) { st.w = c; }
+    __device__ static bool acting(const State &st) { return !terminal(st); }
+    __device__ static bool ended(const State &st) { return terminal(st); }
+    __device__ static void settle(State &) {}
+    __device__ static float mover(const MView &M, State &st, int b) {
+        float r;
+        uint64_t z;
+        step<false>(M, st, b, 0, 0, 0, 0, r, z);
+        return r;
+    }
+    __device__ static int rock_distance(const State &st, int rx, int ry) {
+        return abs((st.w & 31) - rx) + abs(((st.w >> 5) & 31) - ry);
+    }
+    __device__ static bool at(const State &st, int rx, int ry) { return rock_distance(st, rx, ry) == 0; }
+    // The move c < 4 (any other c: none); true if it leaves the grid.
+    __device__ static bool walk(const MView &M, State &st, int c) {
+        const int n = M.h->grid, x = st.w & 31, y = (st.w >> 5) & 31;
+        if (c == 2 && x + 1 == n) {
+            st.w |= 1 << 30;
+            return true;
+        }
+        const int nx = c == 2 ? x + 1 : c == 3 && x > 0 ? x - 1 : x;
+        const int ny = c == 0 && y + 1 < n ? y + 1 : c == 1 && y > 0 ? y - 1 : y;
+        st.w = (st.w & ~0x3ff) | nx | (ny << 5);
+        return false;
+    }
+    // term[d] = 10 gamma^d
+    __device__ static double exits(const MView &M, const State &st, const double *term) {
+        return term[M.h->grid - 1 - (st.w & 31)];
+    }
+    // The rollout that moves east, of at most R steps.
+    __device__ static void move_east(const MView &M, const State &st, int R, const double *term, double &value,
+                                     int &steps) {
+        const int out = M.h->grid - 1 - (st.w & 31);  // steps before the one that leaves
+        steps = R < 0 ? 0 : R < out + 1 ? R : out + 1;
+        value = out < R ? term[out] : 0.0;
+    }
 };
 
 // ---------------------------------------------------------------------------
@@ -449,6 +497,68 @@ struct MarsOps {
 
     __device__ static int default_action(const MView &M, const State &) {
         return 2 * (5 + M.h->n_rocks) + 2;  // both robots move east
+    }
+
+    // A state as the tiles hold it (run_tile_rocks), after robot 1's action
+    // and with its reward: robot 2's actions below 5, and what follows from
+    // the robots' row alone.
+    static constexpr bool kTwo = true;
+    template <int J>
+    __device__ static bool gone(const State &st) {
+        return (st.p >> (kGone0 + J)) & 1;
+    }
+    __device__ static int cell(const State &st) { return st.p & 0x3fffff; }
+    __device__ static int cell_x(int c) { return (c >> 10) & 31; }
+    __device__ static int cell_y(int c) { return (c >> 15) & 31; }
+    __device__ static uint32_t rocks(const State &st) { return (uint32_t)st.rk; }
+    __device__ static int32_t with_reward(int32_t p, float r) { return p | (r > 0.0f ? 1 << 24 : r < 0.0f ? 2 << 24 : 0); }
+    __device__ static float reward_of(int32_t w) {
+        const int c = (w >> 24) & 3;
+        return c == 1 ? 10.0f : c == 2 ? -10.0f : 0.0f;
+    }
+    __device__ static void from_words(State &st, int32_t w, int32_t rk) {
+        st.p = w & ~(3 << 24);
+        st.rk = rk;
+    }
+    __device__ static void from_cell(State &st, int c) {
+        st.p = c;
+        st.rk = 0;
+    }
+    __device__ static bool acting(const State &st) { return !gone<1>(st); }
+    __device__ static bool ended(const State &st) { return gone<0>(st) && gone<1>(st); }
+    __device__ static void settle(State &st) {
+        if (ended(st)) st.p |= 1 << kTerm;
+    }
+    __device__ static float mover(const MView &M, State &st, int b) {
+        int z;
+        return act<1, false>(M, st, b, 0, z);
+    }
+    __device__ static int rock_distance(const State &st, int rx, int ry) { return near(st.p, rx, ry); }
+    __device__ static bool at(const State &st, int rx, int ry) {
+        return ((st.p >> 10) & 31) == rx && ((st.p >> 15) & 31) == ry;
+    }
+    __device__ static bool walk(const MView &M, State &st, int c) {
+        const int n = M.h->grid, x = (st.p >> 10) & 31, y = (st.p >> 15) & 31;
+        if (c == 2 && x + 1 == n) {
+            st.p |= 1 << (kGone0 + 1);
+            return true;
+        }
+        const int nx = c == 2 ? x + 1 : c == 3 && x > 0 ? x - 1 : x;
+        const int ny = c == 0 && y + 1 < n ? y + 1 : c == 1 && y > 0 ? y - 1 : y;
+        st.p = (st.p & ~(0x3ff << 10)) | (nx << 10) | (ny << 15);
+        return false;
+    }
+    __device__ static double exits(const MView &M, const State &st, const double *term) {
+        const int n1 = M.h->grid - 1;
+        return (gone<0>(st) ? 0.0 : term[n1 - (st.p & 31)]) + (gone<1>(st) ? 0.0 : term[n1 - ((st.p >> 10) & 31)]);
+    }
+    __device__ static void move_east(const MView &M, const State &st, int R, const double *term, double &value,
+                                     int &steps) {
+        const int n1 = M.h->grid - 1;
+        const int o1 = gone<0>(st) ? -1 : n1 - (st.p & 31), o2 = gone<1>(st) ? -1 : n1 - ((st.p >> 10) & 31);
+        const int last = o1 > o2 ? o1 : o2;
+        steps = R < 0 ? 0 : R < last + 1 ? R : last + 1;
+        value = (o1 >= 0 && o1 < R ? term[o1] : 0.0) + (o2 >= 0 && o2 < R ? term[o2] : 0.0);
     }
 };
 

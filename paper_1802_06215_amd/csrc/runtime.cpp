@@ -622,21 +622,35 @@ hdx_status validate_leaves(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t n_leave
     return HDX_OK;
 }
 
-// Actions per tile of a leaf.  Driving: all three, which share every
-// pedestrian's step.  Navigation: a tile's actions share the map,
-// the random numbers and the failure words of each scenario, so it takes all
-// nine (or as many as LDS holds) once the leaves alone fill the GPU; fewer
-// leaves are spread over more tiles, shortening the longest one.
-int32_t tile_actions(const hdx_leaf &L, int64_t call_tiles, int32_t n_cu) {
-    if (L.model->desc.kind == HDX_PEDNAV) return kPedActions;
-    if (L.model->desc.kind != HDX_NAV) return 1;
-    const int32_t most = call_tiles >= kNavActions * (int64_t)n_cu ? kNavActions
-                         : call_tiles >= 3 * (int64_t)n_cu         ? 3
-                                                                   : 1;
-    return nav_tile_actions(L.n, L.rollout.policy, most);
+// Actions per tile of a leaf in a call of call_tiles (leaf, action) pairs.
+// The actions of a tile share what does not depend on the action (see the
+// kernels), so a tile takes as many as there are -- driving all three;
+// RockSample all, or robot 2's under one of robot 1; navigation all nine or as
+// many as LDS holds -- once the leaves alone fill the GPU.  Fewer leaves are
+// spread over more tiles, about one per CU, which shortens the longest one:
+// one leaf of 500 scenarios takes 7.8 us with its 20 actions on a tile each
+// and 11.0 on one tile; with 625 joint actions 12.7 us at three per tile, 16
+// at one and 20 at 25.
+int32_t tile_actions(const hdx_leaf &L, int32_t row, int64_t call_tiles, int32_t n_cu) {
+    switch (L.model->desc.kind) {
+        case HDX_PEDNAV: return kPedActions;
+        case HDX_NAV:
+            return nav_tile_actions(L.n, L.rollout.policy,
+                                    call_tiles >= kNavActions * (int64_t)n_cu ? kNavActions
+                                    : call_tiles >= 3 * (int64_t)n_cu         ? 3
+                                                                              : 1);
+        default: return (int32_t)std::min<int64_t>((call_tiles + n_cu - 1) / n_cu, row);
+    }
 }
 
-int32_t tiles_of(const LeafTask &T) { return (T.n_actions + T.tile_actions - 1) / T.tile_actions; }
+int32_t tiles_of(const LeafTask &T) {
+    return T.n_actions / T.row_actions * ((T.row_actions + T.tile_actions - 1) / T.tile_actions);
+}
+// First action of the leaf's tile t.
+int32_t tile_action(const LeafTask &T, int32_t t) {
+    const int32_t per_row = (T.row_actions + T.tile_actions - 1) / T.tile_actions;
+    return t / per_row * T.row_actions + t % per_row * T.tile_actions;
+}
 
 // Pairs of a tile as the navigation layout counts them.
 int32_t tile_pairs(const LeafTask &T) {
@@ -654,8 +668,9 @@ int64_t pack_leaves(const hdx_leaf *leaves, int32_t n_leaves, LeafTask *tasks, T
         memset(&T, 0, sizeof(T));
         T.model = L.model->d_model;
         T.kind = (int16_t)L.model->desc.kind;
-        T.tile_actions = (int16_t)tile_actions(L, call_tiles, n_cu);
-        T.n_actions = L.model->desc.n_actions;
+        T.n_actions = (int16_t)L.model->desc.n_actions;
+        T.row_actions = (int16_t)(T.kind == HDX_MARS ? 5 + L.model->desc.n_rocks : L.model->desc.n_actions);
+        T.tile_actions = (int16_t)tile_actions(L, T.row_actions, call_tiles, n_cu);
         T.k0 = L.seed;
         T.k1 = L.step;
         T.policy = L.rollout.policy;
@@ -687,7 +702,7 @@ int64_t pack_leaves(const hdx_leaf *leaves, int32_t n_leaves, LeafTask *tasks, T
         T.L = L.L;
         T.child_of = L.child_of;
         if (tiles)
-            for (int a = 0; a < T.n_actions; a += T.tile_actions) tiles[t++] = Tile{i, a};
+            for (int32_t q = 0; q < tiles_of(T); ++q) tiles[t++] = Tile{i, tile_action(T, q)};
     }
     return t;
 }
@@ -756,7 +771,7 @@ Schedule hdx::class_default_schedule(const Variant &v, int64_t tiles, int32_t n_
     Schedule s;
     s.persistent = s.xcd_remap = 0;
     if (few) s.threads = lanes;
-    else s.threads = v.mode == 0 || v.mode == 3 ? 64 : v.mode == 1 && tiles > n_cu ? lanes / 4 : lanes / 2;
+    else s.threads = v.mode == 0 || v.mode == 3 ? std::min(lanes / 2, 256) : v.mode == 1 && tiles > n_cu ? lanes / 4 : lanes / 2;
     s.threads = std::min(std::max(s.threads, 64), variant_max_threads(v));
     return s;
 }
@@ -875,7 +890,6 @@ bool launch_in_args(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t n_leaves, cons
     pack.n_max = v0.n_max;
     v0.group = 1;  // the driving kernels of these calls spread a scenario over 8 or 16 lanes
     const Schedule sch = ctx->sched_fixed ? ctx->sched : class_default_schedule(v0, sh.n_tiles, ctx->n_cu, true);
-    pack.xcd_remap = sch.xcd_remap;
     const hipError_t e = launch_expand_args(pack, v0, sch, stream);
     *st = e == hipSuccess ? HDX_OK : hip_fail(ctx, e, "expand launch");
     return true;
@@ -959,7 +973,8 @@ void plan_fixed(const LeafTask *tasks, const int8_t *variant, int32_t n_leaves, 
         int64_t o = 0;
         if (count < 2 * kXcds) {
             for (int32_t r = lo; r < hi; ++r)
-                for (int a = 0; a < tasks[order[r]].n_actions; a += tasks[order[r]].tile_actions) t[o++] = Tile{order[r], a};
+                for (int32_t q = 0; q < tiles_of(tasks[order[r]]); ++q)
+                    t[o++] = Tile{order[r], tile_action(tasks[order[r]], q)};
         } else {
             // XCD x takes the leaves of rank x, x + 8, ...; one tile from
             // each XCD's list in turn
@@ -973,9 +988,8 @@ void plan_fixed(const LeafTask *tasks, const int8_t *variant, int32_t n_leaves, 
                 for (int x = 0; x < kXcds; ++x) {
                     if (rank[x] >= nl) continue;
                     const int32_t leaf = order[lo + rank[x]];
-                    t[o++] = Tile{leaf, act[x]};
-                    act[x] += tasks[leaf].tile_actions;
-                    if (act[x] >= tasks[leaf].n_actions) {
+                    t[o++] = Tile{leaf, tile_action(tasks[leaf], act[x])};
+                    if (++act[x] == tiles_of(tasks[leaf])) {
                         act[x] = 0;
                         rank[x] += kXcds;
                     }

@@ -141,3 +141,51 @@ def test_pedestrian_steps_at_the_ends_of_the_range(ctx):
         ref = oracle.expand_leaf(desc, cfgs[0], par, lf["ids"].astype(np.uint32), lf["idx"], lf["depth"], last, 41, 3,
                                  per_pair=True)
         compare_leaf(desc, gpu, ref, n)
+
+
+# (robots, grid, rocks, policy, max_steps, shared cells, leaves): tiles of one
+# action up to a row; no rocks and the most; the shared-cell sums and the
+# per-scenario ones; rollouts of 0 and 1 steps
+ROCKS = [
+    (1, 7, 8, 0, 1 << 30, True, 40),
+    (1, 7, 8, 0, 1 << 30, True, 300),
+    (1, 7, 8, 0, 1 << 30, False, 300),
+    (1, 31, 20, 0, 1 << 30, True, 60),
+    (1, 5, 0, 0, 1 << 30, True, 60),
+    (1, 7, 8, 2, 30, True, 100),
+    (1, 7, 8, 2, 30, False, 100),
+    (1, 7, 8, 1, 30, True, 100),
+    (1, 7, 8, 0, 0, True, 60),
+    (1, 7, 8, 0, 1, False, 60),
+    (2, 7, 4, 0, 1 << 30, True, 21),
+    (2, 7, 4, 0, 1 << 30, True, 100),
+    (2, 7, 4, 0, 1 << 30, False, 100),
+    (2, 31, 20, 0, 1 << 30, True, 3),
+    (2, 5, 0, 0, 1 << 30, True, 60),
+    (2, 7, 4, 2, 20, True, 21),
+    (2, 7, 4, 2, 20, False, 21),
+    (2, 7, 4, 1, 20, True, 21),
+    (2, 7, 4, 0, 1, False, 21),
+]
+
+
+@pytest.mark.parametrize("case", ROCKS)
+def test_rock_tiles(ctx, case):
+    robots, grid, rocks, policy, steps, shared, count = case
+    desc = (W.rocksample_model if robots == 1 else W.mars_model)(grid, rocks, 3)
+    if robots == 1:
+        make = lambda d, n_par, n, seed, depth: W.rocksample_leaf(d, n_par, n, seed, depth=depth, shared_cell=shared,  # noqa: E731
+                                                                  p_term=0.1)
+    else:
+        make = lambda d, n_par, n, seed, depth: W.mars_leaf(d, n_par, n, seed, depth=depth, shared_cells=shared,  # noqa: E731
+                                                            p_term=0.1)
+    # the constant policy samples (robot 2, when there are two)
+    check(ctx, desc, make, count, cfg_pair(policy, steps, 90, 4), 700, oracle_every=11)
+
+
+@pytest.mark.parametrize("n", [0, 1, 2048])
+@pytest.mark.parametrize("robots", [1, 2])
+def test_rock_tiles_at_the_ends(ctx, robots, n):
+    desc = W.rocksample_model(7, 8, 3) if robots == 1 else W.mars_model(7, 4, 3)
+    make = W.rocksample_leaf if robots == 1 else W.mars_leaf
+    check(ctx, desc, make, 3, cfg_pair(0, 1 << 30, 90), 800, sizes=[n, max(n, 1)], oracle_every=1)
