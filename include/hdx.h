@@ -463,8 +463,8 @@ hdx_status hdx_features(hdx_ctx *ctx, const hdx_model *model, hdx_states states,
  * the same outputs as hdx_expand_leaf, except that child_l0 is the mean of
  * MLP(features(s')) over the child's scenarios (features at depth+1 with
  * the given horizon), steps[a][1] is 0, and L (if given) receives the
- * surrogate value per (action, scenario).  Scratch for the stepped states,
- * features and values belongs to the MLP handle (grown on demand); calls
+ * surrogate value per (action, scenario).  Scratch for the stepped states
+ * (driving), features and values belongs to the MLP handle (grown on demand); calls
  * on one handle are serialised.  HDX_E_UNSUPPORTED for a multi-agent or navigation leaf. */
 hdx_status hdx_expand_leaf_surrogate(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t n_leaves, hdx_mlp *mlp,
                                      int32_t horizon, hdx_stream stream);

@@ -72,24 +72,20 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
-// h = bf16(relu(acc + bias)) into LDS (and, when STORE, to Hout)
-template <bool STORE>
-__device__ __forceinline__ void fused_store(uint16_t (*Hs)[kHP], const f32x4 (&acc)[kMI][4],
-                                            const float *__restrict__ bias, int nb, int lane, uint16_t *Hout,
-                                            int64_t r0, int64_t n) {
+// h = bf16(relu(acc + bias)) into LDS
+template <int MI>
+__device__ __forceinline__ void fused_store(uint16_t (*Hs)[kHP], const f32x4 (&acc)[MI][4],
+                                            const float *__restrict__ bias, int nb, int lane) {
     const int g = lane >> 4, q = lane & 15;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int col = nb + j * 16 + g * 4;
         const float4 bv = *(const float4 *)(bias + col);
 #pragma unroll
-        for (int i = 0; i < kMI; ++i) {
-            const int row = i * 16 + q;
-            const uint2 v = make_uint2(pack_bf16(fmaxf(acc[i][j][0] + bv.x, 0.f), fmaxf(acc[i][j][1] + bv.y, 0.f)),
-                                       pack_bf16(fmaxf(acc[i][j][2] + bv.z, 0.f), fmaxf(acc[i][j][3] + bv.w, 0.f)));
-            *(uint2 *)&Hs[row][col] = v;
-            if (STORE && r0 + row < n) *(uint2 *)(Hout + (r0 + row) * kMlpHidden + col) = v;
-        }
+        for (int i = 0; i < MI; ++i)
+            *(uint2 *)&Hs[i * 16 + q][col] =
+                make_uint2(pack_bf16(fmaxf(acc[i][j][0] + bv.x, 0.f), fmaxf(acc[i][j][1] + bv.y, 0.f)),
+                           pack_bf16(fmaxf(acc[i][j][2] + bv.z, 0.f), fmaxf(acc[i][j][3] + bv.w, 0.f)));
     }
 }
 
@@ -103,43 +99,15 @@ __device__ __forceinline__ void copy_rows_out(const uint16_t (*Hs)[kHP], uint16_
     }
 }
 
-// STORE: also write H1..H3 (training), through LDS as whole rows; the
-// inference form writes only y.
-template <bool STORE>
-__global__ __launch_bounds__(kFwdThreads, 2) void mlp_fused_fwd(const uint16_t *__restrict__ X, int64_t n,
-                                                             const MlpDev P, float *__restrict__ y, uint16_t *H1,
-                                                             uint16_t *H2, uint16_t *H3) {
-    __shared__ __align__(16) uint16_t Hs[kFR][kHP];
-    __shared__ float yp[4][kFR];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// The output layer of a wavefront's 64 columns: y = bf16(h3) . bf16(w4), per
+// row into yp[cw]; STORE: h3 also into Hs.
+template <int MI, bool STORE>
+__device__ __forceinline__ void output_layer(uint16_t (*Hs)[kHP], const f32x4 (&acc)[MI][4], const MlpDev &P, int nb,
+                                             int lane, float *yp) {
     const int g = lane >> 4, q = lane & 15;
-    const int64_t r0 = (int64_t)blockIdx.x * kFR;
-    const int cw = wave, nb = cw * 64;
-    constexpr int kV = kMlpIn / 8;  // uint4 per input row
-    for (int i = tid; i < kFR * kV; i += kFwdThreads) {
-        const int r = i / kV, c = (i % kV) * 8;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (r0 + r < n) v = *(const uint4 *)(X + (r0 + r) * kMlpIn + c);
-        *(uint4 *)&Hs[r][c] = v;
-    }
-    __syncthreads();
-    f32x4 acc[kMI][4];
-    fused_layer<kMlpIn>(Hs, P.w1t, nb, lane, acc);
-    __syncthreads();
-    fused_store<false>(Hs, acc, P.b1, nb, lane, nullptr, r0, n);
-    __syncthreads();
-    if (STORE) copy_rows_out(Hs, H1, r0, n);
-    fused_layer<kMlpHidden>(Hs, P.w2t, nb, lane, acc);
-    __syncthreads();
-    fused_store<false>(Hs, acc, P.b2, nb, lane, nullptr, r0, n);
-    __syncthreads();
-    if (STORE) copy_rows_out(Hs, H2, r0, n);
-    fused_layer<kMlpHidden>(Hs, P.w3t, nb, lane, acc);
-    if (STORE) __syncthreads();  // H3 goes through Hs once every wavefront has read H2
-    // output layer: y = bf16(h3) . bf16(w4) + b4
-    float rowsum[kMI];
+    float rowsum[MI];
 #pragma unroll
-    for (int i = 0; i < kMI; ++i) rowsum[i] = 0.f;
+    for (int i = 0; i < MI; ++i) rowsum[i] = 0.f;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int col = nb + j * 16 + g * 4;
@@ -148,7 +116,7 @@ __global__ __launch_bounds__(kFwdThreads, 2) void mlp_fused_fwd(const uint16_t *
         const float w0 = __uint_as_float(wv.x << 16), w1 = __uint_as_float(wv.x & 0xffff0000u);
         const float w2 = __uint_as_float(wv.y << 16), w3 = __uint_as_float(wv.y & 0xffff0000u);
 #pragma unroll
-        for (int i = 0; i < kMI; ++i) {
+        for (int i = 0; i < MI; ++i) {
             const int row = i * 16 + q;
             const uint32_t h01 = pack_bf16(fmaxf(acc[i][j][0] + bv.x, 0.f), fmaxf(acc[i][j][1] + bv.y, 0.f));
             const uint32_t h23 = pack_bf16(fmaxf(acc[i][j][2] + bv.z, 0.f), fmaxf(acc[i][j][3] + bv.w, 0.f));
@@ -162,12 +130,47 @@ __global__ __launch_bounds__(kFwdThreads, 2) void mlp_fused_fwd(const uint16_t *
         }
     }
 #pragma unroll
-    for (int i = 0; i < kMI; ++i) {
+    for (int i = 0; i < MI; ++i) {
         float s = rowsum[i];
         s += __shfl_xor(s, 16, 64);
         s += __shfl_xor(s, 32, 64);
-        if (g == 0) yp[cw][i * 16 + q] = s;
+        if (g == 0) yp[i * 16 + q] = s;
     }
+}
+
+// STORE: also write H1..H3 (training), through LDS as whole rows; the
+// inference form writes only y.
+template <bool STORE>
+__global__ __launch_bounds__(kFwdThreads, 2) void mlp_fused_fwd(const uint16_t *__restrict__ X, int64_t n,
+                                                             const MlpDev P, float *__restrict__ y, uint16_t *H1,
+                                                             uint16_t *H2, uint16_t *H3) {
+    __shared__ __align__(16) uint16_t Hs[kFR][kHP];
+    __shared__ float yp[4][kFR];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t r0 = (int64_t)blockIdx.x * kFR;
+    const int nb = wave * 64;
+    constexpr int kV = kMlpIn / 8;  // uint4 per input row
+    for (int i = tid; i < kFR * kV; i += kFwdThreads) {
+        const int r = i / kV, c = (i % kV) * 8;
+        uint4 v = make_uint4(0, 0, 0, 0);
+        if (r0 + r < n) v = *(const uint4 *)(X + (r0 + r) * kMlpIn + c);
+        *(uint4 *)&Hs[r][c] = v;
+    }
+    __syncthreads();
+    f32x4 acc[kMI][4];
+    fused_layer<kMlpIn>(Hs, P.w1t, nb, lane, acc);
+    __syncthreads();
+    fused_store(Hs, acc, P.b1, nb, lane);
+    __syncthreads();
+    if (STORE) copy_rows_out(Hs, H1, r0, n);
+    fused_layer<kMlpHidden>(Hs, P.w2t, nb, lane, acc);
+    __syncthreads();
+    fused_store(Hs, acc, P.b2, nb, lane);
+    __syncthreads();
+    if (STORE) copy_rows_out(Hs, H2, r0, n);
+    fused_layer<kMlpHidden>(Hs, P.w3t, nb, lane, acc);
+    if (STORE) __syncthreads();  // H3 goes through Hs once every wavefront has read H2
+    output_layer<kMI, STORE>(Hs, acc, P, nb, lane, yp[wave]);
     __syncthreads();
     if (STORE) copy_rows_out(Hs, H3, r0, n);
     if (tid < kFR && r0 + tid < n) y[r0 + tid] = (((yp[0][tid] + yp[1][tid]) + yp[2][tid]) + yp[3][tid]) + P.b4[0];
@@ -643,35 +646,57 @@ __device__ __forceinline__ uint4 feature_chunk(const HDX_CONST ModelHdr *M, cons
     return v;
 }
 
-// Features of row k of one state array.
+// Row k of one state array, and chunks of eight of its features.
+template <class Args>
+struct FeatureRow {
+    const Args &A;
+    const HDX_CONST ModelHdr *M;
+    int64_t k;
+    bool rs;
+    int32_t w = 0, car = 0;
+    int x = 0, y = 0;
+    float inv = 0.f, s = 0.f, remain;
+    __device__ __forceinline__ FeatureRow(const Args &A_, int64_t k_) : A(A_), k(k_) {
+        M = (const HDX_CONST ModelHdr *)&A.model->h;
+        const int depth = A.depths ? A.depths[k] : A.depth_const;
+        remain = (float)max(A.horizon - depth, 0) * 0.01f;
+        rs = M->kind == HDX_ROCKSAMPLE;
+        if (rs) {
+            if (A.parents > 0) {
+                const uint32_t c = (uint32_t)k / (uint32_t)A.parents;
+                RsOps::State st = {A.states.w[(uint32_t)k - c * (uint32_t)A.parents]};
+                if (!RsOps::terminal(st)) RsOps::mover(make_view(A.model, nullptr), st, (int)c);
+                w = st.w;
+            } else {
+                w = A.states.w[k];
+            }
+            x = w & 31;
+            y = (w >> 5) & 31;
+            inv = 1.0f / (float)M->grid;
+        } else {
+            s = A.states.s[k];
+            car = A.states.car[k];
+        }
+    }
+    template <int J0>
+    __device__ __forceinline__ uint4 chunk() const {
+        return feature_chunk<J0>(M, A.states, k, rs, w, x, y, inv, s, car, remain);
+    }
+};
+
 template <class Args>
 __device__ __forceinline__ void features_row(const Args &A, int64_t k) {
     if (k >= A.n) return;
-    const HDX_CONST ModelHdr *M = (const HDX_CONST ModelHdr *)&A.model->h;
-    const int depth = A.depths ? A.depths[k] : A.depth_const;
-    const float remain = (float)max(A.horizon - depth, 0) * 0.01f;
-    const bool rs = M->kind == HDX_ROCKSAMPLE;
-    int32_t w = 0, car = 0;
-    int x = 0, y = 0;
-    float inv = 0.f, s = 0.f;
-    if (rs) {
-        w = A.states.w[k];
-        x = w & 31;
-        y = (w >> 5) & 31;
-        inv = 1.0f / (float)M->grid;
-    } else {
-        s = A.states.s[k];
-        car = A.states.car[k];
-    }
+    const FeatureRow<Args> R(A, k);
     uint4 *dst = (uint4 *)(A.X + k * kMlpIn);
-    dst[0] = feature_chunk<0>(M, A.states, k, rs, w, x, y, inv, s, car, remain);
-    dst[1] = feature_chunk<8>(M, A.states, k, rs, w, x, y, inv, s, car, remain);
-    dst[2] = feature_chunk<16>(M, A.states, k, rs, w, x, y, inv, s, car, remain);
-    dst[3] = feature_chunk<24>(M, A.states, k, rs, w, x, y, inv, s, car, remain);
-    dst[4] = feature_chunk<32>(M, A.states, k, rs, w, x, y, inv, s, car, remain);
-    dst[5] = feature_chunk<40>(M, A.states, k, rs, w, x, y, inv, s, car, remain);
-    dst[6] = feature_chunk<48>(M, A.states, k, rs, w, x, y, inv, s, car, remain);
-    dst[7] = feature_chunk<56>(M, A.states, k, rs, w, x, y, inv, s, car, remain);
+    dst[0] = R.template chunk<0>();
+    dst[1] = R.template chunk<8>();
+    dst[2] = R.template chunk<16>();
+    dst[3] = R.template chunk<24>();
+    dst[4] = R.template chunk<32>();
+    dst[5] = R.template chunk<40>();
+    dst[6] = R.template chunk<48>();
+    dst[7] = R.template chunk<56>();
 }
 
 // One state array, its arguments by value.
@@ -686,9 +711,87 @@ __global__ __launch_bounds__(128) void features_many(const FeatArgs *args) {
     features_row(A, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
-// A few state arrays, their arguments in the kernel arguments.
-__global__ __launch_bounds__(128) void features_pack(const FeatPack P) {
-    features_row(P.a[blockIdx.y], (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+// ---- forward pass of a few leaves -----------------------------------------
+// A few leaves have too few rows for the tile above to fill the GPU, and what
+// counts is how soon a tile ends: 32 rows per workgroup, their features computed
+// into LDS (no pass over memory of their own), a layer's weights loaded whole
+// into registers ahead of the barrier that its input waits for.  The same
+// products in the same order, so a row has the same value as above.
+constexpr int kSR = 32, kSI = kSR / 16;
+
+template <int K>
+struct Weights {
+    bf16x8 b[K / 32][4];
+    __device__ __forceinline__ void load(const uint16_t *__restrict__ wt, int nb, int lane) {
+        const uint16_t *wrow = wt + (size_t)(nb + (lane & 15)) * K + (lane >> 4) * 8;
+#pragma unroll
+        for (int t = 0; t < K / 32; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) b[t][j] = *(const bf16x8 *)(wrow + (size_t)j * 16 * K + t * 32);
+    }
+    __device__ __forceinline__ void layer(const uint16_t (*Hs)[kHP], int lane, f32x4 (&acc)[kSI][4]) const {
+#pragma unroll
+        for (int i = 0; i < kSI; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < K / 32; ++t)
+#pragma unroll
+            for (int i = 0; i < kSI; ++i) {
+                const bf16x8 a = *(const bf16x8 *)&Hs[i * 16 + (lane & 15)][t * 32 + (lane >> 4) * 8];
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[t][j], a, acc[i][j], 0, 0, 0);
+            }
+    }
+};
+
+// Leaf blockIdx.y of a pack in the kernel arguments, rows 32 blockIdx.x on.
+__global__ __launch_bounds__(kFwdThreads, 2) void mlp_fwd_pack(const FeatPack F, const MlpDev P) {
+    __shared__ __align__(16) uint16_t Hs[kSR][kHP];
+    __shared__ float yp[4][kSR];
+    const FeatArgs &A = F.a[blockIdx.y];
+    const int64_t r0 = (int64_t)blockIdx.x * kSR;
+    if (r0 >= A.n) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nb = wave * 64;
+    Weights<kMlpIn> w1;
+    Weights<kMlpHidden> w2;
+    w1.load(P.w1t, nb, lane);
+    w2.load(P.w2t, nb, lane);
+    {
+        // eight threads per row, a chunk of its features each
+        const int r = tid & (kSR - 1), c = tid / kSR;
+        uint4 v = make_uint4(0, 0, 0, 0);
+        if (r0 + r < A.n) {
+            const FeatureRow<FeatArgs> R(A, r0 + r);
+            switch (c) {
+                case 0: v = R.chunk<0>(); break;
+                case 1: v = R.chunk<8>(); break;
+                case 2: v = R.chunk<16>(); break;
+                case 3: v = R.chunk<24>(); break;
+                case 4: v = R.chunk<32>(); break;
+                case 5: v = R.chunk<40>(); break;
+                case 6: v = R.chunk<48>(); break;
+                default: v = R.chunk<56>(); break;
+            }
+        }
+        *(uint4 *)&Hs[r][c * 8] = v;
+    }
+    __syncthreads();
+    f32x4 acc[kSI][4];
+    w1.layer(Hs, lane, acc);
+    __syncthreads();
+    fused_store(Hs, acc, P.b1, nb, lane);
+    __syncthreads();
+    w2.layer(Hs, lane, acc);
+    w2.load(P.w3t, nb, lane);  // the third layer's
+    __syncthreads();
+    fused_store(Hs, acc, P.b2, nb, lane);
+    __syncthreads();
+    w2.layer(Hs, lane, acc);
+    output_layer<kSI, false>(Hs, acc, P, nb, lane, yp[wave]);
+    __syncthreads();
+    if (tid < kSR && r0 + tid < A.n) A.y[r0 + tid] = (((yp[0][tid] + yp[1][tid]) + yp[2][tid]) + yp[3][tid]) + P.b4[0];
 }
 
 inline int blocks_for(int64_t n, int t) { return (int)((n + t - 1) / t); }
@@ -769,11 +872,11 @@ hipError_t launch_features(const FeatArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_features_pack(const FeatPack &P, int count, int64_t n_max, hipStream_t s) {
+hipError_t launch_forward_pack(const FeatPack &F, int count, int64_t n_max, const MlpDev &P, hipStream_t s) {
     if (count <= 0 || n_max <= 0) return hipSuccess;
-    const int64_t bx = (n_max + 127) / 128;
+    const int64_t bx = (n_max + kSR - 1) / kSR;
     if (bx > 0x7fffffff || count > kArgPack) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(features_pack, dim3((unsigned)bx, count), dim3(128), 0, s, P);
+    hipLaunchKernelGGL(mlp_fwd_pack, dim3((unsigned)bx, count), dim3(kFwdThreads), 0, s, F, P);
     return hipGetLastError();
 }
 
@@ -803,7 +906,7 @@ __device__ __forceinline__ void child_means(const Args &A) {
     const int a = blockIdx.y;
     if (a >= A.n_actions) return;
     const int n = A.n, lane = threadIdx.x;
-    const float *v = A.values + (int64_t)a * n;
+    const float *v = A.values + (int64_t)min(a, A.successors - 1) * n;
     const int nch = min(A.n_children[a], A.cap);
     const int16_t *perm = A.perm + (int64_t)a * n;
     if (nch <= 16) {

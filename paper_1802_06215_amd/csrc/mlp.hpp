@@ -47,6 +47,14 @@ struct MlpScratch {
     float *part = nullptr;  // kMlpPartFloats
 };
 
+// A surrogate expansion's values per scenario: RockSample's actions lead to at
+// most six states (four moves, a sample; every sense leaves the state as it
+// is), so action a >= 5 takes the values of successor 5.
+constexpr int kRockSuccessors = 6;
+inline int32_t successors_of(int32_t kind, int32_t n_actions) {
+    return kind == HDX_ROCKSAMPLE && n_actions > kRockSuccessors ? kRockSuccessors : n_actions;
+}
+
 struct FeatArgs {
     const DevModel *model;
     StatesPtr states;
@@ -54,6 +62,10 @@ struct FeatArgs {
     int64_t n;
     int32_t horizon, depth_const;
     uint16_t *X;
+    // RockSample: 0, or the number of states, and row c * parents + k is state
+    // k after action c (terminal states as they are)
+    int32_t parents, pad;
+    float *y;  // launch_forward_pack: the rows' values
 };
 
 // y = MLP(X) for n rows; H1..H3 (row stride 256) receive the activations
@@ -64,9 +76,9 @@ hipError_t mlp_backward(const MlpDev &P, const uint16_t *X, const float *t, int 
                         float *loss, hipStream_t s);
 hipError_t mlp_adam(MlpDev &P, const float *grads, float lr, int step, hipStream_t s);
 hipError_t mlp_refresh_bf16(MlpDev &P, hipStream_t s);
-// Features of one state array (arguments by value), of up to kArgPack
-// arrays (arguments in the kernel arguments), or of `count` arrays whose
-// arguments are in device memory (n_max: the longest array).
+// Features of one state array (arguments by value), or of `count` arrays whose
+// arguments are in device memory (n_max: the longest array); values of up to
+// kArgPack arrays without their features' detour through memory.
 constexpr int kArgPack = 8;       // a surrogate expansion of this many leaves takes the packs
 constexpr int kMaxGridY = 65535;  // arrays per launch of the argument-array kernels
 struct FeatPack {
@@ -74,16 +86,16 @@ struct FeatPack {
 };
 static_assert(sizeof(FeatPack) <= 1024, "kernel argument pack too large");
 hipError_t launch_features(const FeatArgs &a, hipStream_t s);
-hipError_t launch_features_pack(const FeatPack &P, int count, int64_t n_max, hipStream_t s);
+hipError_t launch_forward_pack(const FeatPack &F, int count, int64_t n_max, const MlpDev &P, hipStream_t s);
 hipError_t launch_features_many(const FeatArgs *d_args, int count, int64_t n_max, hipStream_t s);
 
 struct SurArgs {
-    const float *values;  // [A][n] surrogate value per (action, scenario)
+    const float *values;  // [successors][n] surrogate values; action a's row is min(a, successors - 1)
     const int16_t *perm;
     const int32_t *n_children, *child_n, *child_off;
     float *child_l0;
     float *L_out;  // optional [A][n]
-    int32_t n, cap, n_actions, pad;
+    int32_t n, cap, n_actions, successors;
 };
 // Child means of up to kArgPack leaves (a pack in the kernel arguments) or
 // of `count` leaves whose arguments are in device memory.

@@ -279,6 +279,8 @@ hdx_status hdx_features(hdx_ctx *ctx, const hdx_model *model, hdx_states states,
     a.horizon = horizon;
     a.depth_const = 0;
     a.X = X;
+    a.parents = a.pad = 0;
+    a.y = nullptr;
     return launch_features(a, (hipStream_t)stream) == hipSuccess ? HDX_OK : HDX_E_DEVICE;
 }
 
@@ -286,7 +288,8 @@ hdx_status hdx_expand_leaf_surrogate(hdx_ctx *ctx, const hdx_leaf *leaves, int32
                                      int32_t horizon, hdx_stream stream) {
     if (!ctx || !mlp || n_leaves < 0 || (n_leaves > 0 && !leaves)) return HDX_E_INVALID;
     if (n_leaves == 0) return HDX_OK;
-    // scratch: stepped states of every (action, scenario), their features and values
+    // scratch: the distinct stepped states of every scenario (RockSample's follow from the leaf's states), their
+    // features and values
     std::vector<size_t> st_off(n_leaves), pair_off(n_leaves);
     size_t st_bytes = 0;
     int64_t pairs = 0;
@@ -297,10 +300,11 @@ hdx_status hdx_expand_leaf_surrogate(hdx_ctx *ctx, const hdx_leaf *leaves, int32
             hdx_internal_set_error(ctx, "no surrogate features for this model");
             return HDX_E_UNSUPPORTED;
         }
-        const int64_t np = (int64_t)d.n_actions * (leaves[i].n > 0 ? leaves[i].n : 0);
+        const int64_t np =
+            (int64_t)successors_of(d.kind, d.n_actions) * (leaves[i].n > 0 ? leaves[i].n : 0);
         st_off[i] = st_bytes;
         pair_off[i] = (size_t)pairs;
-        const size_t per = d.kind == HDX_ROCKSAMPLE ? 4 : (size_t)(8 + 9 * d.n_peds);
+        const size_t per = d.kind == HDX_ROCKSAMPLE ? 0 : (size_t)(8 + 9 * d.n_peds);
         st_bytes += ((size_t)np * per + 64) & ~(size_t)15;
         pairs += np;
     }
@@ -319,7 +323,7 @@ hdx_status hdx_expand_leaf_surrogate(hdx_ctx *ctx, const hdx_leaf *leaves, int32
     char *base = (char *)mlp->sur;
     uint16_t *X = (uint16_t *)(base + st_bytes);
     float *vals = (float *)(base + st_bytes + (size_t)pairs * kMlpIn * sizeof(uint16_t));
-    // expansion without rollouts, stepped states kept
+    // expansion without rollouts, driving's stepped states kept
     std::vector<hdx_leaf> mod(leaves, leaves + n_leaves);
     for (int32_t i = 0; i < n_leaves; ++i) {
         const hdx_model_desc &d = *hdx_internal_desc(leaves[i].model);
@@ -327,18 +331,14 @@ hdx_status hdx_expand_leaf_surrogate(hdx_ctx *ctx, const hdx_leaf *leaves, int32
         hdx_leaf &L = mod[i];
         L.rollout.max_steps = 0;
         L.L = nullptr;
-        if (d.kind == HDX_ROCKSAMPLE ? L.sprime.w != nullptr : L.sprime.s != nullptr) continue;  // caller's
+        if (d.kind == HDX_ROCKSAMPLE || L.sprime.s != nullptr) continue;  // (the caller's)
         memset(&L.sprime, 0, sizeof(L.sprime));
         char *p = base + st_off[i];
-        if (d.kind == HDX_ROCKSAMPLE) {
-            L.sprime.w = (int32_t *)p;
-        } else {
-            L.sprime.s = (float *)p;
-            L.sprime.car = (int32_t *)(p + 4 * np);
-            L.sprime.px = (float *)(p + 8 * np);
-            L.sprime.py = (float *)(p + (8 + 4 * (size_t)d.n_peds) * np);
-            L.sprime.goal = (uint8_t *)(p + (8 + 8 * (size_t)d.n_peds) * np);
-        }
+        L.sprime.s = (float *)p;
+        L.sprime.car = (int32_t *)(p + 4 * np);
+        L.sprime.px = (float *)(p + 8 * np);
+        L.sprime.py = (float *)(p + (8 + 4 * (size_t)d.n_peds) * np);
+        L.sprime.goal = (uint8_t *)(p + (8 + 8 * (size_t)d.n_peds) * np);
         L.sprime.stride = np;
     }
     hdx_status st = hdx_expand_leaf(ctx, mod.data(), n_leaves, stream);
@@ -350,16 +350,21 @@ hdx_status hdx_expand_leaf_surrogate(hdx_ctx *ctx, const hdx_leaf *leaves, int32
     sa.reserve(n_leaves);
     for (int32_t i = 0; i < n_leaves; ++i) {
         const int32_t A = hdx_model_actions(leaves[i].model);
-        const int64_t np = (int64_t)A * (leaves[i].n > 0 ? leaves[i].n : 0);
+        const bool rocks = hdx_internal_desc(leaves[i].model)->kind == HDX_ROCKSAMPLE;
+        const int32_t S = successors_of(hdx_internal_desc(leaves[i].model)->kind, A);
+        const int64_t np = (int64_t)S * (leaves[i].n > 0 ? leaves[i].n : 0);
         if (np == 0) continue;
         FeatArgs a;
         a.model = hdx_internal_devmodel(leaves[i].model);
-        a.states = to_states(mod[i].sprime);
+        a.states = to_states(rocks ? mod[i].states_out : mod[i].sprime);
+        a.parents = rocks ? leaves[i].n : 0;
+        a.pad = 0;
         a.depths = nullptr;
         a.depth_const = leaves[i].depth + 1;
         a.n = np;
         a.horizon = horizon;
         a.X = X + pair_off[i] * kMlpIn;
+        a.y = vals + pair_off[i];
         fa.push_back(a);
         SurArgs r;
         r.values = vals + pair_off[i];
@@ -372,7 +377,7 @@ hdx_status hdx_expand_leaf_surrogate(hdx_ctx *ctx, const hdx_leaf *leaves, int32
         r.n = leaves[i].n;
         r.cap = leaves[i].cap;
         r.n_actions = A;
-        r.pad = 0;
+        r.successors = S;
         sa.push_back(r);
     }
     if (fa.empty()) return HDX_OK;
@@ -390,8 +395,7 @@ hdx_status hdx_expand_leaf_surrogate(hdx_ctx *ctx, const hdx_leaf *leaves, int32
         memset(&sp, 0, sizeof(sp));
         std::copy(fa.begin(), fa.end(), fp.a);
         std::copy(sa.begin(), sa.end(), sp.a);
-        if ((e = launch_features_pack(fp, (int)fa.size(), n_max, s)) != hipSuccess) return dev_fail(ctx, e, "features");
-        if (pairs > 0 && (e = mlp_forward(mlp->P, X, pairs, nullptr, nullptr, nullptr, vals, s)) != hipSuccess)
+        if ((e = launch_forward_pack(fp, (int)fa.size(), n_max, mlp->P, s)) != hipSuccess)
             return dev_fail(ctx, e, "forward");
         if ((e = launch_surrogate_reduce_pack(sp, (int)sa.size(), a_max, s)) != hipSuccess)
             return dev_fail(ctx, e, "child means");
