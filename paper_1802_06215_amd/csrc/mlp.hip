@@ -29,7 +29,7 @@ __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint
 // One workgroup of four wavefronts takes kFR = 128 rows.  The layer input
 // (X, then H1, H2) sits in LDS; wavefront w computes all 128 rows x columns
 // [64 w, +64) with 16x16x32 BF16 MFMAs (8 x 4 accumulator tiles), its weight
-// fragments read straight from the transposed BF16 weights, each fragment
+// fragments read straight from the BF16 weights in fragment order, each fragment
 // feeding eight row tiles.  The MFMA is
 // fed (weights, activations), i.e. it produces the transposed tile, so a
 // lane ends up holding four consecutive output columns of one row: the
@@ -48,12 +48,12 @@ __device__ __forceinline__ void fused_layer(const uint16_t (*Hs)[kHP], const uin
     for (int i = 0; i < kMI; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const uint16_t *wrow = wt + (size_t)(nb + q) * K + g * 8;
+    const uint16_t *frag = wt + (size_t)(nb / 16) * (K / 32) * 512 + lane * 8;
 #pragma unroll 2
     for (int k0 = 0; k0 < K; k0 += 32) {
         bf16x8 b[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) b[j] = *(const bf16x8 *)(wrow + (size_t)j * 16 * K + k0);
+        for (int j = 0; j < 4; ++j) b[j] = *(const bf16x8 *)(frag + (size_t)(j * (K / 32) + k0 / 32) * 512);
 #pragma unroll
         for (int i = 0; i < kMI; ++i) {
             const bf16x8 a = *(const bf16x8 *)&Hs[i * 16 + q][k0 + g * 8];
@@ -179,8 +179,7 @@ __global__ __launch_bounds__(kFwdThreads, 2) void mlp_fused_fwd(const uint16_t *
 // ---- training step: fused backward, weight gradients, reductions --------
 // Backward of one 128-row block, laid out as the fused forward: dy, then
 // G3 = dy w4 [H3 > 0], G2 = (G3 W3^T) [H2 > 0] and G1 = (G2 W2^T) [H1 > 0]
-// with 16x16x32 BF16 MFMAs (a row of W_l as stored, [in][out], holds an
-// output column's products contiguously), each G rounded to BF16 and written
+// with 16x16x32 BF16 MFMAs, each G rounded to BF16 and written
 // out for the weight gradients; the block's column sums of G1..G3 (bias
 // gradients), of dy H3 (dw4), of dy (db4) and its share of the loss go to
 // its row of `part`, each sum in a fixed order.
@@ -334,7 +333,7 @@ __global__ __launch_bounds__(kFwdThreads, 2) void mlp_fused_bwd(const float *__r
     f32x4 acc[kMI][4];
     __syncthreads();
     // G2 = (G3 W3^T) [H2 > 0]
-    fused_layer<kMlpHidden>(Gs, P.w3b, nb, lane, acc);
+    fused_layer<kMlpHidden>(Gs, P.w3r, nb, lane, acc);
     __syncthreads();
     copy_rows_in(Gs, H2, r0, B);
     __syncthreads();
@@ -342,7 +341,7 @@ __global__ __launch_bounds__(kFwdThreads, 2) void mlp_fused_bwd(const float *__r
     __syncthreads();
     copy_rows_out(Gs, G2, r0, B);
     // G1 = (G2 W2^T) [H1 > 0]
-    fused_layer<kMlpHidden>(Gs, P.w2b, nb, lane, acc);
+    fused_layer<kMlpHidden>(Gs, P.w2r, nb, lane, acc);
     __syncthreads();
     copy_rows_in(Gs, H1, r0, B);
     __syncthreads();
@@ -515,46 +514,36 @@ __global__ __launch_bounds__(kRedCols * kRedSeg) void reduce_bias(const float *_
     }
 }
 
-// W1..W3 transposed to [out][in] (BF16), for the fused forward
-__global__ void transpose_weights(const uint16_t *__restrict__ pb, uint16_t *__restrict__ pt) {
+// Element (output column, k) of a weight matrix in fragment order: a
+// wavefront's 16 x 32 MFMA operand (lane 16 g + q: column q, products 8 g ..
+// 8 g + 7) lies in one piece, so that its load is one kilobyte in eight whole
+// cache lines.  Read from [out][in] rows, a load took half a line of each of 16
+// rows, and the other halves were gone from the 32 KB L1 when their turn came:
+// 128 KB of weights took a workgroup 7400 cycles alone on its CU.
+__device__ __forceinline__ int64_t fragment_at(int col, int k, int K) {
+    return ((int64_t)(col >> 4) * (K / 32) + (k >> 5)) * 512 + (((k & 31) >> 3) * 16 + (col & 15)) * 8 + (k & 7);
+}
+
+// BF16 value b of packed parameter i into the fragments that hold it: those of
+// the forward pass (products over a row of W) and of the backward (over a
+// column); other parameters have none.
+__device__ __forceinline__ void scatter_weight(int64_t i, uint16_t b, uint16_t *pt) {
+    if (i < kOffB1) {
+        pt[fragment_at((int)i % kMlpHidden, (int)i / kMlpHidden, kMlpIn)] = b;
+    } else if ((i >= kOffW2 && i < kOffB2) || (i >= kOffW3 && i < kOffB3)) {
+        const bool third = i >= kOffW3;
+        const int o = (int)(i - (third ? kOffW3 : kOffW2)), r = o / kMlpHidden, c = o % kMlpHidden;  // W[r][c]
+        pt[(third ? kFragW3 : kFragW2) + fragment_at(c, r, kMlpHidden)] = b;
+        pt[(third ? kFragW3T : kFragW2T) + fragment_at(r, c, kMlpHidden)] = b;
+    }
+}
+
+__global__ void scatter_weights(const uint16_t *__restrict__ pb, uint16_t *__restrict__ pt) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= kMlpWtElems) return;
-    constexpr int64_t n1 = (int64_t)kMlpHidden * kMlpIn, n2 = (int64_t)kMlpHidden * kMlpHidden;
-    int64_t o = i, base = kOffW1;
-    int K = kMlpIn;
-    if (o >= n1) {
-        o -= n1;
-        base = kOffW2;
-        K = kMlpHidden;
-        if (o >= n2) {
-            o -= n2;
-            base = kOffW3;
-        }
-    }
-    const int64_t col = o / K, k = o % K;  // pt[col][k] = W[k][col]
-    pt[i] = pb[base + k * kMlpHidden + col];
+    if (i < kMlpParams) scatter_weight(i, pb[i], pt);
 }
 
-// Place of packed parameter i (an element of W1..W3) in the transposed
-// BF16 weights ([out][in]), or -1 for the other parameters.
-__device__ __forceinline__ int64_t transposed_at(int64_t i) {
-    constexpr int64_t n1 = (int64_t)kMlpIn * kMlpHidden, n2 = (int64_t)kMlpHidden * kMlpHidden;
-    int64_t o, base;
-    int K;
-    if (i >= kOffW1 && i < kOffB1) {
-        o = i - kOffW1, base = 0, K = kMlpIn;
-    } else if (i >= kOffW2 && i < kOffB2) {
-        o = i - kOffW2, base = n1, K = kMlpHidden;
-    } else if (i >= kOffW3 && i < kOffB3) {
-        o = i - kOffW3, base = n1 + n2, K = kMlpHidden;
-    } else {
-        return -1;
-    }
-    const int64_t k = o / kMlpHidden, col = o % kMlpHidden;  // W[k][col]
-    return base + col * K + k;
-}
-
-// Adam on FP32 master weights; the BF16 copy and its transpose refreshed in
+// Adam on FP32 master weights; the BF16 copy and its fragments refreshed in
 // the same pass
 __global__ void adam_step(float *p, const float *g, float *m, float *v, int64_t n, float lr, float b1, float b2,
                           float eps, float c1, float c2, uint16_t *pbf, uint16_t *pt) {
@@ -570,8 +559,7 @@ __global__ void adam_step(float *p, const float *g, float *m, float *v, int64_t 
     p[i] = np;
     const uint16_t b = f2bf(np);
     pbf[i] = b;
-    const int64_t ti = transposed_at(i);
-    if (ti >= 0) pt[ti] = b;
+    scatter_weight(i, b, pt);
 }
 
 __global__ void to_bf16(const float *src, int64_t n, uint16_t *dst) {
@@ -723,11 +711,11 @@ template <int K>
 struct Weights {
     bf16x8 b[K / 32][4];
     __device__ __forceinline__ void load(const uint16_t *__restrict__ wt, int nb, int lane) {
-        const uint16_t *wrow = wt + (size_t)(nb + (lane & 15)) * K + (lane >> 4) * 8;
+        const uint16_t *frag = wt + (size_t)(nb / 16) * (K / 32) * 512 + lane * 8;
 #pragma unroll
         for (int t = 0; t < K / 32; ++t)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) b[t][j] = *(const bf16x8 *)(wrow + (size_t)j * 16 * K + t * 32);
+            for (int j = 0; j < 4; ++j) b[t][j] = *(const bf16x8 *)(frag + (size_t)(j * (K / 32) + t) * 512);
     }
     __device__ __forceinline__ void layer(const uint16_t (*Hs)[kHP], int lane, f32x4 (&acc)[kSI][4]) const {
 #pragma unroll
@@ -860,7 +848,7 @@ hipError_t mlp_adam(MlpDev &P, const float *grads, float lr, int step, hipStream
 
 hipError_t mlp_refresh_bf16(MlpDev &P, hipStream_t s) {
     hipLaunchKernelGGL(to_bf16, dim3(blocks_for(kMlpParams, 256)), dim3(256), 0, s, P.p, (int64_t)kMlpParams, P.pb);
-    hipLaunchKernelGGL(transpose_weights, dim3(blocks_for(kMlpWtElems, 256)), dim3(256), 0, s, P.pb, P.pt);
+    hipLaunchKernelGGL(scatter_weights, dim3(blocks_for(kMlpParams, 256)), dim3(256), 0, s, P.pb, P.pt);
     return hipGetLastError();
 }
 

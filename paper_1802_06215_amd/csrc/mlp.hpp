@@ -20,7 +20,14 @@ constexpr int64_t kOffB4 = kOffW4 + kMlpHidden;
 constexpr int64_t kMlpParams = kOffB4 + 1;
 static_assert(kMlpParams == HDX_MLP_PARAMS, "parameter count");
 
-constexpr int64_t kMlpWtElems = (int64_t)kMlpHidden * kMlpIn + 2 * (int64_t)kMlpHidden * kMlpHidden;
+// BF16 weights in MFMA fragment order: W1, W2, W3 for the forward pass, W2 and
+// W3 transposed for the backward
+constexpr int64_t kFragW1 = 0;
+constexpr int64_t kFragW2 = kFragW1 + (int64_t)kMlpHidden * kMlpIn;
+constexpr int64_t kFragW3 = kFragW2 + (int64_t)kMlpHidden * kMlpHidden;
+constexpr int64_t kFragW2T = kFragW3 + (int64_t)kMlpHidden * kMlpHidden;
+constexpr int64_t kFragW3T = kFragW2T + (int64_t)kMlpHidden * kMlpHidden;
+constexpr int64_t kFragElems = kFragW3T + (int64_t)kMlpHidden * kMlpHidden;
 // partials of one training step: the weight gradients of the three layers
 // over at most kMlpMaxSlices row slices, then the backward's per-block
 // column sums (kMlpBwdPart floats per 128-row block)
@@ -32,11 +39,11 @@ constexpr int64_t kMlpPartFloats =
 struct MlpDev {
     float *p;      // FP32 master parameters
     uint16_t *pb;  // BF16 copy
-    uint16_t *pt;  // BF16 W1..W3 transposed ([out][in]) for the fused forward
+    uint16_t *pt;  // BF16 W1..W3 in fragment order
     float *m, *v;  // Adam moments
     float *g;      // gradients
-    const uint16_t *w1b, *w2b, *w3b, *w4b;
-    const uint16_t *w1t, *w2t, *w3t;
+    const uint16_t *w4b;
+    const uint16_t *w1t, *w2t, *w3t, *w2r, *w3r;  // in pt: forward, backward
     const float *b1, *b2, *b3, *b4;
 };
 

@@ -70,13 +70,12 @@ bool grow_scratch(MlpScratch &S, int64_t rows) {
 }
 
 void bind(MlpDev &P) {
-    P.w1b = P.pb + kOffW1;
-    P.w2b = P.pb + kOffW2;
-    P.w3b = P.pb + kOffW3;
     P.w4b = P.pb + kOffW4;
-    P.w1t = P.pt;
-    P.w2t = P.pt + (int64_t)kMlpHidden * kMlpIn;
-    P.w3t = P.w2t + (int64_t)kMlpHidden * kMlpHidden;
+    P.w1t = P.pt + kFragW1;
+    P.w2t = P.pt + kFragW2;
+    P.w3t = P.pt + kFragW3;
+    P.w2r = P.pt + kFragW2T;
+    P.w3r = P.pt + kFragW3T;
     P.b1 = P.p + kOffB1;
     P.b2 = P.p + kOffB2;
     P.b3 = P.p + kOffB3;
@@ -131,7 +130,7 @@ hdx_status hdx_mlp_create(hdx_ctx *ctx, uint32_t seed, hdx_mlp **out) {
     hdx_mlp *m = new hdx_mlp();
     const size_t pbytes = kMlpParams * sizeof(float);
     if (hipMalloc(&m->P.p, pbytes) != hipSuccess || hipMalloc(&m->P.pb, kMlpParams * sizeof(uint16_t)) != hipSuccess ||
-        hipMalloc(&m->P.pt, kMlpWtElems * sizeof(uint16_t)) != hipSuccess ||
+        hipMalloc(&m->P.pt, kFragElems * sizeof(uint16_t)) != hipSuccess ||
         hipMalloc(&m->P.m, pbytes) != hipSuccess || hipMalloc(&m->P.v, pbytes) != hipSuccess ||
         hipMalloc(&m->grads, pbytes) != hipSuccess || hipMalloc(&m->loss, sizeof(float)) != hipSuccess ||
         hipEventCreateWithFlags(&m->last, hipEventDisableTiming) != hipSuccess) {
