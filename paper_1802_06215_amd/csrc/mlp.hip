@@ -37,7 +37,7 @@ __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint
 // output layer sums each row's 256 products over a lane's 16 columns, the
 // four lanes of the row, then the four column wavefronts, in a fixed order,
 // so a row's value does not depend on the other rows.
-constexpr int kFR = 128, kHP = kMlpHidden + 8, kFwdThreads = 256, kMI = kFR / 16;
+constexpr int kFR = kMlpTileRows, kHP = kMlpHidden + 8, kFwdThreads = 256, kMI = kFR / 16;
 
 // acc[i][j][r] = output (row 16 i + q, column nb + 16 j + 4 g + r)
 template <int K>
@@ -138,23 +138,187 @@ __device__ __forceinline__ void output_layer(uint16_t (*Hs)[kHP], const f32x4 (&
     }
 }
 
+// ---- state features --------------------------------------------------------
+// State features for the surrogate (64 values, BF16): RockSample x/n, y/n,
+// terminal, remaining depth/100, rock qualities, rock offsets dx/n, dy/n;
+// crowd driving s/path_len, speed level/(levels-1), terminal, remaining
+// depth/100, then per pedestrian (px - s)/10, py/10, goal/n_goals; zeros
+// to 64.  Eight threads take a row, eight features each, so a wavefront
+// writes whole rows.  A RockSample feature is a number t = value -+ a field of
+// the state word, times 1/n or 1; a table in LDS says which, so that no branch
+// is left and the network's tiles can afford to form their rows themselves (the
+// forward of 307 thousand rows 118 us with it, 97 and 27 in two passes).
+// Entry: bits 0-4 the field's first bit, 5-9 its width, 10 negative, 11 times
+// 1/n, 16-31 the value.
+struct FeatureTable {
+    uint32_t at[kMlpIn];
+    int x[24], y[24];  // the rocks
+};
+__device__ __forceinline__ void stage_features(const HDX_CONST ModelHdr *M, FeatureTable &T) {  // then a barrier
+    const int j = (int)threadIdx.x;
+    if (M->kind != HDX_ROCKSAMPLE || j >= kMlpIn) return;
+    const int m = M->n_rocks, i = j - 4;
+    auto entry = [](int first, int width, int negative, int scaled, int value) {
+        return (uint32_t)(first | (width << 5) | (negative << 10) | (scaled << 11) | (value << 16));
+    };
+    uint32_t e = 0;  // (feature 3, the remaining depth, and the padding)
+    if (j == 0) e = entry(0, 5, 0, 1, 0);
+    if (j == 1) e = entry(5, 5, 0, 1, 0);
+    if (j == 2) e = entry(30, 1, 0, 0, 0);
+    if (i >= 0 && i < m) e = entry(10 + i, 1, 0, 0, 0);
+    if (i >= m && i < 2 * m) e = entry(0, 5, 1, 1, M->rock_x[i - m]);
+    if (i >= 2 * m && i < 3 * m) e = entry(5, 5, 1, 1, M->rock_y[i - 2 * m]);
+    T.at[j] = e;
+    if (j < 24) {
+        T.x[j] = j < m ? M->rock_x[j] : -1;
+        T.y[j] = j < m ? M->rock_y[j] : -1;
+    }
+}
+
+// What a row's features are computed from, but for driving's pedestrians.
+struct RowState {
+    int32_t w = 0, car = 0;  // RockSample's word; driving's car and
+    float s = 0.f;           // its place
+    uint32_t action = 0;     // the action still to take (FeatArgs::parents)
+};
+template <class Args>
+__device__ __forceinline__ RowState load_row(const Args &A, const HDX_CONST ModelHdr *M, int64_t k) {
+    RowState r;
+    if (M->kind != HDX_ROCKSAMPLE) {
+        r.s = A.states.s[k];
+        r.car = A.states.car[k];
+    } else if (A.parents > 0) {
+        r.action = (uint32_t)k / (uint32_t)A.parents;
+        r.w = A.states.w[(uint32_t)k - r.action * (uint32_t)A.parents];
+    } else {
+        r.w = A.states.w[k];
+    }
+    return r;
+}
+
+// Features 8 c .. 8 c + 7 of row k of one state array.  Called by the eight
+// threads of a row together.
+template <class Args>
+__device__ __forceinline__ uint4 features_of(const Args &A, const HDX_CONST ModelHdr *M, const FeatureTable &T,
+                                             const RowState &row, int64_t k, int c) {
+    const int depth = A.depths ? A.depths[k] : A.depth_const;
+    const float remain = (float)max(A.horizon - depth, 0) * 0.01f;
+    float f[8];
+    if (M->kind == HDX_ROCKSAMPLE) {
+        RsOps::State st = {row.w};
+        if (A.parents > 0) {
+            // the rock under the robot: each of the row's eight threads looks at three
+            int32_t rock = 0;
+#pragma unroll
+            for (int q = 0; q < 24; q += 8) rock |= RsOps::at(st, T.x[c + q], T.y[c + q]) ? 1 << (10 + c + q) : 0;
+            rock |= __shfl_xor(rock, 1, 64);
+            rock |= __shfl_xor(rock, 2, 64);
+            rock |= __shfl_xor(rock, 4, 64);
+            if (!RsOps::terminal(st)) {
+                RsOps::walk(make_view(A.model, nullptr), st, (int)row.action);
+                if (row.action == 4) st.w &= ~rock;  // sampled: bad from now on
+            }
+        }
+        const float inv = 1.0f / (float)M->grid;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const uint32_t d = T.at[8 * c + e];
+            const int32_t field = (int32_t)__builtin_amdgcn_ubfe((uint32_t)st.w, d, d >> 5);  // (their low five bits)
+            const int32_t sign = __builtin_amdgcn_sbfe((int32_t)d, 10u, 1u), value = (int32_t)(d >> 16);
+            f[e] = (float)(value + ((field ^ sign) - sign)) * (d & 0x800u ? inv : 1.0f);
+        }
+        if (c == 0) f[3] = remain;
+        // neither a NaN nor a denormal among them
+        return make_uint4(pack_bf16(f[0], f[1]), pack_bf16(f[2], f[3]), pack_bf16(f[4], f[5]), pack_bf16(f[6], f[7]));
+    } else {
+        const float s = row.s;
+        const int32_t car = row.car;
+        const int64_t stride = A.states.stride;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int i = 8 * c + e - 4, p = i >= 0 ? i / 3 : 0, w = i - 3 * p;  // pedestrian p, its w-th feature
+            float v = 0.f;
+            if (i < 0)
+                v = e == 0   ? s / M->path_len
+                    : e == 1 ? (float)(car & 0xff) / (float)max(M->n_levels - 1, 1)
+                    : e == 2 ? (float)((car >> 8) & 1)
+                             : remain;
+            else if (p < M->n_peds)
+                v = w == 0   ? (A.states.px[p * stride + k] - s) * 0.1f
+                    : w == 1 ? A.states.py[p * stride + k] * 0.1f
+                             : (float)A.states.goal[p * stride + k] / (float)M->n_goals;
+            f[e] = v;
+        }
+    }
+    auto two = [&](int e) { return (uint32_t)f2bf(f[e]) | ((uint32_t)f2bf(f[e + 1]) << 16); };
+    return make_uint4(two(0), two(2), two(4), two(6));
+}
+
+constexpr int kFeatThreads = 256, kFeatRows = kFeatThreads / 8;
+template <class Args>
+__device__ __forceinline__ void features_rows(const Args &A, FeatureTable &T) {
+    const HDX_CONST ModelHdr *M = (const HDX_CONST ModelHdr *)&A.model->h;
+    const int64_t k = (int64_t)blockIdx.x * kFeatRows + (threadIdx.x >> 3);
+    if ((int64_t)blockIdx.x * kFeatRows >= A.n) return;
+    RowState row;
+    if (k < A.n) row = load_row(A, M, k);
+    stage_features(M, T);
+    __syncthreads();
+    const int c = threadIdx.x & 7;
+    if (k < A.n) *(uint4 *)(A.X + k * kMlpIn + c * 8) = features_of(A, M, T, row, k, c);
+}
+
+// Where the rows of a forward pass come from: stored features, 128 rows a
+// workgroup, or the states of many leaves, whose features are computed into LDS
+// (a leaf's tiles begin at first_tile; leaf_of: the leaf of each tile).
+struct StoredRows {
+    const uint16_t *X;
+    int64_t n;
+    float *y;
+};
+struct LeafRows {
+    const FeatArgs *args;
+    const int32_t *leaf_of;
+};
+
 // STORE: also write H1..H3 (training), through LDS as whole rows; the
 // inference form writes only y.
-template <bool STORE>
-__global__ __launch_bounds__(kFwdThreads, 2) void mlp_fused_fwd(const uint16_t *__restrict__ X, int64_t n,
-                                                             const MlpDev P, float *__restrict__ y, uint16_t *H1,
+template <bool STORE, class Rows>
+__global__ __launch_bounds__(kFwdThreads, 2) void mlp_fused_fwd(const Rows rows, const MlpDev P, uint16_t *H1,
                                                              uint16_t *H2, uint16_t *H3) {
     __shared__ __align__(16) uint16_t Hs[kFR][kHP];
     __shared__ float yp[4][kFR];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t r0 = (int64_t)blockIdx.x * kFR;
     const int nb = wave * 64;
-    constexpr int kV = kMlpIn / 8;  // uint4 per input row
-    for (int i = tid; i < kFR * kV; i += kFwdThreads) {
-        const int r = i / kV, c = (i % kV) * 8;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (r0 + r < n) v = *(const uint4 *)(X + (r0 + r) * kMlpIn + c);
-        *(uint4 *)&Hs[r][c] = v;
+    int64_t r0 = (int64_t)blockIdx.x * kFR, n;
+    float *y;
+    if constexpr (std::is_same<Rows, StoredRows>::value) {
+        n = rows.n;
+        y = rows.y;
+        constexpr int kV = kMlpIn / 8;  // uint4 per input row
+        for (int i = tid; i < kFR * kV; i += kFwdThreads) {
+            const int r = i / kV, c = (i % kV) * 8;
+            uint4 v = make_uint4(0, 0, 0, 0);
+            if (r0 + r < n) v = *(const uint4 *)(rows.X + (r0 + r) * kMlpIn + c);
+            *(uint4 *)&Hs[r][c] = v;
+        }
+    } else {
+        __shared__ FeatureTable T;
+        const HDX_CONST FeatArgs &A =
+            ((const HDX_CONST FeatArgs *)rows.args)[((const HDX_CONST int32_t *)rows.leaf_of)[blockIdx.x]];
+        const HDX_CONST ModelHdr *M = (const HDX_CONST ModelHdr *)&A.model->h;
+        r0 = (int64_t)((int)blockIdx.x - A.first_tile) * kFR;
+        n = A.n;
+        y = A.y;
+        stage_features(M, T);
+        __syncthreads();
+        const int c = tid & 7;
+#pragma unroll
+        for (int r = tid >> 3; r < kFR; r += kFwdThreads / 8) {
+            uint4 v = make_uint4(0, 0, 0, 0);
+            if (r0 + r < n) v = features_of(A, M, T, load_row(A, M, r0 + r), r0 + r, c);
+            *(uint4 *)&Hs[r][c * 8] = v;
+        }
     }
     __syncthreads();
     f32x4 acc[kMI][4];
@@ -567,136 +731,17 @@ __global__ void to_bf16(const float *src, int64_t n, uint16_t *dst) {
     if (i < n) dst[i] = f2bf(src[i]);
 }
 
-// State features for the surrogate (64 values, BF16): RockSample x/n, y/n,
-// terminal, remaining depth/100, rock qualities, rock offsets dx/n, dy/n;
-// crowd driving s/path_len, speed level/(levels-1), terminal, remaining
-// depth/100, then per pedestrian (px - s)/10, py/10, goal/n_goals; zeros
-// to 64.  Feature j is a compile-time index, so nothing lives in private
-// memory; a row is written as eight 16-byte stores.
-template <int J>
-__device__ __forceinline__ float rs_feature(const HDX_CONST ModelHdr *M, int32_t w, int x, int y, float inv,
-                                            float remain) {
-    if (J == 0) return (float)x * inv;
-    if (J == 1) return (float)y * inv;
-    if (J == 2) return (float)((w >> 30) & 1);
-    if (J == 3) return remain;
-    const int m = M->n_rocks, i = J - 4;
-    if (i < m) return (float)((w >> ((10 + i) & 31)) & 1);  // i < m <= 20
-    if (i < 2 * m) return (float)(M->rock_x[i - m] - x) * inv;
-    if (i < 3 * m) return (float)(M->rock_y[i - 2 * m] - y) * inv;
-    return 0.f;
-}
-
-template <int J>
-__device__ __forceinline__ float ped_feature(const HDX_CONST ModelHdr *M, const StatesPtr &S, int64_t k, float s,
-                                             int32_t car, float remain) {
-    if (J == 0) return s / M->path_len;
-    if (J == 1) return (float)(car & 0xff) / (float)max(M->n_levels - 1, 1);
-    if (J == 2) return (float)((car >> 8) & 1);
-    if (J == 3) return remain;
-    constexpr int p = (J - 4) / 3, c = (J - 4) % 3;
-    if (p >= M->n_peds) return 0.f;
-    if (c == 0) return (S.px[p * S.stride + k] - s) * 0.1f;
-    if (c == 1) return S.py[p * S.stride + k] * 0.1f;
-    return (float)S.goal[p * S.stride + k] / (float)M->n_goals;
-}
-
-template <int J0>
-__device__ __forceinline__ uint4 feature_chunk(const HDX_CONST ModelHdr *M, const StatesPtr &S, int64_t k, bool rs,
-                                               int32_t w, int x, int y, float inv, float s, int32_t car, float remain) {
-    float f[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) f[e] = 0.f;
-    if (rs) {
-        f[0] = rs_feature<J0 + 0>(M, w, x, y, inv, remain);
-        f[1] = rs_feature<J0 + 1>(M, w, x, y, inv, remain);
-        f[2] = rs_feature<J0 + 2>(M, w, x, y, inv, remain);
-        f[3] = rs_feature<J0 + 3>(M, w, x, y, inv, remain);
-        f[4] = rs_feature<J0 + 4>(M, w, x, y, inv, remain);
-        f[5] = rs_feature<J0 + 5>(M, w, x, y, inv, remain);
-        f[6] = rs_feature<J0 + 6>(M, w, x, y, inv, remain);
-        f[7] = rs_feature<J0 + 7>(M, w, x, y, inv, remain);
-    } else {
-        f[0] = ped_feature<J0 + 0>(M, S, k, s, car, remain);
-        f[1] = ped_feature<J0 + 1>(M, S, k, s, car, remain);
-        f[2] = ped_feature<J0 + 2>(M, S, k, s, car, remain);
-        f[3] = ped_feature<J0 + 3>(M, S, k, s, car, remain);
-        f[4] = ped_feature<J0 + 4>(M, S, k, s, car, remain);
-        f[5] = ped_feature<J0 + 5>(M, S, k, s, car, remain);
-        f[6] = ped_feature<J0 + 6>(M, S, k, s, car, remain);
-        f[7] = ped_feature<J0 + 7>(M, S, k, s, car, remain);
-    }
-    uint4 v;
-    v.x = (uint32_t)f2bf(f[0]) | ((uint32_t)f2bf(f[1]) << 16);
-    v.y = (uint32_t)f2bf(f[2]) | ((uint32_t)f2bf(f[3]) << 16);
-    v.z = (uint32_t)f2bf(f[4]) | ((uint32_t)f2bf(f[5]) << 16);
-    v.w = (uint32_t)f2bf(f[6]) | ((uint32_t)f2bf(f[7]) << 16);
-    return v;
-}
-
-// Row k of one state array, and chunks of eight of its features.
-template <class Args>
-struct FeatureRow {
-    const Args &A;
-    const HDX_CONST ModelHdr *M;
-    int64_t k;
-    bool rs;
-    int32_t w = 0, car = 0;
-    int x = 0, y = 0;
-    float inv = 0.f, s = 0.f, remain;
-    __device__ __forceinline__ FeatureRow(const Args &A_, int64_t k_) : A(A_), k(k_) {
-        M = (const HDX_CONST ModelHdr *)&A.model->h;
-        const int depth = A.depths ? A.depths[k] : A.depth_const;
-        remain = (float)max(A.horizon - depth, 0) * 0.01f;
-        rs = M->kind == HDX_ROCKSAMPLE;
-        if (rs) {
-            if (A.parents > 0) {
-                const uint32_t c = (uint32_t)k / (uint32_t)A.parents;
-                RsOps::State st = {A.states.w[(uint32_t)k - c * (uint32_t)A.parents]};
-                if (!RsOps::terminal(st)) RsOps::mover(make_view(A.model, nullptr), st, (int)c);
-                w = st.w;
-            } else {
-                w = A.states.w[k];
-            }
-            x = w & 31;
-            y = (w >> 5) & 31;
-            inv = 1.0f / (float)M->grid;
-        } else {
-            s = A.states.s[k];
-            car = A.states.car[k];
-        }
-    }
-    template <int J0>
-    __device__ __forceinline__ uint4 chunk() const {
-        return feature_chunk<J0>(M, A.states, k, rs, w, x, y, inv, s, car, remain);
-    }
-};
-
-template <class Args>
-__device__ __forceinline__ void features_row(const Args &A, int64_t k) {
-    if (k >= A.n) return;
-    const FeatureRow<Args> R(A, k);
-    uint4 *dst = (uint4 *)(A.X + k * kMlpIn);
-    dst[0] = R.template chunk<0>();
-    dst[1] = R.template chunk<8>();
-    dst[2] = R.template chunk<16>();
-    dst[3] = R.template chunk<24>();
-    dst[4] = R.template chunk<32>();
-    dst[5] = R.template chunk<40>();
-    dst[6] = R.template chunk<48>();
-    dst[7] = R.template chunk<56>();
-}
-
 // One state array, its arguments by value.
-__global__ __launch_bounds__(128) void features_one(const FeatArgs A) {
-    features_row(A, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+__global__ __launch_bounds__(kFeatThreads) void features_one(const FeatArgs A) {
+    __shared__ FeatureTable T;
+    features_rows(A, T);
 }
 
 // Many state arrays, their arguments in device memory (read through the
 // constant address space); blockIdx.y selects the array.
-__global__ __launch_bounds__(128) void features_many(const FeatArgs *args) {
-    const HDX_CONST FeatArgs &A = ((const HDX_CONST FeatArgs *)args)[blockIdx.y];
-    features_row(A, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+__global__ __launch_bounds__(kFeatThreads) void features_many(const FeatArgs *args) {
+    __shared__ FeatureTable T;
+    features_rows(((const HDX_CONST FeatArgs *)args)[blockIdx.y], T);
 }
 
 // ---- forward pass of a few leaves -----------------------------------------
@@ -738,33 +783,23 @@ struct Weights {
 __global__ __launch_bounds__(kFwdThreads, 2) void mlp_fwd_pack(const FeatPack F, const MlpDev P) {
     __shared__ __align__(16) uint16_t Hs[kSR][kHP];
     __shared__ float yp[4][kSR];
+    __shared__ FeatureTable T;
+    static_assert(kFwdThreads == 8 * kSR, "eight threads per row");
     const FeatArgs &A = F.a[blockIdx.y];
     const int64_t r0 = (int64_t)blockIdx.x * kSR;
     if (r0 >= A.n) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nb = wave * 64;
+    const HDX_CONST ModelHdr *M = (const HDX_CONST ModelHdr *)&A.model->h;
+    const int r = tid >> 3, c = tid & 7;
+    RowState row;
+    if (r0 + r < A.n) row = load_row(A, M, r0 + r);
+    stage_features(M, T);
+    __syncthreads();
     Weights<kMlpIn> w1;
     Weights<kMlpHidden> w2;
     w1.load(P.w1t, nb, lane);
     w2.load(P.w2t, nb, lane);
-    {
-        // eight threads per row, a chunk of its features each
-        const int r = tid & (kSR - 1), c = tid / kSR;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (r0 + r < A.n) {
-            const FeatureRow<FeatArgs> R(A, r0 + r);
-            switch (c) {
-                case 0: v = R.chunk<0>(); break;
-                case 1: v = R.chunk<8>(); break;
-                case 2: v = R.chunk<16>(); break;
-                case 3: v = R.chunk<24>(); break;
-                case 4: v = R.chunk<32>(); break;
-                case 5: v = R.chunk<40>(); break;
-                case 6: v = R.chunk<48>(); break;
-                default: v = R.chunk<56>(); break;
-            }
-        }
-        *(uint4 *)&Hs[r][c * 8] = v;
-    }
+    *(uint4 *)&Hs[r][c * 8] = r0 + r < A.n ? features_of(A, M, T, row, r0 + r, c) : make_uint4(0, 0, 0, 0);
     __syncthreads();
     f32x4 acc[kSI][4];
     w1.layer(Hs, lane, acc);
@@ -792,12 +827,22 @@ hipError_t mlp_forward(const MlpDev &P, const uint16_t *X, int64_t n, uint16_t *
     if (n <= 0) return hipSuccess;
     const int64_t blocks = (n + kFR - 1) / kFR;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    const StoredRows rows = {X, n, y};
     if (H1 && H2 && H3)
-        hipLaunchKernelGGL(mlp_fused_fwd<true>, dim3((unsigned)blocks), dim3(kFwdThreads), 0, s, X, n, P, y, H1, H2,
-                           H3);
+        hipLaunchKernelGGL((mlp_fused_fwd<true, StoredRows>), dim3((unsigned)blocks), dim3(kFwdThreads), 0, s, rows, P,
+                           H1, H2, H3);
     else
-        hipLaunchKernelGGL(mlp_fused_fwd<false>, dim3((unsigned)blocks), dim3(kFwdThreads), 0, s, X, n, P, y,
+        hipLaunchKernelGGL((mlp_fused_fwd<false, StoredRows>), dim3((unsigned)blocks), dim3(kFwdThreads), 0, s, rows, P,
                            nullptr, nullptr, nullptr);
+    return hipGetLastError();
+}
+
+hipError_t launch_forward_leaves(const FeatArgs *d_args, const int32_t *d_leaf_of, int32_t tiles, const MlpDev &P,
+                                 hipStream_t s) {
+    if (tiles <= 0) return hipSuccess;
+    const LeafRows rows = {d_args, d_leaf_of};
+    hipLaunchKernelGGL((mlp_fused_fwd<false, LeafRows>), dim3((unsigned)tiles), dim3(kFwdThreads), 0, s, rows, P, nullptr,
+                       nullptr, nullptr);
     return hipGetLastError();
 }
 
@@ -854,9 +899,9 @@ hipError_t mlp_refresh_bf16(MlpDev &P, hipStream_t s) {
 
 hipError_t launch_features(const FeatArgs &a, hipStream_t s) {
     if (a.n <= 0) return hipSuccess;
-    const int64_t bx = (a.n + 127) / 128;
+    const int64_t bx = (a.n + kFeatRows - 1) / kFeatRows;
     if (bx > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(features_one, dim3((unsigned)bx), dim3(128), 0, s, a);
+    hipLaunchKernelGGL(features_one, dim3((unsigned)bx), dim3(kFeatThreads), 0, s, a);
     return hipGetLastError();
 }
 
@@ -870,11 +915,11 @@ hipError_t launch_forward_pack(const FeatPack &F, int count, int64_t n_max, cons
 
 hipError_t launch_features_many(const FeatArgs *d_args, int count, int64_t n_max, hipStream_t s) {
     if (count <= 0 || n_max <= 0) return hipSuccess;
-    const int64_t bx = (n_max + 127) / 128;
+    const int64_t bx = (n_max + kFeatRows - 1) / kFeatRows;
     if (bx > 0x7fffffff) return hipErrorInvalidValue;
     for (int i0 = 0; i0 < count; i0 += kMaxGridY) {
         const int c = std::min(kMaxGridY, count - i0);
-        hipLaunchKernelGGL(features_many, dim3((unsigned)bx, c), dim3(128), 0, s, d_args + i0);
+        hipLaunchKernelGGL(features_many, dim3((unsigned)bx, c), dim3(kFeatThreads), 0, s, d_args + i0);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -71,8 +71,9 @@ struct FeatArgs {
     uint16_t *X;
     // RockSample: 0, or the number of states, and row c * parents + k is state
     // k after action c (terminal states as they are)
-    int32_t parents, pad;
-    float *y;  // launch_forward_pack: the rows' values
+    int32_t parents;
+    int32_t first_tile;  // launch_forward_leaves: the array's first tile of kMlpTileRows rows
+    float *y;            // launch_forward_pack, launch_forward_leaves: the rows' values
 };
 
 // y = MLP(X) for n rows; H1..H3 (row stride 256) receive the activations
@@ -84,8 +85,9 @@ hipError_t mlp_backward(const MlpDev &P, const uint16_t *X, const float *t, int 
 hipError_t mlp_adam(MlpDev &P, const float *grads, float lr, int step, hipStream_t s);
 hipError_t mlp_refresh_bf16(MlpDev &P, hipStream_t s);
 // Features of one state array (arguments by value), or of `count` arrays whose
-// arguments are in device memory (n_max: the longest array); values of up to
-// kArgPack arrays without their features' detour through memory.
+// arguments are in device memory (n_max: the longest array); and values without
+// the features' detour through memory, of arrays whose arguments are in device
+// memory or of up to kArgPack arrays.
 constexpr int kArgPack = 8;       // a surrogate expansion of this many leaves takes the packs
 constexpr int kMaxGridY = 65535;  // arrays per launch of the argument-array kernels
 struct FeatPack {
@@ -93,6 +95,9 @@ struct FeatPack {
 };
 static_assert(sizeof(FeatPack) <= 1024, "kernel argument pack too large");
 hipError_t launch_features(const FeatArgs &a, hipStream_t s);
+constexpr int kMlpTileRows = 128;
+hipError_t launch_forward_leaves(const FeatArgs *d_args, const int32_t *d_leaf_of, int32_t tiles, const MlpDev &P,
+                                 hipStream_t s);
 hipError_t launch_forward_pack(const FeatPack &F, int count, int64_t n_max, const MlpDev &P, hipStream_t s);
 hipError_t launch_features_many(const FeatArgs *d_args, int count, int64_t n_max, hipStream_t s);
 

@@ -278,7 +278,7 @@ hdx_status hdx_features(hdx_ctx *ctx, const hdx_model *model, hdx_states states,
     a.horizon = horizon;
     a.depth_const = 0;
     a.X = X;
-    a.parents = a.pad = 0;
+    a.parents = a.first_tile = 0;
     a.y = nullptr;
     return launch_features(a, (hipStream_t)stream) == hipSuccess ? HDX_OK : HDX_E_DEVICE;
 }
@@ -291,7 +291,7 @@ hdx_status hdx_expand_leaf_surrogate(hdx_ctx *ctx, const hdx_leaf *leaves, int32
     // features and values
     std::vector<size_t> st_off(n_leaves), pair_off(n_leaves);
     size_t st_bytes = 0;
-    int64_t pairs = 0;
+    int64_t pairs = 0, leaf_tiles = 0;
     for (int32_t i = 0; i < n_leaves; ++i) {
         if (!leaves[i].model) return HDX_E_INVALID;
         const hdx_model_desc &d = *hdx_internal_desc(leaves[i].model);
@@ -306,11 +306,17 @@ hdx_status hdx_expand_leaf_surrogate(hdx_ctx *ctx, const hdx_leaf *leaves, int32
         const size_t per = d.kind == HDX_ROCKSAMPLE ? 0 : (size_t)(8 + 9 * d.n_peds);
         st_bytes += ((size_t)np * per + 64) & ~(size_t)15;
         pairs += np;
+        leaf_tiles += (np + kMlpTileRows - 1) / kMlpTileRows;
     }
     std::lock_guard<std::mutex> g(mlp->mu);
     Ordered o(mlp, (hipStream_t)stream);
     const size_t args_off = (st_bytes + (size_t)pairs * (kMlpIn * sizeof(uint16_t) + sizeof(float)) + 255) & ~(size_t)255;
-    const size_t args_bytes = (size_t)n_leaves * (sizeof(FeatArgs) + sizeof(SurArgs));
+    // Many leaves take the network's tiles leaf by leaf, with the features computed in the tile, unless leaves of few
+    // rows would leave more than a fifth of the tiles empty: two passes cost a twentieth more (307 thousand rows: 97
+    // and 27 us, in one 118, and a launch).
+    const bool by_leaf = leaf_tiles <= (pairs + kMlpTileRows - 1) / kMlpTileRows * 5 / 4;
+    const size_t args_bytes =
+        (size_t)n_leaves * (sizeof(FeatArgs) + sizeof(SurArgs)) + (by_leaf ? (size_t)leaf_tiles * sizeof(int32_t) : 0);
     const size_t need = args_off + args_bytes;
     if (mlp->sur_bytes < need) {
         if (mlp->sur) hipFree(mlp->sur);
@@ -357,7 +363,6 @@ hdx_status hdx_expand_leaf_surrogate(hdx_ctx *ctx, const hdx_leaf *leaves, int32
         a.model = hdx_internal_devmodel(leaves[i].model);
         a.states = to_states(rocks ? mod[i].states_out : mod[i].sprime);
         a.parents = rocks ? leaves[i].n : 0;
-        a.pad = 0;
         a.depths = nullptr;
         a.depth_const = leaves[i].depth + 1;
         a.n = np;
@@ -414,17 +419,33 @@ hdx_status hdx_expand_leaf_surrogate(hdx_ctx *ctx, const hdx_leaf *leaves, int32
     if (!mlp->args_done && (e = hipEventCreateWithFlags(&mlp->args_done, hipEventDisableTiming)) != hipSuccess)
         return dev_fail(ctx, e, "event");
     const size_t fa_bytes = fa.size() * sizeof(FeatArgs), sa_bytes = sa.size() * sizeof(SurArgs);
-    memcpy(mlp->h_args, fa.data(), fa_bytes);
     memcpy((char *)mlp->h_args + fa_bytes, sa.data(), sa_bytes);
     FeatArgs *d_fa = (FeatArgs *)(base + args_off);
     SurArgs *d_sa = (SurArgs *)(base + args_off + fa_bytes);
-    if ((e = hipMemcpyAsync(d_fa, mlp->h_args, fa_bytes + sa_bytes, hipMemcpyHostToDevice, s)) != hipSuccess ||
+    int32_t *d_leaf = (int32_t *)(base + args_off + fa_bytes + sa_bytes);
+    int32_t *h_leaf = (int32_t *)((char *)mlp->h_args + fa_bytes + sa_bytes);
+    size_t copied = fa_bytes + sa_bytes;
+    if (by_leaf) {
+        int32_t t = 0;
+        for (size_t i = 0; i < fa.size(); ++i) {
+            fa[i].first_tile = t;
+            for (int64_t r = 0; r < fa[i].n; r += kMlpTileRows) h_leaf[t++] = (int32_t)i;
+        }
+        copied += (size_t)t * sizeof(int32_t);
+    }
+    memcpy(mlp->h_args, fa.data(), fa_bytes);
+    if ((e = hipMemcpyAsync(d_fa, mlp->h_args, copied, hipMemcpyHostToDevice, s)) != hipSuccess ||
         (e = hipEventRecord(mlp->args_done, s)) != hipSuccess)
         return dev_fail(ctx, e, "argument copy");
     mlp->args_used = true;
-    if ((e = launch_features_many(d_fa, (int)fa.size(), n_max, s)) != hipSuccess) return dev_fail(ctx, e, "features");
-    if (pairs > 0 && (e = mlp_forward(mlp->P, X, pairs, nullptr, nullptr, nullptr, vals, s)) != hipSuccess)
-        return dev_fail(ctx, e, "forward");
+    if (by_leaf) {
+        if ((e = launch_forward_leaves(d_fa, d_leaf, (int32_t)leaf_tiles, mlp->P, s)) != hipSuccess)
+            return dev_fail(ctx, e, "forward");
+    } else {
+        if ((e = launch_features_many(d_fa, (int)fa.size(), n_max, s)) != hipSuccess) return dev_fail(ctx, e, "features");
+        if (pairs > 0 && (e = mlp_forward(mlp->P, X, pairs, nullptr, nullptr, nullptr, vals, s)) != hipSuccess)
+            return dev_fail(ctx, e, "forward");
+    }
     if ((e = launch_surrogate_reduce(d_sa, (int)sa.size(), a_max, s)) != hipSuccess)
         return dev_fail(ctx, e, "child means");
     return HDX_OK;
