@@ -25,8 +25,7 @@ constexpr uint64_t kPedTerminalObs = ~0ull;
 
 // Model parameters and tables as the kernels read them (device memory, one
 // per uploaded model).  Derived constants are computed once on the host.
-// The header is read with scalar loads; per-lane lookups of the discount
-// table go through an LDS copy of its first kGpowLds entries.
+// The header is read with scalar loads.
 struct ModelHdr {
     int32_t kind, n_actions;
     // RockSample
@@ -55,8 +54,6 @@ struct ModelHdr {
     int32_t nav_run_begin[9];
     uint32_t nav_runs[HDX_MAX_NAV_UNKNOWN];
 };
-
-constexpr int kGpowLds = 256;
 
 struct DevModel {
     ModelHdr h;
@@ -134,6 +131,7 @@ constexpr int kRockActions = 5 + kMaxRocks;
 constexpr int kRockSuccs = 6;              // a robot's moves, its sample, and no change
 constexpr int kRockCols = kMaxRocks + 1;   // a column per rock, and one for all scenarios
 constexpr int kRockSets = kMaxRocks + 2;   // live, acting, and per rock those reading it good
+constexpr int kRockCells = 1024;           // x | y << 5
 constexpr int kRockTerms = 2 * kMaxGrid + 2;  // distances on a grid are below
 struct RockSucc {
     double value;            // rollout of a live scenario
@@ -142,7 +140,12 @@ struct RockSucc {
 struct RockLayout {
     uint32_t zmask, cmask, term, coef, succ, cells, state, ub, lb, cnt, sums, place, size, pre, misc, total;
 };
-__host__ __device__ inline RockLayout make_rock_layout(int32_t n, bool two) {
+// Words of lb: a value per scenario; where the rollouts run step by step, one
+// per successor, and the effects of each cell.
+__host__ __device__ inline int32_t rock_values(int32_t n, bool stepped) {
+    return stepped ? kRockSuccs * n + kRockCells : n;
+}
+__host__ __device__ inline RockLayout make_rock_layout(int32_t n, int32_t values, bool two) {
     RockLayout L;
     uint32_t o = 0;
     auto take = [&](uint32_t bytes) {
@@ -159,7 +162,7 @@ __host__ __device__ inline RockLayout make_rock_layout(int32_t n, bool two) {
     L.cells = take(4u * chunks);
     L.state = take(4u * (two ? 2 : 1) * n);
     L.ub = take(4u * n);
-    L.lb = take(4u * n);
+    L.lb = take(4u * values);
     L.cnt = take(4u * splits * (kRockSets + 1) * 32);
     L.sums = take(4u * kRockActions * keys * 2);
     L.place = take(4u * kRockActions * keys);
@@ -251,7 +254,7 @@ struct Variant {
     // driving only: the kernel instance with 8 or 16 lanes per scenario
     int32_t group = 0;
     // navigation: the largest (action, scenario) pairs of a tile, counted
-    // twice where the rollouts run step by step
+    // twice where the rollouts run step by step; RockSample: rock_values
     int32_t pairs = 1;
 };
 Variant pick_variant(int32_t has_rs, int32_t has_ped, int32_t ped_max, int32_t n_max, int32_t has_mars,
@@ -316,10 +319,11 @@ hipError_t launch_classes(const LeafTask *d_tasks, const Tile *d_tiles, TileQueu
 // tiles (a call far smaller than the GPU): a lane for every scenario (driving:
 // its lanes), so each tile ends sooner.  Otherwise half a lane per scenario,
 // for RockSample four wavefronts at most (2048 leaves of 31..500 scenarios: 61,
-// 38, 31 and 39 us at 1, 2, 4 and 8); driving a quarter of its
-// lanes with more than one tile per CU (512 leaves of 125..500 scenarios: 500
-// us at 512 lanes, 526 at 1024), else half (256 leaves among others: 930 and
-// 769 us).  Workgroups in tile order, one per tile.
+// 38, 31 and 39 us at 1, 2, 4 and 8) and, with fewer tiles than eight per CU,
+// at least (72 leaves of 67: 11.5 us at one wavefront, 8.3 at four); driving a
+// quarter of its lanes with more than one tile per CU (512 leaves of 125..500
+// scenarios: 500 us at 512 lanes, 526 at 1024), else half (256 leaves among
+// others: 930 and 769 us).  Workgroups in tile order, one per tile.
 Schedule class_default_schedule(const Variant &v, int64_t tiles, int32_t n_cu, bool few);
 hipError_t configure_expand_kernels();
 

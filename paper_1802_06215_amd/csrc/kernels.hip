@@ -72,6 +72,15 @@ __device__ __forceinline__ void seg_step(float &u, float &l, int &f) {
 // moving it.
 __device__ __forceinline__ void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
+// The value of another lane of the lane's quad (quad_perm kCtrl).
+template <int kCtrl>
+__device__ __forceinline__ double quad_swap(double v) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, kCtrl, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), kCtrl, 0xf, 0xf, true);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
 // The descriptor again, so that what is read through it from here on is not
 // read (and held in scalar registers, which run out) from the start.
 __device__ __forceinline__ const HDX_CONST LeafTask *reread(const HDX_CONST LeafTask *T) {
@@ -126,6 +135,51 @@ __device__ __forceinline__ void rock_keys(uint64_t (&keys)[K], uint64_t valid, u
     }
 }
 
+// cell_effects of every cell, by the whole workgroup, with barriers.
+__device__ __forceinline__ void stage_effects(const MView &M, uint32_t *effects) {
+    for (int i = threadIdx.x; i < kRockCells; i += blockDim.x) effects[i] = cell_effects(M, i);
+    __syncthreads();
+    if ((int)threadIdx.x < M.h->n_rocks)
+        effects[M.h->rock_x[threadIdx.x] | (M.h->rock_y[threadIdx.x] << 5)] |= rock_effect((int)threadIdx.x);
+    __syncthreads();
+}
+
+// Rollout step by step (constant or random policy) of the lane's robots, at
+// most R steps from depth d0, accumulated in FP32 in step order.  Lanes come in
+// groups of `width`, all of one scenario, whose random actions are the same for
+// whatever state it is in: lane c of a group draws those of depths c, width + c,
+// ... and the others read them from it.  Called by all lanes of a wavefront.
+template <class Ops>
+__device__ __forceinline__ float rock_rollout(const MView &M, const uint32_t *effects, const RolloutParams &P, uint32_t id,
+                                              int d0, int R, typename Ops::Team t, int width, int c, int &steps) {
+    const Modulus pick((uint32_t)P.n_actions);
+    const int first = lane_id() - c, grid = M.h->grid;
+    float value = 0.0f;
+    steps = 0;
+    bool alive = t.any(grid);
+    int drawn = 0, at = width;
+    float powers = 0.0f;  // lane i: 10 gamma^i of the current 64 depths
+    for (int j = 0;; ++j, ++at) {
+        alive &= j < R;
+        if (!__ballot(alive)) break;
+        if ((j & 63) == 0) powers = 10.0f * M.gpow(min(j + lane_id(), kHorizon - 1));
+        const float ten = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(powers), j & 63));
+        int a = P.const_action;
+        if (P.policy == HDX_POLICY_RANDOM) {
+            if (at == width) {
+                drawn = (int)pick(philox(id, (uint32_t)(d0 + j + c), 0, kTagPolicy, P.k0, P.k1).x);
+                at = 0;
+            }
+            a = width > 1 ? __shfl(drawn, first + at, 64) : drawn;
+        }
+        const float v = value + Ops::act(M, effects, t, a, ten);
+        value = alive ? v : value;
+        steps += alive ? 1 : 0;
+        alive &= t.any(grid);
+    }
+    return value;
+}
+
 // RockSample, one robot (RsOps) or two (MarsOps): nb actions of one leaf from
 // action a_first on.  With two robots a tile stays within one action a1 of
 // robot 1, which acts first and with the same outcome for all of them; what
@@ -149,13 +203,18 @@ __device__ __forceinline__ void rock_keys(uint64_t (&keys)[K], uint64_t valid, u
 //    all live scenarios of a successor, in closed form.
 //  - Leaves whose scenarios differ in their cells, and the other rollout
 //    policies, take per-scenario values instead, summed per chunk by DPP row
-//    reductions, chunks in order.
+//    reductions, chunks in order.  Rollouts step by step run a lane per scenario
+//    and successor (rock_rollout): the successors share their random actions,
+//    and small leaves fill a wavefront.
 // Integers and fixed orders throughout: results do not depend on the width or
 // on how many actions a tile takes.
 // Measured, one action per tile before and now: 2048 leaves of 31..500
-// scenarios with 20 actions 96 -> 31-34 us, 8192 leaves of 6..100 with 13
-// 119 -> 40, 128 leaves of 31..500 with 625 joint actions 375 -> 74; a single
-// leaf of 500 with 20 actions (one action per tile) 7.9 -> 7.8.
+// scenarios with 20 actions 96 -> 34 us, 8192 leaves of 6..100 with 13
+// 119 -> 43, 128 leaves of 31..500 with 625 joint actions 375 -> 74; 1206 leaves
+// of two scenarios with random rollouts 180 -> 51; a single leaf of 500 with 20
+// actions (one action per tile) 7.9 -> 7.9, mostly the launch (its tile 14.7
+// -> 12.6 thousand cycles, one of a leaf of 67 on four wavefronts 20 -> 9.5,
+// with the successors and the children on several wavefronts).
 // (rock_set: a child's live scenarios under one reading of robot 1, as the set
 // `from` without the set `minus`; -1 none.)
 struct RockSet {
@@ -177,18 +236,20 @@ __device__ __forceinline__ void run_tile_rocks(const HDX_CONST LeafTask *T, cons
     constexpr int kSplits = kTwo ? 3 : 1;  // robot 1 read nothing, good, bad
     const int n = T->n, cap = T->cap, nch = (n + 63) >> 6;
     const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id(), wid = tid >> 6, nw = nt >> 6;
-    const MView M = make_view(T->model, nullptr);
+    const MView M = make_view(T->model);
     const int per = T->row_actions, m = per - 5;
     const int a1 = kTwo ? (a_first * M.h->joint_inv) >> 16 : 0;
     const int b0 = kTwo ? a_first - a1 * per : a_first, b1 = b0 + nb;  // the acting robot's actions
     const int j0 = b0 > 5 ? b0 - 5 : 0, j1 = b1 - 5;                  // senses j0 <= j < j1
     const bool split = kTwo && a1 >= 5;                                // robot 1 reads
-    const RockLayout Ly = make_rock_layout(n, kTwo);
+    const bool stepped = T->policy != HDX_POLICY_DEFAULT;
+    const RockLayout Ly = make_rock_layout(n, rock_values(n, stepped), kTwo);
     uint64_t *zmask = (uint64_t *)(lds + Ly.zmask);  // [rock][chunk]: scenarios that read it good
     uint64_t *cmask = (uint64_t *)(lds + Ly.cmask);  // [live, acting, robot 1 good, bad][chunk]
     int32_t *cells = (int32_t *)(lds + Ly.cells);    // per chunk: the live scenarios' cells, -1 none, -2 several
     int32_t *state = (int32_t *)(lds + Ly.state);
-    float *ub = (float *)(lds + Ly.ub), *lb = (float *)(lds + Ly.lb);
+    float *ub = (float *)(lds + Ly.ub), *lb = (float *)(lds + Ly.lb);  // (lb: per successor if they run step by step)
+    uint32_t *effects = (uint32_t *)(lb + kRockSuccs * n);  // (there only then)
     // [split][set][column]: scenarios of a split and a set (0 live, 1 acting, 2 + j those reading rock j good) that
     // hold column i (rock i good; column kRockCols - 1: all)
     int32_t *cnt = (int32_t *)(lds + Ly.cnt);
@@ -243,11 +304,7 @@ __device__ __forceinline__ void run_tile_rocks(const HDX_CONST LeafTask *T, cons
         const uint32_t id = id_ahead;
         gather(t + nw);
         if (valid) {
-            if (last_action >= 0) {
-                float r0;
-                uint64_t z0;
-                Ops::template step<false>(M, st, last_action, id, (uint32_t)(depth - 1), RP.k0, RP.k1, r0, z0);
-            }
+            if (last_action >= 0) Ops::move(M, st, last_action);
             if (a_first == 0) {
                 Ops::store(M, leaf_out, k, st);
                 T->ids_out[k] = id;
@@ -255,6 +312,20 @@ __device__ __forceinline__ void run_tile_rocks(const HDX_CONST LeafTask *T, cons
         }
         const bool live = valid && !Ops::terminal(st);
         const uint64_t lv = __ballot(live);
+        // the shared cell and from it the threshold of lane i's rock, a load in flight while what follows is computed
+        int cell = -1;
+        uint32_t thr_i = 0;
+        auto locate = [&]() {
+            if (!lv) return;
+            const int leader = __ffsll((unsigned long long)lv) - 1;
+            cell = __builtin_amdgcn_readlane(Ops::cell(st), leader);
+            if (__ballot(live && Ops::cell(st) != cell)) cell = -2;
+            if (cell >= 0 && j1 > j0 && lane < m) {
+                const int dx = Ops::cell_x(cell) - rock_x, dy = Ops::cell_y(cell) - rock_y;
+                thr_i = M.thr[(uint32_t)(dx * dx + dy * dy)];
+            }
+        };
+        if constexpr (!kTwo) locate();
         uint4 u = make_uint4(0, 0, 0, 0);
         if (draw && lv) u = philox(id, (uint32_t)depth, 0, kTagStep, RP.k0, RP.k1);
         int z1 = 0;
@@ -274,12 +345,7 @@ __device__ __forceinline__ void run_tile_rocks(const HDX_CONST LeafTask *T, cons
         } else {
             if (valid) state[k] = st.w;
         }
-        int cell = -1;
-        if (lv) {
-            const int leader = __ffsll((unsigned long long)lv) - 1;
-            cell = __builtin_amdgcn_readlane(Ops::cell(st), leader);
-            if (__ballot(live && Ops::cell(st) != cell)) cell = -2;
-        }
+        if constexpr (kTwo) locate();
         const uint64_t ga = split ? __ballot(z1 == 1) : 0, gb = split ? __ballot(z1 == 2) : 0;
         const uint64_t g0 = lv & ~(ga | gb);
         if (lane == 0) {
@@ -315,12 +381,6 @@ __device__ __forceinline__ void run_tile_rocks(const HDX_CONST LeafTask *T, cons
             }
         };
         count(0, lv, act);
-        // the threshold of lane i's rock from the shared cell
-        uint32_t thr_i = 0;
-        if (cell >= 0 && lane < m) {
-            const int dx = Ops::cell_x(cell) - rock_x, dy = Ops::cell_y(cell) - rock_y;
-            thr_i = M.thr[(uint32_t)(dx * dx + dy * dy)];
-        }
         // a reading is good if it is correct of a good rock or wrong of a bad one
         auto reading = [&](int j) -> uint64_t {
             uint32_t thr;
@@ -360,33 +420,56 @@ __device__ __forceinline__ void run_tile_rocks(const HDX_CONST LeafTask *T, cons
 
     // -- per-scenario values where they are needed --------------------------------
     const bool values = !shared || !shared_l || T->U != nullptr || T->L != nullptr;
+    // the successors this tile's actions lead to
+    const int c0 = b0 < 5 ? b0 : 5, c1 = b1 < kRockSuccs ? b1 : kRockSuccs, nc = c1 - c0;
     if (values) {
         for (int i = tid; i < kRockActions * kKeys * 2; i += nt) sums[i] = 0.0f;
-        for (int c = 0; c < kRockSuccs; ++c) {
+        if (stepped) {
+            stage_effects(M, effects);
+            // a lane per scenario and successor, the successors of a scenario side by side
+            const int per_wave = 64 / nc, i = lane / nc, c = lane - i * nc;
+            for (int k0 = wid * per_wave; k0 < n; k0 += nw * per_wave) {
+                const int k = k0 + i;
+                const bool mine = i < per_wave && k < n;
+                typename Ops::State st;
+                Ops::make_terminal(st);
+                uint32_t id = 0;
+                if (mine) {
+                    Ops::from_words(st, state[k], kTwo ? state[n + k] : 0);
+                    id = T->parent_ids[(uint16_t)T->idx[(uint32_t)k]];
+                }
+                typename Ops::Team team = Ops::team(M, st);
+                team.hop(effects, M.h->grid, kTwo ? 1 : 0, c0 + c, 0.0f);  // (5: no effect)
+                int ns;
+                const float L = rock_rollout<Ops>(M, effects, RP, id, depth + 1, R, team, nc, c, ns);
+                if (mine) {
+                    lb[(c0 + c) * n + k] = L;
+                    atomicAdd(&misc[2 + 2 * (c0 + c)], ns);
+                }
+            }
+            __syncthreads();
+        }
+        for (int c = c0; c < c1; ++c) {
             const int lo = c < 5 ? c : (b0 > 5 ? b0 : 5), hi = c < 5 ? c + 1 : b1;  // its actions
-            if (c < 5 ? (c < b0 || c >= b1) : lo >= hi) continue;
+            float *const lc = lb + (stepped ? c * n : 0);
             typename Ops::WaveUpper wave_upper;
             int steps = 0, rewards = 0;
             for (int t = wid; t < nch; t += nw) {
                 const int k = t * 64 + lane;
-                const bool valid = k < n;
                 typename Ops::State st;
                 Ops::make_terminal(st);
-                if (valid) Ops::from_words(st, state[k], kTwo ? state[n + k] : 0);
-                float r = 0.0f;
+                if (k < n) Ops::from_words(st, state[k], kTwo ? state[n + k] : 0);
                 if (!Ops::terminal(st)) {
-                    if (c < 5 && Ops::acting(st)) r = Ops::mover(M, st, c);
+                    if (c < 5 && Ops::acting(st)) rewards += (int)Ops::mover(M, st, c);
                     Ops::settle(st);
                 }
-                rewards += (int)r;
                 const float U = Ops::upper_wave(M, st, wave_upper);
-                float L = 0.0f;
-                if (valid) {
+                if (k < n) {
                     int ns = 0;
-                    L = rollout<Ops>(M, RP, st, T->parent_ids[(uint16_t)T->idx[(uint32_t)k]], depth + 1, ns);
+                    const float L = stepped ? lc[k] : Ops::rollout_east(M, st, R, ns);
                     steps += ns;
                     ub[k] = U;
-                    lb[k] = L;
+                    lc[k] = L;
                     for (int b = lo; b < hi; ++b) {
                         const int64_t at = (int64_t)(a_first + b - b0) * n + k;
                         if (T->U) T->U[at] = U;
@@ -398,14 +481,14 @@ __device__ __forceinline__ void run_tile_rocks(const HDX_CONST LeafTask *T, cons
             rewards = wave_total_i(rewards) / 10;
             if (lane == 0) {
                 atomicAdd(&misc[1 + 2 * c], rewards);
-                atomicAdd(&misc[2 + 2 * c], steps);
+                if (!stepped) atomicAdd(&misc[2 + 2 * c], steps);
             }
             __syncthreads();
             // sums per child of its actions, one wavefront per action
             for (int b = lo + wid; b < hi; b += nw) {
                 for (int t = 0; t < nch; ++t) {
                     const int k = t * 64 + lane;
-                    const float u = k < n ? ub[k] : 0.0f, l = k < n ? lb[k] : 0.0f;
+                    const float u = k < n ? ub[k] : 0.0f, l = k < n ? lc[k] : 0.0f;
                     uint64_t keys[kKeys];
                     rock_keys<kTwo>(keys, chunk_mask(n, t), cmask[t], kTwo ? cmask[nch + t] : 0,
                                     kTwo ? cmask[2 * nch + t] : 0, kTwo ? cmask[3 * nch + t] : 0,
@@ -427,10 +510,10 @@ __device__ __forceinline__ void run_tile_rocks(const HDX_CONST LeafTask *T, cons
         }
     }
 
-    // -- the six successors of the shared cells: bound terms, rollout, reward ----
+    // -- the successors of the shared cells: bound terms, rollout, reward ----
     if (shared) {
         // 32 lanes per successor c, lane i of them column i
-        for (int c = tid >> 5; c < kRockSuccs; c += nt >> 5) {
+        for (int c = c0 + (tid >> 5); c < c1; c += nt >> 5) {
             const int i = lane & 31;
             typename Ops::State sc;
             Ops::from_cell(sc, cell < 0 ? 0 : cell);
@@ -516,52 +599,64 @@ __device__ __forceinline__ void run_tile_rocks(const HDX_CONST LeafTask *T, cons
     __syncthreads();
     T = reread(T);
 
-    // -- children, a lane each ------------------------------------------------------
-    for (int e = tid; e < nb * kKeys; e += nt) {
-        const int i = e / kKeys, q = e - i * kKeys, b = b0 + i, a = a_first + i;
-        const int c = b >= 5 ? 5 : b;
-        const int N = size[e], at0 = place[e], ci = at0 >> 16;
-        if (N > 0 && ci < cap) {
-            const int z1 = kTwo ? q / 3 : 0, z2 = kTwo ? q - 3 * z1 : q;
-            const RockSet w = rock_set<kTwo>(b, z2);
-            float u0, l0;
+    // -- children, a lane each; few of them four lanes each, a quarter of the columns and then the quad's sum (one
+    // lane's twenty columns take 2700 cycles, most of them waits), on other wavefronts than the leaf's first chunks --
+    auto children = [&](auto lanes) {
+        constexpr int kLanes = decltype(lanes)::value, kCols = kMaxRocks / kLanes;
+        for (int g = tid ^ (nt >> 1); g < nb * kKeys * kLanes; g += nt) {
+            const int e = g / kLanes, part = g % kLanes;
+            const int i = e / kKeys, q = e - i * kKeys, b = b0 + i, a = a_first + i;
+            const int c = b >= 5 ? 5 : b;
+            const int N = size[e], at0 = place[e], ci = at0 >> 16;
+            if (N == 0) continue;  // (a quad's lanes together)
+            float u0 = 0.0f, l0 = 0.0f;
             if (shared) {
                 // the terms times the counts, and 1 / N to FP64's last places (the hardware's estimate and two Newton
                 // steps), so the mean is rounded once
+                const int z1 = kTwo ? q / 3 : 0, z2 = kTwo ? q - 3 * z1 : q;
+                const RockSet w = rock_set<kTwo>(b, z2);
                 const int32_t *from = cnt + z1 * kSplitSize + (w.from >= 0 ? w.from : 0) * kSetSize;
                 const int32_t *minus = cnt + z1 * kSplitSize + (w.minus >= 0 ? w.minus : 0) * kSetSize;
                 const int keep = w.from >= 0 ? -1 : 0, drop = w.minus >= 0 ? -1 : 0;
                 const double *f = coef + c * kRockCols;
-                double v = 0.0, x = 0.0;
+                double v = 0.0;
 #pragma unroll
-                for (int r = 0; r < kMaxRocks; r += 2) {  // columns past the last rock hold 0
+                for (int j = 0; j < kCols; ++j) {  // columns past the last rock hold 0
+                    const int r = part * kCols + j;
                     v = __builtin_fma(f[r], (double)((from[r] & keep) - (minus[r] & drop)), v);
-                    x = __builtin_fma(f[r + 1], (double)((from[r + 1] & keep) - (minus[r + 1] & drop)), x);
+                }
+                if constexpr (kLanes == 4) {
+                    v = v + quad_swap<0xB1>(v);  // lanes 1 0 3 2
+                    v = v + quad_swap<0x4E>(v);  // lanes 2 3 0 1
                 }
                 const double counted = (double)((from[kMaxRocks] & keep) - (minus[kMaxRocks] & drop));  // live ones
                 const double dn = (double)N;
                 double rn = __builtin_amdgcn_rcp(dn);
                 rn = __builtin_fma(__builtin_fma(-dn, rn, 1.0), rn, rn);
                 rn = __builtin_fma(__builtin_fma(-dn, rn, 1.0), rn, rn);
-                u0 = (float)(__builtin_fma(f[kMaxRocks], counted, v + x) * rn);
+                u0 = (float)(__builtin_fma(f[kMaxRocks], counted, v) * rn);
                 l0 = (float)(succ[c].value * counted * rn);
-            } else {
-                u0 = sums[e * 2] / (float)N;
             }
-            if (!shared_l) l0 = sums[e * 2 + 1] / (float)N;
-            const int64_t at = (int64_t)a * cap + ci;
-            T->child_z[at] = (uint64_t)q;
-            T->child_n[at] = N;
-            T->child_off[at] = at0 & 0xFFFF;
-            T->child_u0[at] = u0;
-            T->child_l0[at] = l0;
+            if (part == 0 && ci < cap) {
+                if (!shared) u0 = sums[e * 2] / (float)N;
+                if (!shared_l) l0 = sums[e * 2 + 1] / (float)N;
+                const int64_t at = (int64_t)a * cap + ci;
+                T->child_z[at] = (uint64_t)q;
+                T->child_n[at] = N;
+                T->child_off[at] = at0 & 0xFFFF;
+                T->child_u0[at] = u0;
+                T->child_l0[at] = l0;
+            }
         }
-        if (q == 0) {
-            const int reward = misc[0] + (values ? misc[1 + 2 * c] : succ[c].reward);
-            T->r_mean[a] = n > 0 ? 10.0f * (float)reward / (float)n : 0.0f;
-            T->steps[2 * a + 0] = (int64_t)live_n;
-            T->steps[2 * a + 1] = values ? (int64_t)misc[2 + 2 * c] : (int64_t)succ[c].steps * live_n;
-        }
+    };
+    if (nb * kKeys <= 16) children(std::integral_constant<int, 4>());
+    else children(std::integral_constant<int, 1>());
+    for (int i = nt - 1 - tid; i < nb; i += nt) {
+        const int a = a_first + i, c = b0 + i >= 5 ? 5 : b0 + i;
+        const int reward = misc[0] + (values ? misc[1 + 2 * c] : succ[c].reward);
+        T->r_mean[a] = n > 0 ? 10.0f * (float)reward / (float)n : 0.0f;
+        T->steps[2 * a + 0] = (int64_t)live_n;
+        T->steps[2 * a + 1] = values ? (int64_t)misc[2 + 2 * c] : (int64_t)succ[c].steps * live_n;
     }
 
     // -- grouped order ------------------------------------------------------------
@@ -675,7 +770,10 @@ __device__ __forceinline__ void run_tile_rocks(const HDX_CONST LeafTask *T, cons
 // takes as many actions as its LDS holds (nav_tile_actions) and a lane does a
 // scenario's actions one after another.  What an action yields is a word
 // (NavCode) in LDS; rollouts of the default policy are settled from the walk
-// and the failure words (NavOps::walk).  Measured on 1024 leaves of 125..2000
+// and the failure words (NavOps::walk); rollouts step by step run a lane per
+// scenario and action, which share their random words (153 leaves of two
+// scenarios, random rollouts: 36 us with a tile per action, 70 with a lane
+// running three actions in turn, 26 so).  Measured on 1024 leaves of 125..2000
 // scenarios: 0.37 ms (1.1e8 VALU instructions of a wavefront, 0.48 of the
 // issue slots) against 3.26 ms with one action per tile and every rollout
 // step taken; eleven leaves of one to five scenarios 16 against 67 us.
@@ -717,11 +815,11 @@ __device__ __forceinline__ void run_tile_nav(const HDX_CONST LeafTask *T, const 
     uint32_t *meta = (uint32_t *)(lds + Ly.meta);
     float *chunk_r = (float *)(lds + Ly.chunk_r);
     int32_t *expanded = (int32_t *)(lds + Ly.misc);
-    const MView M = make_view(T->model, nullptr);
+    const MView M = make_view(T->model);
 
     for (int j = tid; j <= kNavSums; j += nt) gsum[j] = M.gpow_sum(j);
     for (int d = tid; d <= Ops::kNoDistance; d += nt)
-        ub[d] = d == Ops::kNoDistance ? 0.0f : 20.0f * M.gpow_uniform(d > 0 ? d - 1 : 1);
+        ub[d] = d == Ops::kNoDistance ? 0.0f : 20.0f * M.gpow(d > 0 ? d - 1 : 1);
     for (int i = tid; i < na * kNavKeys; i += nt) cnt[i] = 0;
     if (tid == 0) *expanded = 0;
     __syncthreads();
@@ -781,16 +879,13 @@ __device__ __forceinline__ void run_tile_nav(const HDX_CONST LeafTask *T, const 
             int d = Ops::kNoDistance, kind = Ops::kStuck, m = 0;
             bool settled = true;
             Ops::State s1 = st;
-            float L = 0.0f;
             if (live) {
                 Ops::move(M, s1, a, u_fail, a == 0 ? 0 : (int)((around >> (a - 1)) & 1u), r);
                 if (!Ops::terminal(s1)) {
                     const int x = s1.p & 15, y = (s1.p >> 4) & 15;
                     z = Ops::neighbours(M, rows, x, y) ^ err;
                     d = Ops::distance(M, s1);
-                    if (stepped) {
-                        if (R > 0) L = Ops::rollout_steps(M, RP, rows, s1, id, depth + 1, R, m);
-                    } else if (R > 0) {
+                    if (R > 0 && !stepped) {
                         kind = Ops::walk(M, rows, target, x, y, R, m);
                         settled = kind == Ops::kOver || m == 0;
                         need = settled || need > m ? need : m;
@@ -801,7 +896,7 @@ __device__ __forceinline__ void run_tile_nav(const HDX_CONST LeafTask *T, const 
             }
             if (valid) {
                 code[i * n + k] = NavCode::make(z, d, kind, settled, m);
-                if (stepped) val[i * n + k] = L;
+                if (stepped) val[i * n + k] = __int_as_float(s1.p);  // for its rollout below
                 const int64_t pk = (int64_t)a * n + k;
                 if (pair_out) Ops::store(M, sprime, pk, s1);
                 if (T->r) T->r[pk] = r;
@@ -811,6 +906,22 @@ __device__ __forceinline__ void run_tile_nav(const HDX_CONST LeafTask *T, const 
             // mean step reward: sum of this 64-scenario chunk (lanes past n add 0)
             const float r_chunk = __ballot(r != 0.0f) ? wave_total(r) : 0.0f;
             if (lane == 0) chunk_r[i * nch + (base >> 6)] = r_chunk;
+        }
+        if (stepped) {
+            // a lane per scenario and action, the actions of a scenario side by side
+            const int per_wave = 64 / na, i = lane / na, c = lane - i * na;
+            for (int l0 = 0; l0 < 64 && base + l0 < n; l0 += per_wave) {
+                const int l = (l0 + i) & 63, kk = base + l;
+                const bool mine = i < per_wave && l0 + i < 64 && kk < n;
+                const int32_t p = mine ? __float_as_int(val[c * n + kk]) : 1 << 30;
+                int ns;
+                const float L = Ops::rollout_steps(M, RP, rows - lane + l, p, (uint32_t)__shfl((int)id, l, 64), depth + 1,
+                                                   R, na, c, ns);
+                if (mine) {
+                    val[c * n + kk] = L;
+                    code[c * n + kk] |= (uint32_t)ns << 17;
+                }
+            }
         }
         // the depth at which each walk's moves have all succeeded
         for (int from = 0; from < R && __ballot(need > 0);) {
@@ -1050,7 +1161,7 @@ __device__ __forceinline__ void run_tile_ped(const HDX_CONST LeafTask *T, unsign
     uint8_t *rc = (uint8_t *)(lds + Ly.rcode);
     int32_t *count = (int32_t *)(lds + Ly.misc);  // live scenarios, then rollout steps per action
     const int p2 = Ly.p2;
-    const MView M = make_view(T->model, nullptr);
+    const MView M = make_view(T->model);
     if (tid < 1 + A) count[tid] = 0;
     for (int i = tid; i < A * p2; i += nt)
         if ((i & (p2 - 1)) >= n) {
@@ -1115,7 +1226,7 @@ __device__ __forceinline__ void run_tile_ped(const HDX_CONST LeafTask *T, unsign
                 s = ped_advance(C, s, lv);
                 E.walk(C, j, id, (uint32_t)(depth - 1), RP.k0, RP.k1);
             }
-            const uint32_t see = E.look(C, s, car);
+            const uint32_t see = E.template look<A>(C, s, car);
             live &= !((lv > 0.0f) & ((see & 1u) != 0)) & !(s >= C.path_len);
         }
         if (valid) {
@@ -1141,10 +1252,10 @@ __device__ __forceinline__ void run_tile_ped(const HDX_CONST LeafTask *T, unsign
             s = ped_advance(C, s, lv);
             E.walk(C, j, id, (uint32_t)depth, RP.k0, RP.k1);
         }
-        uint32_t see = E.look(C, s, car);
+        uint32_t see = E.template look<A>(C, s, car);
         const bool hit0 = (lv > 0.0f) & ((see & 1u) != 0), there0 = s >= C.path_len;
         const int code = !live ? 0 : hit0 ? 2 : there0 ? 3 : 1;
-        bool alive = live & !hit0 & !there0;
+        const bool alive = live & !hit0 & !there0;
         const bool term = !alive;
         // the observation: a hash chained over the level and the floored positions, in pedestrian order
         uint64_t z = kPedTerminalObs;
@@ -1181,48 +1292,24 @@ __device__ __forceinline__ void run_tile_ped(const HDX_CONST LeafTask *T, unsign
                     }
             }
         }
-        // the rollouts of the three actions together
-        float value = 0.0f;
-        int steps = 0;
-        uint32_t fails = 0, pol = 0;
-        for (int t = 0; t < R && __ballot(alive); ++t) {
-            const int tg = t & (G - 1);
-            if (tg == 0) {
-                // the next G depths' failure words, one depth per lane
-                const uint32_t d = (uint32_t)(d0 + t + j);
-                fails = (uint32_t)(__ballot(philox(id, d, 0, kTagStep, RP.k0, RP.k1).x < C.fail_thr) >> first);
-                if (RP.policy == HDX_POLICY_RANDOM) {
-                    const uint32_t w = philox(id, d, 0, kTagPolicy, RP.k0, RP.k1).x % (uint32_t)A;
-                    const uint64_t b0 = __ballot(w & 1u), b1 = __ballot(w & 2u);
-                    pol = ((uint32_t)(b0 >> first) & 0xffffu) | ((uint32_t)(b1 >> first) << 16);
-                }
-            }
-            float change = (see & 256u) ? -1.0f : 1.0f;  // brake, or accelerate
-            if (RP.policy == HDX_POLICY_CONST) change = (float)(1 - RP.const_action);
-            if (RP.policy == HDX_POLICY_RANDOM)
-                change = (float)(1 - ((int)((pol >> tg) & 1u) | ((int)((pol >> (16 + tg)) & 1u) << 1)));
-            lv = ped_level(C, lv, change, ((fails >> tg) & 1u) != 0);
-            s = ped_advance(C, s, lv);
-            E.walk(C, j, id, (uint32_t)(d0 + t), RP.k0, RP.k1);
-            see = E.look(C, s, car);
-            const bool hit = (lv > 0.0f) & ((see & 1u) != 0), there = s >= C.path_len;
-            const float v = value + M.gpow_uniform(t) * (hit ? C.r_hit : there ? C.r_goal : C.r_step);
-            value = alive ? v : value;
-            steps += alive ? 1 : 0;
-            alive &= !(hit | there);
-        }
-        if (valid && j < A) {
+        const bool mine = valid && j < A;
+        const int64_t at = (int64_t)j * n + k;
+        if (mine) {
             zk[j * p2 + k] = z;
             pos[j * p2 + k] = (uint16_t)k;
             ub[j * n + k] = U;
-            lb[j * n + k] = value;
             rc[j * n + k] = (uint8_t)code;
             my_exp += j == 0 && live ? 1 : 0;
-            my_steps += steps;
-            const int64_t at = (int64_t)j * n + k;
             if (T->r) T->r[at] = code == 0 ? 0.0f : code == 1 ? C.r_step : code == 2 ? C.r_hit : C.r_goal;
             if (T->z) T->z[at] = z;
             if (T->U) T->U[at] = U;
+        }
+        // the rollouts of the three actions together
+        int steps;
+        const float value = ped_rollout<A>(M, C, RP, E, car, id, d0, R, s, lv, see, alive, steps);
+        if (mine) {
+            lb[j * n + k] = value;
+            my_steps += steps;
             if (T->L) T->L[at] = value;
         }
     }
@@ -1404,13 +1491,14 @@ __global__ __launch_bounds__(max_threads<MODE>()) void expand_args(const ArgPack
     run_mode<MODE, PM, true>(T, a, lds);
 }
 
-// Dynamic LDS of one workgroup for leaves of up to n_max scenarios (and, for
-// navigation, tiles of up to `pairs` pairs).
+// Dynamic LDS of one workgroup for leaves of up to n_max scenarios, tiles of up
+// to `pairs` values per scenario and action (tile_pairs).
 template <int MODE>
 uint32_t lds_bytes(int32_t n_max, int32_t pairs, int32_t threads) {
-    if (rock_mode<MODE>()) return make_rock_layout(n_max, MODE == 3).total;
+    if (rock_mode<MODE>()) return make_rock_layout(n_max, std::max(n_max, pairs), MODE == 3).total;
     if (MODE == 1) return make_ped_layout(n_max).total;
-    if (MODE == 2) return std::max(make_rock_layout(n_max, false).total, make_ped_layout(n_max).total);
+    if (MODE == 2)
+        return std::max(make_rock_layout(n_max, std::max(n_max, pairs), false).total, make_ped_layout(n_max).total);
     const uint32_t b = make_nav_layout((uint32_t)pairs, kNavActions, (uint32_t)(n_max + 63) / 64, (uint32_t)threads / 64,
                                        false).total;
     return std::min(b, (uint32_t)max_dynamic_lds());
@@ -1542,32 +1630,80 @@ __device__ __forceinline__ RolloutParams bounds_params(const BoundsArgs &A, cons
     return RP;
 }
 
+// RockSample, either model: a lane per state.
 template <class Ops>
-__global__ __launch_bounds__(256) void bounds_kernel(const BoundsArgs A) {
-    __shared__ float gpow_lds[kModelLdsFloats];
-    stage_gpow(A.model, gpow_lds);
-    __syncthreads();
+__global__ __launch_bounds__(256) void bounds_rocks(const BoundsArgs A) {
+    __shared__ float term[kRockTerms];  // 10 gamma^d
+    __shared__ uint32_t effects[kRockCells];
+    const MView M = make_view(A.model);
+    for (int d = threadIdx.x; d < kRockTerms; d += blockDim.x) term[d] = 10.0f * M.gpow(d);
+    stage_effects(M, effects);
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= A.n) return;
-    const MView M = make_view(A.model, gpow_lds);
+    const bool valid = k < A.n;
     typename Ops::State st;
-    Ops::load(M, A.states, k, st);
+    Ops::make_terminal(st);
+    if (valid) Ops::load(M, A.states, k, st);
     const RolloutParams RP = bounds_params(A, M);
-    int ns = 0;
-    A.U[k] = Ops::upper(M, st);
-    A.L[k] = rollout<Ops>(M, RP, st, A.ids[k], A.depths[k], ns);
+    const int d0 = valid ? A.depths[k] : 0, R = rollout_length(RP, d0);
+    int ns;
+    const float L = RP.policy == HDX_POLICY_DEFAULT
+                        ? Ops::rollout_east(M, st, R, ns)
+                        : rock_rollout<Ops>(M, effects, RP, valid ? A.ids[k] : 0u, d0, R, Ops::team(M, st), 1, 0, ns);
+    if (!valid) return;
+    A.U[k] = Ops::upper(M, st, [&](int d) { return term[d]; });
+    A.L[k] = L;
+    if (A.steps) A.steps[k] = ns;
+}
+
+// Driving: a state on G lanes, as in the tiles.
+template <int G, int PP>
+__global__ __launch_bounds__(256) void bounds_ped(const BoundsArgs A) {
+    const MView M = make_view(A.model);
+    const PedConst C = ped_const(M);
+    const RolloutParams RP = bounds_params(A, M);
+    const int64_t k = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G;
+    const bool valid = k < A.n;
+    const int j = lane_id() & (G - 1);
+    PedLanes<G, PP> E;
+    E.clear();
+    float s = 0.0f, lv = 0.0f;
+    bool live = false;
+    uint32_t id = 0;
+    int d0 = 0;
+    if (valid) {
+        s = A.states.s[k];
+        const int32_t car = A.states.car[k];
+        lv = (float)(car & 0xff);
+        live = !((car >> 8) & 1);
+        id = A.ids[k];
+        d0 = A.depths[k];
+#pragma unroll
+        for (int q = 0; q < PP; ++q) {
+            const int ped = q * G + j;
+            if (ped < C.n_peds) {
+                const int g = A.states.goal[ped * A.states.stride + k];
+                E.px[q] = A.states.px[ped * A.states.stride + k];
+                E.py[q] = A.states.py[ped * A.states.stride + k];
+                E.gx[q] = M.h->goal_x[g];
+                E.gy[q] = M.h->goal_y[g];
+            }
+        }
+    }
+    const uint32_t see = E.template look<1>(C, s, 0);
+    int ns;
+    const float L = ped_rollout<1>(M, C, RP, E, 0, id, d0, rollout_length(RP, d0), s, lv, see, live, ns);
+    if (!valid || j != 0) return;
+    A.U[k] = ped_upper(M, s, live ? 0 : 1);
+    A.L[k] = L;
     if (A.steps) A.steps[k] = ns;
 }
 
 // Navigation: the map's rows in LDS, the wavefront's lanes together.
 __global__ __launch_bounds__(256) void bounds_nav(const BoundsArgs A) {
-    __shared__ float gpow_lds[kModelLdsFloats];
     __shared__ uint32_t rows_lds[4 * kNavRowBytes / 4];
-    stage_gpow(A.model, gpow_lds);
-    __syncthreads();
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const bool valid = k < A.n;
-    const MView M = make_view(A.model, gpow_lds);
+    const MView M = make_view(A.model);
     NavOps::State st;
     NavOps::make_terminal(st);
     if (valid) NavOps::load(M, A.states, k, st);
@@ -1689,20 +1825,24 @@ hipError_t launch_sample(const SampleArgs *d_args, int32_t K, hipStream_t stream
 
 hipError_t launch_bounds(const BoundsArgs &args, int32_t kind, int32_t n_peds, hipStream_t stream) {
     const int threads = 256;
-    const int64_t blocks = (args.n + threads - 1) / threads;
-    if (blocks == 0) return hipSuccess;
+    if (args.n <= 0) return hipSuccess;
+    auto grid = [&](int lanes) { return dim3((unsigned)((args.n * lanes + threads - 1) / threads)); };  // lanes per state
+    const dim3 block(threads);
     if (kind == HDX_ROCKSAMPLE) {
-        hipLaunchKernelGGL(bounds_kernel<RsOps>, dim3((unsigned)blocks), dim3(threads), 0, stream, args);
+        hipLaunchKernelGGL(bounds_rocks<RsOps>, grid(1), block, 0, stream, args);
     } else if (kind == HDX_MARS) {
-        hipLaunchKernelGGL(bounds_kernel<MarsOps>, dim3((unsigned)blocks), dim3(threads), 0, stream, args);
+        hipLaunchKernelGGL(bounds_rocks<MarsOps>, grid(1), block, 0, stream, args);
     } else if (kind == HDX_NAV) {
-        hipLaunchKernelGGL(bounds_nav, dim3((unsigned)blocks), dim3(threads), 0, stream, args);
+        hipLaunchKernelGGL(bounds_nav, grid(1), block, 0, stream, args);
     } else if (n_peds <= 8) {
-        hipLaunchKernelGGL(bounds_kernel<PedOps<8>>, dim3((unsigned)blocks), dim3(threads), 0, stream, args);
+        constexpr int g = ped_lanes<8, false>();
+        hipLaunchKernelGGL((bounds_ped<g, 8 / g>), grid(g), block, 0, stream, args);
     } else if (n_peds <= 16) {
-        hipLaunchKernelGGL(bounds_kernel<PedOps<16>>, dim3((unsigned)blocks), dim3(threads), 0, stream, args);
+        constexpr int g = ped_lanes<16, false>();
+        hipLaunchKernelGGL((bounds_ped<g, 16 / g>), grid(g), block, 0, stream, args);
     } else {
-        hipLaunchKernelGGL(bounds_kernel<PedOps<32>>, dim3((unsigned)blocks), dim3(threads), 0, stream, args);
+        constexpr int g = ped_lanes<32, false>();
+        hipLaunchKernelGGL((bounds_ped<g, 32 / g>), grid(g), block, 0, stream, args);
     }
     return hipGetLastError();
 }

@@ -215,7 +215,7 @@ __device__ __forceinline__ uint4 features_of(const Args &A, const HDX_CONST Mode
             rock |= __shfl_xor(rock, 2, 64);
             rock |= __shfl_xor(rock, 4, 64);
             if (!RsOps::terminal(st)) {
-                RsOps::walk(make_view(A.model, nullptr), st, (int)row.action);
+                RsOps::walk(make_view(A.model), st, (int)row.action);
                 if (row.action == 4) st.w &= ~rock;  // sampled: bad from now on
             }
         }

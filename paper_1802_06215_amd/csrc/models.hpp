@@ -28,32 +28,25 @@ namespace hdx {
 
 // A model as the kernels see it: the header and the device tables through
 // the constant address space (never written by a kernel, so uniform
-// addresses become scalar loads), and the first kGpowLds discount powers
-// in LDS for per-lane lookups.
+// addresses become scalar loads).
 struct MView {
     const HDX_CONST ModelHdr *h;
     const HDX_CONST uint32_t *thr;
     const HDX_CONST float *gg;
     const HDX_CONST double *gs;
-    const float *gl;
-    __device__ float gpow_uniform(int j) const { return gg[j]; }
-    __device__ float gpow_lane(int j) const { return j < kGpowLds ? gl[j] : gg[j]; }
+    __device__ float gpow(int j) const { return gg[j]; }
     // 1 + gamma + ... + gamma^(j-1), j = 0..kHorizon
     __device__ double gpow_sum(int j) const { return gs[j]; }
     // gamma^j in FP64, j < kHorizon
     __device__ double gpow_exact(int j) const { return gs[j + 1] - gs[j]; }
-    // goal point coordinates, staged in LDS after the discount powers
-    __device__ float goal_x(int g) const { return gl[kGpowLds + g]; }
-    __device__ float goal_y(int g) const { return gl[kGpowLds + kMaxGoals + g]; }
 };
 
-__device__ __forceinline__ MView make_view(const DevModel *gm, const float *gpow_lds) {
+__device__ __forceinline__ MView make_view(const DevModel *gm) {
     MView v;
     v.h = (const HDX_CONST ModelHdr *)&gm->h;
     v.thr = (const HDX_CONST uint32_t *)gm->sense_thr_m1;
     v.gg = (const HDX_CONST float *)gm->gpow;
     v.gs = (const HDX_CONST double *)gm->gsum;
-    v.gl = gpow_lds;
     return v;
 }
 
@@ -67,22 +60,6 @@ __device__ __forceinline__ StatesPtr load_states(const HDX_CONST StatesPtr *s) {
     r.goal = s->goal;
     r.stride = s->stride;
     return r;
-}
-
-// Stage the first kGpowLds discount powers and the goal points of a model
-// into LDS (kModelLdsFloats floats in all; the caller synchronises
-// afterwards).
-constexpr int kModelLdsFloats = kGpowLds + 2 * kMaxGoals;
-__device__ __forceinline__ void stage_gpow(const DevModel *gm, float *gpow_lds) {
-    const HDX_CONST float *g = (const HDX_CONST float *)gm->gpow;
-    const HDX_CONST ModelHdr *h = (const HDX_CONST ModelHdr *)&gm->h;
-    for (int j = threadIdx.x; j < kGpowLds + 2 * kMaxGoals; j += blockDim.x) {
-        float v;
-        if (j < kGpowLds) v = g[j];
-        else if (j < kGpowLds + kMaxGoals) v = h->goal_x[j - kGpowLds];
-        else v = h->goal_y[j - kGpowLds - kMaxGoals];
-        gpow_lds[j] = v;
-    }
 }
 
 // a ^ b ^ c in one instruction.
@@ -124,6 +101,24 @@ struct RolloutParams {
     int32_t policy, const_action, max_steps, max_depth, n_actions;
 };
 
+// Steps a rollout from depth d0 may take.
+__device__ __forceinline__ int rollout_length(const RolloutParams &P, int d0) {
+    int n = P.max_steps;
+    if (P.max_depth >= 0 && P.max_depth - d0 < n) n = P.max_depth - d0;
+    return n > kHorizon ? kHorizon : n;  // the discount table's length
+}
+
+// x mod n for a uniform n >= 1: inv = floor((2^32 - 1) / n) gives the quotient
+// or one less.
+struct Modulus {
+    uint32_t n, inv;
+    __device__ __forceinline__ explicit Modulus(uint32_t n_) : n(n_), inv(0xffffffffu / n_) {}
+    __device__ __forceinline__ uint32_t operator()(uint32_t x) const {
+        const uint32_t r = x - __umulhi(x, inv) * n;
+        return min(r, r - n);  // r - n wraps when r < n
+    }
+};
+
 // Eq. 12 bound of the rock models from tabulated group sums: entry 16 g + m
 // of `tab0` (groups 0-3) or `tab1` (group 4) is the sum of group g's good
 // rocks' terms when the four quality bits of rocks 4g .. 4g+3 read m.  The
@@ -141,6 +136,45 @@ __device__ __forceinline__ float group_table_sum(uint32_t bits, float tab0, floa
     return (((((0.0f + t0) + t1) + t2) + t3) + t4);
 }
 
+// A cell x | y << 5 of the RockSample grid for robots that act step by step
+// (Robots): bit a is set if action a < 5 has an effect there (the move stays
+// on the grid or leaves it east; the sample meets a rock), the upper bits hold
+// 10 + the rock's index.  Column x = grid stands for having left: no effects.
+// A robot's step is then one table read and some twenty instructions, none of
+// them a branch, where comparing the cell with the rocks took a loop over them.
+__device__ __forceinline__ uint32_t cell_effects(const MView &M, int cell) {
+    const int n = M.h->grid, x = cell & 31, y = cell >> 5;
+    if (x >= n || y >= n) return 0u;
+    return (y + 1 < n ? 1u : 0u) | (y > 0 ? 2u : 0u) | 4u | (x > 0 ? 8u : 0u);
+}
+__device__ __forceinline__ uint32_t rock_effect(int rock) { return 16u | ((uint32_t)(10 + rock) << 25); }
+
+// K robots on the grid and the good rocks (bit 10 + i), stepped with actions of
+// the lane's own.
+template <int K>
+struct Robots {
+    uint32_t cell[K], good;
+    __device__ __forceinline__ bool any(int grid) const {
+        bool b = (cell[0] & 31u) != (uint32_t)grid;
+        if constexpr (K == 2) b |= (cell[1] & 31u) != (uint32_t)grid;
+        return b;
+    }
+    // Robot j's action a; returns its reward times g, given ten = 10 g.
+    __device__ __forceinline__ float hop(const uint32_t *effects, int grid, int j, int a, float ten) {
+        const uint32_t e = effects[cell[j]];
+        const int32_t acts = __builtin_amdgcn_sbfe((int)e, (uint32_t)a, 1u);  // -1: it has an effect
+        // byte a of the steps +32, -32, +1, -1 (0 for a sample)
+        const int32_t step = (int8_t)__builtin_amdgcn_perm(0u, 0xFF01E020u, (uint32_t)a);
+        cell[j] += (uint32_t)(step & acts);
+        const uint32_t bit = a == 4 ? (1u << (e >> 25)) & (uint32_t)acts : 0u;
+        // (and-not: for good ^= got, twice, this compiler emits a three-operand bit instruction with a wrong table)
+        const uint32_t got = good & bit;
+        good &= ~bit;
+        const bool left = (acts != 0) & ((cell[j] & 31u) == (uint32_t)grid);
+        return left | (got != 0) ? ten : bit != 0 ? -ten : 0.0f;
+    }
+};
+
 // ---------------------------------------------------------------------------
 // RockSample: one packed int32 word per scenario.
 // ---------------------------------------------------------------------------
@@ -148,68 +182,49 @@ struct RsOps {
     struct State {
         int32_t w;
     };
-    static constexpr bool kSplitRollout = true;  // small step: one rollout loop per policy
-
     __device__ static void load(const MView &, const StatesPtr &S, int64_t p, State &st) { st.w = S.w[p]; }
     __device__ static void make_terminal(State &st) { st.w = 1 << 30; }
     __device__ static void store(const MView &, const StatesPtr &S, int64_t p, const State &st) { S.w[p] = st.w; }
     __device__ static bool terminal(const State &st) { return (st.w >> 30) & 1; }
 
-    template <bool kObs>
-    __device__ static void step(const MView &M, State &st, int a, uint32_t id, uint32_t depth, uint32_t k0,
-                                uint32_t k1, float &r, uint64_t &z) {
-        int32_t w = st.w;
-        r = 0.0f;
-        z = 0;
-        if ((w >> 30) & 1) return;  // absorbing
-        int x = w & 31, y = (w >> 5) & 31;
-        const int n = M.h->grid;
-        int32_t term = 0;
-        if (a == 0) {
-            if (y + 1 < n) ++y;
-        } else if (a == 1) {
-            if (y > 0) --y;
-        } else if (a == 2) {
-            if (x + 1 == n) {
-                r = 10.0f;
-                term = 1 << 30;
-            } else {
-                ++x;
+    // Action a, the same for the wavefront; returns the reward.  A sense
+    // changes nothing, and terminal states are absorbing.
+    __device__ static float move(const MView &M, State &st, int a) {
+        if (terminal(st) || a > 4) return 0.0f;
+        if (a < 4) return walk(M, st, a) ? 10.0f : 0.0f;
+        float r = 0.0f;
+        for (int q = 0; q < M.h->n_rocks; ++q)
+            if (at(st, M.h->rock_x[q], M.h->rock_y[q])) {
+                const int32_t bit = 1 << (10 + q);
+                r = st.w & bit ? 10.0f : -10.0f;
+                st.w &= ~bit;
             }
-        } else if (a == 3) {
-            if (x > 0) --x;
-        } else if (a == 4) {
-            int i = -1;
-            for (int q = 0; q < M.h->n_rocks; ++q)
-                if (M.h->rock_x[q] == x && M.h->rock_y[q] == y) i = q;
-            if (i >= 0) {
-                if ((w >> (10 + i)) & 1) {
-                    r = 10.0f;
-                    w &= ~(1 << (10 + i));
-                } else {
-                    r = -10.0f;
-                }
-            }
-        } else if (kObs) {
-            // a sense leaves the state unchanged; its random reading is only
-            // drawn when the observation is wanted
-            const int i = a - 5;
-            const int dx = x - M.h->rock_x[i], dy = y - M.h->rock_y[i];
-            const uint32_t u = philox(id, depth, 0, kTagStep, k0, k1).x;
-            const int correct = u <= M.thr[(uint32_t)(dx * dx + dy * dy)];
-            const int truth = (w >> (10 + i)) & 1;
-            z = (correct ? truth : !truth) ? 1 : 2;
-        }
-        st.w = (w & ~0x3ff) | x | (y << 5) | term;
+        return r;
+    }
+    // The default rollout, moving east, of at most R steps.
+    __device__ static float rollout_east(const MView &M, const State &st, int R, int &steps) {
+        steps = 0;
+        if (terminal(st) || R <= 0) return 0.0f;
+        const int out = M.h->grid - 1 - (st.w & 31);
+        steps = R < out + 1 ? R : out + 1;
+        return out < R ? 10.0f * M.gpow(out) : 0.0f;
     }
 
-    __device__ static float upper(const MView &M, const State &st) {
-        if ((st.w >> 30) & 1) return 0.0f;
-        const int x = st.w & 31, y = (st.w >> 5) & 31;
+    // Bound of one state, summed as in upper_wave; term(d) = 10 gamma^d.
+    template <class Term>
+    __device__ static float upper(const MView &M, const State &st, Term term) {
+        if (terminal(st)) return 0.0f;
+        const int nr = M.h->n_rocks;
         float u = 0.0f;
-        for (int i = 0; i < M.h->n_rocks; ++i)
-            if ((st.w >> (10 + i)) & 1) u += 10.0f * M.gpow_lane(abs(x - M.h->rock_x[i]) + abs(y - M.h->rock_y[i]));
-        return u + 10.0f * M.gpow_lane(M.h->grid - 1 - x);
+        for (int g = 0; g < nr; g += 4) {
+            float p = 0.0f;
+            for (int i = g; i < g + 4 && i < nr; ++i) {
+                const float t = term(rock_distance(st, M.h->rock_x[i], M.h->rock_y[i]));
+                p = (st.w >> (10 + i)) & 1 ? p + t : p;
+            }
+            u = u + p;
+        }
+        return u + term(M.h->grid - 1 - (st.w & 31));
     }
 
     // Partial sums of the last common cell, kept across the rounds of a
@@ -237,19 +252,9 @@ struct RsOps {
         const int leader = __ffsll((unsigned long long)lv) - 1;
         const int xs = __builtin_amdgcn_readlane(x, leader), ys = __builtin_amdgcn_readlane(y, leader);
         const int nr = M.h->n_rocks;
-        const int ng = (nr + 3) >> 2;
         if (__ballot(live && (x != xs || y != ys)) != 0) {
             // cells differ: per-lane terms, discount powers read from the model table
-            if (!live) return 0.0f;
-            float u = 0.0f;
-            for (int g = 0; g < ng; ++g) {
-                float p = 0.0f;
-                for (int i = 4 * g; i < 4 * g + 4 && i < nr; ++i)
-                    if ((st.w >> (10 + i)) & 1)
-                        p = p + 10.0f * M.gg[abs(x - M.h->rock_x[i]) + abs(y - M.h->rock_y[i])];
-                u = u + p;
-            }
-            return u + 10.0f * M.gg[M.h->grid - 1 - x];
+            return upper(M, st, [&](int d) { return 10.0f * M.gpow(d); });
         }
         if (xs != wu.x || ys != wu.y) {
             const int lane = (int)__lane_id();
@@ -267,7 +272,7 @@ struct RsOps {
             }
             wu.tab0 = t0;
             wu.tab1 = t1;
-            wu.exit = 10.0f * M.gpow_uniform(M.h->grid - 1 - xs);
+            wu.exit = 10.0f * M.gpow(M.h->grid - 1 - xs);
             wu.x = xs;
             wu.y = ys;
         }
@@ -275,11 +280,17 @@ struct RsOps {
         return live ? u : 0.0f;
     }
 
-    __device__ static int default_action(const MView &, const State &) { return 2; }  // move east
-
     // A state as the tiles hold it (run_tile_rocks): the robot's cell, its
     // actions below 5, and what follows from a cell alone.
     static constexpr bool kTwo = false;
+    using Team = Robots<1>;
+    __device__ static Team team(const MView &M, const State &st) {
+        return {{terminal(st) ? (uint32_t)M.h->grid : (uint32_t)st.w & 0x3ffu}, (uint32_t)st.w};
+    }
+    // The reward of action a times g, given ten = 10 g.
+    __device__ static float act(const MView &M, const uint32_t *effects, Team &t, int a, float ten) {
+        return t.hop(effects, M.h->grid, 0, a, ten);
+    }
     __device__ static int cell(const State &st) { return st.w & 0x3ff; }
     __device__ static int cell_x(int c) { return c & 31; }
     __device__ static int cell_y(int c) { return (c >> 5) & 31; }
@@ -289,12 +300,7 @@ struct RsOps {
     __device__ static bool acting(const State &st) { return !terminal(st); }
     __device__ static bool ended(const State &st) { return terminal(st); }
     __device__ static void settle(State &) {}
-    __device__ static float mover(const MView &M, State &st, int b) {
-        float r;
-        uint64_t z;
-        step<false>(M, st, b, 0, 0, 0, 0, r, z);
-        return r;
-    }
+    __device__ static float mover(const MView &M, State &st, int b) { return move(M, st, b); }
     __device__ static int rock_distance(const State &st, int rx, int ry) {
         return abs((st.w & 31) - rx) + abs(((st.w >> 5) & 31) - ry);
     }
@@ -337,7 +343,6 @@ struct MarsOps {
     struct State {
         int32_t p, rk;
     };
-    static constexpr bool kSplitRollout = true;
     static constexpr int kGone0 = 20, kTerm = 30;
     static constexpr int kFar = 62;  // beyond any Manhattan distance on a 31 x 31 grid
 
@@ -355,40 +360,22 @@ struct MarsOps {
     }
     __device__ static bool terminal(const State &st) { return (st.p >> kTerm) & 1; }
 
-    // Robot J's own action b (numbered as in RockSample); returns its reward.
+    // Robot J's own action b (numbered as in RockSample), the same for the
+    // wavefront; returns its reward.
     template <int J, bool kObs>
     __device__ static float act(const MView &M, State &st, int b, uint32_t word, int &zj) {
         zj = 0;
-        int32_t p = st.p;
-        if ((p >> (kGone0 + J)) & 1) return 0.0f;  // this robot has left the map
-        constexpr int sh = 10 * J;
-        int x = (p >> sh) & 31, y = (p >> (sh + 5)) & 31;
-        const int n = M.h->grid;
+        if (gone<J>(st)) return 0.0f;  // this robot has left the map
+        if (b < 4) return walk_one<J>(M, st, b) ? 10.0f : 0.0f;
+        const int x = (st.p >> (10 * J)) & 31, y = (st.p >> (10 * J + 5)) & 31;
         float r = 0.0f;
-        if (b == 0) {
-            if (y + 1 < n) ++y;
-        } else if (b == 1) {
-            if (y > 0) --y;
-        } else if (b == 2) {
-            if (x + 1 == n) {
-                r = 10.0f;
-                p |= 1 << (kGone0 + J);
-            } else {
-                ++x;
-            }
-        } else if (b == 3) {
-            if (x > 0) --x;
-        } else if (b == 4) {
+        if (b == 4) {
             int i = -1;
             for (int q = 0; q < M.h->n_rocks; ++q)
                 if (M.h->rock_x[q] == x && M.h->rock_y[q] == y) i = q;
             if (i >= 0) {
-                if ((st.rk >> i) & 1) {
-                    r = 10.0f;
-                    st.rk &= ~(1 << i);
-                } else {
-                    r = -10.0f;
-                }
+                r = (st.rk >> i) & 1 ? 10.0f : -10.0f;
+                st.rk &= ~(1 << i);
             }
         } else if (kObs) {
             const int i = b - 5;
@@ -397,31 +384,30 @@ struct MarsOps {
             const int truth = (st.rk >> i) & 1;
             zj = (correct ? truth : !truth) ? 1 : 2;
         }
-        st.p = (p & ~(0x3ff << sh)) | ((x | (y << 5)) << sh);
         return r;
     }
 
-    template <bool kObs>
-    __device__ static void step(const MView &M, State &st, int a, uint32_t id, uint32_t depth, uint32_t k0,
-                                uint32_t k1, float &r, uint64_t &z) {
-        r = 0.0f;
-        z = 0;
-        if ((st.p >> kTerm) & 1) return;  // absorbing
+    // Joint action a, the same for the wavefront; returns the reward.
+    __device__ static float move(const MView &M, State &st, int a) {
+        if (terminal(st)) return 0.0f;  // absorbing
         const int per = 5 + M.h->n_rocks;
         const int a1 = (a * M.h->joint_inv) >> 16, a2 = a - a1 * per;  // a / per without a division
-        uint32_t w0 = 0, w1 = 0;
-        if (kObs && (a1 >= 5 || a2 >= 5)) {
-            // a sense's reading is only drawn when the observation is wanted
-            const uint4 u = philox(id, depth, 0, kTagStep, k0, k1);
-            w0 = u.x;
-            w1 = u.y;
-        }
-        int z1, z2;
-        const float r1 = act<0, kObs>(M, st, a1, w0, z1);
-        const float r2 = act<1, kObs>(M, st, a2, w1, z2);
-        r = r1 + r2;
-        z = (uint64_t)(3 * z1 + z2);
-        if (((st.p >> kGone0) & 3) == 3) st.p |= 1 << kTerm;
+        int z;
+        const float r1 = act<0, false>(M, st, a1, 0, z);
+        const float r2 = act<1, false>(M, st, a2, 0, z);
+        settle(st);
+        return r1 + r2;
+    }
+    // The default rollout, both robots moving east, of at most R steps.
+    __device__ static float rollout_east(const MView &M, const State &st, int R, int &steps) {
+        steps = 0;
+        if (terminal(st) || R <= 0) return 0.0f;
+        const int n1 = M.h->grid - 1;
+        const int o1 = gone<0>(st) ? -1 : n1 - (st.p & 31), o2 = gone<1>(st) ? -1 : n1 - ((st.p >> 10) & 31);
+        const int last = o1 > o2 ? o1 : o2;
+        steps = R < last + 1 ? R : last + 1;
+        const float v1 = o1 >= 0 && o1 < R ? 10.0f * M.gpow(o1) : 0.0f;
+        return v1 + (o2 >= 0 && o2 < R ? 10.0f * M.gpow(o2) : 0.0f);
     }
 
     // Distance from the nearer robot still on the map to cell (rx, ry).
@@ -434,20 +420,23 @@ struct MarsOps {
     // Every good rock sampled by the nearer robot on arrival, plus each
     // robot's exit reward at its shortest exit time (rocks summed within
     // groups of four in index order, the group sums in group order, then
-    // robot 1's exit, then robot 2's).
-    __device__ static float upper(const MView &M, const State &st) {
-        if ((st.p >> kTerm) & 1) return 0.0f;
-        float u = 0.0f;
+    // robot 1's exit, then robot 2's); term(d) = 10 gamma^d.
+    template <class Term>
+    __device__ static float upper(const MView &M, const State &st, Term term) {
+        if (terminal(st)) return 0.0f;
         const int nr = M.h->n_rocks;
-        for (int g = 0; g < (nr + 3) >> 2; ++g) {
+        float u = 0.0f;
+        for (int g = 0; g < nr; g += 4) {
             float p = 0.0f;
-            for (int i = 4 * g; i < 4 * g + 4 && i < nr; ++i)
-                if ((st.rk >> i) & 1) p = p + 10.0f * M.gg[near(st.p, M.h->rock_x[i], M.h->rock_y[i])];
+            for (int i = g; i < g + 4 && i < nr; ++i) {
+                const float t = term(near(st.p, M.h->rock_x[i], M.h->rock_y[i]));
+                p = (st.rk >> i) & 1 ? p + t : p;
+            }
             u = u + p;
         }
         const int n1 = M.h->grid - 1;
-        if (!((st.p >> kGone0) & 1)) u += 10.0f * M.gg[n1 - (st.p & 31)];
-        if (!((st.p >> (kGone0 + 1)) & 1)) u += 10.0f * M.gg[n1 - ((st.p >> 10) & 31)];
+        if (!gone<0>(st)) u += term(n1 - (st.p & 31));
+        if (!gone<1>(st)) u += term(n1 - ((st.p >> 10) & 31));
         return u;
     }
 
@@ -468,7 +457,7 @@ struct MarsOps {
         if (lv == 0) return 0.0f;
         const int leader = __ffsll((unsigned long long)lv) - 1;
         const int32_t ps = __builtin_amdgcn_readlane(st.p, leader);
-        if (__ballot(live && st.p != ps) != 0) return upper(M, st);
+        if (__ballot(live && st.p != ps) != 0) return upper(M, st, [&](int d) { return 10.0f * M.gpow(d); });
         const int nr = M.h->n_rocks;
         if (ps != wu.p) {
             const int lane = (int)__lane_id();
@@ -485,8 +474,8 @@ struct MarsOps {
             wu.tab0 = t0;
             wu.tab1 = t1;
             const int n1 = M.h->grid - 1;
-            wu.e0 = ((ps >> kGone0) & 1) ? 0.0f : 10.0f * M.gpow_uniform(n1 - (ps & 31));
-            wu.e1 = ((ps >> (kGone0 + 1)) & 1) ? 0.0f : 10.0f * M.gpow_uniform(n1 - ((ps >> 10) & 31));
+            wu.e0 = ((ps >> kGone0) & 1) ? 0.0f : 10.0f * M.gpow(n1 - (ps & 31));
+            wu.e1 = ((ps >> (kGone0 + 1)) & 1) ? 0.0f : 10.0f * M.gpow(n1 - ((ps >> 10) & 31));
             wu.p = ps;
         }
         float u = group_table_sum((uint32_t)st.rk, wu.tab0, wu.tab1);
@@ -495,14 +484,22 @@ struct MarsOps {
         return live ? u : 0.0f;
     }
 
-    __device__ static int default_action(const MView &M, const State &) {
-        return 2 * (5 + M.h->n_rocks) + 2;  // both robots move east
-    }
-
     // A state as the tiles hold it (run_tile_rocks), after robot 1's action
     // and with its reward: robot 2's actions below 5, and what follows from
     // the robots' row alone.
     static constexpr bool kTwo = true;
+    using Team = Robots<2>;
+    __device__ static Team team(const MView &M, const State &st) {
+        const uint32_t out = (uint32_t)M.h->grid;
+        return {{terminal(st) | gone<0>(st) ? out : (uint32_t)st.p & 0x3ffu,
+                 terminal(st) | gone<1>(st) ? out : (uint32_t)(st.p >> 10) & 0x3ffu},
+                (uint32_t)st.rk << 10};
+    }
+    __device__ static float act(const MView &M, const uint32_t *effects, Team &t, int a, float ten) {
+        const int a1 = (a * M.h->joint_inv) >> 16, a2 = a - a1 * (5 + M.h->n_rocks);
+        const float r1 = t.hop(effects, M.h->grid, 0, a1, ten);
+        return r1 + t.hop(effects, M.h->grid, 1, a2, ten);  // ten times -2..2, exact
+    }
     template <int J>
     __device__ static bool gone(const State &st) {
         return (st.p >> (kGone0 + J)) & 1;
@@ -537,17 +534,21 @@ struct MarsOps {
     __device__ static bool at(const State &st, int rx, int ry) {
         return ((st.p >> 10) & 31) == rx && ((st.p >> 15) & 31) == ry;
     }
-    __device__ static bool walk(const MView &M, State &st, int c) {
-        const int n = M.h->grid, x = (st.p >> 10) & 31, y = (st.p >> 15) & 31;
+    // Robot J's move c < 4 (any other c: none); true if it leaves the grid.
+    template <int J>
+    __device__ static bool walk_one(const MView &M, State &st, int c) {
+        constexpr int sh = 10 * J;
+        const int n = M.h->grid, x = (st.p >> sh) & 31, y = (st.p >> (sh + 5)) & 31;
         if (c == 2 && x + 1 == n) {
-            st.p |= 1 << (kGone0 + 1);
+            st.p |= 1 << (kGone0 + J);
             return true;
         }
         const int nx = c == 2 ? x + 1 : c == 3 && x > 0 ? x - 1 : x;
         const int ny = c == 0 && y + 1 < n ? y + 1 : c == 1 && y > 0 ? y - 1 : y;
-        st.p = (st.p & ~(0x3ff << 10)) | (nx << 10) | (ny << 15);
+        st.p = (st.p & ~(0x3ff << sh)) | (nx << sh) | (ny << (sh + 5));
         return false;
     }
+    __device__ static bool walk(const MView &M, State &st, int c) { return walk_one<1>(M, st, c); }
     __device__ static double exits(const MView &M, const State &st, const double *term) {
         const int n1 = M.h->grid - 1;
         return (gone<0>(st) ? 0.0 : term[n1 - (st.p & 31)]) + (gone<1>(st) ? 0.0 : term[n1 - ((st.p >> 10) & 31)]);
@@ -705,7 +706,7 @@ struct NavOps {
         return ax > ay ? ax : ay;
     }
     __device__ __forceinline__ static float bound_at(const MView &M, int d) {
-        return d == kNoDistance ? 0.0f : 20.0f * M.gpow_lane(d > 0 ? d - 1 : 1);
+        return d == kNoDistance ? 0.0f : 20.0f * M.gpow(d > 0 ? d - 1 : 1);
     }
     __device__ __forceinline__ static float upper(const MView &M, const State &st) { return bound_at(M, distance(M, st)); }
 
@@ -806,7 +807,8 @@ struct NavOps {
                                     int d0, int R, bool live, int &nsteps) {
         nsteps = 0;
         live = live && R > 0 && !terminal(st);
-        if (P.policy != HDX_POLICY_DEFAULT) return live ? rollout_steps(M, P, rows, st, id, d0, R, nsteps) : 0.0f;
+        if (P.policy != HDX_POLICY_DEFAULT)
+            return rollout_steps(M, P, rows, live ? st.p : 1 << 30, id, d0, R, 1, 0, nsteps);
         int m = 0, kind = kOver;
         if (live) kind = walk(M, rows, target_of(M, st), st.p & 15, (st.p >> 4) & 15, R, m);
         int need = live && kind != kOver ? m : 0, T = 0, base = 0;
@@ -828,19 +830,49 @@ struct NavOps {
         return walk_value(kind, T, R, [&](int j) { return M.gpow_sum(j); }, nsteps);
     }
 
-    // Step by step, for the constant and the random policy.
-    __device__ __forceinline__ static float rollout_steps(const MView &M, const RolloutParams &P, const uint32_t *rows, State st,
-                                          uint32_t id, int d0, int n_roll, int &nsteps) {
-        float value = 0.0f;
-        for (int j = 0; j < n_roll && !terminal(st); ++j) {
-            const uint32_t depth = (uint32_t)(d0 + j);
-            const int a = P.policy == HDX_POLICY_CONST
-                              ? P.const_action
-                              : (int)(philox(id, depth, 0, kTagPolicy, P.k0, P.k1).x % (uint32_t)P.n_actions);
-            float r;
-            move(M, rows, st, a, a == 0 ? 0u : philox(id, depth, 0, kTagStep, P.k0, P.k1).x, r);
-            value += M.gpow_uniform(j) * r;
-            ++nsteps;
+    // Step by step, for the constant and the random policy, in FP32 in step
+    // order.  Lanes come in groups of `width`, all of one scenario, whose random
+    // actions and failures are the same for whatever cell it is in: lane c of a
+    // group draws those of depths c, width + c, ... and the others read them
+    // from it.  p: the robot, rows: its scenario's map.  Called by all lanes of
+    // a wavefront, no branch but the loop's own.
+    __device__ __forceinline__ static float rollout_steps(const MView &M, const RolloutParams &P, const uint32_t *rows,
+                                                          int32_t p, uint32_t id, int d0, int R, int width, int c,
+                                                          int &steps) {
+        const Modulus pick((uint32_t)P.n_actions);
+        const int lane = (int)__lane_id(), first = lane - c;
+        const int n = M.h->grid, goal = M.h->nav_goal_x;
+        const uint64_t fail_thr = M.h->fail_thr;
+        int x = p & 15, y = (p >> 4) & 15;
+        bool alive = !((p >> 30) & 1);
+        float value = 0.0f, powers = 0.0f;  // lane i: gamma^i of the current 64 depths
+        int drawn = 0, at = width;
+        steps = 0;
+        for (int j = 0;; ++j, ++at) {
+            alive &= j < R;
+            if (!__ballot(alive)) break;
+            if ((j & 63) == 0) powers = M.gpow(min(j + lane, kHorizon - 1));
+            const float g = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(powers), j & 63));
+            if (at == width) {
+                const uint32_t depth = (uint32_t)(d0 + j + c);
+                drawn = P.const_action;
+                if (P.policy == HDX_POLICY_RANDOM) drawn = (int)pick(philox(id, depth, 0, kTagPolicy, P.k0, P.k1).x);
+                drawn |= (uint64_t)philox(id, depth, 0, kTagStep, P.k0, P.k1).x < fail_thr ? 16 : 0;
+                at = 0;
+            }
+            const int word = width > 1 ? __shfl(drawn, first + at, 64) : drawn;
+            const int a = word & 15, nx = x + dx(a), ny = y + dy(a);
+            const bool stays = a == 0, fails = word >= 16;
+            const uint32_t cells = (row(rows, ny & 15) << 1) | 0x20001u;  // the columns left of 0 and right of 15
+            const bool wall = (((cells >> (nx + 1)) & 1u) != 0) | ((uint32_t)ny >= (uint32_t)n);
+            const bool moves = !(stays | fails | wall), there = moves & (nx == goal) & (ny == n - 1);
+            x = moves ? nx : x;
+            y = moves ? ny : y;
+            const float r = stays ? -0.2f : there ? 20.0f : fails | !wall ? -0.1f : -1.0f;
+            const float v = value + g * r;
+            value = alive ? v : value;
+            steps += alive ? 1 : 0;
+            alive &= !there;
         }
         return value;
     }
@@ -989,20 +1021,25 @@ struct PedLanes {
             }
     }
     // What the lane's car at s sees: bit 0 a pedestrian within the collision
-    // radius, bit 8 one to brake for.  car: j mod 4, at most 2.
+    // radius, bit 8 one to brake for.  Three cars: lane j of every four owns
+    // car j (at most 2); one: all lanes own it (car 0).
+    template <int kCars>
     __device__ __forceinline__ uint32_t look(const PedConst &C, float s, int car) const {
-        float at[kPedActions];
-        at[0] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x00, 0xf, 0xf, true));
-        at[1] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x55, 0xf, 0xf, true));
-        at[2] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0xAA, 0xf, 0xf, true));
-        bool hit[kPedActions] = {}, brake[kPedActions] = {};
+        float at[kCars];
+        at[0] = s;
+        if constexpr (kCars == 3) {
+            at[0] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x00, 0xf, 0xf, true));
+            at[1] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x55, 0xf, 0xf, true));
+            at[2] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0xAA, 0xf, 0xf, true));
+        }
+        bool hit[kCars] = {}, brake[kCars] = {};
 #pragma unroll
         for (int q = 0; q < PP; ++q)
             if (q == 0 || q * G < C.n_peds) {
                 const float py2 = py[q] * py[q];
                 const bool beside = fabsf(py[q]) < 1.5f;
 #pragma unroll
-                for (int c = 0; c < kPedActions; ++c) {
+                for (int c = 0; c < kCars; ++c) {
                     const float dx = px[q] - at[c];
                     hit[c] |= dx * dx + py2 < C.coll_r2;
                     brake[c] |= beside & (dx >= 0.0f) & (dx <= 3.0f);
@@ -1010,7 +1047,7 @@ struct PedLanes {
             }
         int b = 0;
 #pragma unroll
-        for (int c = 0; c < kPedActions; ++c) b |= (hit[c] ? 1 << c : 0) | (brake[c] ? 256 << c : 0);
+        for (int c = 0; c < kCars; ++c) b |= (hit[c] ? 1 << c : 0) | (brake[c] ? 256 << c : 0);
         b |= __builtin_amdgcn_update_dpp(0, b, 0xB1, 0xf, 0xf, true);  // quad_perm 1,0,3,2
         b |= __builtin_amdgcn_update_dpp(0, b, 0x4E, 0xf, 0xf, true);  // quad_perm 2,3,0,1
         if (G >= 8) b |= __builtin_amdgcn_update_dpp(0, b, 0x141, 0xf, 0xf, true);   // row_half_mirror
@@ -1019,158 +1056,47 @@ struct PedLanes {
     }
 };
 
-template <int PM>
-struct PedOps {
-    struct State {
-        float s;
-        int32_t level, term;
-        float px[PM], py[PM];
-        int32_t goal[PM];
-    };
-    static constexpr bool kSplitRollout = false;  // large step: one loop keeps the code small
-
-    __device__ static void load(const MView &M, const StatesPtr &S, int64_t p, State &st) {
-        st.s = S.s[p];
-        const int32_t car = S.car[p];
-        st.level = car & 0xff;
-        st.term = (car >> 8) & 1;
-#pragma unroll
-        for (int j = 0; j < PM; ++j) {
-            if (j < M.h->n_peds) {
-                st.px[j] = S.px[j * S.stride + p];
-                st.py[j] = S.py[j * S.stride + p];
-                st.goal[j] = S.goal[j * S.stride + p];
-            } else {
-                st.px[j] = 0.0f;
-                st.py[j] = 0.0f;
-                st.goal[j] = 0;
-            }
-        }
-    }
-    __device__ static bool terminal(const State &st) { return st.term != 0; }
-
-    // One step of one scenario on one lane (the stand-alone bounds call).
-    template <bool kObs>
-    __device__ static void step(const MView &M, State &st, int a, uint32_t id, uint32_t depth, uint32_t k0,
-                                uint32_t k1, float &r, uint64_t &z) {
-        static_assert(!kObs, "observations come from the tiles");
-        z = 0;
-        r = 0.0f;
-        if (st.term) return;
-        const PedConst C = ped_const(M);
-        const uint4 u0 = philox(id, depth, 0, kTagStep, k0, k1);
-        const float level = ped_level(C, (float)st.level, (float)(1 - a), u0.x < C.fail_thr);
-        const float s_next = ped_advance(C, st.s, level);
-#pragma unroll
-        for (int j = 0; j < PM; ++j) {
-            if (j < M.h->n_peds) {
-                const uint4 u = philox(id, depth, (uint32_t)(j + 1), kTagStep, k0, k1);
-                move_ped(C, u, M.goal_x(st.goal[j]), M.goal_y(st.goal[j]), st.px[j], st.py[j]);
-            }
-        }
-        bool collided = false;
-        if (level > 0.0f) {
-#pragma unroll
-            for (int j = 0; j < PM; ++j) {
-                if (j < M.h->n_peds) {
-                    const float ddx = st.px[j] - s_next;
-                    const float d2 = ddx * ddx + st.py[j] * st.py[j];
-                    collided = collided || (d2 < M.h->coll_r2);
-                }
-            }
-        }
-        r = M.h->r_step;
-        if (collided) {
-            r = M.h->r_step + M.h->r_collision;
-            st.term = 1;
-        } else if (s_next >= M.h->path_len) {
-            r = M.h->r_step + M.h->r_goal;
-            st.term = 1;
-        }
-        st.s = s_next;
-        st.level = (int32_t)level;
-    }
-
-    __device__ static float upper(const MView &M, const State &st) { return ped_upper(M, st.s, st.term); }
-
-    __device__ static int default_action(const MView &M, const State &st) {
-        bool brake = false;
-#pragma unroll
-        for (int j = 0; j < PM; ++j) {
-            if (j < M.h->n_peds) {
-                const float ahead = st.px[j] - st.s;
-                brake = brake || (ahead >= 0.0f && ahead <= 3.0f && fabsf(st.py[j]) < 1.5f);
-            }
-        }
-        return brake ? 2 : 0;
-    }
-};
-
-// Steps a rollout from depth d0 may take.
-__device__ __forceinline__ int rollout_length(const RolloutParams &P, int d0) {
-    int n = P.max_steps;
-    if (P.max_depth >= 0 && P.max_depth - d0 < n) n = P.max_depth - d0;
-    return n > kHorizon ? kHorizon : n;  // the discount table's length
-}
-
-// Default-policy rollout from depth d0 (Eq. 13): discounted from d0, stops
-// at a terminal state or after min(max_steps, max_depth - d0) steps; the
-// tail value past the horizon is 0.  Accumulates in FP32 in step order.
-// The loop is compiled once per policy, so the policy is not re-decided at
-// every step and a model whose default action is a constant (RockSample's
-// move east) steps through that action's code alone.
-template <class Ops, int POL>
-__device__ __forceinline__ float rollout_loop(const MView &M, const RolloutParams &P, typename Ops::State st,
-                                              uint32_t id, int d0, int n_roll, int &nsteps) {
+// Rollouts of a group's cars from depth d0, of at most R steps (one car: each
+// group its own d0 and R): discounted from d0, ending with the car's episode, the tail
+// value past the horizon 0; accumulated in FP32 in step order.  see: what the
+// cars see at the start.  Called by all lanes of a wavefront.
+template <int kCars, int G, int PP>
+__device__ __forceinline__ float ped_rollout(const MView &M, const PedConst C, const RolloutParams P,
+                                             PedLanes<G, PP> &E, int car, uint32_t id, int d0, int R, float s, float lv,
+                                             uint32_t see, bool alive, int &steps) {
+    const int lane = (int)__lane_id(), j = lane & (G - 1), first = lane & ~(G - 1);
     float value = 0.0f;
-    for (int j = 0; j < n_roll; ++j) {
-        if (Ops::terminal(st)) break;
-        const uint32_t depth = (uint32_t)(d0 + j);
-        int a;
-        if (POL == HDX_POLICY_CONST) {
-            a = P.const_action;
-        } else if (POL == HDX_POLICY_RANDOM) {
-            a = (int)(philox(id, depth, 0, kTagPolicy, P.k0, P.k1).x % (uint32_t)P.n_actions);
-        } else {
-            a = Ops::default_action(M, st);
+    uint32_t fails = 0, pol = 0;
+    steps = 0;
+    for (int t = 0; kCars == 1 || t < R; ++t) {
+        if constexpr (kCars == 1) alive &= t < R;
+        if (!__ballot(alive)) break;
+        const int tg = t & (G - 1);
+        if (tg == 0) {
+            // the next G depths' failure words, one depth per lane
+            const uint32_t d = (uint32_t)(d0 + t + j);
+            fails = (uint32_t)(__ballot(philox(id, d, 0, kTagStep, P.k0, P.k1).x < C.fail_thr) >> first);
+            if (P.policy == HDX_POLICY_RANDOM) {
+                const uint32_t w = philox(id, d, 0, kTagPolicy, P.k0, P.k1).x % (uint32_t)kPedActions;
+                const uint64_t b0 = __ballot(w & 1u), b1 = __ballot(w & 2u);
+                pol = ((uint32_t)(b0 >> first) & 0xffffu) | ((uint32_t)(b1 >> first) << 16);
+            }
         }
-        float r;
-        uint64_t z;
-        Ops::template step<false>(M, st, a, id, depth, P.k0, P.k1, r, z);
-        value += M.gpow_uniform(j) * r;
-        ++nsteps;
+        float change = (see & 256u) ? -1.0f : 1.0f;  // brake, or accelerate
+        if (P.policy == HDX_POLICY_CONST) change = (float)(1 - P.const_action);
+        if (P.policy == HDX_POLICY_RANDOM)
+            change = (float)(1 - ((int)((pol >> tg) & 1u) | ((int)((pol >> (16 + tg)) & 1u) << 1)));
+        lv = ped_level(C, lv, change, ((fails >> tg) & 1u) != 0);
+        s = ped_advance(C, s, lv);
+        E.walk(C, j, id, (uint32_t)(d0 + t), P.k0, P.k1);
+        see = E.template look<kCars>(C, s, car);
+        const bool hit = (lv > 0.0f) & ((see & 1u) != 0), there = s >= C.path_len;
+        const float v = value + M.gpow(t) * (hit ? C.r_hit : there ? C.r_goal : C.r_step);
+        value = alive ? v : value;
+        steps += alive ? 1 : 0;
+        alive &= !(hit | there);
     }
     return value;
-}
-
-template <class Ops>
-__device__ __forceinline__ float rollout(const MView &M, const RolloutParams &P, typename Ops::State st,
-                                         uint32_t id, int d0, int &nsteps) {
-    const int n_roll = rollout_length(P, d0);
-    if (!Ops::kSplitRollout) {
-        float value = 0.0f;
-        for (int j = 0; j < n_roll; ++j) {
-            if (Ops::terminal(st)) break;
-            const uint32_t depth = (uint32_t)(d0 + j);
-            int a;
-            if (P.policy == HDX_POLICY_CONST) {
-                a = P.const_action;
-            } else if (P.policy == HDX_POLICY_RANDOM) {
-                a = (int)(philox(id, depth, 0, kTagPolicy, P.k0, P.k1).x % (uint32_t)P.n_actions);
-            } else {
-                a = Ops::default_action(M, st);
-            }
-            float r;
-            uint64_t z;
-            Ops::template step<false>(M, st, a, id, depth, P.k0, P.k1, r, z);
-            value += M.gpow_uniform(j) * r;
-            ++nsteps;
-        }
-        return value;
-    }
-    if (P.policy == HDX_POLICY_CONST) return rollout_loop<Ops, HDX_POLICY_CONST>(M, P, st, id, d0, n_roll, nsteps);
-    if (P.policy == HDX_POLICY_RANDOM) return rollout_loop<Ops, HDX_POLICY_RANDOM>(M, P, st, id, d0, n_roll, nsteps);
-    return rollout_loop<Ops, HDX_POLICY_DEFAULT>(M, P, st, id, d0, n_roll, nsteps);
 }
 
 }  // namespace hdx

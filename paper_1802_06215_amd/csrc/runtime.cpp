@@ -627,10 +627,10 @@ hdx_status validate_leaves(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t n_leave
 // kernels), so a tile takes as many as there are -- driving all three;
 // RockSample all, or robot 2's under one of robot 1; navigation all nine or as
 // many as LDS holds -- once the leaves alone fill the GPU.  Fewer leaves are
-// spread over more tiles, about one per CU, which shortens the longest one:
-// one leaf of 500 scenarios takes 7.8 us with its 20 actions on a tile each
-// and 11.0 on one tile; with 625 joint actions 12.7 us at three per tile, 16
-// at one and 20 at 25.
+// spread over more tiles, which shortens the longest one -- RockSample about two
+// per CU: one leaf of 500 scenarios takes 7.8 us with its 20 actions on a tile
+// each and 11.0 on one tile; 25 leaves of two with random rollouts 24 us at one
+// per tile and 27.6 at two.
 int32_t tile_actions(const hdx_leaf &L, int32_t row, int64_t call_tiles, int32_t n_cu) {
     switch (L.model->desc.kind) {
         case HDX_PEDNAV: return kPedActions;
@@ -639,7 +639,7 @@ int32_t tile_actions(const hdx_leaf &L, int32_t row, int64_t call_tiles, int32_t
                                     call_tiles >= kNavActions * (int64_t)n_cu ? kNavActions
                                     : call_tiles >= 3 * (int64_t)n_cu         ? 3
                                                                               : 1);
-        default: return (int32_t)std::min<int64_t>((call_tiles + n_cu - 1) / n_cu, row);
+        default: return (int32_t)std::min<int64_t>((call_tiles + 2 * n_cu - 1) / (2 * n_cu), row);
     }
 }
 
@@ -652,9 +652,11 @@ int32_t tile_action(const LeafTask &T, int32_t t) {
     return t / per_row * T.row_actions + t % per_row * T.tile_actions;
 }
 
-// Pairs of a tile as the navigation layout counts them.
+// Values a tile holds in LDS, as the layouts count them (Variant::pairs).
 int32_t tile_pairs(const LeafTask &T) {
-    return T.n * T.tile_actions * (T.policy != HDX_POLICY_DEFAULT ? 2 : 1);
+    const bool stepped = T.policy != HDX_POLICY_DEFAULT;
+    if (T.kind == HDX_NAV) return T.n * T.tile_actions * (stepped ? 2 : 1);
+    return rock_values(T.n, stepped);
 }
 
 // Descriptors (and tiles) of a call of call_tiles (leaf, action) pairs;
@@ -766,13 +768,23 @@ void hdx::plan_classes(const LeafTask *tasks, const int8_t *variant, Tile *tiles
     }
 }
 
+// Widest workgroup a group can use: its model's cap and what its leaves need.
+// RockSample tiles have work beside the scenarios (a successor's terms, the
+// children's places, counts of earlier chunks) that four wavefronts share.
+static int32_t useful_threads(const Variant &v) {
+    const int32_t least = v.mode == 0 || v.mode == 3 ? 256 : 64;
+    return std::min(variant_max_threads(v), std::max(least, pow2_at_least(std::max(variant_lanes(v, v.n_max), 1))));
+}
+
 Schedule hdx::class_default_schedule(const Variant &v, int64_t tiles, int32_t n_cu, bool few) {
     const int32_t lanes = pow2_at_least(std::max(variant_lanes(v, v.n_max), 1));
     Schedule s;
     s.persistent = s.xcd_remap = 0;
+    const bool rocks = v.mode == 0 || v.mode == 3;
     if (few) s.threads = lanes;
-    else s.threads = v.mode == 0 || v.mode == 3 ? std::min(lanes / 2, 256) : v.mode == 1 && tiles > n_cu ? lanes / 4 : lanes / 2;
-    s.threads = std::min(std::max(s.threads, 64), variant_max_threads(v));
+    else s.threads = rocks ? std::min(lanes / 2, 256) : v.mode == 1 && tiles > n_cu ? lanes / 4 : lanes / 2;
+    const int32_t least = rocks && tiles < 8 * (int64_t)n_cu ? 256 : 64;
+    s.threads = std::min(std::max(s.threads, least), variant_max_threads(v));
     return s;
 }
 
@@ -794,7 +806,7 @@ hipError_t hdx::launch_classes(const LeafTask *d_tasks, const Tile *d_tiles, Til
         vg.pairs = std::max(lds_pairs[g], plan.pairs[g]);
         vg.group = spread_lanes(vg, plan.count[g], plan.n_max[g], n_cu);
         // a workgroup no wider than the group's leaves need
-        const int need = std::min(variant_max_threads(vg), std::max(64, pow2_at_least(std::max(variant_lanes(vg, vg.n_max), 1))));
+        const int need = useful_threads(vg);
         Schedule sc = sch[g];
         if (sc.threads > need) sc.threads = need;
         const hipError_t e = launch_expand(d_tasks, d_tiles + plan.begin[g], d_queues + g, (int32_t)plan.count[g], vg,
@@ -1113,7 +1125,7 @@ Variant batch_variant(const hdx_batch *b, int g) {
 // Widest workgroup group g can use: its model's cap and its leaves' need.
 int32_t group_width_cap(const hdx_batch *b, int g) {
     const Variant v = batch_variant(b, g);
-    return std::min(variant_max_threads(v), std::max(64, pow2_at_least(std::max(variant_lanes(v, v.n_max), 1))));
+    return useful_threads(v);
 }
 
 bool same_schedule(const Schedule &a, const Schedule &b) {
