@@ -97,6 +97,7 @@ struct LeafTask {
     uint64_t *z;
     float *U, *L;
     int32_t *child_of;
+    unsigned char *work;  // driving: ped_work_bytes, or null
 };
 
 // A tile: actions [action, action + tile_actions) of a leaf (fewer at the
@@ -173,6 +174,10 @@ __host__ __device__ inline RockLayout make_rock_layout(int32_t n, int32_t values
     return L;
 }
 
+// Workspace of a driving leaf expanded and grouped by two kernels: per action
+// and scenario the observation, U, L, reward code and steps.
+inline size_t ped_work_bytes(int32_t n) { return (size_t)kPedActions * 24u * (size_t)n; }
+constexpr int kPedTile = 12;  // scenarios of a driving leaf that one workgroup expands and groups
 // Driving tile: the three actions of a leaf of n scenarios.
 //   zkey, pos   per action: (observation, position) pairs, sorted in place,
 //               p2 of them (a power of two)
@@ -256,6 +261,8 @@ struct Variant {
     // navigation: the largest (action, scenario) pairs of a tile, counted
     // twice where the rollouts run step by step; RockSample: rock_values
     int32_t pairs = 1;
+    // driving only: the leaves have workspaces
+    bool rows = false;
 };
 Variant pick_variant(int32_t has_rs, int32_t has_ped, int32_t ped_max, int32_t n_max, int32_t has_mars,
                      int32_t has_nav);
@@ -304,6 +311,7 @@ inline Variant group_variant(int g) {
 struct ClassPlan {
     int64_t begin[kGroups], count[kGroups];
     int32_t n_max[kGroups], pairs[kGroups];
+    bool rows = false;  // the driving leaves have workspaces
 };
 // Reorder tiles[0, n_tiles) by group, largest leaf first inside a group
 // (variant[leaf] is the leaf's model variant); fills plan.
@@ -331,8 +339,8 @@ hipError_t configure_expand_kernels();
 // pack stays under the 4 KB kernel-argument limit).
 constexpr int kArgLeaves = 11;
 struct ArgPack {
-    int32_t n_leaves, n_max, pairs;
-    int32_t tile_begin[kArgLeaves + 1];
+    int32_t n_leaves;
+    int32_t tile_end[kArgLeaves];
     LeafTask t[kArgLeaves];
 };
 hipError_t launch_expand_args(const ArgPack &pack, const Variant &v, const Schedule &sch, hipStream_t stream);

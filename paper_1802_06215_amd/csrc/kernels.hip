@@ -1133,43 +1133,38 @@ __device__ __forceinline__ void sort_actions(uint64_t *zk, uint16_t *pos, int p2
 //
 // What bounds it: instruction issue, two thirds of it the random blocks and
 // the walks of the pedestrians.  These are the same for the three actions, so
-// a tile is a whole leaf and takes each pedestrian's step once (one action
-// per tile took it three times).  Four lanes per scenario with up to PM / 4
-// pedestrians each leave the work of a scenario within a few percent of one
-// lane's (the cars are repeated on four lanes, their failure words drawn one
-// depth per lane) and give four times the wavefronts at a third of the
-// registers; 8 or 16 lanes (one or two pedestrians each) cost a quarter more
-// work and are for leaves too few or too small to fill the GPU otherwise.
-// Measured with 16 pedestrians and rollouts of 50 steps: 512 leaves of
-// 125..500 scenarios 0.50 ms (2.4e8 VALU instructions of a wavefront, 0.77 of
-// the issue slots) against 1.35-1.48 ms, one leaf of 500 scenarios 0.40
-// against 0.61 ms.
+// each pedestrian's step is taken once for all of them.  Four lanes per
+// scenario with up to PM / 4 pedestrians each leave the work of a scenario
+// within a few percent of one lane's (the cars are repeated on four lanes,
+// their failure words drawn one depth per lane) and give four times the
+// wavefronts at a third of the registers; 8 or 16 lanes (one or two pedestrians
+// each) cost a quarter more work and are for leaves too few or too small to
+// fill the GPU otherwise.
+//
+// A leaf's scenarios need each other only for the grouping.  Leaves enough to
+// fill the GPU take a workgroup each for the whole (run_tile_ped; 512 leaves of
+// 125..500 scenarios with 16 pedestrians and rollouts of 50 steps 0.51 ms, 2.4e8
+// VALU instructions of a wavefront, 0.77 of the issue slots).  Fewer leave CUs
+// idle and wait for the largest, and take two kernels: the scenarios of all
+// leaves on whatever CUs are free (ped_rows), which leave each pair's
+// observation, bounds, reward and steps in a workspace, and a workgroup per leaf
+// that groups them.  One leaf of 500 scenarios takes 56 us so and 362 whole, 341
+// of 31..500 beside as many RockSample leaves 465 and 622; at 512 leaves it
+// is 618 and 511.  Leaves of up to kPedTile scenarios, three wavefronts, stay on
+// one workgroup and one launch.
 //
 // Grouping: (observation, position) pairs of the three actions sorted in LDS
 // (the observations are hashes, most of them distinct), then one wavefront
 // per action walks the grouped order with segmented DPP scans over 64-aligned
 // chunks, a child's chunk partials added in chunk order.
-template <int G, int PP>
-__device__ __forceinline__ void run_tile_ped(const HDX_CONST LeafTask *T, unsigned char *lds) {
-    constexpr int A = kPedActions;
-    const int n = T->n, cap = T->cap;
-    const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id(), wid = tid >> 6, nw = nt >> 6;
-    const PedLayout Ly = make_ped_layout(n);
-    uint64_t *zk = (uint64_t *)(lds + Ly.zkey);
-    uint16_t *pos = (uint16_t *)(lds + Ly.pos);
-    float *ub = (float *)(lds + Ly.ub), *lb = (float *)(lds + Ly.lb);
-    uint8_t *rc = (uint8_t *)(lds + Ly.rcode);
-    int32_t *count = (int32_t *)(lds + Ly.misc);  // live scenarios, then rollout steps per action
-    const int p2 = Ly.p2;
-    const MView M = make_view(T->model);
-    if (tid < 1 + A) count[tid] = 0;
-    for (int i = tid; i < A * p2; i += nt)
-        if ((i & (p2 - 1)) >= n) {
-            zk[i] = kEmptyKey;
-            pos[i] = 0xFFFFu;
-        }
-    __syncthreads();
 
+// Scenarios begin + lane / G, + stride, ... of a leaf; a pair's results go to
+// sink.stepped and, after its rollout, sink.rolled.
+template <int G, int PP, class Sink>
+__device__ __forceinline__ void ped_scenarios(const HDX_CONST LeafTask *T, int begin, int stride, Sink &sink) {
+    constexpr int A = kPedActions;
+    const int n = T->n, lane = lane_id();
+    const MView M = make_view(T->model);
     RolloutParams RP;
     RP.k0 = T->k0;
     RP.k1 = T->k1;
@@ -1187,10 +1182,7 @@ __device__ __forceinline__ void run_tile_ped(const HDX_CONST LeafTask *T, unsign
     const bool pair_out = has_states(sprime);
     const int j = lane & (G - 1), first = lane & ~(G - 1);  // lane of the group, its first lane
     const int car = min(lane & 3, A - 1);                   // the action whose car this lane owns
-
-    // -- gather + update + expand + bounds + rollouts (Eq. 10, 12, 13) ------
-    int my_exp = 0, my_steps = 0;
-    for (int base = wid * (64 / G); base < n; base += nt / G) {
+    for (int base = begin; base < n; base += stride) {
         const int k = base + lane / G;
         const bool valid = k < n;
         PedLanes<G, PP> E;
@@ -1295,11 +1287,7 @@ __device__ __forceinline__ void run_tile_ped(const HDX_CONST LeafTask *T, unsign
         const bool mine = valid && j < A;
         const int64_t at = (int64_t)j * n + k;
         if (mine) {
-            zk[j * p2 + k] = z;
-            pos[j * p2 + k] = (uint16_t)k;
-            ub[j * n + k] = U;
-            rc[j * n + k] = (uint8_t)code;
-            my_exp += j == 0 && live ? 1 : 0;
+            sink.stepped(j, k, z, U, code);
             if (T->r) T->r[at] = code == 0 ? 0.0f : code == 1 ? C.r_step : code == 2 ? C.r_hit : C.r_goal;
             if (T->z) T->z[at] = z;
             if (T->U) T->U[at] = U;
@@ -1308,15 +1296,64 @@ __device__ __forceinline__ void run_tile_ped(const HDX_CONST LeafTask *T, unsign
         int steps;
         const float value = ped_rollout<A>(M, C, RP, E, car, id, d0, R, s, lv, see, alive, steps);
         if (mine) {
-            lb[j * n + k] = value;
-            my_steps += steps;
+            sink.rolled(j, k, value, steps);
             if (T->L) T->L[at] = value;
         }
     }
-    if (j < A && my_exp) atomicAdd(&count[0], my_exp);
-    if (j < A && my_steps) atomicAdd(&count[1 + j], my_steps);
-    __syncthreads();
+}
 
+// The tile of a leaf in LDS.
+struct PedTile {
+    uint64_t *zk;
+    uint16_t *pos;
+    float *ub, *lb;
+    uint8_t *rc;
+    int32_t *count;  // live scenarios, then rollout steps per action
+    int32_t n, p2;
+    int exp = 0, steps = 0;
+    __device__ __forceinline__ PedTile(int n_, unsigned char *lds) : n(n_) {
+        const PedLayout Ly = make_ped_layout(n);
+        zk = (uint64_t *)(lds + Ly.zkey);
+        pos = (uint16_t *)(lds + Ly.pos);
+        ub = (float *)(lds + Ly.ub);
+        lb = (float *)(lds + Ly.lb);
+        rc = (uint8_t *)(lds + Ly.rcode);
+        count = (int32_t *)(lds + Ly.misc);
+        p2 = Ly.p2;
+    }
+    __device__ __forceinline__ void clear() {  // then a barrier
+        const int tid = threadIdx.x, nt = blockDim.x;
+        if (tid < 1 + kPedActions) count[tid] = 0;
+        for (int i = tid; i < kPedActions * p2; i += nt)
+            if ((i & (p2 - 1)) >= n) {
+                zk[i] = kEmptyKey;
+                pos[i] = 0xFFFFu;
+            }
+    }
+    __device__ __forceinline__ void stepped(int a, int k, uint64_t z, float U, int code) {
+        zk[a * p2 + k] = z;
+        pos[a * p2 + k] = (uint16_t)k;
+        ub[a * n + k] = U;
+        rc[a * n + k] = (uint8_t)code;
+        exp += a == 0 && code != 0 ? 1 : 0;
+    }
+    __device__ __forceinline__ void rolled(int a, int k, float L, int ns) {
+        lb[a * n + k] = L;
+        steps += ns;
+    }
+};
+
+// Sort and children of a filled tile.
+__device__ __forceinline__ void group_children(const HDX_CONST LeafTask *T, const PedTile &tile) {
+    constexpr int A = kPedActions;
+    const int n = tile.n, cap = T->cap, p2 = tile.p2;
+    const int lane = lane_id(), wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    uint64_t *const zk = tile.zk;
+    uint16_t *const pos = tile.pos;
+    const float *ub = tile.ub, *lb = tile.lb;
+    const uint8_t *rc = tile.rc;
+    const int32_t *count = tile.count;
+    const PedConst C = ped_const(make_view(T->model));
     // -- observations ascending, positions ascending within one ----------------
     sort_actions(zk, pos, p2);
 
@@ -1382,6 +1419,81 @@ __device__ __forceinline__ void run_tile_ped(const HDX_CONST LeafTask *T, unsign
     __syncthreads();  // LDS is reused by the next tile
 }
 
+
+// A whole leaf on one workgroup.
+template <int G, int PP>
+__device__ __forceinline__ void run_tile_ped(const HDX_CONST LeafTask *T, unsigned char *lds) {
+    const int wid = threadIdx.x >> 6, j = lane_id() & (G - 1);
+    PedTile tile(T->n, lds);
+    tile.clear();
+    __syncthreads();
+    ped_scenarios<G, PP>(T, wid * (64 / G), blockDim.x / G, tile);
+    if (j < kPedActions && tile.exp) atomicAdd(&tile.count[0], tile.exp);
+    if (j < kPedActions && tile.steps) atomicAdd(&tile.count[1 + j], tile.steps);
+    __syncthreads();
+    group_children(T, tile);
+}
+
+// A leaf's pairs between the two kernels, in its workspace: observation, U, L,
+// reward code and steps.
+struct PedEntries {
+    uint64_t *z;
+    float *u, *l;
+    int32_t *code, *steps;
+    int32_t n;
+    __device__ __forceinline__ explicit PedEntries(const HDX_CONST LeafTask *T) : n(T->n) {
+        const int pairs = kPedActions * n;
+        z = (uint64_t *)T->work;
+        u = (float *)(z + pairs);
+        l = u + pairs;
+        code = (int32_t *)(l + pairs);
+        steps = code + pairs;
+    }
+    __device__ __forceinline__ void stepped(int a, int k, uint64_t z_, float U, int code_) {
+        const int at = a * n + k;
+        z[at] = z_;
+        u[at] = U;
+        code[at] = code_;
+    }
+    __device__ __forceinline__ void rolled(int a, int k, float L, int ns) {
+        const int at = a * n + k;
+        l[at] = L;
+        steps[at] = ns;
+    }
+};
+
+// The scenarios of workgroup `chunk` of a leaf.
+template <int G, int PP>
+__device__ __forceinline__ void ped_chunk(const HDX_CONST LeafTask *T, int chunk) {
+    const int begin = chunk * (int)(blockDim.x / G) + (int)(threadIdx.x >> 6) * (64 / G);
+    if (begin >= T->n) return;
+    PedEntries entries(T);
+    ped_scenarios<G, PP>(T, begin, T->n, entries);  // one round
+}
+
+// The children of a leaf whose scenarios are in its workspace.
+__device__ __forceinline__ void run_tile_ped_grouping(const HDX_CONST LeafTask *T, unsigned char *lds) {
+    PedTile tile(T->n, lds);
+    tile.clear();
+    __syncthreads();
+    const PedEntries E(T);
+    for (int a = 0; a < kPedActions; ++a) {
+        tile.exp = tile.steps = 0;
+        for (int k = threadIdx.x; k < tile.n; k += blockDim.x) {
+            const int at = a * tile.n + k;
+            tile.stepped(a, k, E.z[at], E.u[at], E.code[at]);
+            tile.rolled(a, k, E.l[at], E.steps[at]);
+        }
+        const int exp = wave_total_i(tile.exp), steps = wave_total_i(tile.steps);
+        if (lane_id() == 0) {
+            if (exp) atomicAdd(&tile.count[0], exp);
+            if (steps) atomicAdd(&tile.count[1 + a], steps);
+        }
+    }
+    __syncthreads();
+    group_children(T, tile);
+}
+
 __device__ __forceinline__ int remap_xcd(int b, int grid) {
     // workgroups are dealt to the 8 XCDs round-robin; give each XCD a
     // contiguous run of tiles so the tiles of one leaf share an L2
@@ -1390,7 +1502,8 @@ __device__ __forceinline__ int remap_xcd(int b, int grid) {
 }
 
 // MODE 0: RockSample only; 1: crowd driving only; 2: both; 3: multi-agent
-// RockSample only; 4: navigation only.  Workgroups of RockSample and driving
+// RockSample only; 4: navigation only; 5: crowd driving, the grouping of leaves
+// whose scenarios ped_rows has expanded.  Workgroups of RockSample and driving
 // are capped at 512 lanes; navigation (94 registers) takes up to 1024,
 // because one large leaf's LDS carve-up leaves room for one workgroup per CU.
 template <int MODE>
@@ -1425,6 +1538,8 @@ __device__ __forceinline__ void run_mode(const HDX_CONST LeafTask *T, int a, uns
         run_tile_rocks<RsOps>(T, a, tile_width<MODE>(T, a), lds);
     } else if constexpr (MODE == 1 || MODE == 2) {
         run_tile_ped<ped_lanes<PM, kSpread>(), PM / ped_lanes<PM, kSpread>()>(T, lds);
+    } else if constexpr (MODE == 5) {
+        run_tile_ped_grouping(T, lds);
     }
 }
 
@@ -1480,9 +1595,9 @@ __global__ __launch_bounds__(max_threads<MODE>()) void expand_args(const ArgPack
     // it, so a single leaf takes none
     const int n_leaves = P->n_leaves, t = (int)blockIdx.x;
     int i = 0;
-    while (i + 1 < n_leaves && t >= P->tile_begin[i + 1]) ++i;
+    while (i + 1 < n_leaves && t >= P->tile_end[i]) ++i;
     const HDX_CONST LeafTask *T = &P->t[i];
-    const int local = i > 0 ? t - P->tile_begin[i] : t;
+    const int local = i > 0 ? t - P->tile_end[i - 1] : t;
     int a = local * T->tile_actions;
     if (MODE == 3) {
         const int per_row = (T->row_actions + T->tile_actions - 1) / T->tile_actions, row = local / per_row;
@@ -1491,12 +1606,39 @@ __global__ __launch_bounds__(max_threads<MODE>()) void expand_args(const ArgPack
     run_mode<MODE, PM, true>(T, a, lds);
 }
 
+// Driving, the scenarios of many leaves: `chunks` workgroups per tile of the
+// queue (a tile is a leaf), those past the leaf's scenarios ending at once.  Two
+// pedestrians per lane where the tiles take four: shorter wavefronts, five of
+// them per SIMD (341 leaves of 31..500 scenarios 429 us, 491 with four).
+constexpr int kPedRowThreads = 256;
+template <int PM, bool kSpread>
+constexpr int row_lanes() { return !kSpread && PM > 8 ? PM / 2 < 16 ? PM / 2 : 16 : ped_lanes<PM, kSpread>(); }
+template <int PM, bool kSpread>
+__global__ __launch_bounds__(kPedRowThreads, 5) void ped_rows(const LeafTask *tasks, const Tile *tiles,
+                                                           const TileQueue *queue, int32_t chunks) {
+    const int t = (int)blockIdx.x / chunks;
+    if (t >= __builtin_amdgcn_readfirstlane(queue->n_tiles)) return;
+    const HDX_CONST LeafTask *T = (const HDX_CONST LeafTask *)(tasks + ((const HDX_CONST Tile *)(tiles + t))->leaf);
+    ped_chunk<row_lanes<PM, kSpread>(), PM / row_lanes<PM, kSpread>()>(T, (int)blockIdx.x - t * chunks);
+}
+
+// The same of a few leaves in the kernel arguments; blockIdx.y selects the leaf.
+template <int PM>
+__global__ __launch_bounds__(kPedRowThreads, 4) void ped_rows_args(const ArgPack pack) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const HDX_CONST ArgPack *P = (const HDX_CONST ArgPack *)__builtin_amdgcn_kernarg_segment_ptr();
+#else
+    const ArgPack *P = &pack;
+#endif
+    ped_chunk<row_lanes<PM, true>(), PM / row_lanes<PM, true>()>(&P->t[blockIdx.y], (int)blockIdx.x);
+}
+
 // Dynamic LDS of one workgroup for leaves of up to n_max scenarios, tiles of up
 // to `pairs` values per scenario and action (tile_pairs).
 template <int MODE>
 uint32_t lds_bytes(int32_t n_max, int32_t pairs, int32_t threads) {
     if (rock_mode<MODE>()) return make_rock_layout(n_max, std::max(n_max, pairs), MODE == 3).total;
-    if (MODE == 1) return make_ped_layout(n_max).total;
+    if (MODE == 1 || MODE == 5) return make_ped_layout(n_max).total;
     if (MODE == 2)
         return std::max(make_rock_layout(n_max, std::max(n_max, pairs), false).total, make_ped_layout(n_max).total);
     const uint32_t b = make_nav_layout((uint32_t)pairs, kNavActions, (uint32_t)(n_max + 63) / 64, (uint32_t)threads / 64,
@@ -1519,13 +1661,12 @@ hipError_t configure_t() {
 }
 
 template <int MODE, int PM>
-hipError_t launch_args_t(const ArgPack &pack, const Schedule &sch, hipStream_t stream) {
-    const int grid = pack.tile_begin[pack.n_leaves];
+hipError_t launch_args_t(const ArgPack &pack, const Variant &v, const Schedule &sch, hipStream_t stream) {
+    const int grid = pack.tile_end[pack.n_leaves - 1];
     if (grid < 1) return hipSuccess;
     const int threads = sch.threads > max_threads<MODE>() ? max_threads<MODE>() : sch.threads;
     hipLaunchKernelGGL((expand_args<MODE, PM>), dim3(grid), dim3(threads),
-                       lds_bytes<MODE>(pack.n_max, pack.pairs, threads), stream,
-                       pack);
+                       lds_bytes<MODE>(v.n_max, v.pairs, threads), stream, pack);
     return hipGetLastError();
 }
 
@@ -1540,6 +1681,32 @@ hipError_t launch_expand_t(const LeafTask *d_tasks, const Tile *d_tiles, TileQue
     hipLaunchKernelGGL((expand_tiles<MODE, PM, kSpread>), dim3(grid), dim3(threads),
                        lds_bytes<MODE>(n_max, pairs, threads), stream, d_tasks, d_tiles, d_queue, sch.persistent > 0 ? 1 : 0, sch.xcd_remap);
     return hipGetLastError();
+}
+
+// Workgroups of ped_rows for a leaf of n scenarios.
+template <int PM, bool kSpread>
+int ped_chunks(int32_t n) {
+    return (n * row_lanes<PM, kSpread>() + kPedRowThreads - 1) / kPedRowThreads;
+}
+
+template <int PM, bool kSpread>
+hipError_t launch_ped_t(const LeafTask *d_tasks, const Tile *d_tiles, TileQueue *d_queue, int32_t n_tiles, int32_t n_max,
+                        const Schedule &sch, int32_t n_cu, hipStream_t stream) {
+    const int chunks = ped_chunks<PM, kSpread>(n_max);
+    if (n_tiles < 1) return hipSuccess;
+    if ((int64_t)chunks * n_tiles > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((ped_rows<PM, kSpread>), dim3((unsigned)(chunks * n_tiles)), dim3(kPedRowThreads), 0, stream,
+                       d_tasks, d_tiles, d_queue, chunks);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? launch_expand_t<5, 1>(d_tasks, d_tiles, d_queue, n_tiles, n_max, 0, sch, n_cu, stream) : e;
+}
+
+template <int PM>
+hipError_t launch_ped_args_t(const ArgPack &pack, const Variant &v, const Schedule &sch, hipStream_t stream) {
+    hipLaunchKernelGGL((ped_rows_args<PM>), dim3(ped_chunks<PM, true>(v.n_max), pack.n_leaves), dim3(kPedRowThreads),
+                       0, stream, pack);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? launch_args_t<5, 1>(pack, v, sch, stream) : e;
 }
 
 // ---------------------------------------------------------------------------
@@ -1783,6 +1950,7 @@ hipError_t configure_expand_kernels() {
     if (e == hipSuccess) e = configure_t<1, 8>();
     if (e == hipSuccess) e = configure_t<1, 16>();
     if (e == hipSuccess) e = configure_t<1, 32>();
+    if (e == hipSuccess) e = configure_t<5, 1>();
     if (e == hipSuccess) e = configure_t<2, 8>();
     if (e == hipSuccess) e = configure_t<2, 16>();
     if (e == hipSuccess) e = configure_t<2, 32>();
@@ -1795,22 +1963,33 @@ hipError_t launch_expand(const LeafTask *d_tasks, const Tile *d_tiles, TileQueue
                          const Variant &v, const Schedule &sch, int32_t n_cu, hipStream_t stream) {
 #define HDX_LAUNCH(M, P) launch_expand_t<M, P>(d_tasks, d_tiles, d_queue, n_tiles, v.n_max, v.pairs, sch, n_cu, stream)
 #define HDX_LAUNCH_G(P) launch_expand_t<1, P, true>(d_tasks, d_tiles, d_queue, n_tiles, v.n_max, v.pairs, sch, n_cu, stream)
+#define HDX_LAUNCH_ROWS(P, G) launch_ped_t<P, G>(d_tasks, d_tiles, d_queue, n_tiles, v.n_max, sch, n_cu, stream)
     if (v.mode == 0) return HDX_LAUNCH(0, 1);
     if (v.mode == 3) return HDX_LAUNCH(3, 1);
     if (v.mode == 4) return HDX_LAUNCH(4, 1);
-    if (v.mode == 1 && v.group)
-        return v.pm == 8 ? HDX_LAUNCH_G(8) : v.pm == 16 ? HDX_LAUNCH_G(16) : HDX_LAUNCH_G(32);
+    if (v.rows && v.n_max > kPedTile) {
+        if (v.group)
+            return v.pm == 8 ? HDX_LAUNCH_ROWS(8, true) : v.pm == 16 ? HDX_LAUNCH_ROWS(16, true) : HDX_LAUNCH_ROWS(32, true);
+        return v.pm == 8 ? HDX_LAUNCH_ROWS(8, false) : v.pm == 16 ? HDX_LAUNCH_ROWS(16, false) : HDX_LAUNCH_ROWS(32, false);
+    }
+    if (v.group) return v.pm == 8 ? HDX_LAUNCH_G(8) : v.pm == 16 ? HDX_LAUNCH_G(16) : HDX_LAUNCH_G(32);
     return v.pm == 8 ? HDX_LAUNCH(1, 8) : v.pm == 16 ? HDX_LAUNCH(1, 16) : HDX_LAUNCH(1, 32);
 #undef HDX_LAUNCH_G
+#undef HDX_LAUNCH_ROWS
 #undef HDX_LAUNCH
 }
 
 hipError_t launch_expand_args(const ArgPack &pack, const Variant &v, const Schedule &sch, hipStream_t stream) {
-#define HDX_LAUNCH(M, P) launch_args_t<M, P>(pack, sch, stream)
+#define HDX_LAUNCH(M, P) launch_args_t<M, P>(pack, v, sch, stream)
     if (v.mode == 0) return HDX_LAUNCH(0, 1);
     if (v.mode == 3) return HDX_LAUNCH(3, 1);
     if (v.mode == 4) return HDX_LAUNCH(4, 1);
-    if (v.mode == 1) return v.pm == 8 ? HDX_LAUNCH(1, 8) : v.pm == 16 ? HDX_LAUNCH(1, 16) : HDX_LAUNCH(1, 32);
+    if (v.mode == 1 && !(v.rows && v.n_max > kPedTile))
+        return v.pm == 8 ? HDX_LAUNCH(1, 8) : v.pm == 16 ? HDX_LAUNCH(1, 16) : HDX_LAUNCH(1, 32);
+    if (v.mode == 1)
+        return v.pm == 8    ? launch_ped_args_t<8>(pack, v, sch, stream)
+               : v.pm == 16 ? launch_ped_args_t<16>(pack, v, sch, stream)
+                            : launch_ped_args_t<32>(pack, v, sch, stream);
     return v.pm == 8 ? HDX_LAUNCH(2, 8) : v.pm == 16 ? HDX_LAUNCH(2, 16) : HDX_LAUNCH(2, 32);
 #undef HDX_LAUNCH
 }

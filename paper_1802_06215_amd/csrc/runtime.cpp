@@ -34,6 +34,19 @@ struct Slot {
     int64_t cap_tasks = 0, cap_tiles = 0;
     hipEvent_t done = nullptr;
     hipEvent_t fork = nullptr, join[kGroups] = {};  // launch groups run side by side
+    unsigned char *work = nullptr;                  // driving leaves' workspaces
+    size_t cap_work = 0;
+    bool used = false;
+};
+
+// Workspaces of the driving leaves of a call in the kernel arguments, made at
+// set-up and large enough for any such call.  A call takes the next one and its
+// stream waits for the call that had it before.
+constexpr int kPedSlots = 8;
+constexpr size_t kPedSlotBytes = (size_t)kArgLeaves * (size_t)kPedActions * 24u * HDX_MAX_LEAF_SCENARIOS;
+struct PedSlot {
+    unsigned char *d = nullptr;
+    hipEvent_t done = nullptr;
     bool used = false;
 };
 
@@ -108,6 +121,8 @@ struct hdx_ctx {
     bool sched_fixed = false;
     ArgSlot arg_slots[kArgSlots];
     int next_arg_slot = 0;
+    PedSlot ped_slots[kPedSlots];
+    int next_ped_slot = 0;
     // expansion without allocation: the device's fixed scratch array (its
     // address from hipGetSymbolAddress), pinned host staging and events made
     // here at set-up, and fixed host arrays for planning
@@ -183,6 +198,12 @@ hdx_status hdx_init(int32_t device, hdx_ctx **out) {
             hdx_fini(ctx);
             return HDX_E_NOMEM;
         }
+    for (auto &p : ctx->ped_slots)
+        if (hipMalloc((void **)&p.d, kPedSlotBytes) != hipSuccess ||
+            hipEventCreateWithFlags(&p.done, hipEventDisableTiming) != hipSuccess) {
+            hdx_fini(ctx);
+            return HDX_E_NOMEM;
+        }
     // set-up of hdx_expand_leaf_noalloc: the scratch's device address, host
     // staging and events, so that the call itself allocates nothing
     ctx->err.reserve(kErrCap);
@@ -216,12 +237,20 @@ hdx_status hdx_fini(hdx_ctx *ctx) {
         if (s.d_tiles) hipFree(s.d_tiles);
         if (s.d_queue) hipFree(s.d_queue);
         if (s.h_queue) hipHostFree(s.h_queue);
+        if (s.work) hipFree(s.work);
         if (s.done) hipEventDestroy(s.done);
         destroy_events(&s.fork, s.join);
     }
     if (ctx->na_done) {
         hipEventSynchronize(ctx->na_done);
         hipEventDestroy(ctx->na_done);
+    }
+    for (auto &p : ctx->ped_slots) {
+        if (p.done) {
+            hipEventSynchronize(p.done);
+            hipEventDestroy(p.done);
+        }
+        if (p.d) hipFree(p.d);
     }
     for (auto &a : ctx->arg_slots) {
         if (a.done) {
@@ -711,6 +740,47 @@ int64_t pack_leaves(const hdx_leaf *leaves, int32_t n_leaves, LeafTask *tasks, T
 
 }  // namespace
 
+// Places of the driving leaves' workspaces from `base` on (null: none);
+// returns their bytes.
+static size_t place_ped_work(LeafTask *tasks, int32_t n_leaves, unsigned char *base) {
+    size_t at = 0;
+    for (int32_t i = 0; i < n_leaves; ++i) {
+        if (tasks[i].kind != HDX_PEDNAV) continue;
+        tasks[i].work = base ? base + at : nullptr;
+        at += ped_work_bytes(tasks[i].n);
+    }
+    return at;
+}
+
+// Driving leaves so few that one workgroup each would leave CUs idle: up to two
+// per CU (see the kernels for both sides).
+static bool few_ped_leaves(const LeafTask *tasks, int32_t n_leaves, int32_t n_cu) {
+    int64_t count = 0;
+    for (int32_t i = 0; i < n_leaves; ++i) count += tasks[i].kind == HDX_PEDNAV ? 1 : 0;
+    return count > 0 && count < 2 * (int64_t)n_cu;
+}
+
+// A workspace of at least `need` bytes, given back and taken anew as it grows;
+// without memory for it the leaves go without (one workgroup each).
+static bool grow_ped_work(unsigned char **work, size_t *cap, size_t need) {
+    if (*cap >= need) return true;
+    if (*work) hipFree(*work);  // (waits for what still uses it)
+    *work = nullptr;
+    *cap = 0;
+    if (hipMalloc((void **)work, need + need / 2) != hipSuccess) {
+        (void)hipGetLastError();
+        *work = nullptr;
+        return false;
+    }
+    *cap = need + need / 2;
+    return true;
+}
+
+static bool capturing(hipStream_t stream) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
+}
+
 void hdx::plan_classes(const LeafTask *tasks, const int8_t *variant, Tile *tiles, int64_t n_tiles,
                        ClassPlan *plan, bool split) {
     int32_t vmax[kModelVariants] = {0};
@@ -793,7 +863,7 @@ Schedule hdx::class_default_schedule(const Variant &v, int64_t tiles, int32_t n_
 // (a wavefront of four lanes each would mostly idle) and for launches of fewer
 // wavefronts than two per SIMD.
 static int32_t spread_lanes(const Variant &v, int64_t tiles, int32_t n_max, int32_t n_cu) {
-    return v.mode == 1 && (n_max <= 12 || tiles * ((n_max + 15) / 16) <= 8 * (int64_t)n_cu) ? 1 : 0;
+    return v.mode == 1 && (n_max <= kPedTile || tiles * ((n_max + 15) / 16) <= 8 * (int64_t)n_cu) ? 1 : 0;
 }
 
 hipError_t hdx::launch_classes(const LeafTask *d_tasks, const Tile *d_tiles, TileQueue *d_queues,
@@ -805,6 +875,7 @@ hipError_t hdx::launch_classes(const LeafTask *d_tasks, const Tile *d_tiles, Til
         vg.n_max = std::max(lds_n[g], plan.n_max[g]);
         vg.pairs = std::max(lds_pairs[g], plan.pairs[g]);
         vg.group = spread_lanes(vg, plan.count[g], plan.n_max[g], n_cu);
+        vg.rows = plan.rows;
         // a workgroup no wider than the group's leaves need
         const int need = useful_threads(vg);
         Schedule sc = sch[g];
@@ -892,17 +963,30 @@ bool launch_in_args(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t n_leaves, cons
     ArgPack pack;
     memset(&pack, 0, sizeof(pack));
     pack_leaves(leaves, n_leaves, pack.t, nullptr, sh.n_tiles, ctx->n_cu);
-    pack.tile_begin[0] = 0;
-    pack.pairs = 1;
     for (int32_t i = 0; i < n_leaves; ++i) {
-        pack.tile_begin[i + 1] = pack.tile_begin[i] + tiles_of(pack.t[i]);
-        pack.pairs = std::max(pack.pairs, tile_pairs(pack.t[i]));
+        pack.tile_end[i] = (i > 0 ? pack.tile_end[i - 1] : 0) + tiles_of(pack.t[i]);
+        v0.pairs = std::max(v0.pairs, tile_pairs(pack.t[i]));
     }
     pack.n_leaves = n_leaves;
-    pack.n_max = v0.n_max;
     v0.group = 1;  // the driving kernels of these calls spread a scenario over 8 or 16 lanes
     const Schedule sch = ctx->sched_fixed ? ctx->sched : class_default_schedule(v0, sh.n_tiles, ctx->n_cu, true);
-    const hipError_t e = launch_expand_args(pack, v0, sch, stream);
+    if (v0.mode != 1 || v0.n_max <= kPedTile || capturing(stream)) {
+        const hipError_t e = launch_expand_args(pack, v0, sch, stream);
+        *st = e == hipSuccess ? HDX_OK : hip_fail(ctx, e, "expand launch");
+        return true;
+    }
+    // (a captured call may be replayed beside others: it goes without a workspace, above)
+    std::lock_guard<std::mutex> lock(ctx->mu);
+    PedSlot &slot = ctx->ped_slots[ctx->next_ped_slot];
+    ctx->next_ped_slot = (ctx->next_ped_slot + 1) % kPedSlots;
+    place_ped_work(pack.t, n_leaves, slot.d);
+    v0.rows = true;
+    hipError_t e = slot.used ? hipStreamWaitEvent(stream, slot.done, 0) : hipSuccess;
+    if (e == hipSuccess) e = launch_expand_args(pack, v0, sch, stream);
+    // (recorded whatever came of the launches: the first of them may be under way)
+    const hipError_t marked = hipEventRecord(slot.done, stream);
+    slot.used = true;
+    if (e == hipSuccess) e = marked;
     *st = e == hipSuccess ? HDX_OK : hip_fail(ctx, e, "expand launch");
     return true;
 }
@@ -1037,6 +1121,10 @@ hdx_status hdx_expand_leaf(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t n_leave
     leaf_variants(leaves, n_leaves, var.data());
     ClassPlan plan;
     plan_classes(s.h_tasks, var.data(), s.h_tiles, n_tiles, &plan, false);
+    if (few_ped_leaves(s.h_tasks, n_leaves, ctx->n_cu) && !capturing((hipStream_t)stream)) {
+        plan.rows = grow_ped_work(&s.work, &s.cap_work, place_ped_work(s.h_tasks, n_leaves, nullptr));
+        if (plan.rows) place_ped_work(s.h_tasks, n_leaves, s.work);
+    }
     st = launch_staged(ctx, s.h_tasks, s.h_tiles, s.h_queue, s.d_tasks, s.d_tiles, s.d_queue, n_leaves, n_tiles,
                        plan, (hipStream_t)stream, s.fork, s.join, s.done);
     if (st == HDX_OK) s.used = true;
@@ -1087,6 +1175,9 @@ struct hdx_batch {
     int32_t n_leaves = 0;
     int64_t n_tiles = 0;
     ClassPlan plan{};
+    unsigned char *ped_work = nullptr;  // driving leaves' workspaces, if the call has few
+    size_t cap_ped = 0;
+    bool rows = false, g_rows = false;
     // per launch group: largest leaf seen, most pairs of a tile seen
     int32_t lds_c[kGroups] = {}, lds_p[kGroups] = {};
     ClassPlan g_plan{};
@@ -1143,6 +1234,7 @@ void default_schedules(hdx_batch *b) {
 // to the device on `st`.
 hipError_t replan(hdx_batch *b, hipStream_t st) {
     plan_classes(b->h_tasks, b->var.data(), b->h_tiles, b->n_tiles, &b->plan, b->split);
+    b->plan.rows = b->rows;
     for (int g = 0; g < kGroups; ++g) {
         b->h_queue[g] = TileQueue{0, 0, (int32_t)b->plan.count[g], 0};
         b->lds_c[g] = std::max(b->lds_c[g], b->plan.n_max[g]);
@@ -1206,6 +1298,7 @@ hdx_status hdx_batch_destroy(hdx_ctx *ctx, hdx_batch *b) {
     if (b->d_tasks) hipFree(b->d_tasks);
     if (b->d_tiles) hipFree(b->d_tiles);
     if (b->d_queue) hipFree(b->d_queue);
+    if (b->ped_work) hipFree(b->ped_work);
     if (b->work) hipStreamDestroy(b->work);
     for (int c = 0; c < kGroups; ++c)
         if (b->cls[c]) hipStreamDestroy(b->cls[c]);
@@ -1230,6 +1323,9 @@ hdx_status hdx_batch_set_leaves(hdx_ctx *ctx, hdx_batch *b, const hdx_leaf *leav
         if (e != hipSuccess) return hip_fail(ctx, e, "staging wait");
     }
     b->n_tiles = pack_leaves(leaves, n_leaves, b->h_tasks, b->h_tiles, sh.n_tiles, ctx->n_cu);
+    b->rows = few_ped_leaves(b->h_tasks, n_leaves, ctx->n_cu) &&
+              grow_ped_work(&b->ped_work, &b->cap_ped, place_ped_work(b->h_tasks, n_leaves, nullptr));
+    if (b->rows) place_ped_work(b->h_tasks, n_leaves, b->ped_work);
     b->var.assign(std::max(n_leaves, 1), 0);
     leaf_variants(leaves, n_leaves, b->var.data());
     b->n_leaves = n_leaves;
@@ -1346,14 +1442,16 @@ hdx_status hdx_batch_launch(hdx_ctx *ctx, hdx_batch *b, hdx_stream stream) {
         e = batch_direct_launch(ctx, b, b->sched, hs);
         return e == hipSuccess ? HDX_OK : hip_fail(ctx, e, "batch launch");
     }
-    // the graph bakes in each group's tile offset, LDS size and (non-persistent) grid
-    bool groups_same = true;
+    // the graph bakes in each group's tile offset, LDS size and grid (but for a persistent one; the kernel that
+    // expands driving's scenarios never is)
+    bool groups_same = b->rows == b->g_rows;
     for (int g = 0; g < kGroups; ++g)
         groups_same = groups_same && b->plan.begin[g] == b->g_plan.begin[g] && b->lds_c[g] == b->g_lds[g] &&
                       b->lds_p[g] == b->g_ldp[g] &&
                       same_schedule(b->sched[g], b->g_sched[g]) &&
-                      (b->sched[g].persistent > 0 ? (b->plan.count[g] > 0) == (b->g_plan.count[g] > 0)
-                                                  : b->plan.count[g] == b->g_plan.count[g]);
+                      (b->sched[g].persistent > 0 && group_variant(g).mode != 1
+                           ? (b->plan.count[g] > 0) == (b->g_plan.count[g] > 0)
+                           : b->plan.count[g] == b->g_plan.count[g]);
     const bool same = b->graph_ok && groups_same;
     if (!same) {
         drop_graph(b);
@@ -1371,6 +1469,7 @@ hdx_status hdx_batch_launch(hdx_ctx *ctx, hdx_batch *b, hdx_stream stream) {
         b->graph_ok = true;
         b->g_tiles = b->n_tiles;
         b->g_plan = b->plan;
+        b->g_rows = b->rows;
         for (int g = 0; g < kGroups; ++g) {
             b->g_lds[g] = b->lds_c[g];
             b->g_ldp[g] = b->lds_p[g];
