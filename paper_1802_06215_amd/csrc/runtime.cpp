@@ -27,11 +27,12 @@ struct ArgSlot {
 };
 
 // Pinned staging + device copy of one call's leaf descriptors and tiles.
+// Staging of a call: its leaves, tiles and queue heads in one piece on the
+// host and on the device, so that they travel in one copy (as three, each with
+// its gap, they took 6 of the 180 us of 512 leaves with the surrogate).
 struct Slot {
-    LeafTask *h_tasks = nullptr, *d_tasks = nullptr;
-    Tile *h_tiles = nullptr, *d_tiles = nullptr;
-    TileQueue *h_queue = nullptr, *d_queue = nullptr;
-    int64_t cap_tasks = 0, cap_tiles = 0;
+    unsigned char *h = nullptr, *d = nullptr;
+    size_t cap = 0;
     hipEvent_t done = nullptr;
     hipEvent_t fork = nullptr, join[kGroups] = {};  // launch groups run side by side
     unsigned char *work = nullptr;                  // driving leaves' workspaces
@@ -181,12 +182,6 @@ hdx_status hdx_init(int32_t device, hdx_ctx **out) {
             hdx_fini(ctx);
             return HDX_E_DEVICE;
         }
-        if (hipMalloc(&s.d_queue, kGroups * sizeof(TileQueue)) != hipSuccess ||
-            hipHostMalloc(&s.h_queue, kGroups * sizeof(TileQueue)) != hipSuccess ||
-            hipMemset(s.d_queue, 0, kGroups * sizeof(TileQueue)) != hipSuccess) {
-            hdx_fini(ctx);
-            return HDX_E_NOMEM;
-        }
     }
     if (configure_expand_kernels() != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
         hdx_fini(ctx);
@@ -231,12 +226,8 @@ hdx_status hdx_fini(hdx_ctx *ctx) {
     hipSetDevice(ctx->device);
     for (auto &s : ctx->slots) {
         if (s.done) hipEventSynchronize(s.done);
-        if (s.h_tasks) hipHostFree(s.h_tasks);
-        if (s.h_tiles) hipHostFree(s.h_tiles);
-        if (s.d_tasks) hipFree(s.d_tasks);
-        if (s.d_tiles) hipFree(s.d_tiles);
-        if (s.d_queue) hipFree(s.d_queue);
-        if (s.h_queue) hipHostFree(s.h_queue);
+        if (s.h) hipHostFree(s.h);
+        if (s.d) hipFree(s.d);
         if (s.work) hipFree(s.work);
         if (s.done) hipEventDestroy(s.done);
         destroy_events(&s.fork, s.join);
@@ -994,14 +985,20 @@ bool launch_in_args(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t n_leaves, cons
 // Copy a planned call's descriptors, tiles and queue heads from host staging
 // to their device buffers on `hs`, launch its groups, and record `done`
 // after the launch (the host staging may be rewritten once it has fired).
+// one_copy: the bytes from h_tasks on, when the three lie in one piece.
 hdx_status launch_staged(hdx_ctx *ctx, const LeafTask *h_tasks, const Tile *h_tiles, TileQueue *h_queue,
                          LeafTask *d_tasks, Tile *d_tiles, TileQueue *d_queue, int32_t n_leaves, int64_t n_tiles,
                          const ClassPlan &plan, hipStream_t hs, hipEvent_t fork, const hipEvent_t *join,
-                         hipEvent_t done) {
+                         hipEvent_t done, size_t one_copy = 0) {
     for (int g = 0; g < kGroups; ++g) h_queue[g] = TileQueue{0, 0, (int32_t)plan.count[g], 0};
-    hipError_t e = hipMemcpyAsync(d_tasks, h_tasks, n_leaves * sizeof(LeafTask), hipMemcpyHostToDevice, hs);
-    if (e == hipSuccess) e = hipMemcpyAsync(d_tiles, h_tiles, n_tiles * sizeof(Tile), hipMemcpyHostToDevice, hs);
-    if (e == hipSuccess) e = hipMemcpyAsync(d_queue, h_queue, kGroups * sizeof(TileQueue), hipMemcpyHostToDevice, hs);
+    hipError_t e = hipSuccess;
+    if (one_copy > 0) {
+        e = hipMemcpyAsync(d_tasks, h_tasks, one_copy, hipMemcpyHostToDevice, hs);
+    } else {
+        e = hipMemcpyAsync(d_tasks, h_tasks, n_leaves * sizeof(LeafTask), hipMemcpyHostToDevice, hs);
+        if (e == hipSuccess) e = hipMemcpyAsync(d_tiles, h_tiles, n_tiles * sizeof(Tile), hipMemcpyHostToDevice, hs);
+        if (e == hipSuccess) e = hipMemcpyAsync(d_queue, h_queue, kGroups * sizeof(TileQueue), hipMemcpyHostToDevice, hs);
+    }
     if (e != hipSuccess) return hip_fail(ctx, e, "descriptor copy");
     int32_t no_lds[kGroups] = {};
     Schedule sch[kGroups];
@@ -1113,20 +1110,33 @@ hdx_status hdx_expand_leaf(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t n_leave
         hipError_t e = hipEventSynchronize(s.done);
         if (e != hipSuccess) return hip_fail(ctx, e, "staging wait");
     }
-    st = grow_pinned(ctx, &s.h_tasks, &s.d_tasks, &s.cap_tasks, &s.h_tiles, &s.d_tiles, &s.cap_tiles, n_leaves,
-                     sh.n_tiles);
-    if (st != HDX_OK) return st;
-    const int64_t n_tiles = pack_leaves(leaves, n_leaves, s.h_tasks, s.h_tiles, sh.n_tiles, ctx->n_cu);
+    const size_t tiles_at = align256((size_t)n_leaves * sizeof(LeafTask));
+    const size_t most = align256(tiles_at + (size_t)sh.n_tiles * sizeof(Tile)) + kGroups * sizeof(TileQueue);
+    if (s.cap < most) {
+        if (s.h) hipHostFree(s.h);
+        if (s.d) hipFree(s.d);
+        s.h = s.d = nullptr;
+        s.cap = 0;
+        const size_t cap = most + most / 4;
+        if (hipHostMalloc((void **)&s.h, cap) != hipSuccess || hipMalloc((void **)&s.d, cap) != hipSuccess)
+            return fail(ctx, HDX_E_NOMEM, "descriptor staging allocation");
+        s.cap = cap;
+    }
+    LeafTask *const h_tasks = (LeafTask *)s.h;
+    Tile *const h_tiles = (Tile *)(s.h + tiles_at);
+    const int64_t n_tiles = pack_leaves(leaves, n_leaves, h_tasks, h_tiles, sh.n_tiles, ctx->n_cu);
+    const size_t queue_at = align256(tiles_at + (size_t)n_tiles * sizeof(Tile));
     std::vector<int8_t> var(n_leaves);
     leaf_variants(leaves, n_leaves, var.data());
     ClassPlan plan;
-    plan_classes(s.h_tasks, var.data(), s.h_tiles, n_tiles, &plan, false);
-    if (few_ped_leaves(s.h_tasks, n_leaves, ctx->n_cu) && !capturing((hipStream_t)stream)) {
-        plan.rows = grow_ped_work(&s.work, &s.cap_work, place_ped_work(s.h_tasks, n_leaves, nullptr));
-        if (plan.rows) place_ped_work(s.h_tasks, n_leaves, s.work);
+    plan_classes(h_tasks, var.data(), h_tiles, n_tiles, &plan, false);
+    if (few_ped_leaves(h_tasks, n_leaves, ctx->n_cu) && !capturing((hipStream_t)stream)) {
+        plan.rows = grow_ped_work(&s.work, &s.cap_work, place_ped_work(h_tasks, n_leaves, nullptr));
+        if (plan.rows) place_ped_work(h_tasks, n_leaves, s.work);
     }
-    st = launch_staged(ctx, s.h_tasks, s.h_tiles, s.h_queue, s.d_tasks, s.d_tiles, s.d_queue, n_leaves, n_tiles,
-                       plan, (hipStream_t)stream, s.fork, s.join, s.done);
+    st = launch_staged(ctx, h_tasks, h_tiles, (TileQueue *)(s.h + queue_at), (LeafTask *)s.d, (Tile *)(s.d + tiles_at),
+                       (TileQueue *)(s.d + queue_at), n_leaves, n_tiles, plan, (hipStream_t)stream, s.fork, s.join, s.done,
+                       queue_at + kGroups * sizeof(TileQueue));
     if (st == HDX_OK) s.used = true;
     return st;
 }
