@@ -284,8 +284,10 @@ hdx_status hdx_expand_leaf(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t n_leave
  * last call's contents (the queue heads are rewritten by every call).  Calls
  * on one stream are ordered; calls that overlap on one GPU -- on other
  * streams, from other threads or other contexts -- race and must not be
- * made.  Up to four leaves of one kernel travel in the kernel arguments, as
- * in hdx_expand_leaf, and leave the array untouched. */
+ * made.  Up to eleven leaves of one kernel travel in the kernel arguments, as
+ * in hdx_expand_leaf, and leave the array untouched (driving leaves take one
+ * of the workspaces that hdx_init makes, their stream ordered after its last
+ * user's). */
 #define HDX_NOALLOC_MAX_LEAVES 512
 #define HDX_NOALLOC_MAX_TILES 65536
 #define HDX_NOALLOC_SCRATCH_BYTES (1 << 20)
@@ -298,7 +300,8 @@ hdx_status hdx_expand_leaf_noalloc(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t
  * descriptors live in device memory owned by the batch, so a launch does no
  * host work and can be captured in a HIP graph and replayed; in persistent
  * mode the kernel drains a tile queue with a fixed grid, so one captured
- * graph serves every batch of the same kernel variant.  The library owns
+ * graph serves every batch of the same kernel variant (driving: of the same
+ * number of leaves).  The library owns
  * *out (release with hdx_batch_destroy).  A batch is used on one stream at
  * a time. */
 typedef struct hdx_batch hdx_batch;
@@ -319,9 +322,8 @@ hdx_status hdx_batch_set_leaves(hdx_ctx *ctx, hdx_batch *batch, const hdx_leaf *
  * of 64*2^(c-1) < n <= 64*2^c scenarios, c = 0..5), the groups launched side
  * by side.  Group = variant * HDX_SIZE_CLASSES + class.  set_split re-plans
  * the staged leaves (and later ones).  A group's schedule: workgroup size
- * (multiple of 64; capped at 512 for both RockSample models and 256 for
- * driving, and at
- * what the group's leaves need), persistent workgroups per CU (0 = one
+ * (multiple of 64; capped at 512 for both RockSample models and 1024 for
+ * driving and navigation, and at what the group's leaves need), persistent workgroups per CU (0 = one
  * workgroup per tile), and the XCD-contiguous tile mapping.  set_schedule applies to every group, set_class_schedule to the
  * groups of one size class; get_group_schedule reports one group (and its
  * tile count), get_class_schedule the class's group with the most tiles,
