@@ -44,13 +44,8 @@ template <int K>
 __device__ __forceinline__ void fused_layer(const uint16_t (*Hs)[kHP], const uint16_t *__restrict__ wt, int nb,
                                             int lane, f32x4 (&acc)[kMI][4]) {
     const int g = lane >> 4, q = lane & 15;
-#pragma unroll
-    for (int i = 0; i < kMI; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const uint16_t *frag = wt + (size_t)(nb / 16) * (K / 32) * 512 + lane * 8;
-#pragma unroll 2
-    for (int k0 = 0; k0 < K; k0 += 32) {
+    auto step = [&](int k0, auto first) {
         bf16x8 b[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) b[j] = *(const bf16x8 *)(frag + (size_t)(j * (K / 32) + k0 / 32) * 512);
@@ -58,9 +53,17 @@ __device__ __forceinline__ void fused_layer(const uint16_t (*Hs)[kHP], const uin
         for (int i = 0; i < kMI; ++i) {
             const bf16x8 a = *(const bf16x8 *)&Hs[i * 16 + q][k0 + g * 8];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a, acc[i][j], 0, 0, 0);
+            for (int j = 0; j < 4; ++j) {
+                // (the first products add to an inline zero: no registers to clear)
+                const f32x4 c = decltype(first)::value ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[i][j];
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a, c, 0, 0, 0);
+            }
         }
-    }
+    };
+    step(0, std::true_type());
+    step(32, std::false_type());
+#pragma unroll 2
+    for (int k0 = 64; k0 < K; k0 += 32) step(k0, std::false_type());
 }
 
 // Two FP32 values rounded to BF16 (nearest even) and packed, lo in bits
