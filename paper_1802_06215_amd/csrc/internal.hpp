@@ -18,6 +18,7 @@ constexpr int kMaxLeaf = HDX_MAX_LEAF_SCENARIOS;
 constexpr int kMaxNavLeaf = HDX_MAX_NAV_LEAF_SCENARIOS;
 constexpr int kNavActions = 9;
 constexpr int kPedActions = 3;
+constexpr int kRockTerms = 2 * kMaxGrid + 2;  // distances on a grid are below
 
 enum : uint32_t { kTagStep = 0, kTagInit = 1, kTagPolicy = 2 };
 constexpr uint64_t kEmptyKey = ~0ull;
@@ -60,6 +61,7 @@ struct DevModel {
     uint32_t sense_thr_m1[kSenseEntries];  // floor(acc(d) 2^32) - 1, by squared distance
     float gpow[kHorizon];                  // discount powers gamma^j rounded to FP32
     double gsum[kHorizon + 1];             // 1 + gamma + ... + gamma^(j-1)
+    double gpow64[kRockTerms];             // gamma^d
 };
 
 struct StatesPtr {
@@ -133,7 +135,6 @@ constexpr int kRockSuccs = 6;              // a robot's moves, its sample, and n
 constexpr int kRockCols = kMaxRocks + 1;   // a column per rock, and one for all scenarios
 constexpr int kRockSets = kMaxRocks + 2;   // live, acting, and per rock those reading it good
 constexpr int kRockCells = 1024;           // x | y << 5
-constexpr int kRockTerms = 2 * kMaxGrid + 2;  // distances on a grid are below
 struct RockSucc {
     double value;            // rollout of a live scenario
     int32_t reward, steps;   // the live scenarios' rewards / 10; steps of one's rollout

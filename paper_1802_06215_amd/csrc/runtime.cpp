@@ -409,6 +409,7 @@ hdx_status hdx_upload_model(hdx_ctx *ctx, const hdx_model_desc *d, hdx_model **o
         const double g = pow(d->gamma, j);
         dm->gpow[j] = (float)g;
         dm->gsum[j + 1] = dm->gsum[j] + g;
+        if (j < kRockTerms) dm->gpow64[j] = g;
     }
     hipSetDevice(ctx->device);
     hdx_model *m = new hdx_model();
