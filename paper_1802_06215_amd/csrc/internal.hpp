@@ -73,6 +73,20 @@ struct StatesPtr {
     int64_t stride;
 };
 
+// The states from number `at` on.
+inline StatesPtr states_from(StatesPtr S, int64_t at) {
+    if (S.w) S.w += at;
+    if (S.s) S.s += at;
+    if (S.car) S.car += at;
+    if (S.px) S.px += at;
+    if (S.py) S.py += at;
+    if (S.goal) S.goal += at;
+    return S;
+}
+// A launch of 2^32 threads or more does not run whole, and says nothing: calls
+// that give a row several threads take long arrays in launches of up to so many.
+constexpr int64_t kLaunchThreads = 1ll << 31;
+
 // One leaf as the expansion kernel sees it (built on the host from hdx_leaf).
 struct LeafTask {
     const DevModel *model;

@@ -2011,26 +2011,43 @@ hipError_t launch_sample(const SampleArgs *d_args, int32_t K, hipStream_t stream
     return hipGetLastError();
 }
 
+namespace {
+template <int PM>
+hipError_t launch_bounds_ped(const BoundsArgs &args, hipStream_t stream) {
+    constexpr int threads = 256, g = ped_lanes<PM, false>();
+    constexpr int64_t most = kLaunchThreads / g;
+    for (int64_t at = 0; at < args.n; at += most) {
+        BoundsArgs part = args;
+        part.states = states_from(args.states, at);
+        part.ids = args.ids + at;
+        part.depths = args.depths + at;
+        part.U = args.U + at;
+        part.L = args.L + at;
+        part.steps = args.steps ? args.steps + at : nullptr;
+        part.n = std::min(most, args.n - at);
+        hipLaunchKernelGGL((bounds_ped<g, PM / g>), dim3((unsigned)((part.n * g + threads - 1) / threads)), dim3(threads),
+                           0, stream, part);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+}  // namespace
+
 hipError_t launch_bounds(const BoundsArgs &args, int32_t kind, int32_t n_peds, hipStream_t stream) {
     const int threads = 256;
     if (args.n <= 0) return hipSuccess;
-    auto grid = [&](int lanes) { return dim3((unsigned)((args.n * lanes + threads - 1) / threads)); };  // lanes per state
-    const dim3 block(threads);
+    if (kind == HDX_PEDNAV)
+        return n_peds <= 8    ? launch_bounds_ped<8>(args, stream)
+               : n_peds <= 16 ? launch_bounds_ped<16>(args, stream)
+                              : launch_bounds_ped<32>(args, stream);
+    const dim3 grid((unsigned)((args.n + threads - 1) / threads)), block(threads);  // a lane per state
     if (kind == HDX_ROCKSAMPLE) {
-        hipLaunchKernelGGL(bounds_rocks<RsOps>, grid(1), block, 0, stream, args);
+        hipLaunchKernelGGL(bounds_rocks<RsOps>, grid, block, 0, stream, args);
     } else if (kind == HDX_MARS) {
-        hipLaunchKernelGGL(bounds_rocks<MarsOps>, grid(1), block, 0, stream, args);
-    } else if (kind == HDX_NAV) {
-        hipLaunchKernelGGL(bounds_nav, grid(1), block, 0, stream, args);
-    } else if (n_peds <= 8) {
-        constexpr int g = ped_lanes<8, false>();
-        hipLaunchKernelGGL((bounds_ped<g, 8 / g>), grid(g), block, 0, stream, args);
-    } else if (n_peds <= 16) {
-        constexpr int g = ped_lanes<16, false>();
-        hipLaunchKernelGGL((bounds_ped<g, 16 / g>), grid(g), block, 0, stream, args);
+        hipLaunchKernelGGL(bounds_rocks<MarsOps>, grid, block, 0, stream, args);
     } else {
-        constexpr int g = ped_lanes<32, false>();
-        hipLaunchKernelGGL((bounds_ped<g, 32 / g>), grid(g), block, 0, stream, args);
+        hipLaunchKernelGGL(bounds_nav, grid, block, 0, stream, args);
     }
     return hipGetLastError();
 }

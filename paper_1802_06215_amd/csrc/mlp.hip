@@ -901,11 +901,20 @@ hipError_t mlp_refresh_bf16(MlpDev &P, hipStream_t s) {
 }
 
 hipError_t launch_features(const FeatArgs &a, hipStream_t s) {
+    constexpr int64_t most = kLaunchThreads / kFeatThreads * kFeatRows;
     if (a.n <= 0) return hipSuccess;
-    const int64_t bx = (a.n + kFeatRows - 1) / kFeatRows;
-    if (bx > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(features_one, dim3((unsigned)bx), dim3(kFeatThreads), 0, s, a);
-    return hipGetLastError();
+    for (int64_t at = 0; at < a.n; at += most) {
+        FeatArgs part = a;
+        part.states = states_from(a.states, at);
+        part.depths = a.depths ? a.depths + at : nullptr;
+        part.X = a.X + at * kMlpIn;
+        part.n = std::min(most, a.n - at);
+        const int64_t bx = (part.n + kFeatRows - 1) / kFeatRows;
+        hipLaunchKernelGGL(features_one, dim3((unsigned)bx), dim3(kFeatThreads), 0, s, part);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_forward_pack(const FeatPack &F, int count, int64_t n_max, const MlpDev &P, hipStream_t s) {
