@@ -980,10 +980,11 @@ __device__ __forceinline__ void move_ped(const PedConst &C, const uint4 &u, floa
 
 // The car: its speed level (a small whole number, held as a float) after an
 // action, its position a step later, and the bound of a state.  Action a
-// changes the level by 1 - a within 0..top.
+// changes the level by 1 - a, up to the top and down to 0; a level above the top
+// (a state's eight bits may hold one) can only be kept or lowered.
 __device__ __forceinline__ float ped_level(const PedConst &C, float level, float change, bool failed) {
-    const float l = level + (failed ? 0.0f : change);
-    return ((l >= 0.0f) & (l <= C.top)) ? l : level;
+    const float l = __builtin_amdgcn_fmed3f(level + change, 0.0f, fmaxf(C.top, level));
+    return failed ? level : l;
 }
 __device__ __forceinline__ float ped_advance(const PedConst &C, float s, float level) {
     const float v = 0.5f * level;
