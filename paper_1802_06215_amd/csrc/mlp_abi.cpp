@@ -105,6 +105,35 @@ hdx_status dev_fail(hdx_ctx *ctx, hipError_t e, const char *what) {
     return HDX_E_DEVICE;
 }
 
+// RockSample leaves whose states_out overlaps another's (a caller without use
+// for the states may give every leaf one buffer): their states are gone when the
+// network would form its rows from them.
+std::vector<char> overlapping_states(const hdx_leaf *leaves, int32_t n_leaves) {
+    std::vector<char> lost(n_leaves, 0);
+    std::vector<int32_t> order;
+    order.reserve(n_leaves);
+    bool ascending = true;  // (as slabs of buffers are: nothing to sort)
+    for (int32_t i = 0; i < n_leaves; ++i) {
+        if (leaves[i].n <= 0 || hdx_internal_desc(leaves[i].model)->kind != HDX_ROCKSAMPLE) continue;
+        if (!order.empty()) {
+            const hdx_leaf &p = leaves[order.back()];
+            ascending = ascending && (uintptr_t)leaves[i].states_out.w >= (uintptr_t)(p.states_out.w + p.n);
+        }
+        order.push_back(i);
+    }
+    if (ascending) return lost;
+    std::sort(order.begin(), order.end(),
+              [&](int32_t a, int32_t b) { return (uintptr_t)leaves[a].states_out.w < (uintptr_t)leaves[b].states_out.w; });
+    int32_t far = order[0];  // the leaf that reaches furthest so far
+    for (size_t k = 1; k < order.size(); ++k) {
+        const hdx_leaf &f = leaves[far], &l = leaves[order[k]];
+        const uintptr_t end = (uintptr_t)(f.states_out.w + f.n);
+        if ((uintptr_t)l.states_out.w < end) lost[far] = lost[order[k]] = 1;
+        if ((uintptr_t)(l.states_out.w + l.n) > end) far = order[k];
+    }
+    return lost;
+}
+
 struct Ordered {
     hdx_mlp *m;
     hipStream_t s;
@@ -287,23 +316,25 @@ hdx_status hdx_expand_leaf_surrogate(hdx_ctx *ctx, const hdx_leaf *leaves, int32
                                      int32_t horizon, hdx_stream stream) {
     if (!ctx || !mlp || n_leaves < 0 || (n_leaves > 0 && !leaves)) return HDX_E_INVALID;
     if (n_leaves == 0) return HDX_OK;
-    // scratch: the distinct stepped states of every scenario (RockSample's follow from the leaf's states), their
-    // features and values
+    for (int32_t i = 0; i < n_leaves; ++i)
+        if (!leaves[i].model) return HDX_E_INVALID;
+    // scratch: the distinct stepped states of every scenario (RockSample's follow from the leaf's states, unless those
+    // are overwritten: then the state of every pair), their features and values
+    const std::vector<char> lost = overlapping_states(leaves, n_leaves);
     std::vector<size_t> st_off(n_leaves), pair_off(n_leaves);
     size_t st_bytes = 0;
     int64_t pairs = 0, leaf_tiles = 0;
     for (int32_t i = 0; i < n_leaves; ++i) {
-        if (!leaves[i].model) return HDX_E_INVALID;
         const hdx_model_desc &d = *hdx_internal_desc(leaves[i].model);
         if (d.kind == HDX_MARS || d.kind == HDX_NAV) {
             hdx_internal_set_error(ctx, "no surrogate features for this model");
             return HDX_E_UNSUPPORTED;
         }
-        const int64_t np =
-            (int64_t)successors_of(d.kind, d.n_actions) * (leaves[i].n > 0 ? leaves[i].n : 0);
+        const int64_t np = (int64_t)(lost[i] ? d.n_actions : successors_of(d.kind, d.n_actions)) *
+                           (leaves[i].n > 0 ? leaves[i].n : 0);
         st_off[i] = st_bytes;
         pair_off[i] = (size_t)pairs;
-        const size_t per = d.kind == HDX_ROCKSAMPLE ? 0 : (size_t)(8 + 9 * d.n_peds);
+        const size_t per = d.kind != HDX_ROCKSAMPLE ? (size_t)(8 + 9 * d.n_peds) : lost[i] ? sizeof(int32_t) : 0;
         st_bytes += ((size_t)np * per + 64) & ~(size_t)15;
         pairs += np;
         leaf_tiles += (np + kMlpTileRows - 1) / kMlpTileRows;
@@ -328,7 +359,7 @@ hdx_status hdx_expand_leaf_surrogate(hdx_ctx *ctx, const hdx_leaf *leaves, int32
     char *base = (char *)mlp->sur;
     uint16_t *X = (uint16_t *)(base + st_bytes);
     float *vals = (float *)(base + st_bytes + (size_t)pairs * kMlpIn * sizeof(uint16_t));
-    // expansion without rollouts, driving's stepped states kept
+    // expansion without rollouts, stepped states kept (driving, and RockSample leaves that lose theirs)
     std::vector<hdx_leaf> mod(leaves, leaves + n_leaves);
     for (int32_t i = 0; i < n_leaves; ++i) {
         const hdx_model_desc &d = *hdx_internal_desc(leaves[i].model);
@@ -336,9 +367,14 @@ hdx_status hdx_expand_leaf_surrogate(hdx_ctx *ctx, const hdx_leaf *leaves, int32
         hdx_leaf &L = mod[i];
         L.rollout.max_steps = 0;
         L.L = nullptr;
-        if (d.kind == HDX_ROCKSAMPLE || L.sprime.s != nullptr) continue;  // (the caller's)
+        if (d.kind == HDX_ROCKSAMPLE ? !lost[i] || L.sprime.w != nullptr : L.sprime.s != nullptr) continue;  // (the caller's)
         memset(&L.sprime, 0, sizeof(L.sprime));
         char *p = base + st_off[i];
+        if (d.kind == HDX_ROCKSAMPLE) {
+            L.sprime.w = (int32_t *)p;
+            L.sprime.stride = np;
+            continue;
+        }
         L.sprime.s = (float *)p;
         L.sprime.car = (int32_t *)(p + 4 * np);
         L.sprime.px = (float *)(p + 8 * np);
@@ -355,8 +391,8 @@ hdx_status hdx_expand_leaf_surrogate(hdx_ctx *ctx, const hdx_leaf *leaves, int32
     sa.reserve(n_leaves);
     for (int32_t i = 0; i < n_leaves; ++i) {
         const int32_t A = hdx_model_actions(leaves[i].model);
-        const bool rocks = hdx_internal_desc(leaves[i].model)->kind == HDX_ROCKSAMPLE;
-        const int32_t S = successors_of(hdx_internal_desc(leaves[i].model)->kind, A);
+        const bool rocks = hdx_internal_desc(leaves[i].model)->kind == HDX_ROCKSAMPLE && !lost[i];
+        const int32_t S = lost[i] ? A : successors_of(hdx_internal_desc(leaves[i].model)->kind, A);
         const int64_t np = (int64_t)S * (leaves[i].n > 0 ? leaves[i].n : 0);
         if (np == 0) continue;
         FeatArgs a;
