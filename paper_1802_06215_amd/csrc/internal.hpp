@@ -262,9 +262,30 @@ __host__ __device__ inline NavLayout make_nav_layout(uint32_t pairs, uint32_t na
     L.total = o;
     return L;
 }
+// Words that a navigation tile holds per (action, scenario): its codes, and
+// beside them the rollouts' values where those run step by step, each of the two
+// rounded as make_nav_layout rounds them.
+inline int32_t nav_values(int32_t n, int32_t actions, bool stepped) {
+    return stepped ? 2 * ((n * actions + 3) & ~3) : n * actions;
+}
+constexpr int32_t kMaxDynamicLds = 160 * 1024 - 256;
+// Dynamic LDS of a workgroup for navigation leaves of up to n_max scenarios and
+// tiles of up to `values` words (nav_values); counters for all nine actions.
+inline uint32_t nav_lds(int32_t n_max, int32_t values, int32_t threads) {
+    const uint32_t b = make_nav_layout((uint32_t)values, kNavActions, (uint32_t)(n_max + 63) / 64,
+                                       (uint32_t)threads / 64, false).total;
+    return b < (uint32_t)kMaxDynamicLds ? b : (uint32_t)kMaxDynamicLds;
+}
 // Actions per navigation tile of a leaf of n scenarios, at most `most`: as
 // many as its LDS holds beside 16 wavefronts.
-int32_t nav_tile_actions(int32_t n, int32_t policy, int32_t most);
+inline int32_t nav_tile_actions(int32_t n, int32_t policy, int32_t most) {
+    for (int32_t w = most; w > 1; --w)
+        if (kNavActions % w == 0 &&
+            make_nav_layout((uint32_t)nav_values(n, w, policy != HDX_POLICY_DEFAULT), kNavActions,
+                            (uint32_t)(n + 63) / 64, 16, false).total <= (uint32_t)kMaxDynamicLds)
+            return w;
+    return 1;
+}
 
 // Kernel variant a set of leaves needs: mode 0 RockSample only, 1 driving
 // only, 2 both; pm = pedestrian capacity of the register state; n_max sizes
@@ -273,8 +294,7 @@ struct Variant {
     int32_t mode, pm, n_max;
     // driving only: the kernel instance with 8 or 16 lanes per scenario
     int32_t group = 0;
-    // navigation: the largest (action, scenario) pairs of a tile, counted
-    // twice where the rollouts run step by step; RockSample: rock_values
+    // the most words of a tile: navigation nav_values, RockSample rock_values
     int32_t pairs = 1;
     // driving only: the leaves have workspaces
     bool rows = false;
@@ -395,8 +415,6 @@ hipError_t launch_philox(const uint32_t *ctr, int64_t count, uint32_t k0, uint32
 
 hipError_t launch_fp32_selftest(const float *a, const float *b, const float *c, int64_t n, float *out,
                                 hipStream_t stream);
-
-int32_t max_dynamic_lds();
 
 }  // namespace hdx
 

@@ -1643,21 +1643,19 @@ __global__ __launch_bounds__(kPedRowThreads, 4) void ped_rows_args(const ArgPack
 }
 
 // Dynamic LDS of one workgroup for leaves of up to n_max scenarios, tiles of up
-// to `pairs` values per scenario and action (tile_pairs).
+// to `pairs` words (tile_pairs).
 template <int MODE>
 uint32_t lds_bytes(int32_t n_max, int32_t pairs, int32_t threads) {
     if (rock_mode<MODE>()) return make_rock_layout(n_max, std::max(n_max, pairs), MODE == 3).total;
     if (MODE == 1 || MODE == 5) return make_ped_layout(n_max).total;
     if (MODE == 2)
         return std::max(make_rock_layout(n_max, std::max(n_max, pairs), false).total, make_ped_layout(n_max).total);
-    const uint32_t b = make_nav_layout((uint32_t)pairs, kNavActions, (uint32_t)(n_max + 63) / 64, (uint32_t)threads / 64,
-                                       false).total;
-    return std::min(b, (uint32_t)max_dynamic_lds());
+    return nav_lds(n_max, pairs, threads);
 }
 
 template <class K>
 hipError_t allow_lds(K *kernel) {
-    return hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, max_dynamic_lds());
+    return hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDynamicLds);
 }
 template <int MODE, int PM>
 hipError_t configure_t() {
@@ -1922,20 +1920,6 @@ hipError_t launch_fp32_selftest(const float *a, const float *b, const float *c, 
     if (blocks == 0) return hipSuccess;
     hipLaunchKernelGGL(fp32_selftest_kernel, dim3((unsigned)blocks), dim3(threads), 0, stream, a, b, c, n, out);
     return hipGetLastError();
-}
-
-int32_t max_dynamic_lds() { return 160 * 1024 - 256; }
-
-int32_t nav_tile_actions(int32_t n, int32_t policy, int32_t most) {
-    const bool stepped = policy != HDX_POLICY_DEFAULT;
-    const uint32_t chunks = (uint32_t)(n + 63) / 64;
-    for (int32_t w = most; w > 1; --w) {
-        // the launch reserves counters for all nine actions
-        const uint32_t pairs = (uint32_t)(w * n) * (stepped ? 2u : 1u);
-        if (kNavActions % w == 0 && make_nav_layout(pairs, kNavActions, chunks, 16, false).total <= (uint32_t)max_dynamic_lds())
-            return w;
-    }
-    return 1;
 }
 
 Variant pick_variant(int32_t has_rs, int32_t has_ped, int32_t ped_max, int32_t n_max, int32_t has_mars,

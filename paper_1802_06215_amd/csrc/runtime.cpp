@@ -673,11 +673,10 @@ int32_t tile_action(const LeafTask &T, int32_t t) {
     return t / per_row * T.row_actions + t % per_row * T.tile_actions;
 }
 
-// Values a tile holds in LDS, as the layouts count them (Variant::pairs).
+// Words a tile holds in LDS, as the layouts count them (Variant::pairs).
 int32_t tile_pairs(const LeafTask &T) {
     const bool stepped = T.policy != HDX_POLICY_DEFAULT;
-    if (T.kind == HDX_NAV) return T.n * T.tile_actions * (stepped ? 2 : 1);
-    return rock_values(T.n, stepped);
+    return T.kind == HDX_NAV ? nav_values(T.n, T.tile_actions, stepped) : rock_values(T.n, stepped);
 }
 
 // Descriptors (and tiles) of a call of call_tiles (leaf, action) pairs;
