@@ -300,8 +300,12 @@ hdx_status hdx_expand_leaf_noalloc(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t
  * descriptors live in device memory owned by the batch, so a launch does no
  * host work and can be captured in a HIP graph and replayed; in persistent
  * mode the kernel drains a tile queue with a fixed grid, so one captured
- * graph serves every batch of the same kernel variant (driving: of the same
- * number of leaves).  The library owns
+ * graph serves every batch of the same kernel variant.  A graph that the
+ * caller captures from a launch serves the leaves that the batch is given
+ * later, whatever their number, sizes and policy, if they make up the one
+ * launch group (model variant and size class, below) of the capture and none
+ * is larger than the largest that the batch had been given; with several
+ * groups, as many leaves of each model in each.  The library owns
  * *out (release with hdx_batch_destroy).  A batch is used on one stream at
  * a time. */
 typedef struct hdx_batch hdx_batch;

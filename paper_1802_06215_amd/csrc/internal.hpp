@@ -128,10 +128,14 @@ struct TileQueue {
     int32_t next, done, n_tiles, pad;
 };
 
+constexpr int32_t kQueued = -1;
 // Launch schedule of the expansion kernel; results never depend on it.
 struct Schedule {
     int32_t threads;     // workgroup size, a multiple of 64
-    int32_t persistent;  // 0: one workgroup per tile; >0: that many workgroups per CU
+    // 0: one workgroup per tile; > 0: that many workgroups per CU, which drain
+    // the queue; kQueued: as many as there are tiles, which drain the queue (so
+    // that they take more tiles, if there are more when the launch is replayed)
+    int32_t persistent;
     int32_t xcd_remap;   // keep consecutive tiles (one leaf) on one XCD
 };
 
@@ -286,6 +290,10 @@ inline int32_t nav_tile_actions(int32_t n, int32_t policy, int32_t most) {
             return w;
     return 1;
 }
+
+// The most words that a tile of a leaf of up to n scenarios holds, whatever its
+// policy and its actions: what a launch is sized for that the caller captured.
+inline int32_t most_values(bool nav, int32_t n) { return nav ? nav_values(n, kNavActions, true) : rock_values(n, true); }
 
 // Kernel variant a set of leaves needs: mode 0 RockSample only, 1 driving
 // only, 2 both; pm = pedestrian capacity of the register state; n_max sizes

@@ -1686,7 +1686,7 @@ hipError_t launch_expand_t(const LeafTask *d_tasks, const Tile *d_tiles, TileQue
     if (grid < 1) return hipSuccess;
     const int threads = sch.threads > max_threads<MODE>() ? max_threads<MODE>() : sch.threads;
     hipLaunchKernelGGL((expand_tiles<MODE, PM, kSpread>), dim3(grid), dim3(threads),
-                       lds_bytes<MODE>(n_max, pairs, threads), stream, d_tasks, d_tiles, d_queue, sch.persistent > 0 ? 1 : 0, sch.xcd_remap);
+                       lds_bytes<MODE>(n_max, pairs, threads), stream, d_tasks, d_tiles, d_queue, sch.persistent != 0 ? 1 : 0, sch.xcd_remap);
     return hipGetLastError();
 }
 

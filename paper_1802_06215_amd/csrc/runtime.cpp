@@ -769,7 +769,9 @@ static bool grow_ped_work(unsigned char **work, size_t *cap, size_t need) {
 
 static bool capturing(hipStream_t stream) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();  // (or the next launch would report it)
+    return true;
 }
 
 void hdx::plan_classes(const LeafTask *tasks, const int8_t *variant, Tile *tiles, int64_t n_tiles,
@@ -866,10 +868,12 @@ hipError_t hdx::launch_classes(const LeafTask *d_tasks, const Tile *d_tiles, Til
         vg.n_max = std::max(lds_n[g], plan.n_max[g]);
         vg.pairs = std::max(lds_pairs[g], plan.pairs[g]);
         vg.group = spread_lanes(vg, plan.count[g], plan.n_max[g], n_cu);
-        vg.rows = plan.rows;
         // a workgroup no wider than the group's leaves need
         const int need = useful_threads(vg);
         Schedule sc = sch[g];
+        // (a persistent grid is to serve any number of leaves; the kernel that expands driving's scenarios has a
+        // workgroup for each chunk of those it was launched for)
+        vg.rows = plan.rows && sc.persistent == 0;
         if (sc.threads > need) sc.threads = need;
         const hipError_t e = launch_expand(d_tasks, d_tiles + plan.begin[g], d_queues + g, (int32_t)plan.count[g], vg,
                                            sc, n_cu, stream);
@@ -1449,19 +1453,38 @@ hdx_status hdx_batch_launch(hdx_ctx *ctx, hdx_batch *b, hdx_stream stream) {
     hipStream_t hs = (hipStream_t)stream;
     hipError_t e;
     if (!b->graph_on) {
-        e = batch_direct_launch(ctx, b, b->sched, hs);
+        if (!capturing(hs)) {
+            e = batch_direct_launch(ctx, b, b->sched, hs);
+        } else {
+            // The caller's graph may be replayed with other leaves staged: no workspaces, tiles from the queue, and LDS
+            // for any policy and number of actions per tile that leaves up to the largest seen can come with.  (Where a
+            // group's tiles begin stays the same with as many leaves of each model: their sizes and policy change the
+            // number of tiles of leaves above 1024 scenarios alone, navigation's, the last group.)
+            ClassPlan plan = b->plan;
+            plan.rows = false;
+            int32_t pairs[kGroups];
+            Schedule sched[kGroups];
+            for (int g = 0; g < kGroups; ++g) {
+                pairs[g] = most_values(group_variant(g).mode == 4, b->lds_c[g]);
+                sched[g] = b->sched[g];
+                if (sched[g].persistent == 0) sched[g].persistent = kQueued;
+            }
+            e = launch_classes_forked(b->d_tasks, b->d_tiles, b->d_queue, plan, b->lds_c, pairs, sched, ctx->n_cu, hs,
+                                      b->cls, b->fork, b->join);
+        }
         return e == hipSuccess ? HDX_OK : hip_fail(ctx, e, "batch launch");
     }
-    // the graph bakes in each group's tile offset, LDS size and grid (but for a persistent one; the kernel that
-    // expands driving's scenarios never is)
-    bool groups_same = b->rows == b->g_rows;
-    for (int g = 0; g < kGroups; ++g)
+    // the graph bakes in each group's tile offset, LDS size, schedule and (but for a persistent one) grid, and whether
+    // driving's scenarios have a kernel of their own
+    bool groups_same = true;
+    for (int g = 0; g < kGroups; ++g) {
+        const bool fixed_grid = b->sched[g].persistent > 0;
         groups_same = groups_same && b->plan.begin[g] == b->g_plan.begin[g] && b->lds_c[g] == b->g_lds[g] &&
-                      b->lds_p[g] == b->g_ldp[g] &&
-                      same_schedule(b->sched[g], b->g_sched[g]) &&
-                      (b->sched[g].persistent > 0 && group_variant(g).mode != 1
-                           ? (b->plan.count[g] > 0) == (b->g_plan.count[g] > 0)
-                           : b->plan.count[g] == b->g_plan.count[g]);
+                      b->lds_p[g] == b->g_ldp[g] && same_schedule(b->sched[g], b->g_sched[g]) &&
+                      (fixed_grid ? (b->plan.count[g] > 0) == (b->g_plan.count[g] > 0)
+                                  : b->plan.count[g] == b->g_plan.count[g]) &&
+                      (fixed_grid || b->plan.count[g] == 0 || group_variant(g).mode != 1 || b->rows == b->g_rows);
+    }
     const bool same = b->graph_ok && groups_same;
     if (!same) {
         drop_graph(b);

@@ -2,7 +2,8 @@
 
 A launch is sized for its largest leaf and its tile of most words; every tile of
 any leaf in it, under any policy, workgroup width and number of actions, must
-find its regions inside.  The layouts are plain functions of a header shared by
+find its regions inside.  A launch that the caller captures is sized for any
+policy and any number of actions.  The layouts are plain functions of a header shared by
 host and device code: a small program compiled here goes through the sizes.
 """
 import os
@@ -24,12 +25,17 @@ int main() {
             for (int32_t most : {1, 3, 9}) {
                 const bool stepped = policy != HDX_POLICY_DEFAULT;
                 const int32_t full = nav_tile_actions(n, policy, most);
+                if (n <= 1024 && full != most && bad++ < 5) printf("navigation n %d: %d actions, not %d\n", n, full, most);
+                const int32_t n_max = n + (most == 3 ? 0 : 70 * most);  // of a captured launch
                 for (int32_t threads = 64; threads <= 1024; threads += 64) {
                     const uint32_t given = nav_lds(n, nav_values(n, full, stepped), threads);
                     for (int32_t na = 1; na <= full; ++na) {
                         const uint32_t used = make_nav_layout((uint32_t)(na * n), (uint32_t)na, (uint32_t)(n + 63) / 64,
                                                               (uint32_t)threads / 64, stepped).total;
                         ++checked;
+                        if (n_max <= HDX_MAX_NAV_LEAF_SCENARIOS && used > nav_lds(n_max, most_values(true, n_max), threads)) {
+                            if (bad++ < 5) printf("navigation, captured: n %d of %d\n", n, n_max);
+                        }
                         if (used > given || given > (uint32_t)kMaxDynamicLds) {
                             if (bad++ < 5) printf("navigation n %d policy %d threads %d actions %d: %u of %u\n", n, policy,
                                                   threads, na, used, given);
@@ -47,9 +53,10 @@ int main() {
                         int32_t values = rock_values(n, stepped);
                         if (rock_values(n_max, other) > values) values = rock_values(n_max, other);
                         const uint32_t given = make_rock_layout(n_max, values > n_max ? values : n_max, two).total;
+                        const uint32_t captured = make_rock_layout(n_max, most_values(false, n_max), two).total;
                         const uint32_t used = make_rock_layout(n, rock_values(n, stepped), two).total;
                         ++checked;
-                        if (used > given || given > (uint32_t)kMaxDynamicLds) {
+                        if (used > given || given > captured || captured > (uint32_t)kMaxDynamicLds) {
                             if (bad++ < 5) printf("rocks n %d of %d: %u of %u\n", n, n_max, used, given);
                         }
                     }
