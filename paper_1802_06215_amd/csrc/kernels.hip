@@ -135,14 +135,11 @@ __device__ __forceinline__ void rock_keys(uint64_t (&keys)[K], uint64_t valid, u
     }
 }
 
-// A thread's place counted from the middle of the workgroup on, for work that
-// is to begin on other wavefronts than the work beside it.  Every place is some
-// thread's, whatever multiple of 64 the workgroup has (tid ^ nt / 2 is that only
-// for powers of two), and a quad stays a quad.
-__device__ __forceinline__ int from_middle(int tid, int nt) {
-    const int t = tid + (nt >> 1);
-    return t < nt ? t : t - nt;
-}
+// A thread's place in work that is to begin on other wavefronts than the work
+// beside it: halves changed about within the largest power of two that divides
+// the workgroup, so that every place is some thread's at any multiple of 64
+// (tid ^ nt / 2 leaves places out at 192), with a scalar operand.
+__device__ __forceinline__ int swapped_half(int tid, int nt) { return tid ^ ((nt & -nt) >> 1); }
 
 // cell_effects of every cell, by the whole workgroup, with barriers.
 __device__ __forceinline__ void stage_effects(const MView &M, uint32_t *effects) {
@@ -584,7 +581,7 @@ __device__ __forceinline__ void run_tile_rocks(const HDX_CONST LeafTask *T, cons
     }
     // scenarios in earlier chunks: of each split those reading rock j good (row j), acting (row kMaxRocks), and not
     // (row kMaxRocks + 1; with the terminal ones, which read nothing)
-    for (int e = from_middle(tid, nt); e < kSplits * 32; e += nt) {
+    for (int e = swapped_half(tid, nt); e < kSplits * 32; e += nt) {
         const int sp = e >> 5, row = e & 31;
         if (row < kRockSets && (row >= kMaxRocks || (row >= j0 && row < j1))) {
             uint16_t *out = pre + (sp * kRockSets + row) * nch;
@@ -612,7 +609,7 @@ __device__ __forceinline__ void run_tile_rocks(const HDX_CONST LeafTask *T, cons
     // lane's twenty columns take 2700 cycles, most of them waits), on other wavefronts than the leaf's first chunks --
     auto children = [&](auto lanes) {
         constexpr int kLanes = decltype(lanes)::value, kCols = kMaxRocks / kLanes;
-        for (int g = from_middle(tid, nt); g < nb * kKeys * kLanes; g += nt) {
+        for (int g = swapped_half(tid, nt); g < nb * kKeys * kLanes; g += nt) {
             const int e = g / kLanes, part = g % kLanes;
             const int i = e / kKeys, q = e - i * kKeys, b = b0 + i, a = a_first + i;
             const int c = b >= 5 ? 5 : b;
