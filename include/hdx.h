@@ -286,8 +286,7 @@ hdx_status hdx_expand_leaf(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t n_leave
  * streams, from other threads or other contexts -- race and must not be
  * made.  Up to eleven leaves of one kernel travel in the kernel arguments, as
  * in hdx_expand_leaf, and leave the array untouched (driving leaves take one
- * of the workspaces that hdx_init makes, their stream ordered after its last
- * user's). */
+ * of the workspaces that hdx_init makes, if one is free). */
 #define HDX_NOALLOC_MAX_LEAVES 512
 #define HDX_NOALLOC_MAX_TILES 65536
 #define HDX_NOALLOC_SCRATCH_BYTES (1 << 20)

@@ -196,6 +196,15 @@ __host__ __device__ inline RockLayout make_rock_layout(int32_t n, int32_t values
 // Workspace of a driving leaf expanded and grouped by two kernels: per action
 // and scenario the observation, U, L, reward code and steps.
 inline size_t ped_work_bytes(int32_t n) { return (size_t)kPedActions * 24u * (size_t)n; }
+// Before the workspaces of a call in the kernel arguments: its leaves that are
+// grouped so far, and the calls that have ended, written to host memory too, so
+// that the host knows which workspaces are free without an event on the caller's
+// stream (which may be gone when the event is asked).
+struct PedHead {
+    uint32_t left, ended;
+    uint32_t *host;
+};
+constexpr size_t kPedHeadBytes = 64;
 constexpr int kPedTile = 12;  // scenarios of a driving leaf that one workgroup expands and groups
 // Driving tile: the three actions of a leaf of n scenarios.
 //   zkey, pos   per action: (observation, position) pairs, sorted in place,

@@ -1586,6 +1586,15 @@ __global__ __launch_bounds__(max_threads<MODE>(), min_waves<MODE>()) void expand
     }
 }
 
+// One of a call's leaves has ended; the last of them tells the host.
+__device__ __forceinline__ void end_ped_leaf(PedHead *head, uint32_t n_leaves) {
+    __threadfence();
+    if (atomicAdd(&head->left, 1u) != n_leaves - 1) return;
+    head->left = 0;
+    const uint32_t ended = atomicAdd(&head->ended, 1u) + 1u;
+    __hip_atomic_store(head->host, ended, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // A few leaves carried in the kernel arguments: no descriptor staging, so
 // the launch is ordered by its stream alone.  The pack is read in place in
 // the kernarg segment (constant address space, scalar loads).
@@ -1610,6 +1619,8 @@ __global__ __launch_bounds__(max_threads<MODE>()) void expand_args(const ArgPack
         a = row * T->row_actions + (local - row * per_row) * T->tile_actions;
     }
     run_mode<MODE, PM, true>(T, a, lds);
+    if constexpr (MODE == 5)  // (a leaf is a tile; all have read their workspace)
+        if (threadIdx.x == 0) end_ped_leaf((PedHead *)(P->t[0].work - kPedHeadBytes), (uint32_t)n_leaves);
 }
 
 // Driving, the scenarios of many leaves: `chunks` workgroups per tile of the

@@ -41,14 +41,16 @@ struct Slot {
 };
 
 // Workspaces of the driving leaves of a call in the kernel arguments, made at
-// set-up and large enough for any such call.  A call takes the next one and its
-// stream waits for the call that had it before.
-constexpr int kPedSlots = 8;
-constexpr size_t kPedSlotBytes = (size_t)kArgLeaves * (size_t)kPedActions * 24u * HDX_MAX_LEAF_SCENARIOS;
+// set-up and large enough for any such call, one for each thread of the largest
+// search (104 MB).
+constexpr int kPedSlots = 64;
+constexpr size_t kPedSlotBytes =
+    kPedHeadBytes + (size_t)kArgLeaves * (size_t)kPedActions * 24u * HDX_MAX_LEAF_SCENARIOS;
+static_assert(sizeof(PedHead) <= kPedHeadBytes && kPedSlotBytes % 64 == 0, "workspace layout");
 struct PedSlot {
-    unsigned char *d = nullptr;
-    hipEvent_t done = nullptr;
-    bool used = false;
+    uint32_t calls = 0;            // launched; the host's word of PedHead says how many have ended
+    hipStream_t stream = nullptr;  // the last one's, if known
+    bool known = false, lost = false;
 };
 
 bool create_events(hipEvent_t *fork, hipEvent_t *join) {
@@ -123,6 +125,8 @@ struct hdx_ctx {
     ArgSlot arg_slots[kArgSlots];
     int next_arg_slot = 0;
     PedSlot ped_slots[kPedSlots];
+    unsigned char *ped_work = nullptr;  // the slots', or null: without memory for them the leaves go without
+    uint32_t *ped_ended = nullptr;      // pinned: calls ended, per slot
     int next_ped_slot = 0;
     // expansion without allocation: the device's fixed scratch array (its
     // address from hipGetSymbolAddress), pinned host staging and events made
@@ -193,12 +197,20 @@ hdx_status hdx_init(int32_t device, hdx_ctx **out) {
             hdx_fini(ctx);
             return HDX_E_NOMEM;
         }
-    for (auto &p : ctx->ped_slots)
-        if (hipMalloc((void **)&p.d, kPedSlotBytes) != hipSuccess ||
-            hipEventCreateWithFlags(&p.done, hipEventDisableTiming) != hipSuccess) {
-            hdx_fini(ctx);
-            return HDX_E_NOMEM;
+    PedHead heads[kPedSlots] = {};
+    if (hipHostMalloc((void **)&ctx->ped_ended, kPedSlots * sizeof(uint32_t)) == hipSuccess) {
+        for (int i = 0; i < kPedSlots; ++i) {
+            ctx->ped_ended[i] = 0;
+            heads[i].host = ctx->ped_ended + i;
         }
+        if (hipMalloc((void **)&ctx->ped_work, kPedSlots * kPedSlotBytes) != hipSuccess) ctx->ped_work = nullptr;
+        if (ctx->ped_work && hipMemcpy2D(ctx->ped_work, kPedSlotBytes, heads, sizeof(PedHead), sizeof(PedHead), kPedSlots,
+                                         hipMemcpyHostToDevice) != hipSuccess) {
+            hipFree(ctx->ped_work);
+            ctx->ped_work = nullptr;
+        }
+    }
+    if (!ctx->ped_work) (void)hipGetLastError();
     // set-up of hdx_expand_leaf_noalloc: the scratch's device address, host
     // staging and events, so that the call itself allocates nothing
     ctx->err.reserve(kErrCap);
@@ -236,13 +248,8 @@ hdx_status hdx_fini(hdx_ctx *ctx) {
         hipEventSynchronize(ctx->na_done);
         hipEventDestroy(ctx->na_done);
     }
-    for (auto &p : ctx->ped_slots) {
-        if (p.done) {
-            hipEventSynchronize(p.done);
-            hipEventDestroy(p.done);
-        }
-        if (p.d) hipFree(p.d);
-    }
+    if (ctx->ped_work) hipFree(ctx->ped_work);  // (waits for the calls that use it)
+    if (ctx->ped_ended) hipHostFree(ctx->ped_ended);
     for (auto &a : ctx->arg_slots) {
         if (a.done) {
             hipEventSynchronize(a.done);
@@ -460,6 +467,7 @@ void hdx_internal_quiesce(hdx_ctx *ctx) {
         if (a.used) hipEventSynchronize(a.done);
         a.used = false;
     }
+    for (auto &p : ctx->ped_slots) p.known = false;
 }
 
 extern "C" {
@@ -945,6 +953,26 @@ hdx_status grow_pinned(hdx_ctx *ctx, LeafTask **h_tasks, LeafTask **d_tasks, int
 
 namespace {
 
+// A workspace for a call on the stream: the one it had last (its calls run one
+// after another), or one whose calls have ended.  Null if calls of other streams
+// hold them all: waiting for them would tie the stream to work that may be far
+// off, and a leaf on a workgroup of its own needs none (one of 500 scenarios 362
+// us instead of 56).  A stream handle that comes back after its stream was
+// destroyed finds that stream's work done, as destroying a stream waits for it
+// (0.2 s with a kernel of 0.2 s on it).  Call with ctx->mu held.
+PedSlot *free_ped_slot(hdx_ctx *ctx, hipStream_t stream) {
+    if (!ctx->ped_work) return nullptr;
+    for (auto &p : ctx->ped_slots)
+        if (p.known && p.stream == stream && !p.lost) return &p;
+    for (int i = 0; i < kPedSlots; ++i) {
+        const int at = ctx->next_ped_slot;
+        ctx->next_ped_slot = (at + 1) % kPedSlots;
+        if (__atomic_load_n(ctx->ped_ended + at, __ATOMIC_ACQUIRE) == ctx->ped_slots[at].calls && !ctx->ped_slots[at].lost)
+            return &ctx->ped_slots[at];
+    }
+    return nullptr;
+}
+
 // Small calls of one kernel carry their descriptors in the kernel arguments
 // (the multi-agent and navigation models have kernels of their own;
 // RockSample and driving share one).  Returns false if the call is not such
@@ -972,16 +1000,19 @@ bool launch_in_args(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t n_leaves, cons
     }
     // (a captured call may be replayed beside others: it goes without a workspace, above)
     std::lock_guard<std::mutex> lock(ctx->mu);
-    PedSlot &slot = ctx->ped_slots[ctx->next_ped_slot];
-    ctx->next_ped_slot = (ctx->next_ped_slot + 1) % kPedSlots;
-    place_ped_work(pack.t, n_leaves, slot.d);
+    PedSlot *const free = free_ped_slot(ctx, stream);
+    if (!free) {
+        const hipError_t e = launch_expand_args(pack, v0, sch, stream);
+        *st = e == hipSuccess ? HDX_OK : hip_fail(ctx, e, "expand launch");
+        return true;
+    }
+    place_ped_work(pack.t, n_leaves, ctx->ped_work + (size_t)(free - ctx->ped_slots) * kPedSlotBytes + kPedHeadBytes);
     v0.rows = true;
-    hipError_t e = slot.used ? hipStreamWaitEvent(stream, slot.done, 0) : hipSuccess;
-    if (e == hipSuccess) e = launch_expand_args(pack, v0, sch, stream);
-    // (recorded whatever came of the launches: the first of them may be under way)
-    const hipError_t marked = hipEventRecord(slot.done, stream);
-    slot.used = true;
-    if (e == hipSuccess) e = marked;
+    const hipError_t e = launch_expand_args(pack, v0, sch, stream);
+    free->calls += 1;
+    free->stream = stream;
+    free->known = true;
+    free->lost = e != hipSuccess;  // (the first of its kernels may be under way, and nothing will say when it ends)
     *st = e == hipSuccess ? HDX_OK : hip_fail(ctx, e, "expand launch");
     return true;
 }
