@@ -53,6 +53,13 @@ struct PedSlot {
     bool known = false, lost = false;
 };
 
+// While it lives, this thread's allocations leave captures of other threads alone.
+struct OutsideCaptures {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    OutsideCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~OutsideCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 bool create_events(hipEvent_t *fork, hipEvent_t *join) {
     if (hipEventCreateWithFlags(fork, hipEventDisableTiming) != hipSuccess) return false;
     for (int c = 0; c < kGroups; ++c)
@@ -1220,8 +1227,7 @@ struct hdx_batch {
     int32_t n_leaves = 0;
     int64_t n_tiles = 0;
     ClassPlan plan{};
-    unsigned char *ped_work = nullptr;  // driving leaves' workspaces, if the call has few
-    size_t cap_ped = 0;
+    unsigned char *ped_work = nullptr;  // driving leaves' workspaces, once the batch has had few of them
     bool rows = false, g_rows = false;
     // per launch group: largest leaf seen, most pairs of a tile seen
     int32_t lds_c[kGroups] = {}, lds_p[kGroups] = {};
@@ -1368,8 +1374,18 @@ hdx_status hdx_batch_set_leaves(hdx_ctx *ctx, hdx_batch *b, const hdx_leaf *leav
         if (e != hipSuccess) return hip_fail(ctx, e, "staging wait");
     }
     b->n_tiles = pack_leaves(leaves, n_leaves, b->h_tasks, b->h_tiles, sh.n_tiles, ctx->n_cu);
-    b->rows = few_ped_leaves(b->h_tasks, n_leaves, ctx->n_cu) &&
-              grow_ped_work(&b->ped_work, &b->cap_ped, place_ped_work(b->h_tasks, n_leaves, nullptr));
+    const bool few = few_ped_leaves(b->h_tasks, n_leaves, ctx->n_cu);
+    if (few && !b->ped_work && !capturing((hipStream_t)stream)) {
+        // once, for as many and as large leaves as there can be, so that staging never frees (a wait for the GPU);
+        // without memory for it the leaves go without
+        const OutsideCaptures outside;
+        const size_t leaves_most = (size_t)std::min<int64_t>(b->max_leaves, 2 * (int64_t)ctx->n_cu - 1);
+        if (hipMalloc((void **)&b->ped_work, leaves_most * ped_work_bytes(kMaxLeaf)) != hipSuccess) {
+            (void)hipGetLastError();
+            b->ped_work = nullptr;
+        }
+    }
+    b->rows = few && b->ped_work;
     if (b->rows) place_ped_work(b->h_tasks, n_leaves, b->ped_work);
     b->var.assign(std::max(n_leaves, 1), 0);
     leaf_variants(leaves, n_leaves, b->var.data());

@@ -1,10 +1,12 @@
 """Driving calls keep to their own stream: a call does not wait for work that
-another stream has still before it, and asks nothing about streams that are gone.
+another stream has still before it, and asks nothing about streams that are gone;
+nor does staging a batch wait for the GPU.
 
 A stream is kept busy with a spinning kernel of bounded length, and calls are
 queued behind it.
 """
 import ctypes
+import threading
 import time
 
 import numpy as np
@@ -171,6 +173,73 @@ def test_streams_that_are_destroyed(ctx):
     torch.cuda.synchronize()
     for it, r in zip(items, ref):
         same(collect(m, it[1]), r)
+
+
+def test_calls_beside_a_capture(ctx):
+    """Calls and staging on other threads while this one captures: neither the capture nor they are disturbed."""
+    from paper_1802_06215_amd import Batch
+    m = ctx.upload_model(W.pednav_model(6, 5, 3))
+    items = build(m, 40, [100, 33, 250, 14])
+    for it in items:
+        ctx.expand_leaf([it[0]])
+    torch.cuda.synchronize()
+    ref = [collect(m, it[1]) for it in items]
+    wipe(items)
+    streams = [torch.cuda.Stream() for _ in range(12)]
+    x = torch.ones(64, device="cuda")
+    b = Batch(ctx, 20, 60)
+    errors = []
+
+    def work():
+        try:
+            for i, it in enumerate(items[:20]):
+                ctx.expand_leaf([it[0]], streams[i % 12])
+            b.set_leaves([it[0] for it in items[20:]], streams[0])
+            b.launch(streams[0])
+        except Exception as e:  # noqa: BLE001
+            errors.append(e)
+
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g):
+        y = x * 2
+        t = threading.Thread(target=work)
+        t.start()
+        t.join()
+        y = y + 1
+    assert not errors, errors
+    g.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(y, torch.full((64,), 3.0, device="cuda"))
+    for it, r in zip(items, ref):
+        same(collect(m, it[1]), r)
+    b.close()
+
+
+def test_staging_does_not_wait_for_the_gpu(ctx):
+    from paper_1802_06215_amd import Batch
+    m = ctx.upload_model(W.pednav_model(6, 5, 3))
+    groups = [build(m, 9, [30, 13]), build(m, 40, [300, 20]), build(m, 200, [70])]
+    refs = []
+    for items in groups:
+        for it in items:
+            ctx.expand_leaf([it[0]])
+        torch.cuda.synchronize()
+        refs.append([collect(m, it[1]) for it in items])
+        wipe(items)
+    busy, free, cycles = busy_and_free()
+    b = Batch(ctx, 200, 600)
+    for items, ref in zip(groups, refs):
+        spun = spin(busy, cycles)
+        b.set_leaves([it[0] for it in items], free)
+        waited = spun.query()
+        b.launch(free)
+        free.synchronize()
+        for it, r in zip(items, ref):
+            same(collect(m, it[1]), r)
+        assert not waited, "staging waited for the work of another stream"
+        torch.cuda.synchronize()
+    b.close()
 
 
 def test_calls_after_a_search(ctx):
