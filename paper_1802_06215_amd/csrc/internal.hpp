@@ -128,13 +128,13 @@ struct TileQueue {
     int32_t next, done, n_tiles, pad;
 };
 
-constexpr int32_t kQueued = -1;
+constexpr int32_t kStrided = -1;
 // Launch schedule of the expansion kernel; results never depend on it.
 struct Schedule {
     int32_t threads;     // workgroup size, a multiple of 64
     // 0: one workgroup per tile; > 0: that many workgroups per CU, which drain
-    // the queue; kQueued: as many as there are tiles, which drain the queue (so
-    // that they take more tiles, if there are more when the launch is replayed)
+    // the queue; kStrided: one per tile, and if there are more tiles when the
+    // launch is replayed, a workgroup takes the one a grid further on next
     int32_t persistent;
     int32_t xcd_remap;   // keep consecutive tiles (one leaf) on one XCD
 };

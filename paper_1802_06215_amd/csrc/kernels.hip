@@ -1553,16 +1553,19 @@ template <int MODE, int PM, bool kSpread = false>
 __global__ __launch_bounds__(max_threads<MODE>(), min_waves<MODE>()) void expand_tiles(const LeafTask *tasks,
                                                                                        const Tile *tiles,
                                                                                        TileQueue *queue,
-                                                                                       int32_t persistent,
+                                                                                       int32_t step,
                                                                                        int32_t xcd_remap) {
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ int32_t s_tile;
     const int32_t n_tiles = __builtin_amdgcn_readfirstlane(queue->n_tiles);
+    // step: 0 a tile per workgroup; -1 tiles from the queue; else from its own place on every step-th tile (the place
+    // kept in LDS, not in a register that the tiles are short of: 0.4 % of 8192 tiles' 42 us)
+    if (step > 0 && threadIdx.x == 0) s_tile = (int)blockIdx.x - step;
     int iter = 0;
     for (;;) {
         int t;
-        if (persistent) {
-            if (threadIdx.x == 0) s_tile = atomicAdd(&queue->next, 1);
+        if (step) {
+            if (threadIdx.x == 0) s_tile = step < 0 ? atomicAdd(&queue->next, 1) : s_tile + step;
             __syncthreads();
             t = __builtin_amdgcn_readfirstlane(s_tile);
             __syncthreads();
@@ -1576,7 +1579,7 @@ __global__ __launch_bounds__(max_threads<MODE>(), min_waves<MODE>()) void expand
         const HDX_CONST LeafTask *T = (const HDX_CONST LeafTask *)(tasks + tile->leaf);
         run_mode<MODE, PM, kSpread>(T, tile->action, lds);
     }
-    if (persistent && threadIdx.x == 0) {
+    if (step < 0 && threadIdx.x == 0) {
         __threadfence();
         if (atomicAdd(&queue->done, 1) == (int)gridDim.x - 1) {
             queue->next = 0;
@@ -1693,8 +1696,9 @@ hipError_t launch_expand_t(const LeafTask *d_tasks, const Tile *d_tiles, TileQue
     const int grid = sch.persistent > 0 ? n_cu * sch.persistent : n_tiles;
     if (grid < 1) return hipSuccess;
     const int threads = sch.threads > max_threads<MODE>() ? max_threads<MODE>() : sch.threads;
+    const int step = sch.persistent > 0 ? -1 : sch.persistent == kStrided ? grid : 0;
     hipLaunchKernelGGL((expand_tiles<MODE, PM, kSpread>), dim3(grid), dim3(threads),
-                       lds_bytes<MODE>(n_max, pairs, threads), stream, d_tasks, d_tiles, d_queue, sch.persistent != 0 ? 1 : 0, sch.xcd_remap);
+                       lds_bytes<MODE>(n_max, pairs, threads), stream, d_tasks, d_tiles, d_queue, step, sch.xcd_remap);
     return hipGetLastError();
 }
 

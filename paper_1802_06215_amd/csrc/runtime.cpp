@@ -1503,7 +1503,7 @@ hdx_status hdx_batch_launch(hdx_ctx *ctx, hdx_batch *b, hdx_stream stream) {
         if (!capturing(hs)) {
             e = batch_direct_launch(ctx, b, b->sched, hs);
         } else {
-            // The caller's graph may be replayed with other leaves staged: no workspaces, tiles from the queue, and LDS
+            // The caller's graph may be replayed with other leaves staged: no workspaces, as many tiles as there are, LDS
             // for any policy and number of actions per tile that leaves up to the largest seen can come with.  (Where a
             // group's tiles begin stays the same with as many leaves of each model: their sizes and policy change the
             // number of tiles of leaves above 1024 scenarios alone, navigation's, the last group.)
@@ -1514,7 +1514,7 @@ hdx_status hdx_batch_launch(hdx_ctx *ctx, hdx_batch *b, hdx_stream stream) {
             for (int g = 0; g < kGroups; ++g) {
                 pairs[g] = most_values(group_variant(g).mode == 4, b->lds_c[g]);
                 sched[g] = b->sched[g];
-                if (sched[g].persistent == 0) sched[g].persistent = kQueued;
+                if (sched[g].persistent == 0) sched[g].persistent = kStrided;
             }
             e = launch_classes_forked(b->d_tasks, b->d_tiles, b->d_queue, plan, b->lds_c, pairs, sched, ctx->n_cu, hs,
                                       b->cls, b->fork, b->join);
