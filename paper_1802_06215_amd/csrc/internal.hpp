@@ -369,9 +369,10 @@ struct ClassPlan {
 // (variant[leaf] is the leaf's model variant); fills plan.
 void plan_classes(const LeafTask *tasks, const int8_t *variant, Tile *tiles, int64_t n_tiles, ClassPlan *plan,
                   bool split);
-// One launch per non-empty group in mask (bit g = group g); lds_n[g] sizes
-// group g's LDS (>= its n_max), for navigation with lds_pairs[g]; sch[g] is its schedule (its width capped at
-// what the group's leaves and model need).
+// One launch per non-empty group in mask (bit g = group g); lds_n[g] and, but
+// for driving, lds_pairs[g] size group g's LDS (at least its n_max and pairs);
+// sch[g] is its schedule (its width capped at what the group's leaves and model
+// need).
 hipError_t launch_classes(const LeafTask *d_tasks, const Tile *d_tiles, TileQueue *d_queues, const ClassPlan &plan,
                           const int32_t *lds_n, const int32_t *lds_pairs, const Schedule *sch, int32_t n_cu,
                           hipStream_t stream, uint64_t mask = ~0ull);
@@ -440,7 +441,3 @@ const hdx_model_desc *hdx_internal_desc(const hdx_model *m);
 void hdx_internal_set_error(hdx_ctx *ctx, const char *msg);
 void hdx_internal_quiesce(hdx_ctx *ctx);
 const hdx::DevModel *hdx_internal_devmodel(const hdx_model *m);
-
-namespace hdx {
-
-}  // namespace hdx

@@ -1509,9 +1509,10 @@ __device__ __forceinline__ int remap_xcd(int b, int grid) {
 
 // MODE 0: RockSample only; 1: crowd driving only; 2: both; 3: multi-agent
 // RockSample only; 4: navigation only; 5: crowd driving, the grouping of leaves
-// whose scenarios ped_rows has expanded.  Workgroups of RockSample and driving
-// are capped at 512 lanes; navigation (94 registers) takes up to 1024,
-// because one large leaf's LDS carve-up leaves room for one workgroup per CU.
+// whose scenarios ped_rows has expanded.  Workgroups of the RockSample tiles are
+// capped at 512 lanes; driving (mixed calls and the grouping too) and navigation
+// take up to 1024, because one large leaf's LDS carve-up leaves room for one
+// workgroup per CU.
 template <int MODE>
 constexpr bool rock_mode() { return MODE == 0 || MODE == 3; }
 template <int MODE>

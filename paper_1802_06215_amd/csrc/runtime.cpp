@@ -26,7 +26,6 @@ struct ArgSlot {
     bool used = false;
 };
 
-// Pinned staging + device copy of one call's leaf descriptors and tiles.
 // Staging of a call: its leaves, tiles and queue heads in one piece on the
 // host and on the device, so that they travel in one copy (as three, each with
 // its gap, they took 6 of the 180 us of 512 leaves with the surrogate).
@@ -1244,7 +1243,6 @@ struct hdx_batch {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     Schedule g_sched[kGroups];
-    int64_t g_tiles = 0;
     bool split = false;         // one launch group per (model variant, size class)
     std::vector<int8_t> var;    // model variant of each staged leaf
 };
@@ -1547,7 +1545,6 @@ hdx_status hdx_batch_launch(hdx_ctx *ctx, hdx_batch *b, hdx_stream stream) {
             return hip_fail(ctx, e, "graph instantiate");
         }
         b->graph_ok = true;
-        b->g_tiles = b->n_tiles;
         b->g_plan = b->plan;
         b->g_rows = b->rows;
         for (int g = 0; g < kGroups; ++g) {
