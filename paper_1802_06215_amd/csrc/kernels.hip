@@ -1154,10 +1154,11 @@ __device__ __forceinline__ void sort_actions(uint64_t *zk, uint16_t *pos, int p2
 // idle and wait for the largest, and take two kernels: the scenarios of all
 // leaves on whatever CUs are free (ped_rows), which leave each pair's
 // observation, bounds, reward and steps in a workspace, and a workgroup per leaf
-// that groups them.  One leaf of 500 scenarios takes 56 us so and 362 whole, 341
-// of 31..500 beside as many RockSample leaves 465 and 622; at 512 leaves it
-// is 618 and 511.  Leaves of up to kPedTile scenarios, three wavefronts, stay on
-// one workgroup and one launch.
+// that groups them.  One leaf of 500 scenarios takes 52 us so and 430 whole, 256
+// of 50..500 among 768 RockSample leaves 485 and 620; at 512 leaves it
+// is 618 and 505.  Leaves of up to kPedTile scenarios, three wavefronts, stay on
+// one workgroup and one launch; so do, whole, those of persistent schedules and
+// captured launches, which are to serve other leaves too.
 //
 // Grouping: (observation, position) pairs of the three actions sorted in LDS
 // (the observations are hashes, most of them distinct), then one wavefront
@@ -1560,13 +1561,12 @@ __global__ __launch_bounds__(max_threads<MODE>(), min_waves<MODE>()) void expand
     __shared__ int32_t s_tile;
     const int32_t n_tiles = __builtin_amdgcn_readfirstlane(queue->n_tiles);
     // step: 0 a tile per workgroup; -1 tiles from the queue; else from its own place on every step-th tile (the place
-    // kept in LDS, not in a register that the tiles are short of: 0.4 % of 8192 tiles' 42 us)
-    if (step > 0 && threadIdx.x == 0) s_tile = (int)blockIdx.x - step;
+    // kept in LDS: in a register that the tiles are short of it cost every launch 0.4 to 0.8 %)
     int iter = 0;
     for (;;) {
         int t;
         if (step) {
-            if (threadIdx.x == 0) s_tile = step < 0 ? atomicAdd(&queue->next, 1) : s_tile + step;
+            if (threadIdx.x == 0) s_tile = step < 0 ? atomicAdd(&queue->next, 1) : iter > 0 ? s_tile + step : (int)blockIdx.x;
             __syncthreads();
             t = __builtin_amdgcn_readfirstlane(s_tile);
             __syncthreads();

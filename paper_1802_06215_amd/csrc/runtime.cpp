@@ -962,8 +962,8 @@ namespace {
 // A workspace for a call on the stream: the one it had last (its calls run one
 // after another), or one whose calls have ended.  Null if calls of other streams
 // hold them all: waiting for them would tie the stream to work that may be far
-// off, and a leaf on a workgroup of its own needs none (one of 500 scenarios 362
-// us instead of 56).  A stream handle that comes back after its stream was
+// off, and a leaf on a workgroup of its own needs none (one of 500 scenarios 430
+// us instead of 52).  A stream handle that comes back after its stream was
 // destroyed finds that stream's work done, as destroying a stream waits for it
 // (0.2 s with a kernel of 0.2 s on it).  Call with ctx->mu held.
 PedSlot *free_ped_slot(hdx_ctx *ctx, hipStream_t stream) {
