@@ -37,14 +37,14 @@ PEAK_HBM_GBS = 8000.0
 # WRITE_SIZE (scaled by a plain copy of known size), recorded with a hash of
 # the kernel's sources: reported only while those sources are unchanged.
 PROFILED_TRAFFIC = {
-    "rs15": dict(bytes=39.412e6, valu_insts=5.550e7, sha="924823d130d8fc36", summary="profiles/expand_tiles_rs15.md"),
-    "rs7": dict(bytes=52.554e6, valu_insts=6.590e7, sha="924823d130d8fc36", summary="profiles/expand_tiles_rs7.md"),
-    "mars20": dict(bytes=60.535e6, valu_insts=2.486e8, sha="924823d130d8fc36",
+    "rs15": dict(bytes=34.849e6, valu_insts=9.385e6, sha="4d56e8bd8272efb1", summary="profiles/expand_tiles_rs15.md"),
+    "rs7": dict(bytes=40.587e6, valu_insts=1.592e7, sha="4d56e8bd8272efb1", summary="profiles/expand_tiles_rs7.md"),
+    "mars20": dict(bytes=60.018e6, valu_insts=2.789e7, sha="4d56e8bd8272efb1",
                    summary="profiles/expand_tiles_mars20.md"),
 }
 # The same for the expand/group stage alone (rollouts off).
 PROFILED_STAGE_TRAFFIC = {
-    "rs15": dict(bytes=39.412e6, sha="924823d130d8fc36", summary="profiles/expand_tiles_rs15.md"),
+    "rs15": dict(bytes=34.849e6, sha="4d56e8bd8272efb1", summary="profiles/expand_tiles_rs15.md"),
 }
 # the kernel and the host code that orders its tiles (the order decides L2 reuse)
 KERNEL_SOURCES = ("paper_1802_06215_amd/csrc/kernels.hip", "paper_1802_06215_amd/csrc/models.hpp",
@@ -1050,8 +1050,8 @@ def main():
                     frac=round(alu_frac, 4), traffic=traffic, traffic_unit="bytes/launch",
                     traffic_source=prof["summary"] if current else None,
                     kernel_ms=round(kernel_ms, 4), ops_per_launch=int(ops),
-                    ops_accounting="%d lane-ops per scenario-step + %d per Philox block drawn" % (STEP_OPS_RS,
-                                                                                              PHILOX_OPS),
+                    ops_accounting="%d lane-ops per scenario-step + %d per Philox block drawn; steps of the method, those "
+                                   "that closed-form rollouts stand for among them" % (STEP_OPS_RS, PHILOX_OPS),
                     hbm=dict(algorithmic_bytes=int(alg_bytes), achieved=round(hbm_gbs, 1), peak=PEAK_HBM_GBS,
                              unit="GB/s", frac=round(hbm_frac, 4),
                              traffic_over_algorithmic=round(traffic / alg_bytes, 2) if traffic else None),
