@@ -1017,7 +1017,7 @@ bool launch_in_args(hdx_ctx *ctx, const hdx_leaf *leaves, int32_t n_leaves, cons
     const hipError_t e = launch_expand_args(pack, v0, sch, stream);
     free->calls += 1;
     free->stream = stream;
-    free->known = true;
+    free->known = stream != hipStreamPerThread;  // (a name for as many streams as there are threads)
     free->lost = e != hipSuccess;  // (the first of its kernels may be under way, and nothing will say when it ends)
     *st = e == hipSuccess ? HDX_OK : hip_fail(ctx, e, "expand launch");
     return true;

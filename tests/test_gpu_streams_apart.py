@@ -8,6 +8,7 @@ queued behind it.
 import ctypes
 import threading
 import time
+from types import SimpleNamespace
 
 import numpy as np
 import pytest
@@ -171,6 +172,37 @@ def test_streams_that_are_destroyed(ctx):
             took = time.perf_counter() - t
             assert took > 0.1, took
     torch.cuda.synchronize()
+    for it, r in zip(items, ref):
+        same(collect(m, it[1]), r)
+
+
+def test_the_per_thread_stream(ctx):
+    """hipStreamPerThread is one handle for a stream of every thread: calls on it do not share a workspace."""
+    per_thread = SimpleNamespace(cuda_stream=2)
+    m = ctx.upload_model(W.pednav_model(6, 5, 3))
+    items = build(m, 40, [100, 33, 250, 14])
+    for it in items:
+        ctx.expand_leaf([it[0]])
+    torch.cuda.synchronize()
+    ref = [collect(m, it[1]) for it in items]
+    wipe(items)
+    errors = []
+
+    def work(t):
+        try:
+            for _ in range(3):
+                for it in items[t::4]:
+                    ctx.expand_leaf([it[0]], per_thread)
+        except Exception as e:  # noqa: BLE001
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not errors, errors
     for it, r in zip(items, ref):
         same(collect(m, it[1]), r)
 
