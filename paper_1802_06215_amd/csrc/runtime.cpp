@@ -204,7 +204,7 @@ hdx_status hdx_init(int32_t device, hdx_ctx **out) {
             return HDX_E_NOMEM;
         }
     PedHead heads[kPedSlots] = {};
-    if (hipHostMalloc((void **)&ctx->ped_ended, kPedSlots * sizeof(uint32_t)) == hipSuccess) {
+    if (hipHostMalloc((void **)&ctx->ped_ended, kPedSlots * sizeof(uint32_t), hipHostMallocCoherent) == hipSuccess) {
         for (int i = 0; i < kPedSlots; ++i) {
             ctx->ped_ended[i] = 0;
             heads[i].host = ctx->ped_ended + i;
